@@ -189,13 +189,12 @@ int bnn_xnor_gemm_bn_sign_pack_kernel(const uint32_t *A, int64_t lda, const uint
  *   out[r][8*w + p] bit j = bit p (p = 0 least significant, the paper's n = p+1) of x[r][32*w + j]
  *   x   [rows][ld_x] uint8, ld_x >= cols
  *   out [rows][ld_out] uint32, ld_out >= 8*ceil(cols/32); elements >= cols read as 0; words beyond
- *       8*ceil(cols/32) untouched.  Fast path when x is 4-byte aligned and ld_x % 4 == 0.
+ *       8*ceil(cols/32) untouched.  Any alignment of x and ld_x takes the same path.
  *
  * bnn_bitplane_gemm:  C[m][n] = sum_k x[m][k] * w[n][k],  x in [0,255] given as bit planes (layout
  *   above, Xp [M][ldx], ldx >= 8*ceil(K/32)), w in {-1,+1} given as packed rows B [N][ldb] as in
- *   bnn_xnor_gemm; C [M][ldc] int32.  Computed plane by plane on the matrix engine with the plane
- *   weight 2^(n-1) as block scale while 255*K < 2^24 (the exact range of its accumulation); larger
- *   K is computed with and/popcount on the vector ALU (slow, exact).  255*K must fit int32
+ *   bnn_xnor_gemm; C [M][ldc] int32.  The planes are turned back into bytes on chip and multiplied on the
+ *   int8 matrix engine with int32 accumulation, exact for every K taken.  255*K must fit int32
  *   (255*K <= 2^31 - 32), else BNN_ERR_INVALID_ARG.  Pad bits of the last K-word of either operand
  *   are ignored.
  *

@@ -1,0 +1,520 @@
+// First layer on 8-bit inputs (Alg. 4 step 1, Sec. 1.6) on the int8 matrix engine:
+//
+//   a_1 = sum_{n=1..8} 2^(n-1) * <a_0^n, W^b_1>  =  sum_k x[m][k] * w[n][k],   x in [0, 255], w = 2b - 1 in {-1, +1}
+//
+// The inputs arrive as packed bit planes (word 8*w + p of a row: bit p of elements 32w .. 32w + 31).  Eight plane
+// words of 32 elements are an 8 x 8 bit transposition away from 32 bytes: 48 vector operations in registers
+// (transpose_bits_8x8), after which ONE pass of v_mfma_i32_32x32x32_i8 replaces the eight of a product taken plane by
+// plane (64 instead of 256 matrix cycles per 64 elements of K and 32 x 32 outputs).  Element 8j + s of a word ends
+// up in byte j of register s; B's bits are widened into the same order, byte j of register s = 2 * bit (8j + s), by a
+// shift and a mask.  The engine's bytes are signed, so plane 7 is inverted first and the bytes are x - 128:
+//
+//   sum_k x (2b - 1) = S + 256 * popcount(B_n) - sum_k x[m][k],      S = sum_k (x - 128) * 2b   (int32 accumulation)
+//
+// The row sums come from the staged bytes (v_dot4), the popcounts from B's words.  Everything is 32-bit integer
+// arithmetic, exact modulo 2^32 and therefore exact for every K with 255*K < 2^31.
+//
+// Two organisations:
+//   tiles   32*WI x 64*WAVES outputs per workgroup, WI x 2 blocks of 32 x 32 per wavefront: 128 x 512 with 8 wavefronts
+//           (the large fused products) or 64 x 256 with 4.  A's rows are transposed once per workgroup while they are
+//           staged into LDS; B stays bits in LDS and is widened by the wavefront that multiplies it (as bytes it would
+//           double the LDS traffic, which is what holds the plain int8 product at a third of the matrix rate).  The wide,
+//           flat tile keeps both cheap: 4.4 vector operations per MFMA in all on 128 x 512 (a 2 x 2 arrangement of
+//           wavefronts on 128 x 256 needs 8).
+//   split   32 x 32 outputs per workgroup, K split over its four wavefronts, operands straight from memory into
+//           registers: for small grids, where the tiles above leave most compute units without work.
+//
+// What bounds the tiles: the matrix engine's power.  A workgroup's tile of 128 bits of K (32 MFMAs per wavefront, 1024
+// cycles each way) takes 1.2 us on constant operands or on a quarter of the chip, 1.7 us on random bytes with every
+// compute unit at work: 2.3 POP/s sustained on random pixels, 2.9 on constant ones, whatever the tile shape.
+// 10000 x 4096 x 784 fused: 42 us (85 us plane by plane on the fp4 engine); 100 x 4096 x 784: 5.2 us (22 us).
+#include <type_traits>
+
+#include "bit_transpose.h"
+#include "bnn_internal.h"
+#include "gemm_staging.h"
+
+namespace bnn {
+namespace planes {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+// Bytes of registers 4u .. 4u + 3: byte j of register s = 2 * bit (8j + s) of w.
+template <int U>
+__device__ inline v4i widen_bits(uint32_t w) {
+    v4i f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int s = 4 * U + e;
+        f[e] = int((s == 0 ? w << 1 : w >> (s - 1)) & 0x02020202u);
+    }
+    return f;
+}
+
+__device__ inline int add_bytes(uint32_t w, int sum) { return __builtin_amdgcn_sdot4(int(w), 0x01010101, sum, false); }
+
+constexpr int kOffsetPerWord = 128 * 32;      // what the x - 128 of one word's 32 elements lacks to their x
+
+// No result exceeds 255 * K in magnitude, so clamping a threshold to one past it changes no output bit; below this
+// K the difference of a result and a clamped threshold stays inside int32.
+constexpr int kSignMaxK = (1 << 30) / 256;
+
+// ----------------------------------------------------------------------------
+// tiles
+// ----------------------------------------------------------------------------
+constexpr int kWordsPerTile = 4;              // K-words per staged tile = 2 pairs = 4 MFMA steps
+
+// WI x 2 blocks of 32 x 32 per wavefront, WAVES wavefronts side by side: a tile of 32*WI rows x 64*WAVES columns.
+template <int WI, int WAVES, bool FUSED>
+__global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
+    const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    constexpr int T = 64 * WAVES, BM = 32 * WI, BN = T;    // one staging thread per column of B
+    constexpr int L = BM * kWordsPerTile / T;              // A words (32 elements, 8 plane words) a thread stages per tile
+    constexpr int ROWS = T / kWordsPerTile;                // rows of a staging pass: 4 neighbouring lanes take the words of one
+    constexpr int PLANE_A = BM + 1;                        // 16-byte slots; odd, so that the 4 words x 2 rows that 8 lanes
+                                                           // store fall into eight different bank groups
+    static_assert(L >= 1 && L * T == BM * kWordsPerTile, "the tile's words must divide among the threads");
+    __shared__ uint4 lds_a[2][2 * kWordsPerTile * PLANE_A];    // [word][half of its 32 bytes][row]
+    __shared__ uint32_t lds_b[2][kWordsPerTile * BN];          // [word][column]
+    __shared__ int rowsum_s[BM];
+    __shared__ __attribute__((aligned(16))) int colterm_s[BN]; // 256 * popcount, less the threshold when the sign decides
+    __shared__ __attribute__((aligned(16))) int thr_s[FUSED ? BN : 4];
+
+    int tile_m, tile_n;
+    tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    const int row0 = tile_m * BM, col0 = tile_n * BN;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 31, fh = lane >> 5;
+    const int kw = (K + 31) >> 5;
+    const uint32_t tmask = tail_mask(K);
+    const int n_ktiles = (kw + kWordsPerTile - 1) / kWordsPerTile;
+    const int n_full = (K >> 5) / kWordsPerTile;           // tiles of complete, unmasked words
+    const int n_pairs = (kw + 1) >> 1;
+
+    const int st_w = tid & 3, st_r = tid >> 2;
+    const uint32_t* pa[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) pa[l] = Xp + int64_t(min(row0 + st_r + ROWS * l, M - 1)) * ldx;
+    const uint32_t* pb = B + int64_t(min(col0 + tid, N - 1)) * ldb;     // rows past the matrix repeat its last one
+
+    uint4 ra[L][2], rb;
+    int cnt_a[L], cnt_b = 0;
+#pragma unroll
+    for (int l = 0; l < L; ++l) cnt_a[l] = 0;
+
+    // Loads carry no control flow (a branch around them makes the compiler wait for them where the branches meet, which
+    // exposes the whole memory latency in every iteration): word indices are clamped into the row, and the last tile's
+    // words that do not exist are sorted out when they are staged.  A row has at least one whole quad (the launcher).
+    auto fetch_a = [&](int kt, int l) {
+        const int w = 8 * min(kWordsPerTile * kt + st_w, kw - 1);
+        ra[l][0] = load_quad_any(pa[l] + w);
+        ra[l][1] = load_quad_any(pa[l] + w + 4);
+    };
+    auto fetch_b = [&](int kt) { rb = load_quad_any(pb + min(kWordsPerTile * kt, kw - kWordsPerTile)); };
+    // The last, partial tile: words past the row's end become zero, the last word's pad bits are masked.
+    auto mask_tail = [&](int kt) {
+        const int w = kWordsPerTile * kt + st_w;
+        const uint32_t mask = w < kw - 1 ? ~0u : w == kw - 1 ? tmask : 0u;
+#pragma unroll
+        for (int l = 0; l < L; ++l)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                ra[l][h] = make_uint4(ra[l][h].x & mask, ra[l][h].y & mask, ra[l][h].z & mask, ra[l][h].w & mask);
+        // rb holds the row's last four words: word 0 of the tile is its word 4 - left.
+        const int left = kw - kWordsPerTile * kt;
+        const uint32_t last = rb.w & tmask;
+        rb = left == 1 ? make_uint4(last, 0u, 0u, 0u) : left == 2 ? make_uint4(rb.z, last, 0u, 0u)
+           : left == 3 ? make_uint4(rb.y, rb.z, last, 0u) : make_uint4(rb.x, rb.y, rb.z, last);
+    };
+    uint32_t bytes[8];
+    auto transpose_a = [&](int l) {
+        bytes[0] = ra[l][0].x; bytes[1] = ra[l][0].y; bytes[2] = ra[l][0].z; bytes[3] = ra[l][0].w;
+        bytes[4] = ra[l][1].x; bytes[5] = ra[l][1].y; bytes[6] = ra[l][1].z; bytes[7] = ~ra[l][1].w;
+        transpose_bits_8x8(bytes);
+    };
+    auto store_a = [&](int l, int buf) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) cnt_a[l] = add_bytes(bytes[s], cnt_a[l]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            lds_a[buf][(2 * st_w + u) * PLANE_A + st_r + ROWS * l] =
+                make_uint4(bytes[4 * u], bytes[4 * u + 1], bytes[4 * u + 2], bytes[4 * u + 3]);
+    };
+    auto store_b = [&](int buf) {
+        cnt_b += __popc(rb.x) + __popc(rb.y) + __popc(rb.z) + __popc(rb.w);
+        lds_b[buf][0 * BN + tid] = rb.x;
+        lds_b[buf][1 * BN + tid] = rb.y;
+        lds_b[buf][2 * BN + tid] = rb.z;
+        lds_b[buf][3 * BN + tid] = rb.w;
+    };
+
+    v16i acc[WI][2];
+#pragma unroll
+    for (int i = 0; i < WI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+
+    // Step (t, u) of a tile: lane half fh takes word 2t + fh, half u of its 32 bytes.
+    auto step = [&](int buf, int t, int u) {
+        v4i fa[WI], fb[2];
+#pragma unroll
+        for (int i = 0; i < WI; ++i) {
+            const uint4 q = lds_a[buf][(2 * (2 * t + fh) + u) * PLANE_A + i * 32 + fr];
+            fa[i] = v4i{int(q.x), int(q.y), int(q.z), int(q.w)};
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t w = lds_b[buf][(2 * t + fh) * BN + (wave * 2 + j) * 32 + fr];
+            fb[j] = u == 0 ? widen_bits<0>(w) : widen_bits<1>(w);
+        }
+#pragma unroll
+        for (int i = 0; i < WI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                // fused: operands swapped, so that a lane holds 16 columns of one output row
+                acc[i][j] = FUSED ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[j], fa[i], acc[i][j], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    };
+
+    int thr = 0;
+    const int lim = 255 * K + 1;
+    if (FUSED) thr = max(-lim, min(lim, bn.thr[min(col0 + tid, N - 1)]));
+    auto fetch = [&](int kt) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) fetch_a(kt, l);
+        fetch_b(kt);
+    };
+    auto stage = [&](int kt, int buf) {
+        if (kt >= n_full) mask_tail(kt);
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            transpose_a(l);
+            store_a(l, buf);
+        }
+        store_b(buf);
+    };
+    fetch(0);
+    stage(0, 0);
+    fetch(1);
+    __syncthreads();
+
+    // Tile kt is multiplied while tile kt + 1 (in registers since the iteration before) is transposed and stored to the
+    // other LDS buffer, and the loads of tile kt + 2 are issued as soon as their registers are free.
+    int kt = 0;
+    for (; kt + 1 < n_full; ++kt) {
+        const int buf = kt & 1;
+        // Slots the scheduler may not cross: it would sink the loads to the end of the iteration and wait for them at
+        // the top of the next.
+        step(buf, 0, 0);
+        transpose_a(0);
+        fetch_a(kt + 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        step(buf, 0, 1);
+        store_a(0, buf ^ 1);
+        store_b(buf ^ 1);
+        fetch_b(kt + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        step(buf, 1, 0);
+        if (L > 1) {
+            transpose_a(L - 1);
+            fetch_a(kt + 2, L - 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        step(buf, 1, 1);
+        if (L > 1) store_a(L - 1, buf ^ 1);
+        __syncthreads();
+    }
+    // The last full tile and the partial one.
+    for (; kt < n_ktiles; ++kt) {
+        const int buf = kt & 1;
+#pragma unroll
+        for (int t = 0; t < kWordsPerTile / 2; ++t) {
+            if (2 * kt + t >= n_pairs) break;
+            step(buf, t, 0);
+            step(buf, t, 1);
+        }
+        if (kt + 1 < n_ktiles) {
+            stage(kt + 1, buf ^ 1);
+            fetch(kt + 2);
+        }
+        __syncthreads();
+    }
+
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        int c = cnt_a[l] + kOffsetPerWord * n_ktiles;                       // words past the row's end included
+        c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
+        c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
+        if (st_w == 0) rowsum_s[st_r + ROWS * l] = c;
+    }
+    const bool sign = FUSED && K <= kSignMaxK;
+    colterm_s[tid] = 256 * cnt_b - (sign ? thr : 0);
+    if (FUSED) thr_s[tid] = thr;
+    __syncthreads();
+
+    if constexpr (!FUSED) {
+        // Accumulator register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32 of its 32 x 32 block.
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int nl = (wave * 2 + j) * 32 + fr, n = col0 + nl;
+            const int ct = colterm_s[nl];
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int ml = i * 32 + 8 * (v / 4) + 4 * fh + (v % 4), m = row0 + ml;
+                    if (m < M && n < N) store_result(&C[int64_t(m) * ldc + n], acc[i][j][v] + ct - rowsum_s[ml]);
+                }
+        }
+    } else {
+        // Register v of lane l: column 8*(v/4) + 4*(l/32) + v%4, row l%32.  The output bit is the complement of the
+        // sign of result - threshold: an add of three, and an alignbit that shifts the sign into the lane's word.
+        // A wavefront's words (2 per row) meet the others' in LDS, from where rows leave in 16-byte pieces.
+        uint32_t* words_s = reinterpret_cast<uint32_t*>(lds_a[0]);          // [BM][BN / 32], free since the last barrier
+        static_assert(BM * BN / 32 * 4 <= sizeof(lds_a), "the tile's output words fit the operand buffers");
+        auto collect = [&](auto sign_tag) {
+            constexpr bool SIGN = decltype(sign_tag)::value;
+            uint32_t part[WI][2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                int4 ct[4], th[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    ct[g] = *reinterpret_cast<const int4*>(&colterm_s[(wave * 2 + j) * 32 + 8 * g + 4 * fh]);
+                    if (!SIGN) th[g] = *reinterpret_cast<const int4*>(&thr_s[(wave * 2 + j) * 32 + 8 * g + 4 * fh]);
+                }
+#pragma unroll
+                for (int i = 0; i < WI; ++i) {
+                    const int r = rowsum_s[i * 32 + fr];
+                    uint32_t neg = 0u;
+#pragma unroll
+                    for (int g = 3; g >= 0; --g) {
+#pragma unroll
+                        for (int e = 3; e >= 0; --e) {
+                            const int c = e == 0 ? ct[g].x : e == 1 ? ct[g].y : e == 2 ? ct[g].z : ct[g].w;
+                            int d = acc[i][j][4 * g + e] + c - r;
+                            if (!SIGN) {
+                                const int t = e == 0 ? th[g].x : e == 1 ? th[g].y : e == 2 ? th[g].z : th[g].w;
+                                d = d >= t ? 0 : -1;
+                            }
+                            neg = __builtin_amdgcn_alignbit(neg, uint32_t(d), 31);
+                        }
+                        if (g > 0) neg <<= 4;
+                    }
+                    part[i][j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
+                }
+            }
+            // One v_permlane32_swap brings the two lane halves' nibbles together: lane half h holds the word of block h.
+#pragma unroll
+            for (int i = 0; i < WI; ++i) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(part[i][0], part[i][1], false, false);
+                words_s[(i * 32 + fr) * (BN / 32) + wave * 2 + fh] = sw[0] | sw[1];
+            }
+        };
+        if (sign) collect(std::true_type{});
+        else collect(std::false_type{});
+        __syncthreads();
+        constexpr int QUADS = BN / 128;                    // 16-byte pieces of a tile row
+        const int64_t nw = (int64_t(N) + 31) >> 5;
+        const int quad = tid % QUADS;
+        const int64_t w0 = (int64_t(col0) >> 5) + 4 * quad;
+        uint32_t flip[4], live[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int64_t left = N - 32 * (w0 + p);
+            live[p] = left >= 32 ? ~0u : left <= 0 ? 0u : ((1u << left) - 1u);
+            flip[p] = bn.flip_bits[w0 + p < nw ? w0 + p : nw - 1];
+        }
+#pragma unroll
+        for (int r = tid / QUADS; r < BM; r += T / QUADS) {
+            if (row0 + r >= M) break;
+            const uint4 v = *reinterpret_cast<const uint4*>(&words_s[r * (BN / 32) + 4 * quad]);
+            const uint32_t w[4] = {(v.x ^ flip[0]) & live[0], (v.y ^ flip[1]) & live[1], (v.z ^ flip[2]) & live[2],
+                                   (v.w ^ flip[3]) & live[3]};
+            uint32_t* o = bn.out + int64_t(row0 + r) * bn.ld_out + w0;
+            if (w0 + 4 <= nw) {
+                store_quad_any(o, make_uint4(w[0], w[1], w[2], w[3]));
+            } else {
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    if (w0 + p < nw) o[p] = w[p];
+            }
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------
+// split: 32 x 32 outputs, K split over the wavefronts
+// ----------------------------------------------------------------------------
+constexpr int kSplitWaves = 4;
+constexpr int kSplitBatch = 2;                // word pairs a wavefront loads at a time (two such batches in flight)
+
+template <bool FUSED>
+__global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
+    const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    __shared__ int4 part[kSplitWaves][4][kWave];           // [wavefront][accumulator registers 4g .. 4g + 3][lane]
+    __shared__ __attribute__((aligned(16))) int sum_part[kSplitWaves][kWave];   // [0, 32) row sums of A, [32, 64) 256 * popcounts of B
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int fr = lane & 31, fh = lane >> 5;
+    int tm, tn;
+    tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    const int row0 = tm * 32, col0 = tn * 32;
+    const int kw = (K + 31) >> 5;
+    const uint32_t tmask = tail_mask(K);
+    const int n_pairs = (kw + 1) >> 1;
+    const uint32_t* a_row = Xp + int64_t(min(row0 + fr, M - 1)) * ldx;
+    const uint32_t* b_row = B + int64_t(min(col0 + fr, N - 1)) * ldb;
+    const int col = col0 + fr;
+    int thr = 0;
+    uint32_t flip_word = 0u;
+    if constexpr (FUSED) {
+        thr = bn.thr[min(col, N - 1)];
+        flip_word = bn.flip_bits[min(col, N - 1) >> 5];
+    }
+
+    v16i acc[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0;
+    int ca = 0, cb = 0;
+
+    // Of a group of 8 pairs wavefront w takes pairs w and w + 4, lane half fh word fh of each.  Word indices are clamped
+    // into the row and what was loaded is masked away where the word does not exist.
+    struct Batch {
+        uint4 a[kSplitBatch][2];
+        uint32_t b[kSplitBatch];
+    };
+    auto load = [&](int pair0, Batch& q) {
+#pragma unroll
+        for (int t = 0; t < kSplitBatch; ++t) {
+            const int w = min(2 * (pair0 + kSplitWaves * t) + fh, kw - 1);
+            q.a[t][0] = load_quad_any(a_row + 8 * w);
+            q.a[t][1] = load_quad_any(a_row + 8 * w + 4);
+            q.b[t] = b_row[w];
+        }
+    };
+    Batch cur, next;
+    if (n_pairs > 0) load(wave, cur);
+    for (int p0 = wave; p0 < n_pairs; p0 += kSplitWaves * kSplitBatch) {
+        const int p1 = p0 + kSplitWaves * kSplitBatch;
+        if (p1 < n_pairs) load(p1, next);
+#pragma unroll
+        for (int t = 0; t < kSplitBatch; ++t) {
+            const int w = 2 * (p0 + kSplitWaves * t) + fh;
+            const uint32_t mask = w < kw - 1 ? ~0u : w == kw - 1 ? tmask : 0u;
+            const uint32_t b = cur.b[t] & mask;
+            uint32_t p[8] = {cur.a[t][0].x & mask, cur.a[t][0].y & mask, cur.a[t][0].z & mask, cur.a[t][0].w & mask,
+                             cur.a[t][1].x & mask, cur.a[t][1].y & mask, cur.a[t][1].z & mask, ~(cur.a[t][1].w & mask)};
+            transpose_bits_8x8(p);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) ca = add_bytes(p[s], ca);
+            ca += kOffsetPerWord;
+            cb += 256 * __popc(b);
+            acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i{int(p[0]), int(p[1]), int(p[2]), int(p[3])}, widen_bits<0>(b),
+                                                          acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i{int(p[4]), int(p[5]), int(p[6]), int(p[7])}, widen_bits<1>(b),
+                                                          acc[1], 0, 0, 0);
+        }
+        if (p1 < n_pairs) cur = next;
+    }
+
+    // Lanes 0-31 end up with the sum of A's row fr over both lane halves, lanes 32-63 with that of B's row fr.
+    const auto sw = __builtin_amdgcn_permlane32_swap(uint32_t(ca), uint32_t(cb), false, false);
+    sum_part[wave][lane] = int(sw[0] + sw[1]);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        part[wave][g][lane] = make_int4(acc[0][4 * g] + acc[1][4 * g], acc[0][4 * g + 1] + acc[1][4 * g + 1],
+                                        acc[0][4 * g + 2] + acc[1][4 * g + 2], acc[0][4 * g + 3] + acc[1][4 * g + 3]);
+    __syncthreads();
+
+    // Accumulator register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.  This wavefront finishes registers
+    // 4*wave .. 4*wave + 3.
+    int dot[4] = {0, 0, 0, 0};
+    int pb = 0;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+        const int4 s4 = part[w][wave][lane];
+        const int4 ra = *reinterpret_cast<const int4*>(&sum_part[w][8 * wave + 4 * fh]);
+        dot[0] += s4.x - ra.x;
+        dot[1] += s4.y - ra.y;
+        dot[2] += s4.z - ra.z;
+        dot[3] += s4.w - ra.w;
+        pb += sum_part[w][32 + fr];
+    }
+    if constexpr (!FUSED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = row0 + 8 * wave + 4 * fh + e;
+            if (row < M && col < N) C[int64_t(row) * ldc + col] = dot[e] + pb;
+        }
+    } else {
+        const bool valid = col < N;
+        const bool flip = (flip_word >> (col & 31)) & 1u;
+        // Ballot e: low half = the word of row 8*wave + e, high half = that of row 8*wave + 4 + e.
+        uint32_t word = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t mask = __ballot(valid && ((dot[e] + pb >= thr) != flip));
+            if ((lane & 3) == e) word = (lane & 4) ? uint32_t(mask >> 32) : uint32_t(mask);
+        }
+        const int row = row0 + 8 * wave + lane;
+        if (lane < 8 && row < M) bn.out[int64_t(row) * bn.ld_out + tn] = word;
+    }
+}
+
+}  // namespace planes
+
+template <int WI, int WAVES, bool FUSED>
+static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
+                        int64_t M, int64_t N, int64_t K, const BnSignArgs& bn, hipStream_t s) {
+    const int64_t tiles_m = ceil_div(M, 32 * WI), tiles_n = ceil_div(N, 64 * WAVES);
+    if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WAVES, FUSED>), dim3(unsigned(tiles_m * tiles_n)), dim3(64 * WAVES), 0,
+                       s, Xp, ldx, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn);
+    return check_launch();
+}
+
+// The choice, from a sweep of 22 shapes with M = 7 .. 10000, N = 33 .. 4096, K = 133 .. 3072 (fused, us, with the packing
+// of the planes):
+//  - split up to 1024 of its 32 x 32 tiles: 100 x 4096 x 784 7.8 vs 10.2 on 64 x 256 tiles, 233 x 4096 x 784 (1024 tiles)
+//    10.1 vs 10.4, 300 x 512 x 3072 11.4 vs 21.5; but 363 x 4096 x 784 12.5 vs 10.5, 501 x 2954 x 3072 33.0 vs 22.8.  Also
+//    rows of fewer than 4 words, which the tiles' quad loads of B do not take.
+//  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5: 4000 x 4096 x 784 21.5 vs 24.3 on
+//    64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs 194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9.  Its
+//    int32 form does not fit the registers.
+//  - 64 x 256 (four workgroups per compute unit) otherwise: 2000 x 4096 x 784 15.4 vs 18.0, 3280 x 1152 x 2394 30 vs 39.
+constexpr int64_t kSplitMaxTiles = 1024;
+constexpr int64_t kComputeUnits = 256;
+
+template <bool FUSED>
+static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
+                         int64_t M, int64_t N, int64_t K, const BnSignArgs& bn, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t small_m = ceil_div(M, 32), small_n = ceil_div(N, 32);
+    if ((K <= 96 && small_m * small_n <= kMaxDim) || small_m * small_n <= kSplitMaxTiles) {
+        hipLaunchKernelGGL(planes::bitplane_gemm_split_kernel<FUSED>, dim3(unsigned(small_m * small_n)), dim3(256), 0, s, Xp,
+                           ldx, B, ldb, C, ldc, int(M), int(N), int(K), int(small_m), int(small_n), bn);
+        return check_launch();
+    }
+    if (K <= 96) return BNN_ERR_UNSUPPORTED;               // more than 2^41 outputs
+    if constexpr (FUSED) {
+        const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 512);
+        const int64_t rounds = ceil_div(tiles, kComputeUnits);
+        if (5 * tiles >= 4 * rounds * kComputeUnits) return launch_tiles<4, 8, true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+    }
+    return launch_tiles<2, 4, FUSED>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+}
+
+// The callers have validated the arguments.  fused: bn holds thresholds, flip words and the output.
+int launch_bitplane_gemm(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
+                         int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn, void* stream) {
+    return fused ? launch_planes<true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream)
+                 : launch_planes<false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream);
+}
+
+}  // namespace bnn

@@ -41,6 +41,19 @@ __device__ inline uint4 load_quad_unchecked(const uint32_t* __restrict__ row_ptr
     return make_uint4(p[0], p[1], p[2], p[3]);
 }
 
+// 16-byte load from an address that is only known to be 4-byte aligned (rows whose leading dimension is not a
+// multiple of 4 words): one global_load_dwordx4, which needs dword alignment alone.
+__device__ inline uint4 load_quad_any(const uint32_t* __restrict__ p) {
+    typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    const quad_t v = *reinterpret_cast<const quad_t*>(p);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+__device__ inline void store_quad_any(uint32_t* p, uint4 v) {
+    typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    *reinterpret_cast<quad_t*>(p) = quad_t{v.x, v.y, v.z, v.w};
+}
+
 __device__ inline uint4 zero_unless(bool keep, uint4 v) {
     return make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
 }

@@ -317,8 +317,7 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
             mfma_epilogue_bits<WM, WN>(acc, pop_a[buf], pop_af[buf], pop_b, thr_s, flip_s, colfix_s, bn, M, N, K,
                                        tile_m * BM, col0, wm, wn, fr, fh);
         else
-            mfma_epilogue<WM, WN, false, false>(acc, pop_a[buf], pop_af[buf], pop_b, thr_s, flip_s, C, ldc, bn, M, N, K,
-                                                tile_m * BM, col0, wm, wn, fr, fh);
+            mfma_epilogue<WM, WN>(acc, pop_a[buf], pop_b, C, ldc, M, N, K, tile_m * BM, col0, wm, wn, fr, fh);
         __syncthreads();                            // next tile staged; this tile's row sums no longer needed
     }
 }

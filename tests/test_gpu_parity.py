@@ -1438,6 +1438,63 @@ def test_bitplane_gemm_first_layer(M, N, K):
     assert (words_to_host(fused) == oracle.pack_bits(oracle.bn_sign(S, *bn, eps=EPS))).all()
 
 
+@pytest.mark.parametrize("M,N,K", [
+    # K split over the wavefronts (at most 1024 tiles of 32 x 32, or rows of fewer than 4 words): one word, an odd
+    # number of words, one pair past a batch, the largest grid
+    (33, 65, 32), (32, 32, 64), (31, 97, 96), (64, 31, 288), (40, 33, 545), (1024, 1024, 784),
+    (5000, 300, 96), (5000, 300, 65),
+    # 64 x 256 tiles: rows of exactly 4 words, 1 .. 4 words in the last tile with and without pad bits, 1 row / column
+    # past a tile, the largest partial round
+    (1100, 1025, 128), (1100, 1025, 127), (1090, 1057, 97), (1089, 1056, 129), (2100, 770, 160), (2113, 769, 223),
+    (1300, 900, 256), (1057, 1000, 383), (3000, 513, 784),
+    # 128 x 512 tiles (fused only): a whole round, rows and columns past the last tile
+    (3300, 4100, 130), (6500, 2050, 257), (4096, 4096, 416),
+])
+def test_bitplane_gemm_kernels_at_the_edges_of_their_tiles(M, N, K):
+    """Every organisation of the 8-bit first layer, int32 and fused, at tile edges and word remainders, with planes and
+    weights whose pad bits are set and rows that are only 4-byte aligned."""
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    x = rng.integers(0, 256, (M, K), dtype=np.uint8)
+    x[rng.random(M) < 0.05] = 255
+    w = synth.pm1(rng, (N, K))
+    want = (x.astype(np.float64) @ w.T.astype(np.float64)).astype(np.int32)      # exact: |sums| < 2^53
+    planes = bnn.pack_bitplanes(torch.from_numpy(x).to(DEV))
+    kw = (K + 31) // 32
+    if K % 32:
+        planes[:, 8 * (kw - 1):] |= int(np.uint32((0xFFFFFFFF << (K % 32)) & 0xFFFFFFFF).view(np.int32))
+    wide = torch.full((M, 8 * kw + 1), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    wide[:, :8 * kw] = planes
+    wb = strided_words(poison_pad_bits(oracle.pack_bits(w), K), kw + 1)
+    assert (bnn.bitplane_gemm(wide[:, :8 * kw], wb, K).cpu().numpy() == want).all()
+    thr = np.rint(rng.standard_normal(N) * 74.0 * np.sqrt(K)).astype(np.int32)
+    thr[::17], thr[1::17] = 2 ** 31 - 1, -2 ** 31
+    flip = rng.integers(0, 2, N).astype(np.int8)
+    bits = (want >= thr[None, :]) != flip[None, :].astype(bool)
+    flip_words = torch.from_numpy(oracle.pack_bits((2 * flip - 1).reshape(1, -1)).view(np.int32)[0].copy()).to(DEV)
+    got = words_to_host(bnn.bitplane_gemm_bn_sign_pack(wide[:, :8 * kw], wb, K, torch.from_numpy(thr).to(DEV), flip_words))
+    assert (got == oracle.pack_bits(np.where(bits, 1, -1).astype(np.int8))).all()
+
+
+@pytest.mark.parametrize("rows,cols", [(3, 1), (5, 17), (4, 31), (300, 32), (257, 33), (9, 63), (7, 65), (2, 4097), (70, 1000)])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_pack_bitplanes_any_byte_alignment(rows, cols, shift):
+    """Rows at every byte alignment, last words that are read back from the row's end, canaries behind every row."""
+    rng = np.random.default_rng(rows * 31 + cols + shift)
+    x = rng.integers(0, 256, (rows, cols), dtype=np.uint8)
+    buf = torch.full((rows * (cols + shift) + 16,), 170, dtype=torch.uint8, device=DEV)
+    view = buf[shift:shift + rows * (cols + shift)].view(rows, cols + shift)[:, :cols]
+    view.copy_(torch.from_numpy(x))
+    kw = (cols + 31) // 32
+    out = torch.full((rows, 8 * kw + 1), -7, dtype=torch.int32, device=DEV)
+    bnn.pack_bitplanes(view, out=out[:, :8 * kw])
+    padded = np.zeros((rows, 32 * kw), np.uint8)
+    padded[:, :cols] = x
+    bits = (padded.reshape(rows, kw, 1, 32) >> np.arange(8, dtype=np.uint8)[None, None, :, None]) & 1
+    want = (bits.astype(np.uint64) << np.arange(32, dtype=np.uint64)).sum(-1).astype(np.uint32).reshape(rows, -1)
+    assert (words_to_host(out[:, :8 * kw].contiguous()) == want).all()
+    assert (out[:, 8 * kw] == -7).all()
+
+
 def test_bitplane_gemm_ignores_pad_bits_of_the_planes():
     rng = np.random.default_rng(8)
     M, N, K = 40, 50, 70
