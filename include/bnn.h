@@ -62,8 +62,8 @@ int64_t bnn_words_per_row(int64_t K);
  *   x     [rows][ld_x] float32, ld_x >= cols
  *   out   [rows][ld_out] uint32, ld_out >= ceil(cols/32); words
  *         [ceil(cols/32), ld_out) of each row are left untouched
- * Fast path when x is 16-byte aligned and ld_x % 4 == 0; any other layout
- * takes a slower element-wise path with the same result.
+ * Any alignment of x (4 bytes or more) and any ld_x take 16-byte loads; rows that are
+ * whole numbers of 128 elements, 16-byte aligned, also leave in 16-byte stores.
  */
 int bnn_pack_sign(const float *x, int64_t rows, int64_t cols, int64_t ld_x,
                   uint32_t *out, int64_t ld_out, void *stream);
@@ -143,7 +143,8 @@ int bnn_bn_fold(const float *gamma, const float *beta, const float *mean,
  *        (any int32 is a valid threshold; pad bits of the last flip word must be 0)
  *   out  [M][ld_out] uint32, ld_out >= ceil(N/32); pad bits of the last word 0;
  *        words beyond ceil(N/32) untouched
- * Fast path when C and thr are 16-byte aligned and ldc % 4 == 0.
+ * Any alignment of C and thr (4 bytes or more) and any ldc take 16-byte loads; rows that are
+ * whole numbers of 128 channels, 16-byte aligned, also leave in 16-byte stores.
  */
 int bnn_bn_sign_pack(const int32_t *C, int64_t ldc, int64_t M, int64_t N,
                      const int32_t *thr, const uint32_t *flip_bits, uint32_t *out,

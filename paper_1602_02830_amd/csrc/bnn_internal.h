@@ -53,31 +53,28 @@ __device__ inline uint32_t or_reduce8(uint32_t v) {
     return v;
 }
 
-// Work split of the streaming kernels' fast path (rows that are whole numbers of 128-element units,
-// 16-byte aligned): a unit is 4 consecutive output words = 128 consecutive elements of one row, taken by
-// an aligned group of 8 lanes; a 256-thread workgroup takes 32 units per step - one 16 KB stretch of a
-// row (units_per_row % 32 == 0) or 32 / units_per_row whole rows (32 % units_per_row == 0) - and
-// `steps` such steps on consecutive rows, so a thread's columns never change.
-struct UnitSplit {
-    int units_per_row;     // cols / 128
-    int slices_per_row;    // workgroups side by side on one row (1 if a workgroup covers whole rows)
-    int rows_per_step;     // rows a workgroup covers per step (1 if a row needs several workgroups)
-    int steps;             // steps per workgroup
+// Work split of the streaming kernels' fast path (rows that are whole numbers of 128-element units, 16-byte
+// aligned): a unit is 4 consecutive output words = 128 consecutive elements of one row, taken by an aligned group
+// of 8 lanes; a 256-thread workgroup takes 32 consecutive units, counted row by row, `rows` rows (1 or 2) at a
+// time - for one row at a time 16 KB of contiguous input when rows are dense.
+constexpr int kUnitsPerBlock = 32;
+
+struct UnitAt {
+    int64_t row;   // first row of the group
+    int unit;      // unit within the row
 };
 
-// False if the shape does not fit the split.
-inline bool unit_split(int64_t cols, int steps, UnitSplit& us) {
-    if (cols <= 0 || cols % 128 != 0 || cols / 128 > (int64_t(1) << 24)) return false;
-    const int upr = int(cols / 128);
-    if (upr % 32 == 0) {
-        us = UnitSplit{upr, upr / 32, 1, steps};
-        return true;
-    }
-    if (32 % upr == 0) {
-        us = UnitSplit{upr, 1, 32 / upr, steps};
-        return true;
-    }
-    return false;
+// Group `gi` of workgroup `block`.
+__device__ inline UnitAt unit_at(uint32_t block, uint32_t gi, int units_per_row, int rows) {
+    const uint32_t u = block * kUnitsPerBlock + gi, r = u / uint32_t(units_per_row);
+    return UnitAt{int64_t(r) * rows, int(u - r * uint32_t(units_per_row))};
+}
+
+// Workgroups of the fast path for `rows_total` rows taken `rows` at a time; 0 if the shape does not fit it.
+inline int64_t unit_blocks(int64_t rows_total, int64_t cols, int rows) {
+    if (cols <= 0 || cols % 128 != 0) return 0;
+    const int64_t blocks = ceil_div(ceil_div(rows_total, rows) * (cols / 128), kUnitsPerBlock);
+    return blocks * kUnitsPerBlock <= int64_t(0xFFFFFFFF) ? blocks : 0;         // units are counted in 32 bits
 }
 
 }  // namespace bnn

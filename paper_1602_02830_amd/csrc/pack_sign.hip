@@ -3,7 +3,7 @@
 // HBM-bound streaming kernel: 4 B read and 1/8 B written per element.
 // Work unit: one output word = 32 consecutive elements of a row, handled by an
 // aligned group of 8 lanes; each lane reads 4 consecutive floats (one 16-byte
-// load on the fast path), forms a 4-bit nibble and the group ORs the shifted
+// load, whatever the row's alignment), forms a 4-bit nibble and the group ORs the shifted
 // nibbles together with three DPP permutes.  A wavefront therefore reads eight
 // 128-byte segments and writes eight words per step, and groups never straddle
 // a row, so rows whose length is not a multiple of 32 cost nothing extra apart
@@ -25,24 +25,26 @@ __device__ inline uint32_t ge_zero(float v) { return v >= 0.0f ? 1u : 0u; }
 // their producer or from the previous step, and a non-temporal read does not find them (31 MB MLP input,
 // re-read every step: 5.8 -> 5.5 TB/s non-temporally).
 constexpr int64_t kOnceMinBytes = int64_t(256) << 20;
+// The address need only be 4-byte aligned: rows of odd length take the same loads as all others (28754 x 3005:
+// 111 us with four 4-byte loads per lane, 55 with one of 16 bytes).
 template <bool ONCE>
 __device__ inline float4 load_input(const float* p) {
-    if (!ONCE) return *reinterpret_cast<const float4*>(p);
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const f4 t = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
+    typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    const quad_t* q = reinterpret_cast<const quad_t*>(p);
+    const quad_t t = ONCE ? __builtin_nontemporal_load(q) : *q;
     return make_float4(t[0], t[1], t[2], t[3]);
 }
 
 // Word groups are numbered row-major (g = row * kw + word).  (row, word) coordinates are stepped by a
-// constant number of groups with a carry instead of being divided out for every group.
+// constant number of groups with a carry instead of being divided out for every group; both fit 32 bits.
 struct WordStep {
-    int64_t d_row;   // groups / kw
-    int64_t d_word;  // groups % kw
+    int d_row;   // groups / kw
+    int d_word;  // groups % kw
 };
 
-inline WordStep word_step(int64_t groups, int64_t kw) { return WordStep{groups / kw, groups % kw}; }
+inline WordStep word_step(int64_t groups, int64_t kw) { return WordStep{int(groups / kw), int(groups % kw)}; }
 
-__device__ inline void advance(int64_t& row, int64_t& w, const WordStep& st, int64_t kw) {
+__device__ inline void advance(uint32_t& row, int& w, const WordStep& st, int kw) {
     row += st.d_row;
     w += st.d_word;
     if (w >= kw) {
@@ -53,110 +55,87 @@ __device__ inline void advance(int64_t& row, int64_t& w, const WordStep& st, int
 
 // A workgroup takes kPackUnroll consecutive slices of 32 word groups per pass (16 KB of contiguous
 // input when rows are dense), thread t group t/8 of each slice; passes are a whole grid apart.
-template <bool VEC, bool ONCE>
+template <bool ONCE>
 __global__ __launch_bounds__(kPackThreads) void pack_sign_kernel(
-    const float* __restrict__ x, int64_t rows, int64_t cols, int64_t ld_x,
-    uint32_t* __restrict__ out, int64_t ld_out, int64_t kw, int64_t n_words, WordStep slice, WordStep pass) {
+    const float* __restrict__ x, int cols, int64_t ld_x,
+    uint32_t* __restrict__ out, int64_t ld_out, int kw, int64_t n_words, WordStep slice, WordStep pass) {
     constexpr int kSlice = kPackThreads / 8;             // word groups per slice
     const int q = threadIdx.x & 7;                       // lane within its group
     const int64_t pass_groups = int64_t(gridDim.x) * kSlice * kPackUnroll;
     int64_t g0 = int64_t(blockIdx.x) * kSlice * kPackUnroll + (threadIdx.x >> 3);
-    int64_t row0 = g0 / kw, w0 = g0 - row0 * kw;         // the only division of the thread
+    uint32_t row0 = uint32_t(g0 / kw);                   // the only division of the thread
+    int w0 = int(g0 - int64_t(row0) * kw);
 
     for (; g0 < n_words; g0 += pass_groups) {
-        float v[kPackUnroll][4];
-        int64_t word_of[kPackUnroll];
-        int64_t row_of[kPackUnroll];
-        int64_t row = row0, w = w0;
-        if (VEC && cols >= 4) {
+        uint32_t nib[kPackUnroll];
+        uint32_t row_of[kPackUnroll];                    // ~0: no such group
+        int word_of[kPackUnroll];
+        uint32_t row = row0;
+        int w = w0;
+        if (cols >= 4) {
             // Four unconditional 16-byte loads, all in flight together: a lane whose four elements do not all
-            // exist (a slice past the last group, the tail of a row) loads the row's last whole quad of
-            // elements instead - an address inside the matrix - and what it needs is sorted out afterwards.
-            const int64_t c_last = (cols & ~int64_t(3)) - 4;         // first element of that quad (16-byte aligned)
+            // exist (a slice past the last group, the tail of a row) loads the row's last four elements instead
+            // and shifts away the bits that belong to the lanes before it.
             float4 f[kPackUnroll];
-            bool whole[kPackUnroll];
-            int64_t c_of[kPackUnroll];
+            int past[kPackUnroll];
 #pragma unroll
             for (int u = 0; u < kPackUnroll; ++u) {
                 const bool live = g0 + u * kSlice < n_words;
-                row_of[u] = live ? row : -1;
+                row_of[u] = live ? row : ~0u;
                 word_of[u] = w;
-                c_of[u] = w * 32 + q * 4;
-                whole[u] = live && c_of[u] + 3 < cols;
-                f[u] = load_input<ONCE>(x + (live ? row : 0) * ld_x + (whole[u] ? c_of[u] : c_last));
+                const int c = live ? w * 32 + q * 4 : 0, c_at = min(c, cols - 4);
+                past[u] = c - c_at;
+                f[u] = load_input<ONCE>(x + int64_t(live ? row : 0u) * ld_x + c_at);
                 advance(row, w, slice, kw);
             }
 #pragma unroll
-            for (int u = 0; u < kPackUnroll; ++u) {
-                // Out-of-range elements take a negative value: bit 0.
-                v[u][0] = whole[u] ? f[u].x : -1.0f;
-                v[u][1] = whole[u] ? f[u].y : -1.0f;
-                v[u][2] = whole[u] ? f[u].z : -1.0f;
-                v[u][3] = whole[u] ? f[u].w : -1.0f;
-                if (!whole[u] && row_of[u] >= 0 && c_of[u] < cols) {   // a row's last, partial quad (cols % 4 != 0)
-                    const float* p = x + row_of[u] * ld_x + c_of[u];
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                        if (c_of[u] + e < cols) v[u][e] = p[e];
-                }
-            }
+            for (int u = 0; u < kPackUnroll; ++u)
+                nib[u] = (ge_zero(f[u].x) | (ge_zero(f[u].y) << 1) | (ge_zero(f[u].z) << 2) | (ge_zero(f[u].w) << 3)) >> past[u];
         } else {
 #pragma unroll
             for (int u = 0; u < kPackUnroll; ++u) {
                 const bool live = g0 + u * kSlice < n_words;
-                row_of[u] = live ? row : -1;
+                row_of[u] = live ? row : ~0u;
                 word_of[u] = w;
-                const int64_t c0 = w * 32 + q * 4;
-                const float* p = x + row * ld_x + c0;
-                // Out-of-range elements take a negative value: bit 0.
-                v[u][0] = v[u][1] = v[u][2] = v[u][3] = -1.0f;
-                if (live) {
+                nib[u] = 0u;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (c0 + e < cols) v[u][e] = p[e];
-                }
+                for (int e = 0; e < 3; ++e)
+                    if (live && q == 0 && e < cols) nib[u] |= ge_zero(x[int64_t(row) * ld_x + e]) << e;
                 advance(row, w, slice, kw);
             }
         }
 #pragma unroll
         for (int u = 0; u < kPackUnroll; ++u) {
-            uint32_t nib = ge_zero(v[u][0]) | (ge_zero(v[u][1]) << 1) |
-                           (ge_zero(v[u][2]) << 2) | (ge_zero(v[u][3]) << 3);
-            const uint32_t word = or_reduce8(nib << (4 * q));
-            if (q == 0 && row_of[u] >= 0) out[row_of[u] * ld_out + word_of[u]] = word;
+            const uint32_t word = or_reduce8(nib[u] << (4 * q));
+            if (q == 0 && row_of[u] != ~0u) out[int64_t(row_of[u]) * ld_out + word_of[u]] = word;
         }
         advance(row0, w0, pass, kw);
     }
 }
 
-// Fast path for rows that are whole numbers of 128-element units (see UnitSplit): a group of 8 lanes
+// Fast path for rows that are whole numbers of 128-element units (see unit_at): a group of 8 lanes
 // takes 4 consecutive output words, each of its four 16-byte loads per lane covers 128 contiguous bytes
 // of the group, and lane 0 writes the four words with one 16-byte store, so a wavefront's store is one
 // full 128-byte line instead of four partial ones.
 template <bool ONCE>
 __global__ __launch_bounds__(kPackThreads) void pack_sign_units_kernel(
     const float* __restrict__ x, int64_t rows, int64_t ld_x, uint32_t* __restrict__ out, int64_t ld_out,
-    UnitSplit us) {
-    const int q = threadIdx.x & 7, gi = threadIdx.x >> 3;
-    const int64_t block_row = int64_t(blockIdx.x) / us.slices_per_row;
-    const int slice = int(int64_t(blockIdx.x) - block_row * us.slices_per_row);
-    const int unit = us.rows_per_step == 1 ? slice * 32 + gi : gi % us.units_per_row;
-    const int row_in_step = us.rows_per_step == 1 ? 0 : gi / us.units_per_row;
-    for (int i = 0; i < us.steps; ++i) {
-        const int64_t row = (block_row * us.steps + i) * us.rows_per_step + row_in_step;
-        if (row >= rows) break;
-        const float* p = x + row * ld_x + int64_t(unit) * 128 + q * 4;
-        float4 v[4];
+    int units_per_row) {
+    const int q = threadIdx.x & 7;
+    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, units_per_row, 1);
+    if (at.row >= rows) return;
+    const float* p = x + at.row * ld_x + int64_t(at.unit) * 128 + q * 4;
+    float4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = load_input<ONCE>(p + 32 * u);
-        uint32_t w[4];
+    for (int u = 0; u < 4; ++u) v[u] = load_input<ONCE>(p + 32 * u);
+    uint32_t w[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t nib = ge_zero(v[u].x) | (ge_zero(v[u].y) << 1) | (ge_zero(v[u].z) << 2) | (ge_zero(v[u].w) << 3);
-            w[u] = or_reduce8(nib << (4 * q));
-        }
-        if (q == 0) *reinterpret_cast<uint4*>(out + row * ld_out + int64_t(unit) * 4) = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t nib = ge_zero(v[u].x) | (ge_zero(v[u].y) << 1) | (ge_zero(v[u].z) << 2) | (ge_zero(v[u].w) << 3);
+        w[u] = or_reduce8(nib << (4 * q));
     }
+    if (q == 0)
+        *reinterpret_cast<uint4*>(out + at.row * ld_out + int64_t(at.unit) * 4) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ----------------------------------------------------------------------------
@@ -266,32 +245,25 @@ extern "C" int bnn_pack_sign(const float* x, int64_t rows, int64_t cols, int64_t
     // (1 GiB: 5.98 TB/s in one pass of 65536 workgroups, 5.60 TB/s with 8192 looping 8 times).
     const int64_t max_blocks = int64_t(1) << 20;
     if (blocks > max_blocks) blocks = max_blocks;
-    const bool vec = aligned_to(x, 16) && (ld_x % 4 == 0);
     const bool once = rows * cols * int64_t(sizeof(float)) > kOnceMinBytes;     // see load_input
     hipStream_t s = static_cast<hipStream_t>(stream);
-    UnitSplit us;
-    if (vec && aligned_to(out, 16) && ld_out % 4 == 0 && unit_split(cols, 1, us)) {
-        const int64_t unit_blocks = ceil_div(rows, int64_t(us.rows_per_step) * us.steps) * us.slices_per_row;
-        if (unit_blocks <= kMaxDim) {
-            if (once)
-                hipLaunchKernelGGL(pack_sign_units_kernel<true>, dim3(unsigned(unit_blocks)), dim3(kPackThreads), 0, s, x, rows,
-                                   ld_x, out, ld_out, us);
-            else
-                hipLaunchKernelGGL(pack_sign_units_kernel<false>, dim3(unsigned(unit_blocks)), dim3(kPackThreads), 0, s, x, rows,
-                                   ld_x, out, ld_out, us);
-            return check_launch();
-        }
+    const int64_t units = unit_blocks(rows, cols, 1);
+    if (units > 0 && aligned_to(x, 16) && ld_x % 4 == 0 && aligned_to(out, 16) && ld_out % 4 == 0) {
+        if (once)
+            hipLaunchKernelGGL(pack_sign_units_kernel<true>, dim3(unsigned(units)), dim3(kPackThreads), 0, s, x, rows, ld_x,
+                               out, ld_out, int(cols / 128));
+        else
+            hipLaunchKernelGGL(pack_sign_units_kernel<false>, dim3(unsigned(units)), dim3(kPackThreads), 0, s, x, rows, ld_x,
+                               out, ld_out, int(cols / 128));
+        return check_launch();
     }
     const WordStep slice = word_step(groups_per_block, kw);
     const WordStep pass = word_step(blocks * groups_per_block * kPackUnroll, kw);
-    if (vec && once)
-        hipLaunchKernelGGL((pack_sign_kernel<true, true>), dim3(unsigned(blocks)), dim3(kPackThreads), 0, s,
-                           x, rows, cols, ld_x, out, ld_out, kw, n_words, slice, pass);
-    else if (vec)
-        hipLaunchKernelGGL((pack_sign_kernel<true, false>), dim3(unsigned(blocks)), dim3(kPackThreads), 0, s,
-                           x, rows, cols, ld_x, out, ld_out, kw, n_words, slice, pass);
+    if (once)
+        hipLaunchKernelGGL(pack_sign_kernel<true>, dim3(unsigned(blocks)), dim3(kPackThreads), 0, s,
+                           x, int(cols), ld_x, out, ld_out, int(kw), n_words, slice, pass);
     else
-        hipLaunchKernelGGL((pack_sign_kernel<false, false>), dim3(unsigned(blocks)), dim3(kPackThreads), 0, s,
-                           x, rows, cols, ld_x, out, ld_out, kw, n_words, slice, pass);
+        hipLaunchKernelGGL(pack_sign_kernel<false>, dim3(unsigned(blocks)), dim3(kPackThreads), 0, s,
+                           x, int(cols), ld_x, out, ld_out, int(kw), n_words, slice, pass);
     return check_launch();
 }

@@ -89,7 +89,7 @@ def test_pack_sign_shapes(rows, cols):
 # BatchNorm + Sign epilogue: several rows per workgroup (fewer than 32 units per row), several workgroups per
 # row, row counts that leave the last workgroup partly empty, strided inputs and outputs with guard words.
 UNIT_SHAPES = [(1, 128), (5, 128), (33, 256), (31, 512), (70, 1024), (7, 4096), (3, 8192), (129, 4096), (9, 12288),
-               (65, 384), (2, 128 * 33)]          # the last two fit neither split: the general kernels
+               (65, 384), (2, 128 * 33)]          # the last two: workgroups that start and end inside rows
 
 
 @pytest.mark.parametrize("rows,cols", UNIT_SHAPES)
@@ -123,6 +123,35 @@ def test_bn_sign_pack_rows_of_whole_128_channel_units(M, N):
     assert (host[1:M + 1, :nw] == oracle.pack_bits(oracle.bn_sign(S[:, 4:4 + N], *bn, eps=EPS))).all()
     host[1:M + 1, :nw] = 0x0BADBEEF
     assert (host == 0x0BADBEEF).all()
+
+
+@pytest.mark.parametrize("cols", [1, 2, 3, 4, 5, 31, 34, 61, 127, 129, 1003])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_streaming_kernels_at_every_row_alignment_and_tail(cols, shift):
+    """pack_sign and bn_sign_pack on rows that start at every 4-byte offset of a 16-byte line and end in every partial
+    quad, between canaries: the last quad of a row is read back from the row's end."""
+    rng = np.random.default_rng(cols * 5 + shift)
+    rows, ld = 37, cols + 4 + shift
+    x = synth.real_input(rng, (rows, ld))
+    x[:, cols:] = 1.0                                               # would read as set bits
+    buf = torch.from_numpy(np.concatenate([np.ones(shift, np.float32), x.ravel()])).to(DEV)
+    kw = (cols + 31) // 32
+    out = torch.full((rows, kw + 1), -7, dtype=torch.int32, device=DEV)
+    bnn.pack_sign(buf[shift:].view(rows, ld)[:, :cols], out=out[:, :kw])
+    assert (words_to_host(out[:, :kw]) == oracle.pack_bits(oracle.sign(x[:, :cols]))).all()
+    assert (out[:, kw] == -7).all()
+    C = rng.integers(-50, 51, (rows, ld)).astype(np.int32)
+    C[:, cols:] = 2 ** 31 - 1
+    thr = rng.integers(-20, 21, cols).astype(np.int32)
+    flip = rng.integers(0, 2, cols).astype(np.int8)
+    cbuf = torch.from_numpy(np.concatenate([np.zeros(shift, np.int32), C.ravel()])).to(DEV)
+    tbuf = torch.from_numpy(np.concatenate([np.zeros(shift, np.int32), thr])).to(DEV)[shift:]
+    flip_words = words_to_dev(oracle.pack_bits((2 * flip - 1).reshape(1, -1)))[0]
+    out.fill_(-7)
+    bnn.bn_sign_pack(cbuf[shift:].view(rows, ld)[:, :cols], tbuf, flip_words, out=out[:, :kw])
+    want = np.where((C[:, :cols] >= thr) != (flip != 0), 1, -1).astype(np.int8)
+    assert (words_to_host(out[:, :kw]) == oracle.pack_bits(want)).all()
+    assert (out[:, kw] == -7).all()
 
 
 def test_pack_sign_unaligned_and_strided():
