@@ -78,8 +78,9 @@ int bnn_pack_sign(const float *x, int64_t rows, int64_t cols, int64_t ld_x,
  *   B  [N][ldb] packed rows of K bits: row n is output unit n's weight vector,
  *      i.e. B is the transpose of W^b in s = a W (both operands K-contiguous)
  *   C  [M][ldc] int32, ldc >= N
- * lda, ldb >= ceil(K/32).  Fast tiles need A, B 16-byte aligned with lda, ldb
- * multiples of 4; other layouts run a slower path with the same result.
+ * lda, ldb >= ceil(K/32).  Any 4-byte alignment of A, B and any lda, ldb run on the matrix
+ * engine; the whole-tile forms of the largest products (kernel ids 8 and 9 below and the
+ * int32 form of 5) ask for 16-byte aligned rows.
  * K == 0 writes C = 0.
  */
 int bnn_xnor_gemm(const uint32_t *A, int64_t lda, const uint32_t *B, int64_t ldb,
@@ -108,9 +109,9 @@ int bnn_xnor_gemm(const uint32_t *A, int64_t lda, const uint32_t *B, int64_t ldb
  * operands read from memory straight into the MFMA's registers (for small
  * outputs with a long K, such as fully connected layers at batch 256; needs
  * K a positive multiple of 128 up to 2^24, A and B 16-byte aligned, lda and
- * ldb multiples of 4, else BNN_ERR_UNSUPPORTED; what 0 picks, from K = 512
- * on, for outputs of at most 256 such tiles, at most 512 with K >= 2048 or
- * at most 1024 with K >= 4096).  Unknown ids give BNN_ERR_INVALID_ARG. */
+ * ldb multiples of 4, else BNN_ERR_UNSUPPORTED; what 0 picks, for any
+ * alignment and 96 < K <= 2^24, for outputs of at most 512 such tiles or at
+ * most 1024 with K >= 512, as it picks 7 for any alignment).  Unknown ids give BNN_ERR_INVALID_ARG. */
 int bnn_xnor_gemm_kernel(const uint32_t *A, int64_t lda, const uint32_t *B, int64_t ldb,
                          int32_t *C, int64_t ldc, int64_t M, int64_t N, int64_t K,
                          int kernel_id, void *stream);

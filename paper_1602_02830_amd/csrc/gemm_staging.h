@@ -54,6 +54,30 @@ __device__ inline void store_quad_any(uint32_t* p, uint4 v) {
     *reinterpret_cast<quad_t*>(p) = quad_t{v.x, v.y, v.z, v.w};
 }
 
+// Quad `quad` of a row of kw >= 4 words, loaded without any check: a quad that is not whole, or not there, loads the
+// row's last four words instead, and place_row_quad puts them right - words in place, words past the row's end zero,
+// the last word's pad bits masked.
+__device__ inline uint4 load_row_quad(const uint32_t* __restrict__ row, int quad, int kw) {
+    return load_quad_any(row + min(4 * quad, kw - 4));
+}
+
+// left: words of the row from the quad's first one on.
+__device__ inline uint4 mask_row_quad(uint4 v, int left, uint32_t tmask) {
+    auto mask = [&](int w) { return left > w + 1 ? ~0u : left == w + 1 ? tmask : 0u; };
+    return make_uint4(v.x & mask(0), v.y & mask(1), v.z & mask(2), v.w & mask(3));
+}
+
+__device__ inline uint4 place_row_quad(uint4 v, int quad, int kw, uint32_t tmask) {
+    const int left = kw - 4 * quad;
+    const bool down1 = left == 3 || left == 1, down2 = left == 2 || left == 1;     // left <= 0: all masked below
+    v = make_uint4(down1 ? v.y : v.x, down1 ? v.z : v.y, down1 ? v.w : v.z, v.w);
+    v = make_uint4(down2 ? v.z : v.x, down2 ? v.w : v.y, v.z, v.w);
+    return mask_row_quad(v, left, tmask);
+}
+
+// Rows that allow aligned 16-byte loads (what the kernels chosen by id ask for; the automatic choice does not).
+inline bool rows_16_byte_aligned(const uint32_t* P, int64_t ld) { return aligned_to(P, 16) && ld % 4 == 0; }
+
 __device__ inline uint4 zero_unless(bool keep, uint4 v) {
     return make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
 }

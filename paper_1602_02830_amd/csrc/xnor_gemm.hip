@@ -380,13 +380,12 @@ bool mfma_big_supports(const uint32_t* A, int64_t lda, const uint32_t* B, int64_
 bool mfma_big_prefers(int64_t M, int64_t N);
 // 32 x 32 output tiles with K split over the wavefronts of a workgroup (xnor_gemm_mfma_splitk.hip), for small
 // outputs with a long K: BNN_ERR_UNSUPPORTED, with nothing launched, for the products it does not take.
-bool mfma_splitk_supports(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M, int64_t N,
-                          int64_t K);
+bool mfma_splitk_supports(int64_t M, int64_t N, int64_t K);
 int launch_xnor_gemm_mfma_splitk(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                                  int64_t ldc, int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn,
                                  void* stream);
 // Short-K organisation of the matrix-engine kernel, defined in xnor_gemm_mfma_shortk.hip.
-bool mfma_shortk_supports(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t K);
+bool mfma_shortk_supports(int64_t K);
 int launch_xnor_gemm_mfma_shortk(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                                  int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream);
 int launch_xnor_gemm_mfma_shortk_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
@@ -416,10 +415,9 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 // per compute unit) wins for long K on a grid of a thousand tiles or more; otherwise the
 // 128 x 128 tile (three workgroups per compute unit) hides short K loops better.  For K up to 1152
 // on a grid that fills the chip, the short-K organisation (B tile resident, several A tiles per
-// workgroup, only the K words that exist) is 5-25 % faster still; it needs operands that allow
-// 16-byte loads (short_ok).  Tiny grids go to the
-// 64 x 64 XNOR tiles, which spread over more compute units; skinny outputs go to the K-split kernel;
-// K beyond the exact-fp32 range stays on the vector ALU.
+// workgroup, only the K words that exist) is 5-25 % faster still (short_ok: 96 < K <= 1152).  Skinny outputs
+// that are too large for the split-K kernel go to the lane-group kernel; K beyond the exact-fp32 range
+// stays on the vector ALU.
 //
 // The 256 x 128 kernel as a tile walk (kernel 8; walk_ok: the product is one it takes, which includes
 // more tiles than the chip's resident slots) against one workgroup per tile, kernel time in us, N = 4096:
@@ -442,16 +440,15 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 static int choose_kernel(int64_t M, int64_t N, int64_t K, bool fused, bool short_ok, bool whole_ok, bool walk_ok,
                          bool big_ok, bool splitk_ok) {
     // Small outputs: 32 x 32 tiles with K split inside the workgroup, while the tiles are few enough for the
-    // workgroup dispatch rate.  Launches replayed from a graph, fused, against the choice below:
-    // 256 x 1024 (256 tiles) K = 512 3.3 vs 3.6 us, 1024 3.7 vs 4.2, 8192 5.3 vs 12.9, 16384 8.1 vs 23.0;
-    // 512 x 1024 (512 tiles) K = 1024 4.7 vs 4.2, 2048 4.7 vs 5.5, 8192 7.1 vs 12.9;
-    // 1024 x 1024 (1024 tiles) K = 2048 6.7 vs 5.5, 4096 6.8 vs 8.0, 16384 19.3 vs 23.2.  The int32 form alike,
-    // skinny outputs included (against the lane-group kernel below: 10000 x 10, K = 4096, 4.3 vs 5.1 us,
-    // 16384 x 16 4.6 vs 6.8, 1 x 4096 3.2 vs 3.6, 4 x 1024, K = 8192, 4.6 vs 4.3).
+    // workgroup dispatch rate.  Launches replayed from a graph, fused, rows of ceil(K / 32) words, against the 64 x 128
+    // tiles below, us: 64 x 1000 (64 tiles) K = 128 3.0 vs 4.0, 1000 3.2 vs 4.6, 4097 4.4 vs 8.7, 16384 6.2 vs 22.6;
+    // 500 x 1000 (512 tiles) K = 128 3.4 vs 4.1, 1000 3.5 vs 4.7, 4097 5.8 vs 8.8; 1000 x 1000 (1024 tiles) K = 300 4.2 vs
+    // 4.1, 520 4.2 vs 4.7, 2100 5.7 vs 6.5, 8192 10.8 vs 13.1; 1500 x 1000 (1504 tiles) K = 1000 5.7 vs 4.8, 4096 9.3 vs
+    // 8.4.  The int32 form alike, skinny outputs included (against the lane-group kernel: 10000 x 10, K = 4096, 4.3 vs
+    // 5.1 us, 16384 x 16 4.6 vs 6.8, 1 x 4096 3.2 vs 3.6, 4 x 1024, K = 8192, 4.6 vs 4.3).
     if (splitk_ok) {
         const int64_t tiles32 = ceil_div(M, 32) * ceil_div(N, 32);
-        if (tiles32 <= 256 || (tiles32 <= 512 && K >= 2048) || (tiles32 <= 1024 && K >= 4096))
-            return KERNEL_MFMA_SPLITK;
+        if (tiles32 <= 512 || (tiles32 <= 1024 && K >= 512)) return KERNEL_MFMA_SPLITK;
     }
     if (!fused && (N <= 16 || M <= 4)) return KERNEL_KSPLIT;
     if (fused && big_ok && mfma_big_prefers(M, N)) return KERNEL_MFMA_BIG;
@@ -469,11 +466,10 @@ static int choose_kernel(int64_t M, int64_t N, int64_t K, bool fused, bool short
         // fused, K = 2048, N = 4096: M = 8192 27.4 vs 28.0 (128 x 128 tiles), 12288 39.4 vs 40.7, 20000 62.4 vs 65.5
         if (fused && K >= 2048 && tiles256 >= 768) return KERNEL_MFMA;
         if (short_ok && tiles128 >= 768) return KERNEL_MFMA_SHORTK;
-        // Small grids, measured against the 64 x 64 vector-ALU tiles (kernel time, fused / int32):
-        // 64 x 1024 x 1024 5.4 vs 6.8 / 7.2 vs 5.8 us, 256 x 1024 x 8192 17.2 vs 26.3 / 18.7 vs 24.6 us,
-        // 512 x 512 x 2048 7.2 vs 9.6 / 8.7 vs 8.5 us: the fused form always wins on the matrix engine,
-        // the int32 form once K is long.
-        if (fused || tiles128 >= 32 || K >= 4096) return KERNEL_MFMA128;
+        // Small grids, measured against the 64 x 64 vector-ALU tiles (fused / int32): 200 x 1000 x 520 4.6 vs 7.0 /
+        // 5.0 vs 6.2 us, 1500 x 1000 x 2100 6.7 vs 15.5 / 7.0 vs 14.6.  Rows of fewer than 4 words: the int32 form
+        // only from a few dozen tiles on.
+        if (fused || tiles128 >= 32 || K > 96) return KERNEL_MFMA128;
     }
     return tiles128 >= 512 ? KERNEL_TILED128 : KERNEL_TILED64;
 }
@@ -483,11 +479,13 @@ static int xnor_gemm_dispatch(const uint32_t* A, int64_t lda, const uint32_t* B,
                               void* stream) {
     if (M < 0 || N < 0 || K < 0 || M > kMaxDim || N > kMaxDim || K > kMaxK) return BNN_ERR_INVALID_ARG;
     if (kernel_id < KERNEL_AUTO || kernel_id > KERNEL_LAST) return BNN_ERR_INVALID_ARG;
+    // Kernels chosen by id keep to what the header says they take; the automatic choice gives 7 and 10 any rows.
+    const bool aligned_rows = rows_16_byte_aligned(A, lda) && rows_16_byte_aligned(B, ldb);
     if ((kernel_id == KERNEL_MFMA || kernel_id == KERNEL_MFMA128 || kernel_id == KERNEL_MFMA_PERSIST ||
          kernel_id == KERNEL_MFMA_BIG) &&
         !mfma_path_supports(K))
         return BNN_ERR_UNSUPPORTED;
-    if (kernel_id == KERNEL_MFMA_SHORTK && !mfma_shortk_supports(A, lda, B, ldb, K)) return BNN_ERR_UNSUPPORTED;
+    if (kernel_id == KERNEL_MFMA_SHORTK && !(mfma_shortk_supports(K) && aligned_rows)) return BNN_ERR_UNSUPPORTED;
     const int64_t kw = ceil_div(K, 32);
     if (lda < kw || ldb < kw || ldc < N) return BNN_ERR_INVALID_ARG;
     if (M == 0 || N == 0) return BNN_OK;
@@ -500,11 +498,12 @@ static int xnor_gemm_dispatch(const uint32_t* A, int64_t lda, const uint32_t* B,
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int m = int(M), n = int(N), k = int(K);
 
+    if (kernel_id == KERNEL_MFMA_SPLITK && !(K % 128 == 0 && aligned_rows)) return BNN_ERR_UNSUPPORTED;
     if (kernel_id == KERNEL_AUTO)
-        kernel_id = choose_kernel(M, N, K, /*fused=*/false, mfma_shortk_supports(A, lda, B, ldb, K),
+        kernel_id = choose_kernel(M, N, K, /*fused=*/false, mfma_shortk_supports(K),
                                   mfma_persist_supports(A, lda, B, ldb, ldc, M, N, K, false, false),
                                   mfma_persist_supports(A, lda, B, ldb, ldc, M, N, K, false, true), false,
-                                  K >= 512 && mfma_splitk_supports(A, lda, B, ldb, M, N, K));
+                                  mfma_splitk_supports(M, N, K));
 
     switch (kernel_id) {
         case KERNEL_NAIVE: {
@@ -583,11 +582,13 @@ static int xnor_gemm_bn_sign_pack_dispatch(const uint32_t* A, int64_t lda, const
         kernel_id != KERNEL_MFMA && kernel_id != KERNEL_MFMA128 && kernel_id != KERNEL_MFMA_SHORTK &&
         kernel_id != KERNEL_MFMA_PERSIST && kernel_id != KERNEL_MFMA_BIG && kernel_id != KERNEL_MFMA_SPLITK)
         return BNN_ERR_INVALID_ARG;
+    // Kernels chosen by id keep to what the header says they take; the automatic choice gives 7 and 10 any rows.
+    const bool aligned_rows = rows_16_byte_aligned(A, lda) && rows_16_byte_aligned(B, ldb);
     if ((kernel_id == KERNEL_MFMA || kernel_id == KERNEL_MFMA128 || kernel_id == KERNEL_MFMA_PERSIST ||
          kernel_id == KERNEL_MFMA_BIG) &&
         !mfma_path_supports(K))
         return BNN_ERR_UNSUPPORTED;
-    if (kernel_id == KERNEL_MFMA_SHORTK && !mfma_shortk_supports(A, lda, B, ldb, K)) return BNN_ERR_UNSUPPORTED;
+    if (kernel_id == KERNEL_MFMA_SHORTK && !(mfma_shortk_supports(K) && aligned_rows)) return BNN_ERR_UNSUPPORTED;
     const int64_t kw = ceil_div(K, 32);
     if (lda < kw || ldb < kw || ld_out < ceil_div(N, 32)) return BNN_ERR_INVALID_ARG;
     if (M == 0 || N == 0) return BNN_OK;
@@ -600,12 +601,13 @@ static int xnor_gemm_bn_sign_pack_dispatch(const uint32_t* A, int64_t lda, const
         return BNN_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const BnSignArgs bn{thr, flip_bits, out, ld_out};
+    if (kernel_id == KERNEL_MFMA_SPLITK && !(K % 128 == 0 && aligned_rows)) return BNN_ERR_UNSUPPORTED;
     if (kernel_id == KERNEL_AUTO)
-        kernel_id = choose_kernel(M, N, K, /*fused=*/true, mfma_shortk_supports(A, lda, B, ldb, K),
+        kernel_id = choose_kernel(M, N, K, /*fused=*/true, mfma_shortk_supports(K),
                                   mfma_persist_supports(A, lda, B, ldb, 0, M, N, K, true, false),
                                   mfma_persist_supports(A, lda, B, ldb, 0, M, N, K, true, true),
                                   mfma_big_supports(A, lda, B, ldb, M, N, K, bn),
-                                  K >= 512 && mfma_splitk_supports(A, lda, B, ldb, M, N, K));
+                                  mfma_splitk_supports(M, N, K));
     if (kernel_id == KERNEL_MFMA_SHORTK) return launch_xnor_gemm_mfma_shortk_fused(A, lda, B, ldb, M, N, K, bn, stream);
     if (kernel_id == KERNEL_MFMA_PERSIST)
         return launch_xnor_gemm_mfma_persist(A, lda, B, ldb, nullptr, 0, M, N, K, true, true, bn, stream);

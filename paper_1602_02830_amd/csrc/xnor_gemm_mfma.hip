@@ -42,7 +42,8 @@
 
 namespace bnn {
 
-template <int WM, int WN, bool VEC, bool FUSED, bool CONV>
+// TINY: rows of fewer than 4 words (K <= 96), which have no whole quad to load.
+template <int WM, int WN, bool FUSED, bool CONV, bool TINY>
 __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn,
@@ -76,10 +77,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     const int kw = (K + 31) >> 5;
     const uint32_t tmask = tail_mask(K);
     const int n_ktiles = (kw + kMfmaKT - 1) / kMfmaKT;
-    // K-tiles made only of complete, unmasked words take branch-free loads (row index clamped
-    // into the matrix, result zeroed at staging if the row does not exist); the last, partial
-    // K-tile goes through checked, masking loads.
-    const int n_full_ktiles = (K >> 5) / kMfmaKT;
+    const int n_full_ktiles = (K >> 5) / kMfmaKT;      // K-tiles made only of complete, unmasked words
 
     const int st_q = tid % kMfmaKQ, st_r = tid / kMfmaKQ;
     // conv: per staged row the word offset of its image and its output pixel (oy << 16 | ox);
@@ -134,34 +132,37 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
             fill_a[l] = (!live_a[l] || quad * 4 >= kw) ? 2 : (inside ? 0 : 1);
         }
     };
+    // The loads carry no control flow: a branch around them makes the compiler wait for them where the branches
+    // meet, which exposes the whole memory latency in every iteration (and checked loads in the last K-tile are a chain
+    // of such waits).  What is not a whole quad is put right when it is staged.
+    auto load_words = [&](const uint32_t* row, int quad) {
+        if (!TINY) return load_row_quad(row, quad, kw);
+        return make_uint4(row[0], row[min(1, kw - 1)], row[min(2, kw - 1)], 0u);      // one K-tile, quad 0 only
+    };
+    auto place_words = [&](uint4 v, int quad) {
+        return TINY ? mask_row_quad(v, kw - 4 * quad, tmask) : place_row_quad(v, quad, kw, tmask);
+    };
     auto fetch = [&](int kt) {
         const int quad = kt * kMfmaKQ + st_q;
         if (CONV) {
             fetch_conv(quad);
-            if (kt < n_full_ktiles) {
-#pragma unroll
-                for (int l = 0; l < LOADS_B; ++l) rb[l] = load_quad_unchecked<VEC>(pb[l], quad);
-            } else {
-#pragma unroll
-                for (int l = 0; l < LOADS_B; ++l)
-                    rb[l] = load_quad<VEC>(B, ldb, N, kw, tmask, col0 + st_r + l * ST_ROWS, quad);
-            }
-        } else if (kt < n_full_ktiles) {
-#pragma unroll
-            for (int l = 0; l < LOADS_A; ++l) ra[l] = load_quad_unchecked<VEC>(pa[l], quad);
-#pragma unroll
-            for (int l = 0; l < LOADS_B; ++l) rb[l] = load_quad_unchecked<VEC>(pb[l], quad);
         } else {
 #pragma unroll
-            for (int l = 0; l < LOADS_A; ++l)
-                ra[l] = load_quad<VEC>(A, lda, M, kw, tmask, row0 + st_r + l * ST_ROWS, quad);
-#pragma unroll
-            for (int l = 0; l < LOADS_B; ++l)
-                rb[l] = load_quad<VEC>(B, ldb, N, kw, tmask, col0 + st_r + l * ST_ROWS, quad);
+            for (int l = 0; l < LOADS_A; ++l) ra[l] = load_words(pa[l], quad);
         }
+#pragma unroll
+        for (int l = 0; l < LOADS_B; ++l) rb[l] = load_words(pb[l], quad);
     };
     // Writes the fetched words to LDS and adds their set bits to this thread's row sums.
-    auto stage = [&](int buf) {
+    auto stage = [&](int kt, int buf) {
+        if (kt >= n_full_ktiles) {
+            const int quad = kt * kMfmaKQ + st_q;
+#pragma unroll
+            for (int l = 0; l < LOADS_A; ++l)
+                if (!CONV) ra[l] = place_words(ra[l], quad);
+#pragma unroll
+            for (int l = 0; l < LOADS_B; ++l) rb[l] = place_words(rb[l], quad);
+        }
 #pragma unroll
         for (int l = 0; l < LOADS_A; ++l) {
             // Rows beyond the matrix hold a copy of its last row (clamped load): their sums and
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     }
     if (n_ktiles > 0) {
         fetch(0);
-        stage(0);
+        stage(0, 0);
     }
     __syncthreads();
 
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
 #pragma unroll
             for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(acc[i][j]) : : "memory");
 
-        if (kt + 1 < n_ktiles) stage(buf ^ 1);
+        if (kt + 1 < n_ktiles) stage(kt + 1, buf ^ 1);
         __syncthreads();
     }
 
@@ -285,23 +286,16 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
         mfma_epilogue<WM, WN>(acc, pop_a, pop_b, C, ldc, M, N, K, row0, col0, wm, wn, fr, fh);
 }
 
-template <int WM, bool FUSED, bool CONV>
+template <int WM, bool FUSED, bool CONV, bool TINY = false>
 static int launch_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                        int64_t M, int64_t N, int64_t K, BnSignArgs bn, ConvArgs cv, void* stream) {
     constexpr int WN = 2;
     const int64_t tiles_m = ceil_div(M, 64 * WM), tiles_n = ceil_div(N, 64 * WN);
     if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
-    // The conv kernel always reads whole 16-byte channel quads of A (its caller has checked that it can).
-    const bool vec_a = CONV || (aligned_to(A, 16) && lda % 4 == 0);
-    const bool vec = vec_a && aligned_to(B, 16) && ldb % 4 == 0;
     const dim3 grid{unsigned(tiles_m * tiles_n)};
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec)
-        hipLaunchKernelGGL((xnor_gemm_mfma_kernel<WM, WN, true, FUSED, CONV>), grid, dim3(256), 0, s, A,
-                           lda, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn, cv);
-    else
-        hipLaunchKernelGGL((xnor_gemm_mfma_kernel<WM, WN, false, FUSED, CONV>), grid, dim3(256), 0, s, A,
-                           lda, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn, cv);
+    hipLaunchKernelGGL((xnor_gemm_mfma_kernel<WM, WN, FUSED, CONV, TINY>), grid, dim3(256), 0,
+                       static_cast<hipStream_t>(stream), A, lda, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m),
+                       int(tiles_n), bn, cv);
     return check_launch();
 }
 
@@ -310,11 +304,13 @@ bool mfma_path_supports(int64_t K) { return K <= kMfmaMaxAcc; }
 
 int launch_xnor_gemm_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                           int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
+    if (K <= 96) return launch_mfma<1, false, false, true>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
     return launch_mfma<4, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
 }
 
 int launch_xnor_gemm_mfma_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
                                 int64_t N, int64_t K, BnSignArgs bn, void* stream) {
+    if (K <= 96) return launch_mfma<1, true, false, true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
     return launch_mfma<4, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
 }
 
@@ -327,6 +323,7 @@ static bool wants_half_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * c
 
 int launch_xnor_gemm_mfma128(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                              int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
+    if (K <= 96) return launch_mfma<1, false, false, true>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
     if (wants_half_tiles(M, N))
         return launch_mfma<1, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
     return launch_mfma<2, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
@@ -334,6 +331,7 @@ int launch_xnor_gemm_mfma128(const uint32_t* A, int64_t lda, const uint32_t* B, 
 
 int launch_xnor_gemm_mfma128_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
                                    int64_t N, int64_t K, BnSignArgs bn, void* stream) {
+    if (K <= 96) return launch_mfma<1, true, false, true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
     if (wants_half_tiles(M, N))
         return launch_mfma<1, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
     return launch_mfma<2, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);

@@ -46,13 +46,6 @@ namespace bnn {
 constexpr int kShortMaxQuads = 9;          // K <= 1152
 constexpr int kShortMinWords = 4;          // K > 96: a row has at least one whole quad to load
 
-// A 16-byte load from an address that is only 4-byte aligned (the last four words of a row).
-__device__ inline uint4 load_quad_dword_aligned(const uint32_t* p) {
-    uint4 v;
-    __builtin_memcpy(&v, p, sizeof(v));
-    return v;
-}
-
 template <int LANES>
 __device__ inline int sum_over_lanes(int c) {
     static_assert(LANES == 8 || LANES == 16, "aligned groups of 8 or 16 lanes");
@@ -144,7 +137,7 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
 #pragma unroll
         for (int l = 0; l < PASSES; ++l) {
             const int row = min(r0 + st_r + l * ROWS_PER_PASS, nrows - 1);   // rows beyond the matrix repeat its last row
-            r[l] = load_quad_dword_aligned(P + int64_t(row) * ld + word_off);
+            r[l] = load_quad_any(P + int64_t(row) * ld + word_off);
         }
     };
     // conv: the tap (dy, dx relative to the output pixel's input position) and channel word of this
@@ -322,10 +315,9 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
     }
 }
 
-bool mfma_shortk_supports(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t K) {
+bool mfma_shortk_supports(int64_t K) {
     const int64_t kw = ceil_div(K, 32);
-    return kw >= kShortMinWords && kw <= 4 * kShortMaxQuads && aligned_to(A, 16) && aligned_to(B, 16) &&
-           lda % 4 == 0 && ldb % 4 == 0;
+    return kw >= kShortMinWords && kw <= 4 * kShortMaxQuads;
 }
 
 // Workgroups per 128-column tile: every workgroup of a column tile takes every `groups`-th row tile.
@@ -362,13 +354,13 @@ static int launch_shortk(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 
 int launch_xnor_gemm_mfma_shortk(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                                  int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
-    if (!mfma_shortk_supports(A, lda, B, ldb, K)) return BNN_ERR_UNSUPPORTED;
+    if (!mfma_shortk_supports(K)) return BNN_ERR_UNSUPPORTED;
     return launch_shortk<false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
 }
 
 int launch_xnor_gemm_mfma_shortk_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
                                        int64_t N, int64_t K, BnSignArgs bn, void* stream) {
-    if (!mfma_shortk_supports(A, lda, B, ldb, K)) return BNN_ERR_UNSUPPORTED;
+    if (!mfma_shortk_supports(K)) return BNN_ERR_UNSUPPORTED;
     return launch_shortk<true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
 }
 

@@ -691,6 +691,37 @@ def test_k_split_matrix_engine_kernel_randomized(seed):
         assert (bits == oracle.pack_bits(a_next)).all(), tag
 
 
+# What the automatic choice gives the split-K kernel and the general matrix-engine kernel since rows may start anywhere and
+# end anywhere: every number of words in the last quad, one step past a batch, whole batches, tile edges, both sides of
+# the limits between the kernels (512 and 1024 tiles of 32 x 32, K = 96 / 97 / 512).
+ANY_ROW_SHAPES = [(33, 65, 97), (64, 100, 128), (31, 32, 129), (65, 33, 255), (40, 70, 1023), (40, 70, 1025), (64, 64, 4096),
+                  (35, 31, 4097), (32, 95, 4161), (64, 33, 8192), (33, 40, 8353), (512, 1000, 300), (513, 1024, 300),
+                  (1000, 1000, 511), (1000, 1000, 513), (1025, 1024, 777), (300, 4000, 1153), (700, 700, 3001), (130, 257, 96),
+                  (130, 257, 33), (1500, 260, 2049), (1300, 1290, 96), (2049, 1030, 1600), (4100, 1027, 2085)]
+
+
+@pytest.mark.parametrize("M,N,K", ANY_ROW_SHAPES)
+@pytest.mark.parametrize("extra,first", [(0, 0), (1, 0), (3, 1)])
+def test_products_of_rows_at_any_alignment(M, N, K, extra, first):
+    """int32 and fused products of the automatic choice and of the kernels by id that take any rows, on operands with odd
+    leading dimensions, odd first words and set pad bits, against the int32 product of the +-1 values."""
+    rng = np.random.default_rng(M + 3 * N + 7 * K)
+    A, Bm = synth.pm1(rng, (M, K)), synth.pm1(rng, (N, K))
+    want = (A.astype(np.float32) @ Bm.T.astype(np.float32)).astype(np.int32)          # exact: |sums| < 2^24
+    kw = (K + 31) // 32
+    a = _offset_words(poison_pad_bits(oracle.pack_bits(A), K), kw + extra, first)
+    b = _offset_words(poison_pad_bits(oracle.pack_bits(Bm), K), kw + extra, first)
+    thr = np.rint(rng.standard_normal(N) * np.sqrt(K)).astype(np.int32)
+    thr[::13], thr[1::13] = 2 ** 31 - 1, -2 ** 31
+    flip = rng.integers(0, 2, N).astype(np.int8)
+    flip_words = words_to_dev(oracle.pack_bits((2 * flip - 1).reshape(1, -1)))[0]
+    bits = oracle.pack_bits(np.where((want >= thr) != (flip != 0), 1, -1).astype(np.int8))
+    for kernel in (bnn.KERNEL_AUTO, bnn.KERNEL_MFMA, bnn.KERNEL_MFMA128):
+        assert (bnn.xnor_gemm(a, b, K, kernel=kernel).cpu().numpy() == want).all(), kernel
+        got = bnn.xnor_gemm_bn_sign_pack(a, b, K, torch.from_numpy(thr).to(DEV), flip_words, kernel=kernel)
+        assert (words_to_host(got) == bits).all(), kernel
+
+
 def test_k_split_matrix_engine_kernel_refuses_what_it_does_not_take():
     """Kernel id 10 answers BNN_ERR_UNSUPPORTED, launching nothing, outside its shapes: K not a multiple of
     128 (or zero), operands that do not allow 16-byte loads."""
