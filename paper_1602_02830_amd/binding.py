@@ -4,6 +4,10 @@ Only marshalling happens here: shapes and strides are read off the tensors,
 outputs are allocated with torch on the inputs' device, and the call is
 enqueued on torch's current stream.  No arithmetic of the method is done in
 Python, and nothing falls back to the CPU.
+
+Calls that bring their output take a native path first (``_calls``, csrc/python_calls.cpp), which reads the tensors
+and launches without ctypes; whatever it does not take comes back as -1 and goes through the wrapper below it, whose
+checks then say what is wrong.
 """
 from __future__ import annotations
 
@@ -50,7 +54,10 @@ _SIGNATURES = {
     "bnn_unpack_i8": (_int, [_ptr, _i64, _i64, _i64, _ptr, _i64, _ptr]),
 }
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 _lib = None
+_calls = None            # the native path, bound when the library is loaded
 
 
 class BnnError(RuntimeError):
@@ -66,7 +73,7 @@ def lib_path() -> str:
 
 def load_library():
     """Loads libbnn_hip.so (built in-tree by ``build.build_library``).  Raises if absent."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise ImportError(
@@ -77,6 +84,13 @@ def load_library():
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
+        if _raw_stream is not None:
+            try:
+                from . import _calls as calls
+            except ImportError as e:
+                raise ImportError("the native call path is not built; run `python -m paper_1602_02830_amd.build`") from e
+            calls.bind({name: ctypes.cast(getattr(lib, name), _ptr).value for name in _SIGNATURES}, _raw_stream)
+            _calls = calls
         _lib = lib
     return _lib
 
@@ -90,7 +104,11 @@ def _check(fn: str, status: int):
         raise BnnError(fn, status)
 
 
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+def _took(fn: str, status: int) -> bool:
+    """Whether the native path took the call (and launched it): False for -1, raises for a status of the library."""
+    if status > 0:
+        raise BnnError(fn, status)
+    return status == 0
 
 
 def _stream(t: torch.Tensor):
@@ -137,6 +155,10 @@ def _alloc_words(rows: int, kw: int, device, ld: int | None = None) -> torch.Ten
 
 def pack_sign(x: torch.Tensor, out: torch.Tensor | None = None, ld_out: int | None = None) -> torch.Tensor:
     """bnn_pack_sign: float32 [rows][cols] -> packed int32 words [rows][ceil(cols/32)]."""
+    if out is not None and _calls is not None:
+        st = _calls.pack_sign(x, out)
+        if st == 0 or _took("bnn_pack_sign", st):
+            return out
     lib = load_library()
     _dev(x, torch.float32, "x")
     rows, cols = x.shape
@@ -152,6 +174,10 @@ def pack_sign(x: torch.Tensor, out: torch.Tensor | None = None, ld_out: int | No
 def xnor_gemm(A: torch.Tensor, B: torch.Tensor, K: int, out: torch.Tensor | None = None,
               kernel: int = KERNEL_AUTO) -> torch.Tensor:
     """bnn_xnor_gemm: packed A [M][Kw], packed B [N][Kw] -> int32 C [M][N]."""
+    if out is not None and _calls is not None:
+        st = _calls.xnor_gemm(A, B, K, out, kernel)
+        if st == 0 or _took("bnn_xnor_gemm", st):
+            return out
     lib = load_library()
     _dev(A, torch.int32, "A")
     _dev(B, torch.int32, "B")
@@ -190,6 +216,10 @@ def bn_fold(gamma, beta, mean, var, eps: float, K: int):
 def bn_sign_pack(C: torch.Tensor, thr: torch.Tensor, flip_bits: torch.Tensor,
                  out: torch.Tensor | None = None, ld_out: int | None = None) -> torch.Tensor:
     """bnn_bn_sign_pack: int32 C [M][N] + folded thresholds -> packed bits [M][ceil(N/32)]."""
+    if out is not None and _calls is not None:
+        st = _calls.bn_sign_pack(C, thr, flip_bits, out)
+        if st == 0 or _took("bnn_bn_sign_pack", st):
+            return out
     lib = load_library()
     _dev(C, torch.int32, "C")
     M, N = C.shape
@@ -210,6 +240,10 @@ def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
                            out: torch.Tensor | None = None, ld_out: int | None = None,
                            kernel: int = KERNEL_AUTO) -> torch.Tensor:
     """bnn_xnor_gemm_bn_sign_pack: packed A [M][Kw], packed B [N][Kw], thresholds -> packed bits [M][ceil(N/32)]."""
+    if out is not None and _calls is not None:
+        st = _calls.xnor_gemm_bn_sign_pack(A, B, K, thr, flip_bits, out, kernel)
+        if st == 0 or _took("bnn_xnor_gemm_bn_sign_pack", st):
+            return out
     lib = load_library()
     _dev(A, torch.int32, "A")
     _dev(B, torch.int32, "B")
@@ -238,6 +272,10 @@ def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
 
 def pack_bitplanes(x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_pack_bitplanes: uint8 [rows][cols] -> packed planes int32 [rows][8*ceil(cols/32)] (word 8*w + p)."""
+    if out is not None and _calls is not None:
+        st = _calls.pack_bitplanes(x, out)
+        if st == 0 or _took("bnn_pack_bitplanes", st):
+            return out
     lib = load_library()
     _dev(x, torch.uint8, "x")
     rows, cols = x.shape
@@ -252,6 +290,10 @@ def pack_bitplanes(x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Te
 
 def bitplane_gemm(Xp: torch.Tensor, B: torch.Tensor, K: int, out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_bitplane_gemm: bit planes Xp [M][8*Kw], packed +-1 rows B [N][Kw] -> int32 [M][N] = x @ w^T."""
+    if out is not None and _calls is not None:
+        st = _calls.bitplane_gemm(Xp, B, K, out)
+        if st == 0 or _took("bnn_bitplane_gemm", st):
+            return out
     lib = load_library()
     _dev(Xp, torch.int32, "Xp")
     _dev(B, torch.int32, "B")
@@ -267,6 +309,10 @@ def bitplane_gemm(Xp: torch.Tensor, B: torch.Tensor, K: int, out: torch.Tensor |
 def bitplane_gemm_bn_sign_pack(Xp: torch.Tensor, B: torch.Tensor, K: int, thr: torch.Tensor, flip_bits: torch.Tensor,
                                out: torch.Tensor | None = None, ld_out: int | None = None) -> torch.Tensor:
     """bnn_bitplane_gemm_bn_sign_pack: first layer on 8-bit inputs, fused with Sign(BatchNorm)."""
+    if out is not None and _calls is not None:
+        st = _calls.bitplane_gemm_bn_sign_pack(Xp, B, K, thr, flip_bits, out)
+        if st == 0 or _took("bnn_bitplane_gemm_bn_sign_pack", st):
+            return out
     lib = load_library()
     _dev(Xp, torch.int32, "Xp")
     _dev(B, torch.int32, "B")
@@ -289,6 +335,10 @@ def bitplane_gemm_bn_sign_pack(Xp: torch.Tensor, B: torch.Tensor, K: int, thr: t
 def conv_im2col_pack(x_bits: torch.Tensor, Cin: int, kh: int = 3, kw: int = 3, stride: int = 1, pad: int = 1,
                      out: torch.Tensor | None = None, ld_out: int | None = None) -> torch.Tensor:
     """bnn_conv_im2col_pack: packed NHWC int32 [B][H][W][ceil(Cin/32)] -> [B*Ho*Wo][ceil(kh*kw*Cin/32)]."""
+    if out is not None and _calls is not None:
+        st = _calls.conv_im2col_pack(x_bits, Cin, kh, kw, stride, pad, out)
+        if st == 0 or _took("bnn_conv_im2col_pack", st):
+            return out
     lib = load_library()
     if not x_bits.is_cuda or x_bits.dtype != torch.int32 or x_bits.dim() != 4 or not x_bits.is_contiguous():
         raise ValueError("x_bits must be a contiguous int32 device tensor [B][H][W][ceil(Cin/32)]")
@@ -317,6 +367,10 @@ def _check_nhwc_bits(x_bits: torch.Tensor, Cin: int):
 def conv_xnor(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor, kh: int = 3, kw: int = 3, stride: int = 1,
               pad: int = 1, out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_conv_xnor: packed NHWC input, packed filters [Cout][kh*kw*Cin/32] -> int32 [B*Ho*Wo][Cout]."""
+    if out is not None and _calls is not None:
+        st = _calls.conv_xnor(x_bits, Cin, w_bits, kh, kw, stride, pad, out)
+        if st == 0 or _took("bnn_conv_xnor", st):
+            return out
     lib = load_library()
     _check_nhwc_bits(x_bits, Cin)
     _dev(w_bits, torch.int32, "w_bits")
@@ -335,6 +389,10 @@ def conv_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor, thr:
                       flip_bits: torch.Tensor, kh: int = 3, kw: int = 3, stride: int = 1, pad: int = 1,
                       out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_conv_bn_sign_pack: binary conv + Sign(BatchNorm) -> packed bits [B*Ho*Wo][ceil(Cout/32)]."""
+    if out is not None and _calls is not None:
+        st = _calls.conv_bn_sign_pack(x_bits, Cin, w_bits, kh, kw, stride, pad, thr, flip_bits, out)
+        if st == 0 or _took("bnn_conv_bn_sign_pack", st):
+            return out
     lib = load_library()
     _check_nhwc_bits(x_bits, Cin)
     _dev(w_bits, torch.int32, "w_bits")
@@ -362,6 +420,10 @@ def conv_pool_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor,
     """bnn_conv_pool_bn_sign_pack: binary conv + max pooling + Sign(BatchNorm) in one launch ->
     packed bits [B*(Ho/pool)*(Wo/pool)][ceil(Cout/32)].  Raises BnnError with status 3 (unsupported)
     for geometries the fused kernel does not take."""
+    if out is not None and _calls is not None:
+        st = _calls.conv_pool_bn_sign_pack(x_bits, Cin, w_bits, kh, kw, stride, pad, thr, flip_bits, out, pool)
+        if st == 0 or _took("bnn_conv_pool_bn_sign_pack", st):
+            return out
     lib = load_library()
     _check_nhwc_bits(x_bits, Cin)
     _dev(w_bits, torch.int32, "w_bits")
@@ -390,6 +452,10 @@ def conv_pool_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor,
 def maxpool_bits(x_bits: torch.Tensor, C: int, flip_bits: torch.Tensor | None, ph: int = 2, pw: int = 2,
                  stride: int = 2, out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_maxpool_bits: packed NHWC [B][H][W][Cw] -> [B][Hp][Wp][Cw]; OR where flip = 0, AND where flip = 1."""
+    if out is not None and _calls is not None:
+        st = _calls.maxpool_bits(x_bits, C, flip_bits, ph, pw, stride, out)
+        if st == 0 or _took("bnn_maxpool_bits", st):
+            return out
     lib = load_library()
     _check_nhwc_bits(x_bits, C)
     B, H, W, Cw = x_bits.shape

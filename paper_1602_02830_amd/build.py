@@ -66,6 +66,23 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
+PYTHON_CALLS_LIB = os.path.join(PKG, "_calls.so")
+
+
+def build_python_calls() -> str:
+    """Compiles the native call path of binding.py (csrc/python_calls.cpp) against torch's headers and libraries."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    import torch
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{sysconfig.get_paths()['include']}",
+          *(f"-isystem{p}" for p in cpp_extension.include_paths()), os.path.join(CSRC, "python_calls.cpp"),
+          "-o", PYTHON_CALLS_LIB, *(f"-L{p}" for p in cpp_extension.library_paths()), "-lc10", "-ltorch_cpu",
+          "-ltorch_python"])
+    return PYTHON_CALLS_LIB
+
+
 CLOCK_PROBE_LIB = os.path.join(PKG, "libbnn_clock_probe.so")
 
 
@@ -90,5 +107,6 @@ def build_c_abi_example() -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_python_calls())
     print(build_clock_probe())
     print(build_c_abi_example())

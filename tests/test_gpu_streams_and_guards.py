@@ -243,3 +243,123 @@ def test_unpack_i8_with_guards_on_two_streams():
         torch.cuda.synchronize()
         got = g.result_and_check()
         assert (got == want).all()        # +-1 for k < K, 0 for K <= k < ld_out
+
+
+# ---- the native call path against the ctypes wrappers it stands in front of --------------------------------
+
+def _call_forms():
+    """(name, function, arguments): calls the native path takes and calls it must leave to the wrappers, valid or not."""
+    g = torch.Generator().manual_seed(5)
+
+    def bits(rows, words, ld=None, dtype=torch.int32):
+        t = torch.randint(-2 ** 31, 2 ** 31 - 1, (rows, ld or words), generator=g, dtype=torch.int64).to(dtype).to(DEV)
+        return t[:, :words]
+
+    K, M, N = 161, 33, 70
+    a, w = bits(M, 6), bits(N, 6, 9)
+    thr, flip = torch.zeros(N, dtype=torch.int32, device=DEV), torch.zeros(3, dtype=torch.int32, device=DEV)
+    x = torch.randn(M, K, generator=g).to(DEV)
+    u8 = torch.randint(0, 256, (M, K), generator=g, dtype=torch.uint8).to(DEV)
+    planes = bits(M, 48)
+    maps, filt = bits(2 * 8 * 8, 4).reshape(2, 8, 8, 4), bits(N, 36)
+    out = lambda rows, cols, dtype=torch.int32: torch.full((rows, cols), -3, dtype=dtype, device=DEV)
+    sub = torch.nn.Parameter(torch.zeros(M, K, device=DEV), requires_grad=False)
+    forms = [
+        ("pack", bnn.pack_sign, (x,), lambda: out(M, 6)),
+        ("pack rows of a wider matrix", bnn.pack_sign, (x[::2, 3:101],), lambda: out(17, 4)),
+        ("pack one row", bnn.pack_sign, (x[:1],), lambda: out(1, 6)),
+        ("pack a parameter", bnn.pack_sign, (sub,), lambda: out(M, 6)),
+        ("pack a transposed matrix", bnn.pack_sign, (x.t(),), lambda: out(K, 2)),
+        ("pack float64", bnn.pack_sign, (x.double(),), lambda: out(M, 6)),
+        ("pack a CPU matrix", bnn.pack_sign, (x.cpu(),), lambda: out(M, 6)),
+        ("pack into too few words", bnn.pack_sign, (x,), lambda: out(M, 5)),
+        ("pack into floats", bnn.pack_sign, (x,), lambda: out(M, 6, torch.float32)),
+        ("pack one dimension", bnn.pack_sign, (x[0],), lambda: out(M, 6)),
+        ("product", bnn.xnor_gemm, (a, w, K), lambda: out(M, N)),
+        ("product, numpy K", bnn.xnor_gemm, (a, w, np.int64(K)), lambda: out(M, N)),
+        ("product, K beyond the rows", bnn.xnor_gemm, (a, w, 193), lambda: out(M, N)),
+        ("product, narrow output", bnn.xnor_gemm, (a, w, K), lambda: out(M, N - 1)),
+        ("product, K a text", bnn.xnor_gemm, (a, w, "161"), lambda: out(M, N)),
+        ("norm", bnn.bn_sign_pack, (bits(M, N), thr, flip), lambda: out(M, 3)),
+        ("norm, short thresholds", bnn.bn_sign_pack, (bits(M, N), thr[1:], flip), lambda: out(M, 3)),
+        ("norm, strided thresholds", bnn.bn_sign_pack, (bits(M, 35), thr[::2], flip[:2]), lambda: out(M, 2)),
+        ("layer", bnn.xnor_gemm_bn_sign_pack, (a, w, K, thr, flip), lambda: out(M, 3)),
+        ("layer, wide flips", bnn.xnor_gemm_bn_sign_pack, (a, w, K, thr, flip.long()), lambda: out(M, 3)),
+        ("planes", bnn.pack_bitplanes, (u8,), lambda: out(M, 48)),
+        ("planes of floats", bnn.pack_bitplanes, (x,), lambda: out(M, 48)),
+        ("bytes product", bnn.bitplane_gemm, (planes, w, K), lambda: out(M, N)),
+        ("bytes layer", bnn.bitplane_gemm_bn_sign_pack, (planes, w, K, thr, flip), lambda: out(M, 3)),
+        ("lowering", bnn.conv_im2col_pack, (maps, 128), lambda: out(128, 36)),
+        ("lowering, other channels", bnn.conv_im2col_pack, (maps, 64), lambda: out(128, 36)),
+        ("conv", bnn.conv_xnor, (maps, 128, filt), lambda: out(128, N)),
+        ("conv layer", bnn.conv_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(128, 3)),
+        ("conv layer, stride 0", bnn.conv_bn_sign_pack, (maps, 128, filt, thr, flip, 3, 3, 0), lambda: out(128, 3)),
+        ("conv layer, transposed map", bnn.conv_bn_sign_pack, (maps.transpose(1, 2), 128, filt, thr, flip), lambda: out(128, 3)),
+        ("pooled layer", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(32, 3)),
+        ("pooled layer, wrong rows", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(31, 3)),
+        ("pooled layer, window 3", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip, 3, 3, 1, 1, 3), lambda: out(8, 3)),
+        ("pooling", bnn.maxpool_bits, (maps, 128, None), lambda: out(32, 4).view(2, 4, 4, 4)),
+        ("pooling, flips", bnn.maxpool_bits, (maps, 128, bits(1, 4)[0]), lambda: out(32, 4).view(2, 4, 4, 4)),
+        ("pooling, wide window", bnn.maxpool_bits, (maps, 128, None, 9, 9), lambda: out(32, 4).view(2, 4, 4, 4)),
+    ]
+    return forms
+
+
+def test_native_calls_do_what_the_wrappers_do(monkeypatch):
+    """Every wrapper with and without the native path: the same output and nothing else written, or the same exception."""
+    from paper_1602_02830_amd import binding
+    bnn.load_library()
+    native = binding._calls
+    assert native is not None
+
+    def outcome(fn, args, make):
+        o = make()
+        try:
+            r = fn(*args, out=o)
+            torch.cuda.synchronize()
+            assert r is o
+            return "ok", o.cpu()
+        except Exception as e:                     # whatever the wrapper raises is what is compared
+            torch.cuda.synchronize()
+            assert (o == -3).all()
+            return type(e), str(e)
+
+    seen = set()
+    for name, fn, args, make in _call_forms():
+        with_native = outcome(fn, args, make)
+        monkeypatch.setattr(binding, "_calls", None)
+        without = outcome(fn, args, make)
+        monkeypatch.setattr(binding, "_calls", native)
+        assert with_native[0] == without[0], name
+        assert torch.equal(with_native[1], without[1]) if with_native[0] == "ok" else with_native[1] == without[1], name
+        seen.add(with_native[0] if with_native[0] == "ok" else with_native[0].__name__)
+    assert {"ok", "ValueError", "BnnError"} <= seen
+
+
+def test_native_calls_use_the_current_stream():
+    """A launch through the native path runs on torch's current stream: behind work that is queued there, inside a capture."""
+    x = torch.randn(64, 1024, device=DEV)
+    want = bnn.pack_sign(x)
+    out = torch.zeros_like(want)
+    s = torch.cuda.Stream()
+    src = torch.zeros_like(x)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        big = torch.randn(4096, 4096, device=DEV)
+        for _ in range(20):
+            big = big @ big * 1e-3
+        src.copy_(x)
+        bnn.pack_sign(src, out=out)
+    s.synchronize()
+    assert torch.equal(out, want)
+    out.zero_()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        bnn.pack_sign(x, out=out)
+    torch.cuda.synchronize()
+    assert (out == 0).all()
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
