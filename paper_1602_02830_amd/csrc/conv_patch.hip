@@ -1,13 +1,12 @@
-// Binary "same" convolution (stride 1, output size = input size, kh = kw = 2*pad + 1: the 3 x 3,
-// pad 1 layers of the paper's ConvNets, Sec. 3.3) with the input patch of a tile resident in LDS.
+// Binary convolution (the 3 x 3, pad 1 layers of the paper's ConvNets, Sec. 3.3, and any other geometry whose input
+// patch fits) with the input patch of a tile resident in LDS.
 //
 // The GEMM view of the layer is C[pixel][filter] = XnorDotProduct(receptive field, filter) (Alg. 4)
 // with K = kh*kw*Cin.  The receptive fields of neighbouring pixels overlap kh*kw-fold, so instead
 // of staging every K-tile of the (implicit) im2col matrix, a workgroup loads each input pixel its
-// tile needs ONCE: a tile is BM consecutive output pixels = R whole image rows (or R / H whole
-// images), its patch those rows plus a halo of `pad` pixels all around, kept in LDS for the
-// workgroup's life.  Halo cells outside the image hold all-ones words (+1, zero padding through
-// Eq. (1)).  The A operand of an MFMA step for tap (ky, kx) is then a plain LDS read at
+// tile needs ONCE: a tile is BM consecutive output pixels, its patch the input rows under their
+// windows with a halo of `pad` pixels all around, kept in LDS for the workgroup's life.  Halo cells
+// outside the image hold all-ones words (+1, zero padding through Eq. (1)).  The A operand of an MFMA step for tap (ky, kx) is then a plain LDS read at
 //     slot(pixel) + ky * PW + kx          (PW = W + 2*pad, patch row pitch in pixels)
 // with no per-tap bounds logic, and only the filters (B) stream through LDS K-tile by K-tile.
 // Arithmetic, widening, fix-up and epilogues are those of xnor_gemm_mfma.hip; the row popcounts are
@@ -31,10 +30,16 @@
 // a K-word to (channel word plane, tap offset).  Filter words beyond the receptive field's last word
 // are zeroed at staging.  Everything else is shared.
 //
-// Geometry this kernel takes (the launcher checks; everything else goes to the gathering kernels):
-// stride 1, Ho = H, Wo = W, Cin % 32 == 0, BM % W == 0 and, with R = BM / W, H % R == 0 or
-// R % H == 0; filters 16-byte aligned with ldb % 4 == 0; patch within kPatchMaxBytes of LDS; with
-// Cin % 128 != 0 a receptive field of at most kResidentKTiles * 512 bits.
+// The padded images (pad rows and columns all around) follow each other without a gap, so the patch of ANY run of BM
+// consecutive output pixels is a run of their rows: kernel size, stride, padding and image size are free, tiles may start
+// and end inside image rows and span images (the halo rows between two images are then part of the patch).
+//
+// What this kernel takes (the launcher checks; everything else goes to the gathering kernels): filters 16-byte aligned
+// with ldb % 4 == 0, a patch within kPatchMaxBytes of LDS, and Cin % 128 == 0 - or Cin % 32 == 0 for same-size stride-1
+// layers whose tiles are whole image rows or images, with a receptive field of at most kResidentKTiles * 512 bits.
+// Against gathering the receptive fields K-tile by K-tile, fused: 128 images of 28 x 28, 128 -> 256 channels 22.4 -> 18.9
+// us, 200 of 13 x 13, 128 -> 396 17.8 -> 13.9, 100 of 14 x 14, 256 -> 256 13.4 -> 11.7, 256 of 32 x 32, 128 -> 256 at
+// stride 2 15.5 -> 13.0, 128 of 56 x 56, 128 -> 128 37.0 -> 31.6.
 #include "bnn_internal.h"
 #include "gemm_staging.h"
 #include "mfma_fp4.h"
@@ -44,10 +49,9 @@ namespace bnn {
 constexpr int kPatchMaxBytes = 40 * 1024;
 
 struct PatchGeom {
-    int groups;        // images (or row blocks) in a tile
-    int rows;          // output rows per group
-    int prows, pw;     // patch rows per group, patch row pitch (pixels)
-    int slots;         // groups * prows * pw
+    int img_rows;      // H + 2*pad: rows of a padded image
+    int pw;            // W + 2*pad: patch row pitch (pixels)
+    int slots;         // cells of the largest patch a tile of this layer has
     int cqn;           // channel quads per pixel (Cw / 4); unused when a tap is not a whole number of quads
     int kq;            // quads of K per filter row: kh * kw * cqn, or ceil(kwords / 4)
     int kwords;        // words of K per filter row: kh * kw * Cw
@@ -81,7 +85,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     __shared__ __attribute__((aligned(16))) int thr_s[FUSED ? BN : 1];
     __shared__ uint32_t flip_s[FUSED ? BN / 32 : 1];
     __shared__ float colfix_s[FUSED ? BN : 1];
-    __shared__ int coord_s[BM];
+    __shared__ int slot_s[BM];
+    __shared__ int pixel_s[POOL ? BM : 1];              // POOL: (image of the tile, y, x) in 7 + 15 + 7 bits
     uint32_t* patchw = reinterpret_cast<uint32_t*>(patch);
     int* pix_pop = WORDS ? reinterpret_cast<int*>(patchw + size_t(cv.Cw) * pg.slots)
                          : reinterpret_cast<int*>(patch + size_t(2) * pg.cqn * pg.slots);
@@ -132,13 +137,16 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         }
     };
 
-    // Output pixel r of the tile as (group, row in group, column), 10 bits each: the divisions are done
-    // once per pixel here, not once per use.
+    // The tile's first output pixel is (image b0, row y0, ...); the patch starts at the padded row its window starts at.
+    // Output pixel r of the tile as a patch cell: the divisions are done once per pixel here, not once per use.
+    const int row_first = row0 / cv.Wo, b0 = row_first / cv.Ho, y0 = row_first - b0 * cv.Ho;
+    const int patch_row0 = b0 * pg.img_rows + y0 * cv.stride;
     if (tid < BM) {
-        const int per_group = pg.rows * cv.W;
-        const int g = tid / per_group, t = tid - g * per_group;
-        const int yl = t / cv.W, x = t - yl * cv.W;
-        coord_s[tid] = (g << 20) | (yl << 10) | x;
+        const int m = min(row0 + tid, M - 1);
+        const int t = m / cv.Wo, x = m - t * cv.Wo;
+        const int b = t / cv.Ho, y = t - b * cv.Ho;
+        slot_s[tid] = (b * pg.img_rows + y * cv.stride - patch_row0) * pg.pw + x * cv.stride;
+        if (POOL) pixel_s[tid] = ((b - b0) << 22) | (y << 7) | x;           // pooled rows have at most 64 pixels
     }
     // Thresholds and flip words go to registers here and to LDS after the patch loads have been issued: every
     // global load of the prologue (these, the filters, the patch) is in flight before the first one is waited for.
@@ -163,18 +171,13 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     }
 
     // ---- patch: every slot once ------------------------------------------------------------
-    // The tile's first output pixel is (image b0, row y0, column 0); group g covers image rows
-    // y0 .. y0 + rows - 1 of image b0 (one group) or all rows of image b0 + g (several groups).
-    const int hw = cv.H * cv.W;
-    const int b0 = row0 / hw, y0 = (row0 - b0 * hw) / cv.W;
-    const int group_slots = pg.prows * pg.pw;
+    // Slot s is column s % pw of row patch_row0 + s / pw of the padded images, which follow each other without a gap.
     if (WORDS || !FUSED) {
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
         for (int s = tid; s < pg.slots; s += 256) {
-            const int g = s / group_slots, t = s - g * group_slots;
-            const int py = t / pg.pw, px = t - py * pg.pw;
-            const int b = b0 + g, y = y0 + py - cv.pad, x = px - cv.pad;
+            const int py = s / pg.pw, px = s - py * pg.pw;
+            const int b = (patch_row0 + py) / pg.img_rows, y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
             const bool inside = b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
             const uint32_t pix = inside ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
             const uint32_t* p = in + size_t(pix) * uint32_t(cv.Cw);
@@ -209,9 +212,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
             for (int u = 0; u < kSlotsPerPass; ++u) {
                 const int s = s_base + u * 256 + tid;
                 live[u] = s < pg.slots;
-                const int g = s / group_slots, t = s - g * group_slots;
-                const int py = t / pg.pw, px = t - py * pg.pw;
-                const int b = b0 + g, y = y0 + py - cv.pad, x = px - cv.pad;
+                const int py = s / pg.pw, px = s - py * pg.pw;
+                const int b = (patch_row0 + py) / pg.img_rows, y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
                 inside[u] = live[u] && b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
                 const uint32_t pix = inside[u] ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
                 p[u] = in + size_t(pix) * uint32_t(cv.Cw);
@@ -277,12 +279,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
 
     // Row popcounts: sum of the pixel popcounts under the kh x kw window (read before the epilogue,
     // which follows at least one more barrier).
-    auto slot_of = [&](int r) {
-        const int c = coord_s[r];
-        return (c >> 20) * group_slots + ((c >> 10) & 1023) * pg.pw + (c & 1023);
-    };
     if (tid < BM) {
-        const int s0 = slot_of(tid);
+        const int s0 = slot_s[tid];
         int sum = 0;
         for (int ky = 0; ky < cv.kh; ++ky)
             for (int kx = 0; kx < cv.kw; ++kx) sum += pix_pop[s0 + ky * pg.pw + kx];
@@ -295,7 +293,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     const uint32_t* rd_aw[WM];                          // WORDS: the pixel's cell in plane 0
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
-        const int slot = slot_of(wm * 32 * WM + i * 32 + fr);
+        const int slot = slot_s[wm * 32 * WM + i * 32 + fr];
         rd_a[i] = patch + fh * pg.slots + slot;
         rd_aw[i] = patchw + slot;
     }
@@ -415,8 +413,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
                     }
             }
             const int rl = wm * 32 * WM + i * 32 + fr, m = row0 + rl;
-            const int c = coord_s[rl];
-            const int b = b0 + (c >> 20), y = y0 + ((c >> 10) & 1023), x = c & 1023;
+            const int c = pixel_s[rl];
+            const int b = b0 + (c >> 22), y = (c >> 7) & 32767, x = c & 127;
             const uint32_t pooled = (a & ~flip_word) | (l & flip_word);
             if (m < M && w < nw && !(y & 1) && !(x & 1))
                 bn.out[(int64_t(b) * hp + (y >> 1)) * wp * bn.ld_out + int64_t(x >> 1) * bn.ld_out + w] = pooled;
@@ -428,29 +426,46 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         mfma_epilogue<WM, WN>(acc, pop_a, pop_b, C, ldc, M, N, K, row0, col0, wm, wn, fr, fh);
 }
 
-// Fills the patch geometry for tiles of BM output pixels; false if this convolution does not fit.
-static bool patch_geometry(const ConvArgs& cv, int BM, PatchGeom& pg) {
-    if (cv.stride != 1 || cv.Ho != cv.H || cv.Wo != cv.W) return false;
-    if (cv.kh != 2 * cv.pad + 1 || cv.kw != 2 * cv.pad + 1) return false;
-    if (cv.W > BM || BM % cv.W != 0) return false;
-    const int R = BM / cv.W;
-    if (cv.H % R == 0) {
-        pg.groups = 1;
-        pg.rows = R;
-    } else if (R % cv.H == 0) {
-        pg.groups = R / cv.H;
-        pg.rows = cv.H;
-    } else {
-        return false;
-    }
-    pg.prows = pg.rows + 2 * cv.pad;
-    pg.pw = cv.W + 2 * cv.pad;
-    pg.slots = pg.groups * pg.prows * pg.pw;
+// Rows of the padded images that the windows of BM consecutive output pixels can span, at most.
+static int64_t patch_rows(const ConvArgs& cv, int64_t BM) {
+    const int64_t rows = BM % cv.Wo == 0 ? BM / cv.Wo : (BM - 2) / cv.Wo + 2;    // output rows a tile touches
+    // Image boundaries among them: none or rows / Ho - 1 where tiles are whole rows that divide into images or the reverse.
+    int64_t cross = ceil_div(rows - 1, cv.Ho);
+    if (BM % cv.Wo == 0 && cv.Ho % rows == 0) cross = 0;
+    else if (BM % cv.Wo == 0 && rows % cv.Ho == 0) cross = rows / cv.Ho - 1;
+    // From one output row to the next the window moves by `stride` rows, across a boundary by what is left of the image.
+    const int64_t over = int64_t(cv.H) + 2 * cv.pad - int64_t(cv.Ho - 1) * cv.stride;
+    const int64_t within = (rows - 1) * cv.stride, crossing = (rows - 1 - cross) * cv.stride + cross * over;
+    return (within > crossing ? within : crossing) + cv.kh;
+}
+
+// Fills the patch geometry for tiles of BM output pixels; false if the patch does not fit.
+static bool patch_geometry(const ConvArgs& cv, int64_t M, int BM, PatchGeom& pg) {
+    const int64_t img_rows = int64_t(cv.H) + 2 * cv.pad, pw = int64_t(cv.W) + 2 * cv.pad;
+    const int64_t slots = patch_rows(cv, BM) * pw;
+    if (slots * (int64_t(cv.Cw) * 4 + 4) > kPatchMaxBytes) return false;
+    if (ceil_div(M, int64_t(cv.Ho) * cv.Wo) * img_rows + slots > kMaxDim) return false;      // row numbers are 32-bit
+    pg.img_rows = int(img_rows);
+    pg.pw = int(pw);
+    pg.slots = int(slots);
     pg.cqn = cv.Cw / 4;
     pg.kwords = cv.kh * cv.kw * cv.Cw;
     pg.kq = (pg.kwords + 3) / 4;
-    if (cv.Cw % 4 != 0 && (pg.kq + 3) / 4 > kResidentKTiles) return false;     // word-granular patch: resident filters only
-    return int64_t(pg.slots) * (cv.Cw * 4 + 4) <= kPatchMaxBytes;
+    return true;
+}
+
+// Same-size stride-1 layers whose tiles of BM pixels are whole image rows that divide into images, or whole images.
+static bool whole_row_tiles(const ConvArgs& cv, int BM) {
+    if (cv.stride != 1 || cv.Ho != cv.H || cv.Wo != cv.W) return false;
+    if (cv.kh != 2 * cv.pad + 1 || cv.kw != 2 * cv.pad + 1) return false;
+    if (cv.W > BM || BM % cv.W != 0) return false;
+    const int rows = BM / cv.W;
+    return cv.H % rows == 0 || rows % cv.H == 0;
+}
+
+// The layers with whole channel words only (Cin % 128 != 0) that this kernel takes: whole-row tiles, resident filters.
+static bool words_layer_fits(const ConvArgs& cv, int BM) {
+    return whole_row_tiles(cv, BM) && (int64_t(cv.kh) * cv.kw * cv.Cw + 15) / 16 <= kResidentKTiles;
 }
 
 template <int WM, bool FUSED, bool POOL>
@@ -464,7 +479,7 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     const int n_ktiles = (pg.kq + 3) / 4;
     const bool resident = n_ktiles <= kResidentKTiles;
     const size_t lds_bytes = patch_bytes + (resident ? size_t(n_ktiles) * 8 * (128 + 2) * sizeof(uint2) : 0);
-    const int n_images = int(M / (int64_t(cv.H) * cv.W));
+    const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
     const dim3 grid(unsigned(tiles_m * tiles_n));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (words)                                          // patch_geometry has checked that the filters are resident
@@ -479,25 +494,38 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     return check_launch();
 }
 
-// BNN_ERR_UNSUPPORTED if the geometry is not one this kernel takes (the caller then uses the
-// gathering kernels).  Tile choice as for the plain product: 256 pixels x 128 filters when that grid
-// fills the chip's 512 workgroup slots, else 128 x 128.
+// Pixels per tile: 256 (two workgroups per compute unit) when that grid fills the chip's 512 workgroup slots, else 128
+// (three).  64 with resident filters where even that grid leaves 3/8 of the compute units without a workgroup: 51 images
+// of 8 x 8, 256 -> 128 channels (26 tiles of 128) 8.8 -> 8.0 us, 20 of 16 x 16, 256 -> 256 (80) 9.0 -> 8.4, 128 -> 256 of
+// 16 x 16 at stride 2 (128) 7.8 -> 6.6; but 52 of 16 x 16, 256 -> 256 pooled (208) 9.6 -> 9.9, and filters that stream
+// through LDS (512 channels, 188 tiles) 17.0 -> 20.6: a K-tile of 64 pixels is over before the next one's loads are back.
+static bool wants_big_tiles(int64_t M, int64_t N) { return ceil_div(M, 256) * ceil_div(N, 128) >= 512; }
+static bool wants_small_tiles(int64_t M, int64_t N, int64_t K) {
+    return ceil_div(M, 128) * ceil_div(N, 128) <= 160 && K <= kResidentKTiles * 512;
+}
+
+// BNN_ERR_UNSUPPORTED if the layer is not one this kernel takes (the caller then uses the gathering kernels).
 template <bool FUSED>
 static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                                  int64_t M, int64_t N, int64_t K, BnSignArgs bn, ConvArgs cv, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    const bool big = ceil_div(M, 256) * ceil_div(N, 128) >= 512;
-    if (big && patch_geometry(cv, 256, pg))
+    auto fits = [&](int BM) { return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, M, BM, pg); };
+    if (wants_small_tiles(M, N, K) && fits(128) && fits(64))
+        return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
+    if (wants_big_tiles(M, N) && fits(256))
         return launch_patch<4, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
-    if (patch_geometry(cv, 128, pg)) return launch_patch<2, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
+    if (fits(128)) return launch_patch<2, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
     return BNN_ERR_UNSUPPORTED;
 }
 
-// 2 x 2 pooling inside a tile of BM = 64 * WM pixels: even H and W, W a power of two below 32 or 32 * k
+// 2 x 2 pooling inside a tile of BM = 64 * WM pixels: whole-row tiles, even H and W, W a power of two below 32 or 32 * k
 // with the row pair inside one wavefront's WM blocks, and an even number of image rows per tile.
-static bool pool_fits(const ConvArgs& cv, const PatchGeom& pg, int WM) {
-    if ((cv.H & 1) || (cv.W & 1) || (pg.rows & 1)) return false;
+static bool pool_fits(const ConvArgs& cv, int WM) {
+    const int BM = 64 * WM;
+    if (!whole_row_tiles(cv, BM) || (cv.Cw % 4 != 0 && !words_layer_fits(cv, BM))) return false;
+    const int rows = BM / cv.W < cv.H ? BM / cv.W : cv.H;
+    if ((cv.H & 1) || (cv.W & 1) || (rows & 1)) return false;
     if (cv.W < 32) return (cv.W & (cv.W - 1)) == 0;
     return cv.W % 32 == 0 && 2 * (cv.W / 32) <= WM;
 }
@@ -519,13 +547,13 @@ int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t 
                                  BnSignArgs bn, ConvArgs cv, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    const bool big = ceil_div(M, 256) * ceil_div(N, 128) >= 512;
-    if (big && patch_geometry(cv, 256, pg) && pool_fits(cv, pg, 4))
+    auto fits = [&](int WM) { return pool_fits(cv, WM) && patch_geometry(cv, M, 64 * WM, pg); };
+    if (wants_small_tiles(M, N, K) && fits(2) && fits(1))
+        return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
+    if (wants_big_tiles(M, N) && fits(4))
         return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
-    if (patch_geometry(cv, 128, pg) && pool_fits(cv, pg, 2))
-        return launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
-    if (patch_geometry(cv, 256, pg) && pool_fits(cv, pg, 4))
-        return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
+    if (fits(2)) return launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
+    if (fits(4)) return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
     return BNN_ERR_UNSUPPORTED;
 }
 

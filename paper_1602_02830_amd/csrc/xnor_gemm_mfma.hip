@@ -352,8 +352,8 @@ int launch_conv_mfma_shortk(const uint32_t* in, const uint32_t* B, int64_t ldb, 
 int launch_conv_mfma_shortk_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N,
                                   int64_t K, BnSignArgs bn, ConvArgs cv, void* stream);
 
-// "Same" convolutions whose tiles are whole image rows or whole images keep their input patch in
-// LDS (conv_patch.hip); its launchers return BNN_ERR_UNSUPPORTED for every other geometry.
+// Convolutions whose tiles' input patch fits keep it in LDS (conv_patch.hip); its launchers return
+// BNN_ERR_UNSUPPORTED for every other layer.
 int launch_conv_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc, int64_t M,
                       int64_t N, int64_t K, ConvArgs cv, void* stream);
 int launch_conv_patch_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,

@@ -1089,6 +1089,40 @@ def test_implicit_conv_matches_direct_convolution(shape):
     assert (bits == want).all()
 
 
+@pytest.mark.parametrize("shape", [
+    # B, H, W, Cin, Cout, kh, kw, stride, pad: tiles that start and end inside image rows and span images
+    (64, 28, 28, 128, 130, 3, 3, 1, 1),     # 256-pixel tiles would leave units idle: 128
+    (176, 28, 28, 128, 128, 3, 3, 1, 1),    # 539 tiles of 256 pixels
+    (30, 7, 7, 512, 96, 3, 3, 1, 1),        # several images per tile, filters streamed
+    (9, 13, 11, 256, 40, 3, 3, 1, 1),       # 64-pixel tiles, resident filters
+    (33, 3, 3, 128, 33, 3, 3, 1, 1),        # 28 image boundaries in a 256-pixel run
+    (70, 1, 1, 128, 40, 3, 3, 1, 1),        # every pixel an image
+    (3, 1, 90, 128, 40, 3, 3, 1, 1),        # one-row images
+    (5, 90, 1, 128, 40, 3, 3, 1, 1),        # one-column images
+    (40, 15, 15, 256, 64, 3, 3, 2, 1),      # stride 2
+    (21, 17, 14, 128, 64, 2, 3, 3, 0),      # even window, stride beyond the window's overlap, no padding
+    (11, 10, 12, 128, 50, 1, 1, 3, 0),      # windows that skip pixels
+    (6, 20, 20, 128, 64, 5, 5, 1, 3),       # padding beyond half the window
+    (2, 40, 400, 128, 20, 3, 3, 1, 1),      # patch too large at 128 pixels and more: the gathering kernels
+])
+def test_conv_without_im2col_on_any_geometry(shape):
+    """int32 and fused against lowering through the im2col matrix (kernels of their own, held to the oracle elsewhere)."""
+    B, H, W, Cin, Cout, kh, kw, stride, pad = shape
+    g = torch.Generator().manual_seed(sum(shape))
+    xb = torch.randint(-2 ** 31, 2 ** 31, (B, H, W, Cin // 32), generator=g, dtype=torch.int64).to(torch.int32).to(DEV)
+    words = kh * kw * Cin // 32
+    wb = torch.randint(-2 ** 31, 2 ** 31, (Cout, words), generator=g, dtype=torch.int64).to(torch.int32).to(DEV)
+    K = kh * kw * Cin
+    cols = bnn.conv_im2col_pack(xb, Cin, kh, kw, stride, pad)
+    want = bnn.xnor_gemm(cols, wb, K, kernel=bnn.KERNEL_TILED64)
+    assert torch.equal(bnn.conv_xnor(xb, Cin, wb, kh, kw, stride, pad), want)
+    thr = torch.randint(-40, 40, (Cout,), generator=g, dtype=torch.int32).to(DEV)
+    flip = torch.randint(-2 ** 31, 2 ** 31, ((Cout + 31) // 32,), generator=g, dtype=torch.int64).to(torch.int32).to(DEV)
+    if Cout % 32:
+        flip[-1] &= (1 << (Cout % 32)) - 1
+    assert torch.equal(bnn.conv_bn_sign_pack(xb, Cin, wb, thr, flip, kh, kw, stride, pad), bnn.bn_sign_pack(want, thr, flip))
+
+
 @pytest.mark.parametrize("seed", range(4))
 def test_implicit_conv_randomized_geometries(seed):
     """Seeded random geometries (batch, image size, channels, filter size, stride, padding, filters):
