@@ -69,7 +69,7 @@ constexpr int kWordsPerTile = 4;              // K-words per staged tile = 2 pai
 template <int WI, int WAVES, bool FUSED>
 __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     constexpr int T = 64 * WAVES, BM = 32 * WI, BN = T;    // one staging thread per column of B
     constexpr int L = BM * kWordsPerTile / T;              // A words (32 elements, 8 plane words) a thread stages per tile
     constexpr int ROWS = T / kWordsPerTile;                // rows of a staging pass: 4 neighbouring lanes take the words of one
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     __shared__ __attribute__((aligned(16))) int thr_s[FUSED ? BN : 4];
 
     int tile_m, tile_n;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of_block(blockIdx.x, tiles, tile_m, tile_n);
     const int row0 = tile_m * BM, col0 = tile_n * BN;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -357,13 +357,13 @@ constexpr int kSplitBatch = 2;                // word pairs a wavefront loads at
 template <bool FUSED>
 __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     __shared__ int4 part[kSplitWaves][4][kWave];           // [wavefront][accumulator registers 4g .. 4g + 3][lane]
     __shared__ __attribute__((aligned(16))) int sum_part[kSplitWaves][kWave];   // [0, 32) row sums of A, [32, 64) 256 * popcounts of B
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 31, fh = lane >> 5;
     int tm, tn;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tile_of_block(blockIdx.x, tiles, tm, tn);
     const int row0 = tm * 32, col0 = tn * 32;
     const int kw = (K + 31) >> 5;
     const uint32_t tmask = tail_mask(K);
@@ -475,7 +475,7 @@ static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int6
     const int64_t tiles_m = ceil_div(M, 32 * WI), tiles_n = ceil_div(N, 64 * WAVES);
     if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WAVES, FUSED>), dim3(unsigned(tiles_m * tiles_n)), dim3(64 * WAVES), 0,
-                       s, Xp, ldx, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn);
+                       s, Xp, ldx, B, ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     return check_launch();
 }
 
@@ -498,7 +498,7 @@ static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int
     const int64_t small_m = ceil_div(M, 32), small_n = ceil_div(N, 32);
     if ((K <= 96 && small_m * small_n <= kMaxDim) || small_m * small_n <= kSplitMaxTiles) {
         hipLaunchKernelGGL(planes::bitplane_gemm_split_kernel<FUSED>, dim3(unsigned(small_m * small_n)), dim3(256), 0, s, Xp,
-                           ldx, B, ldb, C, ldc, int(M), int(N), int(K), int(small_m), int(small_n), bn);
+                           ldx, B, ldb, C, ldc, int(M), int(N), int(K), tile_map(small_m, small_n), bn);
         return check_launch();
     }
     if (K <= 96) return BNN_ERR_UNSUPPORTED;               // more than 2^41 outputs

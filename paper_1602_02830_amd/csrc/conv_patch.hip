@@ -55,6 +55,7 @@ struct PatchGeom {
     int cqn;           // channel quads per pixel (Cw / 4); unused when a tap is not a whole number of quads
     int kq;            // quads of K per filter row: kh * kw * cqn, or ceil(kwords / 4)
     int kwords;        // words of K per filter row: kh * kw * Cw
+    FastDiv by_wo, by_ho, by_img_rows, by_pw;
 };
 
 // Word offset of the K-word table behind the word-granular patch ([Cw][slots] words + slots pixel popcounts).
@@ -69,7 +70,7 @@ constexpr int kResidentKTiles = 5;
 template <int WM, bool FUSED, bool POOL, bool BRES, bool WORDS>
 __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, int32_t* __restrict__ C,
-    int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn, ConvArgs cv, PatchGeom pg,
+    int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn, ConvArgs cv, PatchGeom pg,
     int n_images) {
     constexpr int WN = 2, BM = 64 * WM, BN = 64 * WN;
     constexpr int PLANE_B = BN + 2;                     // 8-byte slots per B plane (2 pad slots)
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
                            : patch + size_t(2) * pg.cqn * pg.slots + (pg.slots + 1) / 2;
 
     int tile_m, tile_n;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of_block(blockIdx.x, tiles, tile_m, tile_n);
     const int row0 = tile_m * BM, col0 = tile_n * BN;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -139,12 +140,12 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
 
     // The tile's first output pixel is (image b0, row y0, ...); the patch starts at the padded row its window starts at.
     // Output pixel r of the tile as a patch cell: the divisions are done once per pixel here, not once per use.
-    const int row_first = row0 / cv.Wo, b0 = row_first / cv.Ho, y0 = row_first - b0 * cv.Ho;
+    const int row_first = pg.by_wo(row0), b0 = pg.by_ho(row_first), y0 = row_first - b0 * cv.Ho;
     const int patch_row0 = b0 * pg.img_rows + y0 * cv.stride;
     if (tid < BM) {
         const int m = min(row0 + tid, M - 1);
-        const int t = m / cv.Wo, x = m - t * cv.Wo;
-        const int b = t / cv.Ho, y = t - b * cv.Ho;
+        const int t = pg.by_wo(m), x = m - t * cv.Wo;
+        const int b = pg.by_ho(t), y = t - b * cv.Ho;
         slot_s[tid] = (b * pg.img_rows + y * cv.stride - patch_row0) * pg.pw + x * cv.stride;
         if (POOL) pixel_s[tid] = ((b - b0) << 22) | (y << 7) | x;           // pooled rows have at most 64 pixels
     }
@@ -176,8 +177,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
         for (int s = tid; s < pg.slots; s += 256) {
-            const int py = s / pg.pw, px = s - py * pg.pw;
-            const int b = (patch_row0 + py) / pg.img_rows, y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+            const int py = pg.by_pw(s), px = s - py * pg.pw;
+            const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
             const bool inside = b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
             const uint32_t pix = inside ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
             const uint32_t* p = in + size_t(pix) * uint32_t(cv.Cw);
@@ -212,8 +213,8 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
             for (int u = 0; u < kSlotsPerPass; ++u) {
                 const int s = s_base + u * 256 + tid;
                 live[u] = s < pg.slots;
-                const int py = s / pg.pw, px = s - py * pg.pw;
-                const int b = (patch_row0 + py) / pg.img_rows, y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+                const int py = pg.by_pw(s), px = s - py * pg.pw;
+                const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
                 inside[u] = live[u] && b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
                 const uint32_t pix = inside[u] ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
                 p[u] = in + size_t(pix) * uint32_t(cv.Cw);
@@ -451,6 +452,10 @@ static bool patch_geometry(const ConvArgs& cv, int64_t M, int BM, PatchGeom& pg)
     pg.cqn = cv.Cw / 4;
     pg.kwords = cv.kh * cv.kw * cv.Cw;
     pg.kq = (pg.kwords + 3) / 4;
+    pg.by_wo = fast_div(cv.Wo);
+    pg.by_ho = fast_div(cv.Ho);
+    pg.by_img_rows = fast_div(img_rows);
+    pg.by_pw = fast_div(pw);
     return true;
 }
 
@@ -484,13 +489,13 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (words)                                          // patch_geometry has checked that the filters are resident
         hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, true, true>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn, cv, pg, n_images);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
     else if (resident)
         hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, true, false>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn, cv, pg, n_images);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
     else
         hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, false, false>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn, cv, pg, n_images);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
     return check_launch();
 }
 

@@ -82,23 +82,49 @@ __device__ inline uint4 zero_unless(bool keep, uint4 v) {
     return make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
 }
 
+// Division of n < 2^31 by a number that the host knows: a multiply-high, an add and a shift (Granlund & Montgomery,
+// "Division by Invariant Integers using Multiplication") instead of the 30 dependent operations of an integer division,
+// which a workgroup would go through several times in a row before it can issue its first load.
+struct FastDiv {
+    uint32_t magic, shift;
+    __device__ inline int operator()(int n) const {
+        return int((__umulhi(uint32_t(n), magic) + uint32_t(n)) >> shift);
+    }
+};
+
+inline FastDiv fast_div(int64_t d) {
+    if (d > kMaxDim) d = kMaxDim;      // n / d is 0 either way
+    uint32_t l = 0;
+    while ((int64_t(1) << l) < d) ++l;
+    return FastDiv{uint32_t((uint64_t((int64_t(1) << l) - d) << 32) / uint64_t(d) + 1), l};
+}
+
 // Maps the hardware's round-robin placement of consecutive workgroups on the 8
 // accelerator dies (each with its own L2) to compact panels of tiles: die d
 // gets the contiguous range [d*per, (d+1)*per) of logical tile ids, and
 // logical ids walk the tile grid in column-major bands of 8 tile-rows, so the
 // tiles resident on one die at a time share a few A panels and B panels.
-__device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int total = tiles_m * tiles_n;
-    constexpr int kDies = 8;
+constexpr int kDies = 8, kBand = 8;
+
+struct TileMap {
+    int tiles_m, tiles_n;
+    int per_die;
+    FastDiv band;      // by the tiles of a whole band
+    FastDiv tail;      // by the rows of the last, partial band
+};
+
+inline TileMap tile_map(int64_t tiles_m, int64_t tiles_n) {
+    return TileMap{int(tiles_m), int(tiles_n), int(tiles_m * tiles_n / kDies), fast_div(kBand * tiles_n),
+                   fast_div(tiles_m % kBand ? tiles_m % kBand : kBand)};
+}
+
+__device__ inline void tile_of_block(int bid, const TileMap& t, int& tm, int& tn) {
     int logical = bid;
-    const int per = total / kDies;
-    if (bid < per * kDies) logical = (bid % kDies) * per + bid / kDies;
-    constexpr int kBand = 8;
-    const int band_tiles = kBand * tiles_n;
-    const int band = logical / band_tiles;
-    const int in_band = logical - band * band_tiles;
-    const int rows_in_band = min(kBand, tiles_m - band * kBand);
-    tn = in_band / rows_in_band;
+    if (bid < t.per_die * kDies) logical = (bid % kDies) * t.per_die + bid / kDies;
+    const int band = t.band(logical);
+    const int in_band = logical - band * kBand * t.tiles_n;
+    const int rows_in_band = min(kBand, t.tiles_m - band * kBand);
+    tn = rows_in_band == kBand ? in_band / kBand : t.tail(in_band);
     tm = band * kBand + (in_band - tn * rows_in_band);
 }
 

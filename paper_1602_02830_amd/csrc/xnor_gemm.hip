@@ -73,13 +73,13 @@ struct TileCfg {
 template <int TM, int TN, int KT, bool VEC, bool FUSED>
 __global__ __launch_bounds__(256, 3) void xnor_gemm_tiled_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     using Cfg = TileCfg<TM, TN, KT>;
     __shared__ uint4 lds_a[2][Cfg::SLOTS_A];
     __shared__ uint4 lds_b[2][Cfg::SLOTS_B];
 
     int tile_m, tile_n;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of_block(blockIdx.x, tiles, tile_m, tile_n);
     const int row0 = tile_m * Cfg::BM;
     const int col0 = tile_n * Cfg::BN;
 
@@ -404,10 +404,10 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
     const dim3 grid(unsigned(int64_t(tiles_m) * tiles_n));
     if (vec)
         hipLaunchKernelGGL((xnor_gemm_tiled_kernel<TM, TN, KT, true, FUSED>), grid, dim3(256), 0, s, A, lda,
-                           B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, bn);
+                           B, ldb, C, ldc, M, N, K, tile_map(tiles_m, tiles_n), bn);
     else
         hipLaunchKernelGGL((xnor_gemm_tiled_kernel<TM, TN, KT, false, FUSED>), grid, dim3(256), 0, s, A, lda,
-                           B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, bn);
+                           B, ldb, C, ldc, M, N, K, tile_map(tiles_m, tiles_n), bn);
 }
 
 // Kernel choice, from measurements on MI355X: the matrix-engine kernels are 2-4x faster than the

@@ -46,7 +46,7 @@ namespace bnn {
 template <int WM, int WN, bool FUSED, bool CONV, bool TINY>
 __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn,
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn,
     ConvArgs cv) {
     constexpr int BM = 64 * WM, BN = 64 * WN;          // 2 x 2 wavefronts
     constexpr int PLANE_A = BM + 2, PLANE_B = BN + 2;  // 16-byte slots per quad plane (2 pad slots)
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     __shared__ float colfix_s[FUSED ? BN : 1];              // column term of the folded threshold
 
     int tile_m, tile_n;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of_block(blockIdx.x, tiles, tile_m, tile_n);
     const int row0 = tile_m * BM, col0 = tile_n * BN;
 
     const int tid = threadIdx.x;
@@ -294,8 +294,8 @@ static int launch_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_
     if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
     const dim3 grid{unsigned(tiles_m * tiles_n)};
     hipLaunchKernelGGL((xnor_gemm_mfma_kernel<WM, WN, FUSED, CONV, TINY>), grid, dim3(256), 0,
-                       static_cast<hipStream_t>(stream), A, lda, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m),
-                       int(tiles_n), bn, cv);
+                       static_cast<hipStream_t>(stream), A, lda, B, ldb, C, ldc, int(M), int(N), int(K),
+                       tile_map(tiles_m, tiles_n), bn, cv);
     return check_launch();
 }
 

@@ -92,7 +92,7 @@ __device__ inline void persist_epilogue_int32(const v16f (&acc)[WM][WN], const i
 template <bool FUSED, bool THROUGH>
 __global__ __launch_bounds__(256, 2) void xnor_gemm_mfma_persist_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     constexpr int WM = 4, WN = 2;
     constexpr int BM = 64 * WM, BN = 64 * WN;          // 2 x 2 wavefronts
     constexpr int PLANE_A = BM + 2, PLANE_B = BN + 2;  // 16-byte slots per quad plane (2 pad slots)
@@ -118,10 +118,10 @@ __global__ __launch_bounds__(256, 2) void xnor_gemm_mfma_persist_kernel(
     const uint32_t a_off = (uint32_t(st_r) * uint32_t(lda) + 4u * st_q) * 4u;
     const uint32_t b_off = (uint32_t(st_r) * uint32_t(ldb) + 4u * st_q) * 4u;
 
-    const int total_tiles = tiles_m * tiles_n;
+    const int total_tiles = tiles.tiles_m * tiles.tiles_n;
     int tile = blockIdx.x;
     int tile_m, tile_n;
-    tile_of_block(tile, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of_block(tile, tiles, tile_m, tile_n);
     // (row0, col0) of the tile whose K-tiles are being fetched.  The tile order divides by run-time
     // values on the vector ALU; readfirstlane brings the (uniform) result back into scalar registers so
     // that tile addresses are scalar bases.
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, 2) void xnor_gemm_mfma_persist_kernel(
             if (!last) {
                 fetch(kt + 1);
             } else if (has_next) {
-                tile_of_block(tile + int(gridDim.x), tiles_m, tiles_n, tile_m, tile_n);
+                tile_of_block(tile + int(gridDim.x), tiles, tile_m, tile_n);
                 row0 = __builtin_amdgcn_readfirstlane(min(tile_m * BM, M - BM));
                 col0 = __builtin_amdgcn_readfirstlane(tile_n * BN);
                 fetch(0);
@@ -335,13 +335,13 @@ int launch_xnor_gemm_mfma_persist(const uint32_t* A, int64_t lda, const uint32_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (fused)
         hipLaunchKernelGGL((xnor_gemm_mfma_persist_kernel<true, false>), dim3(unsigned(slots)), dim3(256), 0, s, A, lda, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     else if (M * N * int64_t(sizeof(int32_t)) <= kThroughMaxBytes)
         hipLaunchKernelGGL((xnor_gemm_mfma_persist_kernel<false, true>), dim3(unsigned(slots)), dim3(256), 0, s, A, lda, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     else
         hipLaunchKernelGGL((xnor_gemm_mfma_persist_kernel<false, false>), dim3(unsigned(slots)), dim3(256), 0, s, A, lda, B,
-                           ldb, C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), bn);
+                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     return check_launch();
 }
 

@@ -39,14 +39,14 @@ constexpr int kBatch = 4;                 // quads of each operand a lane loads 
 template <bool FUSED>
 __global__ __launch_bounds__(256, 4) void xnor_gemm_mfma_splitk_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
-    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, BnSignArgs bn) {
+    int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     __shared__ float4 part[kWaves][4][kWave];     // [wavefront][accumulator registers 4g .. 4g+3][lane]
     __shared__ __attribute__((aligned(16))) int pop_part[kWaves][kWave];   // 2*popcount over the wavefront's share of K:
                                                                           // [0, 32) rows of A, [32, 64) rows of B
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 31, fh = lane >> 5;
     int tm, tn;
-    tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tile_of_block(blockIdx.x, tiles, tm, tn);
     const int row0 = tm * kTile, col0 = tn * kTile;
 
     // Rows beyond the matrix repeat its last row; their results are never stored.
@@ -192,10 +192,10 @@ int launch_xnor_gemm_mfma_splitk(const uint32_t* A, int64_t lda, const uint32_t*
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (fused)
         hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_kernel<true>), grid, dim3(256), 0, s, A, lda, B, ldb,
-                           static_cast<int32_t*>(nullptr), int64_t(0), int(M), int(N), int(K), tiles_m, tiles_n, bn);
+                           static_cast<int32_t*>(nullptr), int64_t(0), int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     else
         hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_kernel<false>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                           int(M), int(N), int(K), tiles_m, tiles_n, bn);
+                           int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     return check_launch();
 }
 
