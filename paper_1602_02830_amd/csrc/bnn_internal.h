@@ -36,6 +36,13 @@ __device__ inline void store_result(int32_t* p, int32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Four consecutive results, 4-byte aligned, with the same policy.
+__device__ inline void store_result4(int32_t* p, int4 v) {
+    typedef int quad_t __attribute__((ext_vector_type(4)));
+    const quad_t q = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(q) : "memory");
+}
+
 // Mask of the valid bits of the last word of a K-bit row (all ones if K % 32 == 0).
 __host__ __device__ inline uint32_t tail_mask(int64_t K) {
     const int r = int(K & 31);

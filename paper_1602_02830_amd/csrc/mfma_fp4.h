@@ -64,6 +64,68 @@ __device__ inline void mfma_epilogue(const v16f (&acc)[WM][WN], const int* pop_a
     }
 }
 
+// int32 epilogue of a wavefront whose accumulators hold the TRANSPOSED blocks (operands swapped, as for
+// mfma_epilogue_bits below): a lane holds 16 columns of one output row in groups of 4.  16 rows x 64 columns at a time
+// go through a wavefront's own piece of LDS (kStoreScratch floats, any memory that the K loop has left; rows padded to
+// 68 floats, so that the 16-byte writes of 8 rows fall into different banks) and leave as 16-byte stores of 256
+// consecutive bytes per row: a quarter of the store instructions of mfma_epilogue, and half of the lines that two of
+// them share where rows are not whole 128-byte lines.
+constexpr int kStoreRows = 16, kStorePitch = 68, kStoreScratch = kStoreRows * kStorePitch;
+
+// Which int32 outputs take it: rows that are not whole, aligned 128-byte lines (6000 x 3000 x 2100 35.0 -> 29.8 us,
+// 13000 x 2001 x 1300 35.4 -> 31.7, 9000 x 3000 x 3000 50.5 -> 45.1, 9000 x 2500 x 400 24.7 -> 22.4, 3000 x 3000 x 784
+// 12.8 -> 12.1).  Where mfma_epilogue's stores are whole lines it is level or better (8192 x 4096 x 1200 35.9 vs 34.7, but
+// 6144 x 2048 x 1500 15.3 vs 16.8; the whole-tile kernel, 8192 x 8192 x 2048, 67.6 vs 75.8).
+inline bool wants_row_stores(const int32_t* C, int64_t ldc) { return ldc % 32 != 0 || !aligned_to(C, 128); }
+
+template <int WM, int WN>
+__device__ inline void mfma_epilogue_rows(const v16f (&acc)[WM][WN], float* scratch, const int* pop_a, const int* pop_b,
+                                          int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int row0, int col0,
+                                          int wm, int wn, int lane) {
+    static_assert(WN == 2, "a wavefront's rows are 64 columns");
+    const int fr = lane & 31, fh = lane >> 5;
+    const int cg = lane & 15, rr = lane >> 4;              // on the way out: column group and row of four
+    const int n = col0 + wn * 64 + 4 * cg;
+    const int4 pb2 = *reinterpret_cast<const int4*>(&pop_b[wn * 64 + 4 * cg]);
+    int32_t* to = C + int64_t(row0 + wm * 32 * WM + rr) * ldc + n;              // the lane's rows are 4 apart
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if ((fr >> 4) == p) {
+                float* at = scratch + (fr & 15) * kStorePitch + 4 * fh;
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<float4*>(at + j * 32 + 8 * g) =
+                            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+            }
+            asm volatile("" : : : "memory");               // LDS is in order within a wavefront; so is the code
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < kStoreRows / 4; ++t) {
+                const int lr = 4 * t + rr, ml = wm * 32 * WM + i * 32 + 16 * p + lr, m = row0 + ml;
+                const float4 s = *reinterpret_cast<const float4*>(scratch + lr * kStorePitch + 4 * cg);
+                const int base = K - pop_a[ml];
+                const int4 dot = make_int4(base - pb2.x + (int(s.x) << 2), base - pb2.y + (int(s.y) << 2),
+                                           base - pb2.z + (int(s.z) << 2), base - pb2.w + (int(s.w) << 2));
+                if (m < M) {
+                    if (n + 4 <= N) {
+                        store_result4(to, dot);
+                    } else {
+                        if (n < N) store_result(to, dot.x);
+                        if (n + 1 < N) store_result(to + 1, dot.y);
+                        if (n + 2 < N) store_result(to + 2, dot.z);
+                    }
+                }
+                to += 4 * ldc;
+            }
+            asm volatile("" : : : "memory");
+            __builtin_amdgcn_wave_barrier();
+        }
+}
+
 // Largest K for which the fused binary epilogue below may fold its threshold into the accumulators:
 // every term is a multiple of 1/8 and the largest magnitude is about 2K, exact in fp32 below 2^21.
 constexpr int kMfmaFoldMaxK = 1 << 19;

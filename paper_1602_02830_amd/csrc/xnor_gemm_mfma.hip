@@ -43,7 +43,8 @@
 namespace bnn {
 
 // TINY: rows of fewer than 4 words (K <= 96), which have no whole quad to load.
-template <int WM, int WN, bool FUSED, bool CONV, bool TINY>
+// ROWS: the int32 form stores rows through LDS (mfma_epilogue_rows).
+template <int WM, int WN, bool FUSED, bool CONV, bool TINY, bool ROWS>
 __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn,
@@ -55,15 +56,18 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     constexpr int LOADS_B = BN / ST_ROWS;
     static_assert(BM % ST_ROWS == 0 && BN % ST_ROWS == 0, "tile rows must divide among the staging threads");
     static_assert(kMfmaKQ == 4, "the row-popcount reduction below assumes 4 staging lanes per row");
-    __shared__ uint4 lds_a[2][kMfmaKQ * PLANE_A];
-    __shared__ uint4 lds_b[2][kMfmaKQ * PLANE_B];
+    __shared__ uint4 lds[2 * kMfmaKQ * (PLANE_A + PLANE_B)];
+    auto lds_a = [&](int buf) { return lds + buf * (kMfmaKQ * PLANE_A); };
+    auto lds_b = [&](int buf) { return lds + 2 * kMfmaKQ * PLANE_A + buf * (kMfmaKQ * PLANE_B); };
+    static_assert(sizeof(lds) >= 4 * kStoreScratch * sizeof(float), "the int32 rows leave through the operand buffers");
     __shared__ __attribute__((aligned(16))) int pop_a[BM];
     __shared__ __attribute__((aligned(16))) int pop_b[BN];
     __shared__ __attribute__((aligned(16))) float pop_af[FUSED ? BM : 4];   // row term of the float threshold
     __shared__ __attribute__((aligned(16))) int thr_s[FUSED ? BN : 1];                  // the tile's thresholds and flip words, fetched
     __shared__ uint32_t flip_s[FUSED ? BN / 32 : 1];       // before the K loop (read in the epilogue)
-    // The fused kernel multiplies with the operands swapped: its accumulator blocks are the
-    // transposes of the output blocks, which lets the epilogue pack a row's bits inside a lane.
+    // With the operands swapped the accumulator blocks are the transposes of the output blocks, which lets the fused
+    // epilogue pack a row's bits inside a lane and the int32 one store 4 columns of a row at a time.
+    constexpr bool SWAPPED = FUSED || ROWS;
     __shared__ float colfix_s[FUSED ? BN : 1];              // column term of the folded threshold
 
     int tile_m, tile_n;
@@ -175,13 +179,13 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
                                keep ? ra[l].w : fill);
             }
             cnt_a[l] += popc4(v);
-            lds_a[buf][st_q * PLANE_A + st_r + l * ST_ROWS] = v;
+            lds_a(buf)[st_q * PLANE_A + st_r + l * ST_ROWS] = v;
         }
 #pragma unroll
         for (int l = 0; l < LOADS_B; ++l) {
             const uint4 v = rb[l];
             cnt_b[l] += popc4(v);
-            lds_b[buf][st_q * PLANE_B + st_r + l * ST_ROWS] = v;
+            lds_b(buf)[st_q * PLANE_B + st_r + l * ST_ROWS] = v;
         }
     };
 
@@ -215,9 +219,9 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
         for (int hq = 0; hq < 2; ++hq) {
             uint4 aw[WM], bw[WN];
 #pragma unroll
-            for (int i = 0; i < WM; ++i) aw[i] = lds_a[buf][(2 * fh + hq) * PLANE_A + wm * 32 * WM + i * 32 + fr];
+            for (int i = 0; i < WM; ++i) aw[i] = lds_a(buf)[(2 * fh + hq) * PLANE_A + wm * 32 * WM + i * 32 + fr];
 #pragma unroll
-            for (int j = 0; j < WN; ++j) bw[j] = lds_b[buf][(2 * fh + hq) * PLANE_B + wn * 32 * WN + j * 32 + fr];
+            for (int j = 0; j < WN; ++j) bw[j] = lds_b(buf)[(2 * fh + hq) * PLANE_B + wn * 32 * WN + j * 32 + fr];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 v8i fa[WM], fb[WN];
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
                 for (int i = 0; i < WM; ++i)
 #pragma unroll
                     for (int j = 0; j < WN; ++j) {
-                        if (FUSED)
+                        if (SWAPPED)
                             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                                 fb[j], fa[i], acc[i][j], 4 /* fp4 */, 4 /* fp4 */, 0, 0, 0, 0);
                         else
@@ -282,6 +286,9 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void xnor_gemm_mfma_kernel(
     if constexpr (FUSED)
         mfma_epilogue_bits<WM, WN>(acc, pop_a, pop_af, pop_b, thr_s, flip_s, colfix_s, bn, M, N, K, row0, col0, wm, wn,
                                    fr, fh);
+    else if constexpr (ROWS)
+        mfma_epilogue_rows<WM, WN>(acc, reinterpret_cast<float*>(lds) + wave * kStoreScratch, pop_a, pop_b, C, ldc, M, N, K,
+                                   row0, col0, wm, wn, lane);
     else
         mfma_epilogue<WM, WN>(acc, pop_a, pop_b, C, ldc, M, N, K, row0, col0, wm, wn, fr, fh);
 }
@@ -293,9 +300,16 @@ static int launch_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_
     const int64_t tiles_m = ceil_div(M, 64 * WM), tiles_n = ceil_div(N, 64 * WN);
     if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
     const dim3 grid{unsigned(tiles_m * tiles_n)};
-    hipLaunchKernelGGL((xnor_gemm_mfma_kernel<WM, WN, FUSED, CONV, TINY>), grid, dim3(256), 0,
-                       static_cast<hipStream_t>(stream), A, lda, B, ldb, C, ldc, int(M), int(N), int(K),
-                       tile_map(tiles_m, tiles_n), bn, cv);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream), A, lda, B, ldb, C, ldc, int(M),
+                           int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv);
+    };
+    // The 64 x 128 tiles are for grids that are over before stores queue up: straight from the accumulators
+    // (834 x 2414 x 1343 6.9 vs 7.4 us through LDS).
+    if (!FUSED && WM >= 2 && wants_row_stores(C, ldc))
+        launch(xnor_gemm_mfma_kernel<WM, WN, FUSED, CONV, TINY, !FUSED && (WM >= 2)>);
+    else
+        launch(xnor_gemm_mfma_kernel<WM, WN, FUSED, CONV, TINY, false>);
     return check_launch();
 }
 

@@ -89,7 +89,7 @@ __device__ inline void advance(Pixel& p, Pixel d, int Ho, int Wo) {
     p.b += d.b;
 }
 
-template <int TPR, bool FUSED, bool CONV>
+template <int TPR, bool FUSED, bool CONV, bool ROWS>
 __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n, int groups,
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
     constexpr int PLANE = BM + 2;                       // 8-byte slots per plane (2 pad slots)
     constexpr int ROWS_PER_PASS = 256 / TPR;            // TPR threads fetch one row's quads
     constexpr int PASSES = BM / ROWS_PER_PASS;
-    extern __shared__ uint2 lds_planes[];               // A planes, then B planes
+    extern __shared__ uint2 lds_planes[];               // A planes, then B planes, then (ROWS) the int32 rows on their way out
     __shared__ __attribute__((aligned(16))) int pop_a[2][BM];
     __shared__ __attribute__((aligned(16))) float pop_af[2][FUSED ? BM : 4];
     __shared__ __attribute__((aligned(16))) int pop_b[BN];
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
                         for (int v = 0; v < 16; ++v) addend[v] = 0.0f;
                     }
                     // fused: operands swapped, the accumulators hold the transposed blocks (mfma_epilogue_bits)
-                    if (FUSED)
+                    if (FUSED || ROWS)
                         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j], fa[i], addend, 4 /* fp4 */,
                                                                                     4 /* fp4 */, 0, 0, 0, 0);
                     else
@@ -309,6 +309,9 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_mfma_shortk_kernel(
         if constexpr (FUSED)
             mfma_epilogue_bits<WM, WN>(acc, pop_a[buf], pop_af[buf], pop_b, thr_s, flip_s, colfix_s, bn, M, N, K,
                                        tile_m * BM, col0, wm, wn, fr, fh);
+        else if constexpr (ROWS)
+            mfma_epilogue_rows<WM, WN>(acc, reinterpret_cast<float*>(lds_planes + 4 * kq * PLANE) + wave * kStoreScratch,
+                                       pop_a[buf], pop_b, C, ldc, M, N, K, tile_m * BM, col0, wm, wn, lane);
         else
             mfma_epilogue<WM, WN>(acc, pop_a[buf], pop_b, C, ldc, M, N, K, tile_m * BM, col0, wm, wn, fr, fh);
         __syncthreads();                            // next tile staged; this tile's row sums no longer needed
@@ -337,18 +340,21 @@ static int launch_shortk(const uint32_t* A, int64_t lda, const uint32_t* B, int6
     const int groups = shortk_groups(tiles_m, tiles_n);
     if (tiles_n * groups > kMaxDim) return BNN_ERR_UNSUPPORTED;
     const int64_t kq = ceil_div(ceil_div(K, 32), 4);
-    const size_t lds_bytes = size_t(2) * 2 * kq * (128 + 2) * sizeof(uint2);
+    // The int32 form sends its rows out through LDS (mfma_epilogue_rows) where three workgroups still fit a compute unit.
+    const bool rows = !FUSED && !CONV && kq <= 7 && wants_row_stores(C, ldc);
+    const size_t lds_bytes = size_t(2) * 2 * kq * (128 + 2) * sizeof(uint2) + (rows ? 4 * kStoreScratch * sizeof(float) : 0);
     // conv: word offset of the input's last 16-byte quad (the input holds whole images of M / (Ho * Wo)).
     const uint32_t a_last_quad =
         CONV ? uint32_t(M / (int64_t(cv.Ho) * cv.Wo) * cv.H * cv.W * cv.Cw - 4) : 0u;
     const dim3 grid(unsigned(tiles_n * groups));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (kq <= 8)
-        hipLaunchKernelGGL((xnor_gemm_mfma_shortk_kernel<8, FUSED, CONV>), grid, dim3(256), lds_bytes, s, A, lda, B, ldb,
-                           C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), groups, bn, cv, a_last_quad);
-    else
-        hipLaunchKernelGGL((xnor_gemm_mfma_shortk_kernel<16, FUSED, CONV>), grid, dim3(256), lds_bytes, s, A, lda, B, ldb,
-                           C, ldc, int(M), int(N), int(K), int(tiles_m), int(tiles_n), groups, bn, cv, a_last_quad);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds_bytes, s, A, lda, B, ldb, C, ldc, int(M), int(N), int(K), int(tiles_m),
+                           int(tiles_n), groups, bn, cv, a_last_quad);
+    };
+    if (rows) launch(xnor_gemm_mfma_shortk_kernel<8, FUSED, CONV, !FUSED && !CONV>);
+    else if (kq <= 8) launch(xnor_gemm_mfma_shortk_kernel<8, FUSED, CONV, false>);
+    else launch(xnor_gemm_mfma_shortk_kernel<16, FUSED, CONV, false>);
     return check_launch();
 }
 

@@ -722,6 +722,30 @@ def test_products_of_rows_at_any_alignment(M, N, K, extra, first):
         assert (words_to_host(got) == bits).all(), kernel
 
 
+@pytest.mark.parametrize("M,N,K,pad,first", [
+    (2900, 1450, 1300, 0, 0),      # 128 x 128 tiles, rows of 1450: every 4-byte phase of a 16-byte store
+    (2901, 1472, 1300, 0, 1),      # whole lines, but one word off
+    (2901, 1472, 1300, 0, 0),      # whole, aligned lines: straight from the accumulators
+    (4100, 4097, 4100, 2, 0),      # 256 x 128 tiles
+    (6600, 2002, 770, 1, 0),       # short-K kernel, rows through LDS
+    (6600, 2002, 1000, 1, 0),      # short-K kernel, LDS full: straight
+])
+def test_int32_rows_of_every_alignment(M, N, K, pad, first):
+    """int32 results whose rows start at any 4-byte offset of a line, last columns in partial quads, canaries behind every row."""
+    rng = np.random.default_rng(M + N + K)
+    A, Bm = synth.pm1(rng, (M, K)), synth.pm1(rng, (N, K))
+    want = A.astype(np.float32) @ Bm.T.astype(np.float32)
+    a, b = words_to_dev(oracle.pack_bits(A)), words_to_dev(oracle.pack_bits(Bm))
+    ld = N + pad
+    for kernel in (bnn.KERNEL_AUTO, bnn.KERNEL_MFMA, bnn.KERNEL_MFMA128):
+        flat = torch.full((first + M * ld + 8,), 0x6B6B6B6B, dtype=torch.int32, device=DEV)
+        out = flat[first:first + M * ld].view(M, ld)[:, :N]
+        bnn.xnor_gemm(a, b, K, out=out, kernel=kernel)
+        assert (out.cpu().numpy() == want).all(), kernel
+        out.fill_(0x6B6B6B6B)
+        assert (flat == 0x6B6B6B6B).all(), kernel
+
+
 def test_k_split_matrix_engine_kernel_refuses_what_it_does_not_take():
     """Kernel id 10 answers BNN_ERR_UNSUPPORTED, launching nothing, outside its shapes: K not a multiple of
     128 (or zero), operands that do not allow 16-byte loads."""
