@@ -63,21 +63,33 @@ __host__ __device__ inline size_t words_patch_koff_offset(int Cw, int slots) {
     return (size_t(Cw + 1) * size_t(slots) + 1) & ~size_t(1);
 }
 
-// BRES: the filters' whole K extent (at most kResidentKTiles K-tiles of 4 quads) is staged once, next
-// to the patch, and the K loop runs without a barrier; otherwise B streams through two K-tile buffers.
-constexpr int kResidentKTiles = 5;
+// RES > 0: the filters' whole K extent (at most RES K-tiles of 4 quads) is staged once, next to the patch, and the K
+// loop runs without a barrier; RES = 0: B streams through two K-tile buffers.  kResidentKTiles fit beside the patches of
+// two or three workgroups.  kResidentKTilesAlone (3 x 3 over 512 channels) fill a compute unit by themselves: for grids
+// that give a compute unit one workgroup at most, where every K-tile streamed is a memory round trip that nothing else
+// covers (52 images of 8 x 8, 512 -> 512 pooled 13.9 -> 12.8 us, 20 of 16 x 16, 384 -> 256 11.5 -> 10.7).
+constexpr int kResidentKTiles = 5, kResidentKTilesAlone = 9;
+constexpr int64_t kLoneGrid = 224;        // workgroups that leave no compute unit with two
 
-template <int WM, bool FUSED, bool POOL, bool BRES, bool WORDS>
-__global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
+// KS = 2: eight wavefronts, the second four taking the second half of K of the same tile; their sums join the first
+// four's in LDS.  For grids that give a compute unit one workgroup at most: a wavefront alone on its SIMD waits for every
+// LDS read, widening and product in turn (16 images of 8 x 8, 512 -> 512 12.6 -> 10.4 us, 20 of 16 x 16, 256 -> 256 8.1 ->
+// 7.6).  Not for 128-pixel tiles with a short K, where joining the sums costs what it saves (26 of 32 x 32, 128 -> 128
+// 6.7 -> 7.2).
+template <int WM, bool FUSED, bool POOL, int RES, bool WORDS, int KS>
+__global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, int32_t* __restrict__ C,
     int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn, ConvArgs cv, PatchGeom pg,
     int n_images) {
     constexpr int WN = 2, BM = 64 * WM, BN = 64 * WN;
     constexpr int PLANE_B = BN + 2;                     // 8-byte slots per B plane (2 pad slots)
-    constexpr int ST_ROWS = 256 / 4;                    // filter rows per staging pass (4 threads per row)
+    constexpr int T = 256 * KS;
+    constexpr int ST_ROWS = T / 4;                      // filter rows per staging pass (4 threads per row)
+    static_assert(KS == 1 || (RES > 0 && WM <= 2), "K is split over wavefronts for small tiles with resident filters");
     constexpr int LOADS_B = BN / ST_ROWS;
+    constexpr bool BRES = RES > 0;
     static_assert(!WORDS || BRES, "the word-granular patch is built for resident filters only");
-    extern __shared__ uint2 patch[];                    // [cqn][2][slots], int pix_pop[slots], resident B tiles
+    extern __shared__ __attribute__((aligned(16))) uint2 patch[];                    // [cqn][2][slots], int pix_pop[slots], resident B tiles
                                                         // WORDS: uint32 [Cw][slots], pix_pop, int koff[4*kq], B tiles
     __shared__ uint2 lds_b_stream[BRES ? 1 : 2 * 8 * PLANE_B];
     __shared__ __attribute__((aligned(16))) int pop_a[BM];
@@ -103,7 +115,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     const int row0 = tile_m * BM, col0 = tile_n * BN;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = KS > 1 ? (wave >> 1) & 1 : wave >> 1, wn = wave & 1, kg = KS > 1 ? wave >> 2 : 0;
     const int fr = lane & 31, fh = lane >> 5;
 
     // ---- B staging: K-tiles of 4 quads, as planes [quad][half] ---------------------------------
@@ -158,10 +170,10 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         if (tid < BN / 32 && col0 + 32 * tid < N) flip_reg = bn.flip_bits[(col0 >> 5) + tid];
     }
     // The filter loads are issued first, so that they are in flight while the patch is addressed and loaded.
-    uint4 all_b[BRES ? kResidentKTiles : 1][LOADS_B];
+    uint4 all_b[BRES ? RES : 1][LOADS_B];
     if (BRES) {
 #pragma unroll
-        for (int kt = 0; kt < kResidentKTiles; ++kt)
+        for (int kt = 0; kt < RES; ++kt)
             if (kt < n_ktiles) {
                 fetch_b(kt);
 #pragma unroll
@@ -176,7 +188,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     if (WORDS || !FUSED) {
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
-        for (int s = tid; s < pg.slots; s += 256) {
+        for (int s = tid; s < pg.slots; s += T) {
             const int py = pg.by_pw(s), px = s - py * pg.pw;
             const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
             const bool inside = b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
@@ -205,13 +217,13 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         // of a pass are issued before the first LDS write waits for one.  Slots that do not exist and cells
         // outside the image load input pixel 0 (a valid address) and are not written / written as all ones.
         constexpr int kSlotsPerPass = 2, kQuadsPerPass = 4;
-        for (int s_base = 0; s_base < pg.slots; s_base += kSlotsPerPass * 256) {
+        for (int s_base = 0; s_base < pg.slots; s_base += kSlotsPerPass * T) {
             const uint32_t* p[kSlotsPerPass];
             bool live[kSlotsPerPass], inside[kSlotsPerPass];
             int pop[kSlotsPerPass];
 #pragma unroll
             for (int u = 0; u < kSlotsPerPass; ++u) {
-                const int s = s_base + u * 256 + tid;
+                const int s = s_base + u * T + tid;
                 live[u] = s < pg.slots;
                 const int py = pg.by_pw(s), px = s - py * pg.pw;
                 const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
@@ -229,7 +241,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
                         if (cq0 + c < pg.cqn) v[u][c] = *reinterpret_cast<const uint4*>(p[u] + 4 * (cq0 + c));
 #pragma unroll
                 for (int u = 0; u < kSlotsPerPass; ++u) {
-                    const int s = s_base + u * 256 + tid;
+                    const int s = s_base + u * T + tid;
 #pragma unroll
                     for (int c = 0; c < kQuadsPerPass; ++c)
                         if (cq0 + c < pg.cqn) {
@@ -244,7 +256,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
             }
 #pragma unroll
             for (int u = 0; u < kSlotsPerPass; ++u)
-                if (live[u]) pix_pop[s_base + u * 256 + tid] = pop[u];
+                if (live[u]) pix_pop[s_base + u * T + tid] = pop[u];
         }
     }
     if (FUSED) {
@@ -254,7 +266,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
     if (WORDS) {
         // K-word kwi of a receptive field = channel word kwi % Cw of tap kwi / Cw; words past the field's
         // end point at a valid cell (their filter words are zero).
-        for (int kwi = tid; kwi < 4 * pg.kq; kwi += 256) {
+        for (int kwi = tid; kwi < 4 * pg.kq; kwi += T) {
             int off = 0;
             if (kwi < pg.kwords) {
                 const int tap = kwi / cv.Cw, cw = kwi - tap * cv.Cw;
@@ -267,7 +279,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
 
     if (BRES) {
 #pragma unroll
-        for (int kt = 0; kt < kResidentKTiles; ++kt)
+        for (int kt = 0; kt < RES; ++kt)
             if (kt < n_ktiles) {
 #pragma unroll
                 for (int l = 0; l < LOADS_B; ++l) rb[l] = all_b[kt][l];
@@ -310,7 +322,15 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
 
     // (tap row, tap column, channel quad) of the next quad of K, stepped with carries.
     int ky = 0, kx = 0, cq = 0;
-    for (int kt = 0; kt < n_ktiles; ++kt) {
+    // KS > 1: this wavefront's half of the K-tiles' quads.
+    const int kt_first = KS > 1 && kg == 1 ? n_ktiles / 2 : 0, kt_end = KS > 1 && kg == 0 ? n_ktiles / 2 : n_ktiles;
+    if (KS > 1 && !WORDS && kt_first > 0) {
+        const int tap = 4 * kt_first / pg.cqn;
+        cq = 4 * kt_first - tap * pg.cqn;
+        ky = tap / cv.kw;
+        kx = tap - ky * cv.kw;
+    }
+    for (int kt = kt_first; kt < kt_end; ++kt) {
         const int buf = BRES ? kt : kt & 1;
         if (!BRES && kt + 1 < n_ktiles) fetch_b(kt + 1);
         const int quads_here = min(4, pg.kq - 4 * kt);
@@ -369,6 +389,39 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         }
     }
 
+    if constexpr (KS > 1) {
+        // The second half's sums, through the memory of the filters, which every wavefront has finished reading.
+        // (16-byte aligned: dynamic LDS starts so, lds_b is 8-byte aligned in it.)
+        const size_t at = (size_t(lds_b - patch) + 1) & ~size_t(1);
+        float4* sums = reinterpret_cast<float4*>(patch + at) + (wave & 3) * (WM * WN * 4 * kWave);
+        __syncthreads();
+        if (kg == 1) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        sums[((i * WN + j) * 4 + g) * kWave + lane] =
+                            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const float4 v = sums[((i * WN + j) * 4 + g) * kWave + lane];
+                        acc[i][j][4 * g] += v.x;
+                        acc[i][j][4 * g + 1] += v.y;
+                        acc[i][j][4 * g + 2] += v.z;
+                        acc[i][j][4 * g + 3] += v.w;
+                    }
+        }
+    }
+
 #pragma unroll
     for (int l = 0; l < LOADS_B; ++l) {
         int c = cnt_b[l];
@@ -380,6 +433,7 @@ __global__ __launch_bounds__(256, WM >= 4 ? 2 : 3) void conv_patch_mfma_kernel(
         }
     }
     __syncthreads();
+    if (KS > 1 && kg > 0) return;                       // no barrier follows
 
     if constexpr (POOL) {
         static_assert(FUSED, "pooling acts on output bits");
@@ -482,20 +536,26 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     const size_t patch_bytes = words ? (words_patch_koff_offset(cv.Cw, pg.slots) + size_t(4) * pg.kq) * 4
                                      : size_t(pg.slots) * size_t(cv.Cw) * 4 + size_t((pg.slots + 1) / 2) * 8;
     const int n_ktiles = (pg.kq + 3) / 4;
-    const bool resident = n_ktiles <= kResidentKTiles;
-    const size_t lds_bytes = patch_bytes + (resident ? size_t(n_ktiles) * 8 * (128 + 2) * sizeof(uint2) : 0);
+    const bool alone = WM <= 2 && n_ktiles > kResidentKTiles && n_ktiles <= kResidentKTilesAlone && tiles_m * tiles_n <= kLoneGrid;
+    const bool resident = n_ktiles <= kResidentKTiles || alone;
+    const bool split = WM <= 2 && resident && !words && tiles_m * tiles_n <= kLoneGrid &&
+                       n_ktiles >= (WM == 1 ? 2 : 4);
+    const size_t filter_bytes = resident ? size_t(n_ktiles) * 8 * (128 + 2) * sizeof(uint2) : 0;
+    const size_t sum_bytes = split ? size_t(4) * WM * 2 * 4 * kWave * sizeof(float4) + 16 : 0;   // of the second half of K
+    const size_t lds_bytes = patch_bytes + (filter_bytes > sum_bytes ? filter_bytes : sum_bytes);
     const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
     const dim3 grid(unsigned(tiles_m * tiles_n));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (words)                                          // patch_geometry has checked that the filters are resident
-        hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, true, true>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
-    else if (resident)
-        hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, true, false>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
-    else
-        hipLaunchKernelGGL((conv_patch_mfma_kernel<WM, FUSED, POOL, false, false>), grid, dim3(256), lds_bytes, s, in, B,
-                           ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds_bytes, s, in, B, ldb, C, ldc, int(M), int(N), int(K),
+                           tile_map(tiles_m, tiles_n), bn, cv, pg, n_images);
+    };
+    constexpr int WS = WM <= 2 ? WM : 2;                // the forms below this line are for small tiles
+    if (words) launch(conv_patch_mfma_kernel<WM, FUSED, POOL, kResidentKTiles, true, 1>, 256);   // resident: words_layer_fits
+    else if (alone) launch(conv_patch_mfma_kernel<WS, FUSED, POOL, kResidentKTilesAlone, false, 2>, 512);
+    else if (split) launch(conv_patch_mfma_kernel<WS, FUSED, POOL, kResidentKTiles, false, 2>, 512);
+    else if (n_ktiles <= kResidentKTiles) launch(conv_patch_mfma_kernel<WM, FUSED, POOL, kResidentKTiles, false, 1>, 256);
+    else launch(conv_patch_mfma_kernel<WM, FUSED, POOL, 0, false, 1>, 256);
     return check_launch();
 }
 
@@ -506,7 +566,8 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
 // through LDS (512 channels, 188 tiles) 17.0 -> 20.6: a K-tile of 64 pixels is over before the next one's loads are back.
 static bool wants_big_tiles(int64_t M, int64_t N) { return ceil_div(M, 256) * ceil_div(N, 128) >= 512; }
 static bool wants_small_tiles(int64_t M, int64_t N, int64_t K) {
-    return ceil_div(M, 128) * ceil_div(N, 128) <= 160 && K <= kResidentKTiles * 512;
+    return ceil_div(M, 128) * ceil_div(N, 128) <= 160 &&
+           (K <= kResidentKTiles * 512 || (K <= kResidentKTilesAlone * 512 && ceil_div(M, 64) * ceil_div(N, 128) <= kLoneGrid));
 }
 
 // BNN_ERR_UNSUPPORTED if the layer is not one this kernel takes (the caller then uses the gathering kernels).

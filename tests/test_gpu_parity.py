@@ -1127,6 +1127,11 @@ def test_implicit_conv_matches_direct_convolution(shape):
     (21, 17, 14, 128, 64, 2, 3, 3, 0),      # even window, stride beyond the window's overlap, no padding
     (11, 10, 12, 128, 50, 1, 1, 3, 0),      # windows that skip pixels
     (6, 20, 20, 128, 64, 5, 5, 1, 3),       # padding beyond half the window
+    (16, 8, 8, 512, 512, 3, 3, 1, 1),       # one workgroup per compute unit at most: all filters resident, K split in two
+    (26, 14, 14, 512, 130, 3, 3, 1, 1),     # the same on 64-pixel tiles that span images
+    (20, 16, 16, 384, 256, 3, 3, 1, 1),     # 27 quads of K: a last K-tile of 3 in the second half
+    (20, 16, 16, 256, 256, 3, 3, 1, 1),     # 18 quads, 4 + 5 K-tiles wide halves of 2 and 3
+    (3, 20, 20, 640, 64, 2, 2, 1, 1),       # 20 quads, taps that start inside a K-tile
     (2, 40, 400, 128, 20, 3, 3, 1, 1),      # patch too large at 128 pixels and more: the gathering kernels
 ])
 def test_conv_without_im2col_on_any_geometry(shape):
