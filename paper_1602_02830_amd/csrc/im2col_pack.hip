@@ -7,13 +7,14 @@
 //
 // HBM-bound on the write side: (kh*kw*Cin)/8 bytes written per output pixel;
 // reads mostly hit cache (each input pixel is used kh*kw times).
-//   quads   - Cin % 128 == 0 (the paper's layers): 16-byte copies.  A thread keeps one 16-byte unit
-//             of the receptive field (its tap and channel quad, fixed for the kernel's life) and
-//             walks over output pixels with carried (row, column) coordinates, so the copy loop
+//   units   - Cin % 32 == 0: copies of 4, 2 or 1 words (Cin a multiple of 128, 64 or 32).  A thread
+//             keeps one unit of the receptive field (its tap and channel words, fixed for the
+//             kernel's life) and walks over the batch's output pixels by carries, so the copy loop
 //             has no division; the threads of a pass write whole consecutive output rows.
-//   words   - Cin % 32 == 0: every output word is a copy of one input word or all-ones.
+//   words   - the same a word at a time, for batches of 2^31 pixels and more.
 //   bits    - any Cin: an output word gathers bit runs from up to 32 taps.
 #include "bnn_internal.h"
+#include "gemm_staging.h"
 
 namespace bnn {
 
@@ -26,19 +27,16 @@ struct ConvGeom {
     int Kwords;                  // ceil(Kbits/32)
 };
 
-// VW = words moved per thread (1 or 4); Cin % (32*VW) == 0.
-template <int VW>
 __global__ __launch_bounds__(256) void im2col_words_kernel(const uint32_t* __restrict__ in, ConvGeom g,
                                                            uint32_t* __restrict__ out, int64_t ld_out,
                                                            int64_t n_units) {
-    const int units_per_tap = g.Cw / VW;
-    const int units_per_row = g.kh * g.kw * units_per_tap;
+    const int words_per_row = g.kh * g.kw * g.Cw;
     for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < n_units;
          u += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t m = u / units_per_row;
-        const int r = int(u - m * units_per_row);
-        const int tap = r / units_per_tap;
-        const int cu = r - tap * units_per_tap;
+        const int64_t m = u / words_per_row;
+        const int r = int(u - m * words_per_row);
+        const int tap = r / g.Cw;
+        const int cu = r - tap * g.Cw;
         const int ky = tap / g.kw, kx = tap - ky * g.kw;
         const int ox = int(m % g.Wo);
         const int64_t t = m / g.Wo;
@@ -47,51 +45,54 @@ __global__ __launch_bounds__(256) void im2col_words_kernel(const uint32_t* __res
         const int y = oy * g.stride + ky - g.pad;
         const int x = ox * g.stride + kx - g.pad;
         const bool inside = y >= 0 && y < g.H && x >= 0 && x < g.W;
-        uint32_t* dst = out + m * ld_out + int64_t(tap) * g.Cw + cu * VW;
-        const uint32_t* src = in + ((b * g.H + y) * g.W + x) * g.Cw + cu * VW;
-        if (VW == 4) {
-            uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
-            if (inside) v = *reinterpret_cast<const uint4*>(src);
-            *reinterpret_cast<uint4*>(dst) = v;
-        } else {
-            *dst = inside ? *src : ~0u;
-        }
+        out[m * ld_out + r] = inside ? in[((b * g.H + y) * g.W + x) * g.Cw + cu] : ~0u;
     }
 }
 
-// Cin % 128 == 0, 16-byte aligned buffers, at most 256 units of 16 bytes per receptive field.
-// Grid: (chunks of an image's output pixels, images).  P = 256 / units pixels per pass.
-__global__ __launch_bounds__(256) void im2col_quads_kernel(const uint32_t* __restrict__ in, ConvGeom g,
-                                                           uint32_t* __restrict__ out, int64_t ld_out,
-                                                           int units, int pixels_per_block) {
-    const int P = 256 / units;
-    const int p = threadIdx.x / units, r = threadIdx.x - p * units;
-    if (p >= P) return;                                  // 256 % units leftover threads
-    const int units_per_tap = g.Cw / 4;
-    const int tap = r / units_per_tap, cu = r - tap * units_per_tap;
-    const int ky = tap / g.kw, kx = tap - ky * g.kw;
-    const int n_pix = g.Ho * g.Wo;
-    const int q_end = min((int(blockIdx.x) + 1) * pixels_per_block, n_pix);
-    int q = int(blockIdx.x) * pixels_per_block + p;
-    int oy = q / g.Wo, ox = q - oy * g.Wo;
-    const int step_y = P / g.Wo, step_x = P - step_y * g.Wo;
-    const int64_t b = blockIdx.y;
-    const uint32_t* img = in + b * g.H * g.W * g.Cw + cu * 4;
-    uint32_t* dst = out + (b * n_pix + q) * ld_out + tap * g.Cw + cu * 4;
-    const int64_t dst_step = int64_t(P) * ld_out;
-    for (; q < q_end; q += P) {
+// Units of VW words, 4-byte aligned (one load and one store each).  A pass is P pixels, per_pass threads each.
+struct UnitCopy {
+    FastDiv by_pass, by_chunks, by_tap, by_kw, by_Wo, by_Ho;
+    int units, per_pass, P, chunks, pixels_per_block;
+    int step_b, step_y, step_x;                          // P pixels further, before the carries
+};
+
+template <int VW>
+__global__ __launch_bounds__(256) void im2col_units_kernel(const uint32_t* __restrict__ in, ConvGeom g,
+                                                           uint32_t* __restrict__ out, int64_t ld_out, UnitCopy c) {
+    typedef uint32_t unit_t __attribute__((ext_vector_type(VW), aligned(4)));
+    const int pixel_chunk = c.by_chunks(int(blockIdx.x)), chunk = int(blockIdx.x) - pixel_chunk * c.chunks;
+    const int p = c.by_pass(int(threadIdx.x)), r = chunk * 256 + int(threadIdx.x) - p * c.per_pass;
+    if (p >= c.P || r >= c.units) return;                // 256 % units leftover threads
+    const int tap = c.by_tap(r), cu = r - tap * (g.Cw / VW);
+    const int ky = c.by_kw(tap), kx = tap - ky * g.kw;
+    const int first = pixel_chunk * c.pixels_per_block;
+    const int M = int(g.M), q_end = min(first + c.pixels_per_block, M);
+    int q = first + p;
+    const int row = c.by_Wo(q);
+    int b = c.by_Ho(row), ox = q - row * g.Wo, oy = row - b * g.Ho;
+    const uint32_t* src = in + cu * VW;
+    uint32_t* dst = out + q * ld_out + r * VW;
+    const int64_t dst_step = c.P * ld_out;
+    for (; q < q_end; q += c.P) {
         const int y = oy * g.stride + ky - g.pad;
         const int x = ox * g.stride + kx - g.pad;
-        uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
+        unit_t v;
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] = ~0u;
         if (y >= 0 && y < g.H && x >= 0 && x < g.W)
-            v = *reinterpret_cast<const uint4*>(img + (int64_t(y) * g.W + x) * g.Cw);
-        *reinterpret_cast<uint4*>(dst) = v;
+            v = *reinterpret_cast<const unit_t*>(src + ((b * g.H + y) * g.W + x) * g.Cw);
+        *reinterpret_cast<unit_t*>(dst) = v;
         dst += dst_step;
-        ox += step_x;
-        oy += step_y;
+        ox += c.step_x;
+        oy += c.step_y;
+        b += c.step_b;
         if (ox >= g.Wo) {
             ox -= g.Wo;
             ++oy;
+        }
+        if (oy >= g.Ho) {
+            oy -= g.Ho;
+            ++b;
         }
     }
 }
@@ -169,24 +170,40 @@ extern "C" int bnn_conv_im2col_pack(const uint32_t* in, int64_t B, int64_t H, in
         return unsigned(b > max_blocks ? max_blocks : b);
     };
     if (Cin % 32 == 0) {
-        const bool v4 = Cin % 128 == 0 && aligned_to(in, 16) && aligned_to(out, 16) && ld_out % 4 == 0;
-        const int64_t row_units = kwords / 4, n_pix = Ho * Wo;
-        if (v4 && row_units <= 256 && n_pix <= kMaxDim - 4096 && B <= 65535) {
-            // Pixels per workgroup: a few passes each, and enough workgroups to fill the chip.
-            const int P = int(256 / row_units);
-            int64_t per_block = int64_t(P) * 8;
-            while (per_block > P && ceil_div(n_pix, per_block) * B < 2048) per_block -= P;
-            const dim3 grid(unsigned(ceil_div(n_pix, per_block)), unsigned(B));
-            hipLaunchKernelGGL(im2col_quads_kernel, grid, dim3(256), 0, s, in, g, out, ld_out, int(row_units),
-                               int(per_block));
-        } else if (v4) {
-            const int64_t units = g.M * (kwords / 4);
-            hipLaunchKernelGGL(im2col_words_kernel<4>, dim3(blocks_for(units)), dim3(256), 0, s, in, g, out,
-                               ld_out, units);
+        // 64 channels of 30 x 30 images, batch 100: 10.1 us word by word, with six 64-bit divisions for each; 4.9 in units
+        // of two words.  128 channels of 32 x 32, batch 256: 10.2 with the images one by one in the grid and 64-bit places,
+        // 9.7 now (75 MB written); 14 x 14 x 96, batch 100: 4.7 -> 3.5.
+        const int vw = g.Cw % 4 == 0 ? 4 : g.Cw % 2 == 0 ? 2 : 1;
+        // Pixels per workgroup: eight passes, and fewer until there are enough workgroups to fill the chip.
+        UnitCopy c;
+        c.units = int(kwords / vw);
+        c.per_pass = c.units < 256 ? c.units : 256;
+        c.P = 256 / c.per_pass;
+        c.chunks = int(ceil_div(c.units, 256));
+        c.pixels_per_block = c.P * 8;
+        while (c.pixels_per_block > c.P && ceil_div(g.M, c.pixels_per_block) * c.chunks < 2048) c.pixels_per_block -= c.P;
+        const int64_t blocks = ceil_div(g.M, c.pixels_per_block) * c.chunks;
+        // 32-bit places and indexes: everything but batches of more than 2^31 pixels or input words.
+        if (g.M <= kMaxDim - 4096 && B * H * W <= kMaxDim / g.Cw && blocks <= kMaxDim / 256) {
+            const int64_t n_pix = Ho * Wo;
+            c.step_b = int(c.P / n_pix);
+            c.step_y = int(c.P % n_pix / Wo);
+            c.step_x = int(c.P % n_pix % Wo);
+            c.by_pass = fast_div(c.per_pass);
+            c.by_chunks = fast_div(c.chunks);
+            c.by_tap = fast_div(g.Cw / vw);
+            c.by_kw = fast_div(kw);
+            c.by_Wo = fast_div(Wo);
+            c.by_Ho = fast_div(Ho);
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(256), 0, s, in, g, out, ld_out, c);
+            };
+            if (vw == 4) launch(im2col_units_kernel<4>);
+            else if (vw == 2) launch(im2col_units_kernel<2>);
+            else launch(im2col_units_kernel<1>);
         } else {
             const int64_t units = g.M * kwords;
-            hipLaunchKernelGGL(im2col_words_kernel<1>, dim3(blocks_for(units)), dim3(256), 0, s, in, g, out,
-                               ld_out, units);
+            hipLaunchKernelGGL(im2col_words_kernel, dim3(blocks_for(units)), dim3(256), 0, s, in, g, out, ld_out, units);
         }
     } else {
         const int64_t units = g.M * kwords;

@@ -1029,6 +1029,38 @@ def test_im2col_pack_matches_oracle_lowering(shape):
     assert (got == want).all()
 
 
+@pytest.mark.parametrize("shape", [
+    # B, H, W, Cin, kh, kw, stride, pad
+    (300, 1, 1, 32, 1, 1, 1, 0),       # 256 one-word units: many images in a pass
+    (41, 3, 2, 32, 3, 3, 1, 1),        # 9 units, 28 pixels: a pass goes over several images
+    (7, 13, 11, 64, 3, 3, 2, 0),       # units of two words, the last pass partly empty
+    (3, 4, 300, 64, 1, 3, 1, 1),       # rows longer than a pass
+    (2, 5, 6, 96, 3, 3, 1, 1),         # three words per tap: units of one
+    (2, 3, 3, 4096, 3, 3, 1, 1),       # 288 units of four words: two chunks
+    (2, 3, 5, 1056, 3, 3, 1, 2),       # 297 units of one word: two chunks
+    (0, 4, 4, 64, 3, 3, 1, 1),
+])
+@pytest.mark.parametrize("first,pad_words", [(0, 0), (1, 3)])
+def test_im2col_units_at_every_word_alignment(shape, first, pad_words):
+    """Copies of 4, 2 and 1 words from and to any 4-byte offset; nothing written between or behind the rows."""
+    B, H, W, Cin, kh, kw, stride, pad = shape
+    rng = np.random.default_rng(sum(shape))
+    x = synth.pm1(rng, (max(B, 1), H, W, Cin))
+    want = oracle.pack_bits(oracle.im2col(x, kh, kw, stride, pad))
+    kwords = want.shape[1]
+    rows = want.shape[0] if B else 0
+    xb = _pack_nhwc(x)[:B]
+    flat_in = torch.zeros(first + xb.size, dtype=torch.int32, device=DEV)
+    flat_in[first:] = torch.from_numpy(xb.reshape(-1).view(np.int32)).to(DEV)
+    ld = kwords + pad_words
+    flat = torch.full((first + rows * ld + 8,), 0x6B6B6B6B, dtype=torch.int32, device=DEV)
+    out = flat[first:first + rows * ld].view(rows, ld)[:, :kwords]
+    bnn.conv_im2col_pack(flat_in[first:].view(B, H, W, Cin // 32), Cin, kh, kw, stride, pad, out=out)
+    assert (words_to_host(out) == want[:rows]).all()
+    out.fill_(0x6B6B6B6B)
+    assert (flat == 0x6B6B6B6B).all()
+
+
 def test_conv_layers_end_to_end_small_batch():
     """The three conv layer shapes (128@32x32, 256@16x16, 512@8x8), batch 2:
     im2col -> XNOR GEMM -> BN+Sign against direct convolution + float BN + Sign."""
