@@ -1324,6 +1324,43 @@ def test_maxpool_bits_matches_pooling_of_preactivations(shape):
 
 
 @pytest.mark.parametrize("shape", [
+    # B, H, W, C, ph, pw, stride
+    (3, 6, 4, 128, 2, 2, 2),        # units of four words
+    (5, 7, 5, 256, 2, 2, 1),        # overlapping windows
+    (2, 9, 7, 96, 2, 2, 2),         # three words: units of one
+    (2, 9, 8, 384, 3, 2, 3),        # windows of other sizes
+    (1, 2, 2, 32, 2, 2, 2),         # one word
+    (300, 3, 3, 40, 3, 1, 1),
+])
+@pytest.mark.parametrize("first", [0, 1])
+@pytest.mark.parametrize("with_flip", [False, True])
+def test_maxpool_units_at_every_word_alignment(shape, first, with_flip):
+    """OR (AND where flip = 1) over each window, any 4-byte offset of the operands, nothing written past the end."""
+    B, H, W, C, ph, pw, stride = shape
+    rng = np.random.default_rng(sum(shape))
+    Cw = (C + 31) // 32
+    x = rng.integers(0, 2**32, (B, H, W, Cw), dtype=np.uint32)
+    flip = rng.integers(0, 2**32, Cw, dtype=np.uint32) if with_flip else np.zeros(Cw, np.uint32)
+    Hp, Wp = (H - ph) // stride + 1, (W - pw) // stride + 1
+    some = np.zeros((B, Hp, Wp, Cw), np.uint32)
+    every = ~some
+    for dy in range(ph):
+        for dx in range(pw):
+            v = x[:, dy:dy + (Hp - 1) * stride + 1:stride, dx:dx + (Wp - 1) * stride + 1:stride]
+            some, every = some | v, every & v
+    want = (some & ~flip) | (every & flip)
+    flat_in = torch.zeros(first + x.size, dtype=torch.int32, device=DEV)
+    flat_in[first:] = torch.from_numpy(x.reshape(-1).view(np.int32)).to(DEV)
+    flat = torch.full((first + want.size + 8,), 0x6B6B6B6B, dtype=torch.int32, device=DEV)
+    out = flat[first:first + want.size].view(want.shape)
+    f = torch.from_numpy(flip.view(np.int32)).to(DEV) if with_flip else None
+    bnn.maxpool_bits(flat_in[first:].view(x.shape), C, f, ph, pw, stride, out=out)
+    assert (words_to_host(out) == want).all()
+    out.fill_(0x6B6B6B6B)
+    assert (flat == 0x6B6B6B6B).all()
+
+
+@pytest.mark.parametrize("shape", [
     # B, H, W, Cin, Cout
     (3, 32, 32, 128, 130),      # row pairs in neighbouring accumulator blocks
     (5, 16, 16, 256, 64),       # vertical neighbour 16 lanes away
