@@ -132,6 +132,13 @@ def _ld(t: torch.Tensor) -> int:
     return t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
 
 
+def _holds(t: torch.Tensor, rows: int, cols: int, name: str):
+    """`t` has the [rows][cols] elements a call reads or writes.  The library sees a pointer and a leading dimension:
+    one that is too short it refuses itself, but too few rows, or a narrow slice of a wide buffer, only show here."""
+    if rows > 0 and 0 < cols <= _ld(t) and (t.shape[0] < rows or t.shape[1] < cols):
+        raise ValueError(f"{name} must hold [{rows}][{cols}] elements, got {list(t.shape)}")
+
+
 def version() -> int:
     return int(load_library().bnn_version())
 
@@ -166,6 +173,7 @@ def pack_sign(x: torch.Tensor, out: torch.Tensor | None = None, ld_out: int | No
     if out is None:
         out = _alloc_words(rows, kw, x.device, ld_out)
     _dev(out, torch.int32, "out")
+    _holds(out, rows, kw, "out")
     _check("bnn_pack_sign", lib.bnn_pack_sign(x.data_ptr(), rows, cols, _ld(x), out.data_ptr(), _ld(out),
                                              _stream(out)))
     return out
@@ -188,6 +196,7 @@ def xnor_gemm(A: torch.Tensor, B: torch.Tensor, K: int, out: torch.Tensor | None
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=A.device)
     _dev(out, torch.int32, "out")
+    _holds(out, M, N, "out")
     if kernel == KERNEL_AUTO:
         st = lib.bnn_xnor_gemm(A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), out.data_ptr(), _ld(out), M, N, K,
                                _stream(out))
@@ -231,6 +240,7 @@ def bn_sign_pack(C: torch.Tensor, thr: torch.Tensor, flip_bits: torch.Tensor,
     if out is None:
         out = _alloc_words(M, nw, C.device, ld_out)
     _dev(out, torch.int32, "out")
+    _holds(out, M, nw, "out")
     _check("bnn_bn_sign_pack", lib.bnn_bn_sign_pack(C.data_ptr(), _ld(C), M, N, thr.data_ptr(),
                                                    flip_bits.data_ptr(), out.data_ptr(), _ld(out), _stream(out)))
     return out
@@ -259,6 +269,7 @@ def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
     if out is None:
         out = _alloc_words(M, nw, A.device, ld_out)
     _dev(out, torch.int32, "out")
+    _holds(out, M, nw, "out")
     if kernel == KERNEL_AUTO:
         st = lib.bnn_xnor_gemm_bn_sign_pack(A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), M, N, K, thr.data_ptr(),
                                             flip_bits.data_ptr(), out.data_ptr(), _ld(out), _stream(out))
@@ -283,6 +294,7 @@ def pack_bitplanes(x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Te
     if out is None:
         out = torch.empty((rows, kw8), dtype=torch.int32, device=x.device)
     _dev(out, torch.int32, "out")
+    _holds(out, rows, kw8, "out")
     _check("bnn_pack_bitplanes", lib.bnn_pack_bitplanes(x.data_ptr(), rows, cols, _ld(x), out.data_ptr(), _ld(out),
                                                        _stream(out)))
     return out
@@ -301,6 +313,9 @@ def bitplane_gemm(Xp: torch.Tensor, B: torch.Tensor, K: int, out: torch.Tensor |
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=Xp.device)
     _dev(out, torch.int32, "out")
+    _holds(Xp, M if N else 0, 8 * words_per_row(K), "Xp")
+    _holds(B, N if M else 0, words_per_row(K), "B")
+    _holds(out, M, N, "out")
     _check("bnn_bitplane_gemm", lib.bnn_bitplane_gemm(Xp.data_ptr(), _ld(Xp), B.data_ptr(), _ld(B), out.data_ptr(),
                                                      _ld(out), M, N, K, _stream(out)))
     return out
@@ -325,6 +340,9 @@ def bitplane_gemm_bn_sign_pack(Xp: torch.Tensor, B: torch.Tensor, K: int, thr: t
     if out is None:
         out = _alloc_words(M, nw, Xp.device, ld_out)
     _dev(out, torch.int32, "out")
+    _holds(Xp, M if N else 0, 8 * words_per_row(K), "Xp")
+    _holds(B, N if M else 0, words_per_row(K), "B")
+    _holds(out, M, nw, "out")
     _check("bnn_bitplane_gemm_bn_sign_pack",
            lib.bnn_bitplane_gemm_bn_sign_pack(Xp.data_ptr(), _ld(Xp), B.data_ptr(), _ld(B), M, N, K,
                                               thr.data_ptr(), flip_bits.data_ptr(), out.data_ptr(), _ld(out),
@@ -351,6 +369,7 @@ def conv_im2col_pack(x_bits: torch.Tensor, Cin: int, kh: int = 3, kw: int = 3, s
     if out is None:
         out = _alloc_words(B * max(Ho, 0) * max(Wo, 0), kwords, x_bits.device, ld_out)
     _dev(out, torch.int32, "out")
+    _holds(out, B * max(Ho, 0) * max(Wo, 0), kwords, "out")
     _check("bnn_conv_im2col_pack",
            lib.bnn_conv_im2col_pack(x_bits.data_ptr(), B, H, W, Cin, kh, kw, stride, pad, out.data_ptr(),
                                     _ld(out), _stream(out)))
@@ -380,6 +399,9 @@ def conv_xnor(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor, kh: int = 3,
     if out is None:
         out = torch.empty((B * Ho * Wo, Cout), dtype=torch.int32, device=x_bits.device)
     _dev(out, torch.int32, "out")
+    M = B * max(Ho, 0) * max(Wo, 0)
+    _holds(w_bits, Cout if M else 0, words_per_row(kh * kw * Cin), "w_bits")
+    _holds(out, M, Cout, "out")
     _check("bnn_conv_xnor", lib.bnn_conv_xnor(x_bits.data_ptr(), B, H, W, Cin, w_bits.data_ptr(), _ld(w_bits), Cout,
                                              kh, kw, stride, pad, out.data_ptr(), _ld(out), _stream(out)))
     return out
@@ -407,6 +429,9 @@ def conv_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor, thr:
     if out is None:
         out = torch.empty((B * Ho * Wo, nw), dtype=torch.int32, device=x_bits.device)
     _dev(out, torch.int32, "out")
+    M = B * max(Ho, 0) * max(Wo, 0)
+    _holds(w_bits, Cout if M else 0, words_per_row(kh * kw * Cin), "w_bits")
+    _holds(out, M, nw, "out")
     _check("bnn_conv_bn_sign_pack",
            lib.bnn_conv_bn_sign_pack(x_bits.data_ptr(), B, H, W, Cin, w_bits.data_ptr(), _ld(w_bits), Cout, kh, kw,
                                      stride, pad, thr.data_ptr(), flip_bits.data_ptr(), out.data_ptr(), _ld(out),
@@ -440,6 +465,7 @@ def conv_pool_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor,
     if out is None:
         out = torch.empty((B * (Ho // pool) * (Wo // pool), nw), dtype=torch.int32, device=x_bits.device)
     _dev(out, torch.int32, "out")
+    _holds(w_bits, Cout if B * max(Ho, 0) * max(Wo, 0) else 0, words_per_row(kh * kw * Cin), "w_bits")
     if out.shape[0] != B * (Ho // pool) * (Wo // pool) or out.shape[1] != nw:
         raise ValueError("out must be [B*(Ho/pool)*(Wo/pool)][ceil(Cout/32)]")
     _check("bnn_conv_pool_bn_sign_pack",
@@ -485,6 +511,7 @@ def gemm_i8_mfma(A: torch.Tensor, B: torch.Tensor, out: torch.Tensor | None = No
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=A.device)
     _dev(out, torch.int32, "out")
+    _holds(out, M, N, "out")
     _check("bnn_gemm_i8_mfma", lib.bnn_gemm_i8_mfma(A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), out.data_ptr(),
                                                    _ld(out), M, N, K, _stream(out)))
     return out
@@ -495,6 +522,7 @@ def unpack_i8(bits: torch.Tensor, K: int, ld_out: int | None = None) -> torch.Te
     lib = load_library()
     _dev(bits, torch.int32, "bits")
     rows = bits.shape[0]
+    _holds(bits, rows, words_per_row(K), "bits")
     ld = ld_out if ld_out is not None else (K + 15) // 16 * 16
     buf = torch.empty((rows, ld), dtype=torch.int8, device=bits.device)
     _check("bnn_unpack_i8", lib.bnn_unpack_i8(bits.data_ptr(), _ld(bits), rows, K, buf.data_ptr(), ld, _stream(buf)))

@@ -77,6 +77,9 @@ struct Matrix {
     }
     template <typename T>
     T* as() const { return static_cast<T*>(data); }
+    // The [r][c] elements a call reads or writes are there.  A leading dimension that is too short is left to the library,
+    // which refuses it; too few rows, or a narrow slice of a wide buffer, it cannot see.
+    bool holds(int64_t r, int64_t c) const { return r <= 0 || c <= 0 || ld < c || (rows >= r && cols >= c); }
 };
 
 // A packed map [B][H][W][words], contiguous.
@@ -163,7 +166,7 @@ PyObject* entry_of(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (x, out)
 PyObject* pack_sign(PyObject* const* a) {
     Matrix x, out;
-    if (!x.read(a[0], at::kFloat) || !out.read(a[1], at::kInt)) return long_way();
+    if (!x.read(a[0], at::kFloat) || !out.read(a[1], at::kInt) || !out.holds(x.rows, words(x.cols))) return long_way();
     return launch(*out.t, [&](void* s) { return entry.pack_sign(x.as<float>(), x.rows, x.cols, x.ld, out.as<uint32_t>(), out.ld, s); });
 }
 
@@ -173,7 +176,7 @@ PyObject* xnor_gemm(PyObject* const* a) {
     int64_t K;
     int kernel;
     if (!A.read(a[0], at::kInt) || !B.read(a[1], at::kInt) || !integer(a[2], K) || !out.read(a[3], at::kInt) ||
-        !small_integer(a[4], kernel) || K < 0 || A.cols < words(K) || B.cols < words(K))
+        !small_integer(a[4], kernel) || K < 0 || A.cols < words(K) || B.cols < words(K) || !out.holds(A.rows, B.rows))
         return long_way();
     return launch(*out.t, [&](void* s) {
         return kernel == 0 ? entry.xnor_gemm(A.as<uint32_t>(), A.ld, B.as<uint32_t>(), B.ld, out.as<int32_t>(), out.ld, A.rows,
@@ -189,7 +192,7 @@ PyObject* bn_sign_pack(PyObject* const* a) {
     if (!C.read(a[0], at::kInt)) return long_way();
     const void* thr = vector_of(a[1], C.cols);
     const void* flip = vector_of(a[2], words(C.cols));
-    if (!thr || !flip || !out.read(a[3], at::kInt)) return long_way();
+    if (!thr || !flip || !out.read(a[3], at::kInt) || !out.holds(C.rows, words(C.cols))) return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.bn_sign_pack(C.as<int32_t>(), C.ld, C.rows, C.cols, static_cast<const int32_t*>(thr),
                                   static_cast<Words>(flip), out.as<uint32_t>(), out.ld, s);
@@ -206,7 +209,8 @@ PyObject* xnor_gemm_bn_sign_pack(PyObject* const* a) {
         return long_way();
     const void* thr = vector_of(a[3], B.rows);
     const void* flip = vector_of(a[4], words(B.rows));
-    if (!thr || !flip || !out.read(a[5], at::kInt) || !small_integer(a[6], kernel)) return long_way();
+    if (!thr || !flip || !out.read(a[5], at::kInt) || !small_integer(a[6], kernel) || !out.holds(A.rows, words(B.rows)))
+        return long_way();
     return launch(*out.t, [&](void* s) {
         return kernel == 0
                    ? entry.xnor_gemm_bn_sign_pack(A.as<uint32_t>(), A.ld, B.as<uint32_t>(), B.ld, A.rows, B.rows, K,
@@ -221,15 +225,22 @@ PyObject* xnor_gemm_bn_sign_pack(PyObject* const* a) {
 // (x, out)
 PyObject* pack_bitplanes(PyObject* const* a) {
     Matrix x, out;
-    if (!x.read(a[0], at::kByte) || !out.read(a[1], at::kInt)) return long_way();
+    if (!x.read(a[0], at::kByte) || !out.read(a[1], at::kInt) || !out.holds(x.rows, 8 * words(x.cols))) return long_way();
     return launch(*out.t, [&](void* s) { return entry.pack_bitplanes(x.as<uint8_t>(), x.rows, x.cols, x.ld, out.as<uint32_t>(), out.ld, s); });
+}
+
+// The operands of a product on bit planes, where there is one.
+bool planes_hold(const Matrix& X, const Matrix& B, int64_t K) {
+    return X.holds(B.rows > 0 ? X.rows : 0, 8 * words(K)) && B.holds(X.rows > 0 ? B.rows : 0, words(K));
 }
 
 // (Xp, B, K, out)
 PyObject* bitplane_gemm(PyObject* const* a) {
     Matrix X, B, out;
     int64_t K;
-    if (!X.read(a[0], at::kInt) || !B.read(a[1], at::kInt) || !integer(a[2], K) || !out.read(a[3], at::kInt)) return long_way();
+    if (!X.read(a[0], at::kInt) || !B.read(a[1], at::kInt) || !integer(a[2], K) || !out.read(a[3], at::kInt) ||
+        !planes_hold(X, B, K) || !out.holds(X.rows, B.rows))
+        return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.bitplane_gemm(X.as<uint32_t>(), X.ld, B.as<uint32_t>(), B.ld, out.as<int32_t>(), out.ld, X.rows, B.rows, K, s);
     });
@@ -239,10 +250,10 @@ PyObject* bitplane_gemm(PyObject* const* a) {
 PyObject* bitplane_gemm_bn_sign_pack(PyObject* const* a) {
     Matrix X, B, out;
     int64_t K;
-    if (!X.read(a[0], at::kInt) || !B.read(a[1], at::kInt) || !integer(a[2], K)) return long_way();
+    if (!X.read(a[0], at::kInt) || !B.read(a[1], at::kInt) || !integer(a[2], K) || !planes_hold(X, B, K)) return long_way();
     const void* thr = vector_of(a[3], B.rows);
     const void* flip = vector_of(a[4], words(B.rows));
-    if (!thr || !flip || !out.read(a[5], at::kInt)) return long_way();
+    if (!thr || !flip || !out.read(a[5], at::kInt) || !out.holds(X.rows, words(B.rows))) return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.bitplane_gemm_bn_sign_pack(X.as<uint32_t>(), X.ld, B.as<uint32_t>(), B.ld, X.rows, B.rows, K,
                                                 static_cast<const int32_t*>(thr), static_cast<Words>(flip), out.as<uint32_t>(),
@@ -250,15 +261,26 @@ PyObject* bitplane_gemm_bn_sign_pack(PyObject* const* a) {
     });
 }
 
+// Output pixels of a convolution; 0 for a geometry that the library refuses.
+int64_t conv_pixels(const Map& x, int kh, int kw, int stride, int pad) {
+    const int64_t dh = x.H + 2 * int64_t(pad) - kh, dw = x.W + 2 * int64_t(pad) - kw;
+    return dh < 0 || dw < 0 ? 0 : x.B * (dh / stride + 1) * (dw / stride + 1);
+}
+
 struct Conv {
     Map x;
     Matrix w;
-    int64_t Cin = 0;
+    int64_t Cin = 0, M = 0;
     int kh = 0, kw = 0, stride = 0, pad = 0;
     // (x_bits, Cin, w_bits, kh, kw, stride, pad)
     bool read(PyObject* const* a) {
-        return integer(a[1], Cin) && Cin > 0 && x.read(a[0], Cin) && w.read(a[2], at::kInt) && small_integer(a[3], kh) &&
-               small_integer(a[4], kw) && small_integer(a[5], stride) && small_integer(a[6], pad) && stride > 0;
+        if (!integer(a[1], Cin) || Cin <= 0 || !x.read(a[0], Cin) || !w.read(a[2], at::kInt) || !small_integer(a[3], kh) ||
+            !small_integer(a[4], kw) || !small_integer(a[5], stride) || !small_integer(a[6], pad) || stride < 1)
+            return false;
+        M = conv_pixels(x, kh, kw, stride, pad);
+        // (a window whose bits do not fit 64 is the wrapper's and the library's to refuse)
+        return kh > 0 && kw > 0 && Cin <= INT32_MAX && int64_t(kh) * kw <= INT32_MAX &&
+               w.holds(M > 0 ? w.rows : 0, words(int64_t(kh) * kw * Cin));
     }
 };
 
@@ -266,7 +288,7 @@ struct Conv {
 PyObject* conv_xnor(PyObject* const* a) {
     Conv c;
     Matrix out;
-    if (!c.read(a) || !out.read(a[7], at::kInt)) return long_way();
+    if (!c.read(a) || !out.read(a[7], at::kInt) || !out.holds(c.M, c.w.rows)) return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.conv_xnor(c.x.data, c.x.B, c.x.H, c.x.W, c.Cin, c.w.as<uint32_t>(), c.w.ld, c.w.rows, c.kh, c.kw, c.stride,
                                c.pad, out.as<int32_t>(), out.ld, s);
@@ -280,7 +302,7 @@ PyObject* conv_bn_sign_pack(PyObject* const* a) {
     if (!c.read(a)) return long_way();
     const void* thr = vector_of(a[7], c.w.rows);
     const void* flip = vector_of(a[8], words(c.w.rows));
-    if (!thr || !flip || !out.read(a[9], at::kInt)) return long_way();
+    if (!thr || !flip || !out.read(a[9], at::kInt) || !out.holds(c.M, words(c.w.rows))) return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.conv_bn_sign_pack(c.x.data, c.x.B, c.x.H, c.x.W, c.Cin, c.w.as<uint32_t>(), c.w.ld, c.w.rows, c.kh, c.kw,
                                        c.stride, c.pad, static_cast<const int32_t*>(thr), static_cast<Words>(flip),
@@ -314,7 +336,9 @@ PyObject* conv_im2col_pack(PyObject* const* a) {
     int64_t Cin;
     int kh, kw, stride, pad;
     if (!integer(a[1], Cin) || Cin <= 0 || !x.read(a[0], Cin) || !small_integer(a[2], kh) || !small_integer(a[3], kw) ||
-        !small_integer(a[4], stride) || !small_integer(a[5], pad) || stride < 1 || !out.read(a[6], at::kInt))
+        !small_integer(a[4], stride) || !small_integer(a[5], pad) || stride < 1 || !out.read(a[6], at::kInt) || kh < 1 || kw < 1 ||
+        Cin > INT32_MAX || int64_t(kh) * kw > INT32_MAX ||
+        !out.holds(conv_pixels(x, kh, kw, stride, pad), words(int64_t(kh) * kw * Cin)))
         return long_way();
     return launch(*out.t, [&](void* s) {
         return entry.conv_im2col_pack(x.data, x.B, x.H, x.W, Cin, kh, kw, stride, pad, out.as<uint32_t>(), out.ld, s);

@@ -302,6 +302,28 @@ def _call_forms():
         ("pooling, flips", bnn.maxpool_bits, (maps, 128, bits(1, 4)[0]), lambda: out(32, 4).view(2, 4, 4, 4)),
         ("pooling, wide window", bnn.maxpool_bits, (maps, 128, None, 9, 9), lambda: out(32, 4).view(2, 4, 4, 4)),
     ]
+    # Memory that does not hold what the call reads or writes, in ways a leading dimension does not show.
+    for name, fn, args, rows, cols in [
+            ("pack", bnn.pack_sign, (x,), M, 6), ("product", bnn.xnor_gemm, (a, w, K), M, N),
+            ("norm", bnn.bn_sign_pack, (bits(M, N), thr, flip), M, 3),
+            ("layer", bnn.xnor_gemm_bn_sign_pack, (a, w, K, thr, flip), M, 3), ("planes", bnn.pack_bitplanes, (u8,), M, 48),
+            ("bytes product", bnn.bitplane_gemm, (planes, w, K), M, N),
+            ("bytes layer", bnn.bitplane_gemm_bn_sign_pack, (planes, w, K, thr, flip), M, 3),
+            ("lowering", bnn.conv_im2col_pack, (maps, 128), 128, 36), ("conv", bnn.conv_xnor, (maps, 128, filt), 128, N),
+            ("conv layer", bnn.conv_bn_sign_pack, (maps, 128, filt, thr, flip), 128, 3)]:
+        forms.append((f"refused: {name}, too few rows", fn, args, lambda rows=rows, cols=cols: out(rows - 1, cols)))
+        forms.append((f"refused: {name}, one row", fn, args, lambda cols=cols: out(1, cols)))
+        forms.append((f"refused: {name}, a narrow slice", fn, args, lambda rows=rows, cols=cols: out(rows, cols + 1)[:, :cols - 1]))
+        forms.append((f"taken: {name}, room to spare", fn, args, lambda rows=rows, cols=cols: out(rows + 1, cols + 2)))
+    forms += [
+        ("refused: bytes product, narrow planes", bnn.bitplane_gemm, (planes[:, :47], w, K), lambda: out(M, N)),
+        ("refused: bytes product, narrow weights", bnn.bitplane_gemm, (planes, w[:, :5], K), lambda: out(M, N)),
+        ("refused: bytes layer, narrow planes", bnn.bitplane_gemm_bn_sign_pack, (planes[:, :47], w, K, thr, flip), lambda: out(M, 3)),
+        ("refused: bytes layer, narrow weights", bnn.bitplane_gemm_bn_sign_pack, (planes, w[:, :5], K, thr, flip), lambda: out(M, 3)),
+        ("refused: conv, narrow filters", bnn.conv_xnor, (maps, 128, filt[:, :35]), lambda: out(128, N)),
+        ("refused: conv layer, narrow filters", bnn.conv_bn_sign_pack, (maps, 128, filt[:, :35], thr, flip), lambda: out(128, 3)),
+        ("refused: pooled layer, narrow filters", bnn.conv_pool_bn_sign_pack, (maps, 128, filt[:, :35], thr, flip), lambda: out(32, 3)),
+    ]
     return forms
 
 
@@ -333,6 +355,10 @@ def test_native_calls_do_what_the_wrappers_do(monkeypatch):
         assert with_native[0] == without[0], name
         assert torch.equal(with_native[1], without[1]) if with_native[0] == "ok" else with_native[1] == without[1], name
         seen.add(with_native[0] if with_native[0] == "ok" else with_native[0].__name__)
+        if name.startswith("refused: "):
+            assert with_native[0] is ValueError, name
+        if name.startswith("taken: "):
+            assert with_native[0] == "ok", name
     assert {"ok", "ValueError", "BnnError"} <= seen
 
 
