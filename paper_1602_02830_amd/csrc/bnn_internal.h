@@ -36,11 +36,12 @@ __device__ inline void store_result(int32_t* p, int32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Four consecutive results, 4-byte aligned, with the same policy.
+// Four consecutive results, 4-byte aligned, with the same policy.  The compiler keeps vector writes to the data registers
+// of a store of more than 64 bits two wait states behind it, but does not see a store in assembly: the wait is part of it.
 __device__ inline void store_result4(int32_t* p, int4 v) {
     typedef int quad_t __attribute__((ext_vector_type(4)));
     const quad_t q = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(q) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(q) : "memory");
 }
 
 // Mask of the valid bits of the last word of a K-bit row (all ones if K % 32 == 0).

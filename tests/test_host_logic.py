@@ -219,3 +219,19 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(binding, "_LIB_PATH", "/nonexistent/libbnn_hip.so")
     with pytest.raises(ImportError):
         binding.load_library()
+
+
+# ------------------------------------------------------------------ what the compiler does not check
+
+def test_wide_stores_in_assembly_bring_their_wait_states():
+    """A store of more than 64 bits reads its data registers late: a vector write to them has to stay two wait states
+    behind.  The compiler sees to that for its own stores only, so one in inline assembly carries the wait in its text."""
+    csrc = os.path.join(ROOT, "paper_1602_02830_amd", "csrc")
+    seen = 0
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for block in re.findall(r'asm(?:\s+volatile)?\s*\(\s*"((?:[^"\\]|\\.)*)"', text):
+            if re.search(r"(?:global|flat|buffer)_store_(?:dwordx[34]|b96|b128)", block):
+                seen += 1
+                assert re.search(r"_store_[^\\]*\\n(?:\\t)?s_nop [1-9]", block), f"{name}: {block}"
+    assert seen > 0
