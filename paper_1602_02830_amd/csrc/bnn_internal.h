@@ -28,6 +28,9 @@ inline int check_launch() {
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Most workgroups of one launch: it holds fewer than 2^32 work items in a dimension.
+inline constexpr int64_t max_blocks(int threads) { return ((int64_t(1) << 32) - 1) / threads; }
+
 // Store of an int32 result with agent scope (global_store_dword ... sc1: written through the die's L2).
 // Measured against plain and non-temporal stores on whole int32 products, it is the fastest policy while the
 // output is not much larger than the last-level cache, and by far the fastest where rows of the output are

@@ -222,7 +222,8 @@ extern "C" int bnn_pack_bitplanes(const uint8_t* x, int64_t rows, int64_t cols, 
     if (!x || !out) return BNN_ERR_INVALID_ARG;
     if (!aligned_to(out, 4)) return BNN_ERR_ALIGNMENT;
     const int64_t n_groups = rows * kw;
-    const int64_t blocks = ceil_div(n_groups, kPackThreads) < kMaxDim ? ceil_div(n_groups, kPackThreads) : kMaxDim;
+    int64_t blocks = ceil_div(n_groups, kPackThreads);
+    if (blocks > max_blocks(kPackThreads)) blocks = max_blocks(kPackThreads);      // the kernel loops over the rest
     hipLaunchKernelGGL(pack_bitplanes_kernel, dim3(unsigned(blocks)), dim3(kPackThreads), 0, static_cast<hipStream_t>(stream),
                        x, cols, ld_x, out, ld_out, kw, n_groups);
     return check_launch();

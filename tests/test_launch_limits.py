@@ -1,0 +1,97 @@
+"""CPU-only tests of the launches themselves: what grid an entry point asks the runtime for at sizes near the limits of the
+ABI.  A child process puts a stand-in for the runtime's launch call in front of the real one - it notes each launch,
+refuses what the runtime refuses (a dimension of 2^32 work items or more) and runs nothing - and calls the library with
+addresses that nothing reads."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_1602_02830_amd", "libbnn_hip.so")
+
+RUNTIME = r"""
+#include <stddef.h>
+#include <stdint.h>
+typedef struct { uint32_t x, y, z; } dim3;
+static dim3 next_grid, next_block;
+static size_t next_shared;
+static void* next_stream;
+static int error;
+int64_t launches;
+uint64_t launch_log[64][3];          /* workgroups, threads, first kernel argument */
+
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t shared, void* stream) {
+    next_grid = g; next_block = b; next_shared = shared; next_stream = stream;
+    return 0;
+}
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shared, void** stream) {
+    *g = next_grid; *b = next_block; *shared = next_shared; *stream = next_stream;
+    return 0;
+}
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t shared, void* stream) {
+    (void)f; (void)shared; (void)stream;
+    if ((uint64_t)g.x * b.x >> 32 || g.x == 0 || g.y == 0 || g.z == 0) return error = 9;
+    if (launches < 64) {
+        launch_log[launches][0] = (uint64_t)g.x * g.y * g.z;
+        launch_log[launches][1] = (uint64_t)b.x * b.y * b.z;
+        launch_log[launches][2] = *(uint64_t*)args[0];
+    }
+    ++launches;
+    return 0;
+}
+int hipGetLastError(void) { int e = error; error = 0; return e; }
+int hipGetDevice(int* device) { *device = 0; return 0; }
+int hipDeviceGetAttribute(int* value, int attribute, int device) { (void)attribute; (void)device; *value = 256; return 0; }
+"""
+
+CHILD = r"""
+import ctypes, json, sys
+runtime = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+count = ctypes.c_int64.in_dll(runtime, "launches")
+log = (ctypes.c_uint64 * 3 * 64).in_dll(runtime, "launch_log")
+out = []
+for name, args in json.load(sys.stdin):
+    # integers of the ABI that are not int64 (window sizes, kernel ids) are passed as such in registers or stack slots alike
+    count.value = 0
+    status = getattr(lib, name)(*[ctypes.c_int64(a) for a in args])
+    out.append([status, [list(log[i]) for i in range(min(count.value, 64))]])
+print(json.dumps(out))
+"""
+
+A, B, C, THR, FLIP, OUT = (i << 44 for i in range(1, 7))          # operand addresses
+
+
+@pytest.fixture(scope="module")
+def launches_of(tmp_path_factory):
+    """calls -> [(status, [[workgroups, threads, first argument], ...]), ...]"""
+    folder = tmp_path_factory.mktemp("runtime")
+    src, so = folder / "runtime.c", folder / "runtime.so"
+    src.write_text(RUNTIME)
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+
+    def run(*calls):
+        r = subprocess.run([sys.executable, "-c", CHILD, str(so), LIB], input=json.dumps([[n, list(a)] for n, a in calls]),
+                           stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout)
+
+    return run
+
+
+def test_the_stand_in_sees_launches(launches_of):
+    (st, log), (st_empty, log_empty) = launches_of(("bnn_pack_sign", (A, 4, 100, 100, OUT, 4, 0)),
+                                                   ("bnn_pack_sign", (A, 0, 100, 100, OUT, 4, 0)))
+    assert st == 0 and log == [[1, 256, A]]
+    assert st_empty == 0 and log_empty == []
+
+
+@pytest.mark.parametrize("rows,cols", [(2 ** 31 - 1, 33), (2 ** 31 - 1, 1), (2 ** 26, 2 ** 12), (2 ** 24, 2 ** 31 - 1), (10 ** 6, 10 ** 5)])
+def test_bit_plane_packer_stays_below_the_work_item_limit(launches_of, rows, cols):
+    kw = (cols + 31) // 32
+    (st, log), = launches_of(("bnn_pack_bitplanes", (A, rows, cols, cols, OUT, 8 * kw, 0)))
+    assert st == 0 and len(log) == 1 and log[0][1] == 256
+    assert log[0][0] >= min(-(-rows * kw // 256), 2 ** 23)
