@@ -85,7 +85,7 @@ __device__ inline UnitAt unit_at(uint32_t block, uint32_t gi, int units_per_row,
 inline int64_t unit_blocks(int64_t rows_total, int64_t cols, int rows) {
     if (cols <= 0 || cols % 128 != 0) return 0;
     const int64_t blocks = ceil_div(ceil_div(rows_total, rows) * (cols / 128), kUnitsPerBlock);
-    return blocks * kUnitsPerBlock <= int64_t(0xFFFFFFFF) ? blocks : 0;         // units are counted in 32 bits
+    return blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
 }
 
 }  // namespace bnn

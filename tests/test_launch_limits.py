@@ -95,3 +95,12 @@ def test_bit_plane_packer_stays_below_the_work_item_limit(launches_of, rows, col
     (st, log), = launches_of(("bnn_pack_bitplanes", (A, rows, cols, cols, OUT, 8 * kw, 0)))
     assert st == 0 and len(log) == 1 and log[0][1] == 256
     assert log[0][0] >= min(-(-rows * kw // 256), 2 ** 23)
+
+
+@pytest.mark.parametrize("rows,cols", [(2 ** 22, 2 ** 14), (2 ** 24 - 1, 4096), (2 ** 31 - 1, 128), (2 ** 20, 2 ** 18)])
+def test_streaming_kernels_stay_below_the_work_item_limit(launches_of, rows, cols):
+    """On both sides of the sizes whose rows of whole 128-element units still fit one launch (2^24 - 1 workgroups)."""
+    kw = cols // 32
+    for st, log in launches_of(("bnn_pack_sign", (A, rows, cols, cols, OUT, kw, 0)),
+                               ("bnn_bn_sign_pack", (C, cols, rows, cols, THR, FLIP, OUT, kw, 0))):
+        assert st == 0 and len(log) == 1 and log[0][1] == 256
