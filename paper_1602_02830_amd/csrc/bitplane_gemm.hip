@@ -66,7 +66,8 @@ constexpr int kSignMaxK = (1 << 30) / 256;
 constexpr int kWordsPerTile = 4;              // K-words per staged tile = 2 pairs = 4 MFMA steps
 
 // WI x 2 blocks of 32 x 32 per wavefront, WAVES wavefronts side by side: a tile of 32*WI rows x 64*WAVES columns.
-template <int WI, int WAVES, bool FUSED>
+// TINY: rows of fewer than 4 words (K <= 96), which have no whole quad to load and one K-tile, or none.
+template <int WI, int WAVES, bool FUSED, bool TINY>
 __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
@@ -76,8 +77,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     constexpr int PLANE_A = BM + 1;                        // 16-byte slots; odd, so that the 4 words x 2 rows that 8 lanes
                                                            // store fall into eight different bank groups
     static_assert(L >= 1 && L * T == BM * kWordsPerTile, "the tile's words must divide among the threads");
-    __shared__ uint4 lds_a[2][2 * kWordsPerTile * PLANE_A];    // [word][half of its 32 bytes][row]
-    __shared__ uint32_t lds_b[2][kWordsPerTile * BN];          // [word][column]
+    __shared__ uint4 lds_a[TINY ? 1 : 2][2 * kWordsPerTile * PLANE_A];    // [word][half of its 32 bytes][row]
+    __shared__ uint32_t lds_b[TINY ? 1 : 2][kWordsPerTile * BN];          // [word][column]
     __shared__ int rowsum_s[BM];
     __shared__ __attribute__((aligned(16))) int colterm_s[BN]; // 256 * popcount, less the threshold when the sign decides
     __shared__ __attribute__((aligned(16))) int thr_s[FUSED ? BN : 4];
@@ -113,7 +114,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
         ra[l][0] = load_quad_any(pa[l] + w);
         ra[l][1] = load_quad_any(pa[l] + w + 4);
     };
-    auto fetch_b = [&](int kt) { rb = load_quad_any(pb + min(kWordsPerTile * kt, kw - kWordsPerTile)); };
+    auto fetch_b = [&](int kt) {
+        if (TINY) rb = make_uint4(pb[0], pb[min(1, kw - 1)], pb[min(2, kw - 1)], 0u);
+        else rb = load_quad_any(pb + min(kWordsPerTile * kt, kw - kWordsPerTile));
+    };
     // The last, partial tile: words past the row's end become zero, the last word's pad bits are masked.
     auto mask_tail = [&](int kt) {
         const int w = kWordsPerTile * kt + st_w;
@@ -123,8 +127,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 ra[l][h] = make_uint4(ra[l][h].x & mask, ra[l][h].y & mask, ra[l][h].z & mask, ra[l][h].w & mask);
-        // rb holds the row's last four words: word 0 of the tile is its word 4 - left.
         const int left = kw - kWordsPerTile * kt;
+        if (TINY) {
+            rb = mask_row_quad(rb, left, tmask);
+            return;
+        }
+        // rb holds the row's last four words: word 0 of the tile is its word 4 - left.
         const uint32_t last = rb.w & tmask;
         rb = left == 1 ? make_uint4(last, 0u, 0u, 0u) : left == 2 ? make_uint4(rb.z, last, 0u, 0u)
            : left == 3 ? make_uint4(rb.y, rb.z, last, 0u) : make_uint4(rb.x, rb.y, rb.z, last);
@@ -198,9 +206,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
         }
         store_b(buf);
     };
-    fetch(0);
-    stage(0, 0);
-    fetch(1);
+    if (!TINY || n_ktiles > 0) {
+        fetch(0);
+        stage(0, 0);
+    }
+    if (!TINY) fetch(1);
     __syncthreads();
 
     // Tile kt is multiplied while tile kt + 1 (in registers since the iteration before) is transposed and stored to the
@@ -469,52 +479,62 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
 
 }  // namespace planes
 
-template <int WI, int WAVES, bool FUSED>
+template <int WI, int WAVES, bool FUSED, bool TINY>
 static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
-                        int64_t M, int64_t N, int64_t K, const BnSignArgs& bn, hipStream_t s) {
-    const int64_t tiles_m = ceil_div(M, 32 * WI), tiles_n = ceil_div(N, 64 * WAVES);
-    if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WAVES, FUSED>), dim3(unsigned(tiles_m * tiles_n)), dim3(64 * WAVES), 0,
-                       s, Xp, ldx, B, ldb, C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
-    return check_launch();
+                        int64_t M, int64_t N, int64_t K, BnSignArgs bn, hipStream_t s) {
+    constexpr int BM = 32 * WI, T = 64 * WAVES;
+    const int64_t tiles_n = ceil_div(N, 64 * WAVES);
+    const int64_t rows = max_blocks(T) / tiles_n * BM;      // of one launch: all of them, short of 2^23 tiles
+    for (int64_t m0 = 0; m0 < M; m0 += rows) {
+        const int64_t m = M - m0 < rows ? M - m0 : rows, tiles_m = ceil_div(m, BM);
+        hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WAVES, FUSED, TINY>), dim3(unsigned(tiles_m * tiles_n)), dim3(T), 0, s,
+                           Xp + m0 * ldx, ldx, B, ldb, C + m0 * ldc, ldc, int(m), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
+        const int st = check_launch();
+        if (st != BNN_OK) return st;
+        bn.out += rows * bn.ld_out;
+    }
+    return BNN_OK;
 }
 
 // The choice, from a sweep of 22 shapes with M = 7 .. 10000, N = 33 .. 4096, K = 133 .. 3072 (fused, us, with the packing
-// of the planes):
+// of the planes) and one of 60 with M = 100 .. 1000000, N = 10 .. 4096, K <= 96 (fused, us):
 //  - split up to 1024 of its 32 x 32 tiles: 100 x 4096 x 784 7.8 vs 10.2 on 64 x 256 tiles, 233 x 4096 x 784 (1024 tiles)
-//    10.1 vs 10.4, 300 x 512 x 3072 11.4 vs 21.5; but 363 x 4096 x 784 12.5 vs 10.5, 501 x 2954 x 3072 33.0 vs 22.8.  Also
-//    rows of fewer than 4 words, which the tiles' quad loads of B do not take.
-//  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5: 4000 x 4096 x 784 21.5 vs 24.3 on
-//    64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs 194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9.  Its
-//    int32 form does not fit the registers.
+//    10.1 vs 10.4, 300 x 512 x 3072 11.4 vs 21.5; but 363 x 4096 x 784 12.5 vs 10.5, 501 x 2954 x 3072 33.0 vs 22.8.  Few
+//    words in K leave most of its wavefronts idle: 1000 x 4096 x 64 (4096 tiles) 10.1 vs 3.9, 10000 x 4096 x 64 70 vs 13.7.
+//  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5 and K > 96: 4000 x 4096 x 784 21.5 vs 24.3
+//    on 64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs 194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9, 10000 x
+//    4096 x 64 (one K-tile) 15.3 vs 13.7.  Its int32 form does not fit the registers.
 //  - 64 x 256 (four workgroups per compute unit) otherwise: 2000 x 4096 x 784 15.4 vs 18.0, 3280 x 1152 x 2394 30 vs 39.
 constexpr int64_t kSplitMaxTiles = 1024;
 constexpr int64_t kComputeUnits = 256;
 
-template <bool FUSED>
+template <bool FUSED, bool TINY>
 static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                          int64_t M, int64_t N, int64_t K, const BnSignArgs& bn, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t small_m = ceil_div(M, 32), small_n = ceil_div(N, 32);
-    if ((K <= 96 && small_m * small_n <= kMaxDim) || small_m * small_n <= kSplitMaxTiles) {
+    if (small_m * small_n <= kSplitMaxTiles) {
         hipLaunchKernelGGL(planes::bitplane_gemm_split_kernel<FUSED>, dim3(unsigned(small_m * small_n)), dim3(256), 0, s, Xp,
                            ldx, B, ldb, C, ldc, int(M), int(N), int(K), tile_map(small_m, small_n), bn);
         return check_launch();
     }
-    if (K <= 96) return BNN_ERR_UNSUPPORTED;               // more than 2^41 outputs
-    if constexpr (FUSED) {
+    if constexpr (FUSED && !TINY) {
         const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 512);
         const int64_t rounds = ceil_div(tiles, kComputeUnits);
-        if (5 * tiles >= 4 * rounds * kComputeUnits) return launch_tiles<4, 8, true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+        if (5 * tiles >= 4 * rounds * kComputeUnits)
+            return launch_tiles<4, 8, true, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
     }
-    return launch_tiles<2, 4, FUSED>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+    return launch_tiles<2, 4, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
 }
 
 // The callers have validated the arguments.  fused: bn holds thresholds, flip words and the output.
 int launch_bitplane_gemm(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                          int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn, void* stream) {
-    return fused ? launch_planes<true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream)
-                 : launch_planes<false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream);
+    if (K <= 96)
+        return fused ? launch_planes<true, true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream)
+                     : launch_planes<false, true>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream);
+    return fused ? launch_planes<true, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream)
+                 : launch_planes<false, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, stream);
 }
 
 }  // namespace bnn

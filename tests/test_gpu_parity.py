@@ -1631,10 +1631,11 @@ def test_bitplane_gemm_first_layer(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    # K split over the wavefronts (at most 1024 tiles of 32 x 32, or rows of fewer than 4 words): one word, an odd
-    # number of words, one pair past a batch, the largest grid
+    # K split over the wavefronts (at most 1024 tiles of 32 x 32): one word, an odd number of words, one pair past a
+    # batch, the largest grid
     (33, 65, 32), (32, 32, 64), (31, 97, 96), (64, 31, 288), (40, 33, 545), (1024, 1024, 784),
-    (5000, 300, 96), (5000, 300, 65),
+    # 64 x 256 tiles, rows of 1 .. 3 words with and without pad bits
+    (5000, 300, 96), (5000, 300, 65), (4097, 257, 1), (5000, 256, 31), (2113, 769, 32), (3300, 4100, 33), (1100, 1025, 64),
     # 64 x 256 tiles: rows of exactly 4 words, 1 .. 4 words in the last tile with and without pad bits, 1 row / column
     # past a tile, the largest partial round
     (1100, 1025, 128), (1100, 1025, 127), (1090, 1057, 97), (1089, 1056, 129), (2100, 770, 160), (2113, 769, 223),
@@ -1665,6 +1666,19 @@ def test_bitplane_gemm_kernels_at_the_edges_of_their_tiles(M, N, K):
     flip_words = torch.from_numpy(oracle.pack_bits((2 * flip - 1).reshape(1, -1)).view(np.int32)[0].copy()).to(DEV)
     got = words_to_host(bnn.bitplane_gemm_bn_sign_pack(wide[:, :8 * kw], wb, K, torch.from_numpy(thr).to(DEV), flip_words))
     assert (got == oracle.pack_bits(np.where(bits, 1, -1).astype(np.int8))).all()
+
+
+@pytest.mark.parametrize("M,N", [(7, 33), (2000, 1000)])
+def test_bitplane_gemm_of_no_inputs(M, N):
+    """K = 0, on one tile and on a grid of the larger tiles: sums of nothing, thresholds as the only input."""
+    planes, wb = torch.zeros(M, 0, dtype=torch.int32, device=DEV), torch.zeros(N, 0, dtype=torch.int32, device=DEV)
+    out = torch.full((M, N), 9, dtype=torch.int32, device=DEV)
+    bnn.bitplane_gemm(planes, wb, 0, out=out)
+    assert (out == 0).all()
+    thr = torch.arange(-(N // 2), N - N // 2, dtype=torch.int32, device=DEV)
+    flip = torch.zeros((N + 31) // 32, dtype=torch.int32, device=DEV)
+    want = oracle.pack_bits(np.where(thr.cpu().numpy() <= 0, 1, -1).astype(np.int8)[None, :].repeat(M, 0))
+    assert (words_to_host(bnn.bitplane_gemm_bn_sign_pack(planes, wb, 0, thr, flip)) == want).all()
 
 
 @pytest.mark.parametrize("rows,cols", [(3, 1), (5, 17), (4, 31), (300, 32), (257, 33), (9, 63), (7, 65), (2, 4097), (70, 1000)])

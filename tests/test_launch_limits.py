@@ -104,3 +104,26 @@ def test_streaming_kernels_stay_below_the_work_item_limit(launches_of, rows, col
     for st, log in launches_of(("bnn_pack_sign", (A, rows, cols, cols, OUT, kw, 0)),
                                ("bnn_bn_sign_pack", (C, cols, rows, cols, THR, FLIP, OUT, kw, 0))):
         assert st == 0 and len(log) == 1 and log[0][1] == 256
+
+
+def covers(log, first, ld, M, tiles_n, tile_m):
+    """Launches of tiles of tile_m rows that start at consecutive rows of the first operand and take all M of them."""
+    row = 0
+    for blocks, threads, address in log:
+        assert address == first + 4 * ld * row and blocks % tiles_n == 0 and blocks * threads < 2 ** 32
+        row += blocks // tiles_n * tile_m
+    return M <= row < M + tile_m
+
+
+@pytest.mark.parametrize("M,N,K", [(2 ** 22, 4096, 64), (33_500_000, 512, 27), (2 ** 31 - 1025, 33, 96), (2 ** 31 - 1025, 300, 33),
+                                   (2 ** 22, 4096, 0), (2 ** 31 - 1025, 33, 128), (2 ** 31 - 1025, 600, 200), (5, 2 ** 31 - 1025, 96)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_first_layers_of_any_size_stay_below_the_work_item_limit(launches_of, M, N, K, fused):
+    """8-bit first layers of 2^34 outputs and more, few words in K among them: every row once, in launches the runtime takes."""
+    kw = (K + 31) // 32
+    call = (("bnn_bitplane_gemm_bn_sign_pack", (A, 8 * kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)) if fused else
+            ("bnn_bitplane_gemm", (A, 8 * kw, B, kw, C, N, M, N, K, 0)))
+    (st, log), = launches_of(call)
+    assert st == 0 and log
+    tile_n, tile_m = {256: (256, 64), 512: (512, 128)}[log[0][1]]
+    assert covers(log, A, 8 * kw, M, -(-N // tile_n), tile_m)
