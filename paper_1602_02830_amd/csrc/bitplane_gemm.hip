@@ -15,8 +15,8 @@
 // arithmetic, exact modulo 2^32 and therefore exact for every K with 255*K < 2^31.
 //
 // Two organisations:
-//   tiles   32*WI x 64*WAVES outputs per workgroup, WI x 2 blocks of 32 x 32 per wavefront: 128 x 512 with 8 wavefronts
-//           (the large fused products) or 64 x 256 with 4.  A's rows are transposed once per workgroup while they are
+//   tiles   32*WI*WR x 64*WC outputs per workgroup, WI x 2 blocks of 32 x 32 per wavefront: 128 x 512 with 8 wavefronts
+//           (the large fused products), 64 x 256 with 4, or 64 x 128 with 2 x 2 (few columns).  A's rows are transposed once per workgroup while they are
 //           staged into LDS; B stays bits in LDS and is widened by the wavefront that multiplies it (as bytes it would
 //           double the LDS traffic, which is what holds the plain int8 product at a third of the matrix rate).  The wide,
 //           flat tile keeps both cheap: 4.4 vector operations per MFMA in all on 128 x 512 (a 2 x 2 arrangement of
@@ -65,18 +65,18 @@ constexpr int kSignMaxK = (1 << 30) / 256;
 // ----------------------------------------------------------------------------
 constexpr int kWordsPerTile = 4;              // K-words per staged tile = 2 pairs = 4 MFMA steps
 
-// WI x 2 blocks of 32 x 32 per wavefront, WAVES wavefronts side by side: a tile of 32*WI rows x 64*WAVES columns.
+// WI x 2 blocks of 32 x 32 per wavefront, WR rows of WC wavefronts side by side: a tile of 32*WI*WR rows x 64*WC columns.
 // TINY: rows of fewer than 4 words (K <= 96), which have no whole quad to load and one K-tile, or none.
-template <int WI, int WAVES, bool FUSED, bool TINY>
-__global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
+template <int WI, int WR, int WC, bool FUSED, bool TINY>
+__global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
-    constexpr int T = 64 * WAVES, BM = 32 * WI, BN = T;    // one staging thread per column of B
+    constexpr int T = 64 * WR * WC, BM = 32 * WI * WR, BN = 64 * WC;      // the first BN threads stage a column of B each
     constexpr int L = BM * kWordsPerTile / T;              // A words (32 elements, 8 plane words) a thread stages per tile
     constexpr int ROWS = T / kWordsPerTile;                // rows of a staging pass: 4 neighbouring lanes take the words of one
     constexpr int PLANE_A = BM + 1;                        // 16-byte slots; odd, so that the 4 words x 2 rows that 8 lanes
                                                            // store fall into eight different bank groups
-    static_assert(L >= 1 && L * T == BM * kWordsPerTile, "the tile's words must divide among the threads");
+    static_assert((L == 1 || L == 2) && L * T == BM * kWordsPerTile, "the tile's words must divide among the threads");
     __shared__ uint4 lds_a[TINY ? 1 : 2][2 * kWordsPerTile * PLANE_A];    // [word][half of its 32 bytes][row]
     __shared__ uint32_t lds_b[TINY ? 1 : 2][kWordsPerTile * BN];          // [word][column]
     __shared__ int rowsum_s[BM];
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     tile_of_block(blockIdx.x, tiles, tile_m, tile_n);
     const int row0 = tile_m * BM, col0 = tile_n * BN;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6, wr = WR > 1 ? wave / WC : 0, wc = WR > 1 ? wave % WC : wave;
     const int fr = lane & 31, fh = lane >> 5;
     const int kw = (K + 31) >> 5;
     const uint32_t tmask = tail_mask(K);
@@ -99,7 +99,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
     const uint32_t* pa[L];
 #pragma unroll
     for (int l = 0; l < L; ++l) pa[l] = Xp + int64_t(min(row0 + st_r + ROWS * l, M - 1)) * ldx;
-    const uint32_t* pb = B + int64_t(min(col0 + tid, N - 1)) * ldb;     // rows past the matrix repeat its last one
+    const bool st_b = WR == 1 || tid < BN;
+    const int b_col = min(col0 + (WR == 1 ? tid : tid & (BN - 1)), N - 1);             // rows past the matrix repeat its last one
+    const uint32_t* pb = B + int64_t(b_col) * ldb;
 
     uint4 ra[L][2], rb;
     int cnt_a[L], cnt_b = 0;
@@ -152,6 +154,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
                 make_uint4(bytes[4 * u], bytes[4 * u + 1], bytes[4 * u + 2], bytes[4 * u + 3]);
     };
     auto store_b = [&](int buf) {
+        if (!st_b) return;
         cnt_b += __popc(rb.x) + __popc(rb.y) + __popc(rb.z) + __popc(rb.w);
         lds_b[buf][0 * BN + tid] = rb.x;
         lds_b[buf][1 * BN + tid] = rb.y;
@@ -172,12 +175,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
         v4i fa[WI], fb[2];
 #pragma unroll
         for (int i = 0; i < WI; ++i) {
-            const uint4 q = lds_a[buf][(2 * (2 * t + fh) + u) * PLANE_A + i * 32 + fr];
+            const uint4 q = lds_a[buf][(2 * (2 * t + fh) + u) * PLANE_A + (wr * WI + i) * 32 + fr];
             fa[i] = v4i{int(q.x), int(q.y), int(q.z), int(q.w)};
         }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const uint32_t w = lds_b[buf][(2 * t + fh) * BN + (wave * 2 + j) * 32 + fr];
+            const uint32_t w = lds_b[buf][(2 * t + fh) * BN + (wc * 2 + j) * 32 + fr];
             fb[j] = u == 0 ? widen_bits<0>(w) : widen_bits<1>(w);
         }
 #pragma unroll
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
 
     int thr = 0;
     const int lim = 255 * K + 1;
-    if (FUSED) thr = max(-lim, min(lim, bn.thr[min(col0 + tid, N - 1)]));
+    if (FUSED) thr = max(-lim, min(lim, bn.thr[b_col]));
     auto fetch = [&](int kt) {
 #pragma unroll
         for (int l = 0; l < L; ++l) fetch_a(kt, l);
@@ -263,21 +266,23 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
         if (st_w == 0) rowsum_s[st_r + ROWS * l] = c;
     }
     const bool sign = FUSED && K <= kSignMaxK;
-    colterm_s[tid] = 256 * cnt_b - (sign ? thr : 0);
-    if (FUSED) thr_s[tid] = thr;
+    if (st_b) {
+        colterm_s[tid] = 256 * cnt_b - (sign ? thr : 0);
+        if (FUSED) thr_s[tid] = thr;
+    }
     __syncthreads();
 
     if constexpr (!FUSED) {
         // Accumulator register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32 of its 32 x 32 block.
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int nl = (wave * 2 + j) * 32 + fr, n = col0 + nl;
+            const int nl = (wc * 2 + j) * 32 + fr, n = col0 + nl;
             const int ct = colterm_s[nl];
 #pragma unroll
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int ml = i * 32 + 8 * (v / 4) + 4 * fh + (v % 4), m = row0 + ml;
+                    const int ml = (wr * WI + i) * 32 + 8 * (v / 4) + 4 * fh + (v % 4), m = row0 + ml;
                     if (m < M && n < N) store_result(&C[int64_t(m) * ldc + n], acc[i][j][v] + ct - rowsum_s[ml]);
                 }
         }
@@ -295,12 +300,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
                 int4 ct[4], th[4];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    ct[g] = *reinterpret_cast<const int4*>(&colterm_s[(wave * 2 + j) * 32 + 8 * g + 4 * fh]);
-                    if (!SIGN) th[g] = *reinterpret_cast<const int4*>(&thr_s[(wave * 2 + j) * 32 + 8 * g + 4 * fh]);
+                    ct[g] = *reinterpret_cast<const int4*>(&colterm_s[(wc * 2 + j) * 32 + 8 * g + 4 * fh]);
+                    if (!SIGN) th[g] = *reinterpret_cast<const int4*>(&thr_s[(wc * 2 + j) * 32 + 8 * g + 4 * fh]);
                 }
 #pragma unroll
                 for (int i = 0; i < WI; ++i) {
-                    const int r = rowsum_s[i * 32 + fr];
+                    const int r = rowsum_s[(wr * WI + i) * 32 + fr];
                     uint32_t neg = 0u;
 #pragma unroll
                     for (int g = 3; g >= 0; --g) {
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bitplane_gemm_kernel(
 #pragma unroll
             for (int i = 0; i < WI; ++i) {
                 const auto sw = __builtin_amdgcn_permlane32_swap(part[i][0], part[i][1], false, false);
-                words_s[(i * 32 + fr) * (BN / 32) + wave * 2 + fh] = sw[0] | sw[1];
+                words_s[((wr * WI + i) * 32 + fr) * (BN / 32) + wc * 2 + fh] = sw[0] | sw[1];
             }
         };
         if (sign) collect(std::true_type{});
@@ -479,15 +484,15 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
 
 }  // namespace planes
 
-template <int WI, int WAVES, bool FUSED, bool TINY>
+template <int WI, int WR, int WC, bool FUSED, bool TINY>
 static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                         int64_t M, int64_t N, int64_t K, BnSignArgs bn, hipStream_t s) {
-    constexpr int BM = 32 * WI, T = 64 * WAVES;
-    const int64_t tiles_n = ceil_div(N, 64 * WAVES);
+    constexpr int BM = 32 * WI * WR, T = 64 * WR * WC;
+    const int64_t tiles_n = ceil_div(N, 64 * WC);
     const int64_t rows = max_blocks(T) / tiles_n * BM;      // of one launch: all of them, short of 2^23 tiles
     for (int64_t m0 = 0; m0 < M; m0 += rows) {
         const int64_t m = M - m0 < rows ? M - m0 : rows, tiles_m = ceil_div(m, BM);
-        hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WAVES, FUSED, TINY>), dim3(unsigned(tiles_m * tiles_n)), dim3(T), 0, s,
+        hipLaunchKernelGGL((planes::bitplane_gemm_kernel<WI, WR, WC, FUSED, TINY>), dim3(unsigned(tiles_m * tiles_n)), dim3(T), 0, s,
                            Xp + m0 * ldx, ldx, B, ldb, C + m0 * ldc, ldc, int(m), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
         const int st = check_launch();
         if (st != BNN_OK) return st;
@@ -496,14 +501,18 @@ static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int6
     return BNN_OK;
 }
 
-// The choice, from a sweep of 22 shapes with M = 7 .. 10000, N = 33 .. 4096, K = 133 .. 3072 (fused, us, with the packing
-// of the planes) and one of 60 with M = 100 .. 1000000, N = 10 .. 4096, K <= 96 (fused, us):
+// The choice, from sweeps of 70 shapes with M = 7 .. 1000000, N = 10 .. 4096, K = 9 .. 3072 (fused, us; those of the first
+// and third item with K >= 97 with the packing of the planes):
 //  - split up to 1024 of its 32 x 32 tiles: 100 x 4096 x 784 7.8 vs 10.2 on 64 x 256 tiles, 233 x 4096 x 784 (1024 tiles)
 //    10.1 vs 10.4, 300 x 512 x 3072 11.4 vs 21.5; but 363 x 4096 x 784 12.5 vs 10.5, 501 x 2954 x 3072 33.0 vs 22.8.  Few
 //    words in K leave most of its wavefronts idle: 1000 x 4096 x 64 (4096 tiles) 10.1 vs 3.9, 10000 x 4096 x 64 70 vs 13.7.
-//  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5 and K > 96: 4000 x 4096 x 784 21.5 vs 24.3
-//    on 64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs 194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9, 10000 x
-//    4096 x 64 (one K-tile) 15.3 vs 13.7.  Its int32 form does not fit the registers.
+//  - 64 x 128 up to 128 columns, which wider tiles would multiply as 256 or 512: 262144 x 128 x 27 12.6 vs 19.7 on 64 x 256
+//    and 35.6 on 128 x 512, 262144 x 128 x 147 17.7 vs 24.5 and 49.3, 1000000 x 32 x 75 43.6 vs 75 and 151.  With 129 columns
+//    and more the 64 x 256 tile is level or better (100000 x 300 x 200 20.8 vs 21.3, 40000 x 640 x 784 36.7 vs 33.5).
+//  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5 with at most a quarter of columns that do
+//    not exist, and K > 96: 4000 x 4096 x 784 21.5 vs 24.3 on 64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs
+//    194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9, 262144 x 256 x 147 (half of the columns) 50.4 vs 25.2, 10000 x 4096 x
+//    64 (one K-tile) 15.3 vs 13.7.  Its int32 form does not fit the registers.
 //  - 64 x 256 (four workgroups per compute unit) otherwise: 2000 x 4096 x 784 15.4 vs 18.0, 3280 x 1152 x 2394 30 vs 39.
 constexpr int64_t kSplitMaxTiles = 1024;
 constexpr int64_t kComputeUnits = 256;
@@ -518,13 +527,14 @@ static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int
                            ldx, B, ldb, C, ldc, int(M), int(N), int(K), tile_map(small_m, small_n), bn);
         return check_launch();
     }
+    if (N <= 128) return launch_tiles<1, 2, 2, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
     if constexpr (FUSED && !TINY) {
-        const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 512);
+        const int64_t tiles_n = ceil_div(N, 512), tiles = ceil_div(M, 128) * tiles_n;
         const int64_t rounds = ceil_div(tiles, kComputeUnits);
-        if (5 * tiles >= 4 * rounds * kComputeUnits)
-            return launch_tiles<4, 8, true, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+        if (5 * tiles >= 4 * rounds * kComputeUnits && 4 * N >= 3 * 512 * tiles_n)
+            return launch_tiles<4, 1, 8, true, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
     }
-    return launch_tiles<2, 4, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
+    return launch_tiles<2, 1, 4, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
 }
 
 // The callers have validated the arguments.  fused: bn holds thresholds, flip words and the output.

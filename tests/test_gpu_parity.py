@@ -1640,6 +1640,11 @@ def test_bitplane_gemm_first_layer(M, N, K):
     # past a tile, the largest partial round
     (1100, 1025, 128), (1100, 1025, 127), (1090, 1057, 97), (1089, 1056, 129), (2100, 770, 160), (2113, 769, 223),
     (1300, 900, 256), (1057, 1000, 383), (3000, 513, 784),
+    # 64 x 128 tiles (at most 128 columns): rows and columns past a tile, one and several words, no whole quad
+    (40000, 33, 27), (16500, 128, 96), (11000, 97, 33), (8200, 127, 1), (9000, 128, 97), (33000, 1, 128), (12000, 65, 160),
+    (10001, 100, 784),
+    # columns that fill less than 3/4 of the 512: 64 x 256 tiles where whole rounds of the larger ones exist
+    (27000, 129, 130), (27000, 383, 100),
     # 128 x 512 tiles (fused only): a whole round, rows and columns past the last tile
     (3300, 4100, 130), (6500, 2050, 257), (4096, 4096, 416),
 ])
