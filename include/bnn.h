@@ -93,7 +93,8 @@ int bnn_xnor_gemm(const uint32_t *A, int64_t lda, const uint32_t *B, int64_t ldb
  * 3 = K-split kernel with wavefront reduction (skinny outputs), 4 = 64x64
  * tiled XNOR-popcount kernel, 5 = bits-in / matrix-engine-inside kernel (bits
  * widened to 4-bit floats in registers, MFMA, 256x128 tiles; needs
- * K <= 2^24, else BNN_ERR_UNSUPPORTED), 6 = the same with 128x128 tiles,
+ * K <= 2^24, else BNN_ERR_UNSUPPORTED), 6 = the same with 128x128 tiles (of
+ * 64x128 on small grids; K <= 96 takes these two sizes by either id),
  * 7 = the same arithmetic organised for short K (a workgroup keeps its 128
  * columns of B in LDS and walks over several 128-row tiles of A; needs
  * 96 < K <= 1152, A and B 16-byte aligned, lda and ldb multiples of 4, else

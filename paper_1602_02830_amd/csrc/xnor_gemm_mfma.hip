@@ -313,21 +313,6 @@ static int launch_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_
     return check_launch();
 }
 
-// Entry points used by the dispatchers.  The callers have validated the arguments.
-bool mfma_path_supports(int64_t K) { return K <= kMfmaMaxAcc; }
-
-int launch_xnor_gemm_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
-                          int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
-    if (K <= 96) return launch_mfma<1, false, false, true>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
-    return launch_mfma<4, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
-}
-
-int launch_xnor_gemm_mfma_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
-                                int64_t N, int64_t K, BnSignArgs bn, void* stream) {
-    if (K <= 96) return launch_mfma<1, true, false, true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
-    return launch_mfma<4, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
-}
-
 // 128 x 128 tiles (2 x 2 blocks per wavefront, 3 workgroups per compute unit): more, smaller
 // workgroups for products whose K is short or whose 256 x 128 grid would leave units idle.  Grids
 // of fewer than 256 such tiles take 64 x 128 tiles (1 x 2 blocks per wavefront) instead: with so few
@@ -335,9 +320,35 @@ int launch_xnor_gemm_mfma_fused(const uint32_t* A, int64_t lda, const uint32_t* 
 // (256 x 1024 x 8192 fused: 17.3 -> 13.0 us, 512 x 4096 x 4096: 10.3 -> 8.2 us).
 static bool wants_half_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, 128) < 256; }
 
+// Rows of fewer than 4 words (K <= 96).  The fused form follows the rule above (1000000 x 128 x 64 42 us on 128 x 128 tiles,
+// 58 on 64 x 128; 10000 x 4096 x 64 16.6 and 21.5; 512 x 512 x 96 4.3 and 3.9); the int32 form, all stores, is faster on the
+// smaller tiles whatever the grid (10000 x 4096 x 64 26.6 and 28.8, 50176 x 64 x 32 6.3 and 6.7), while one launch holds them.
+template <bool FUSED>
+static int launch_tiny(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc, int64_t M,
+                       int64_t N, int64_t K, BnSignArgs bn, void* stream) {
+    const bool small = FUSED ? wants_half_tiles(M, N) : ceil_div(M, 64) * ceil_div(N, 128) <= max_blocks(256);
+    return small ? launch_mfma<1, FUSED, false, true>(A, lda, B, ldb, C, ldc, M, N, K, bn, ConvArgs{}, stream)
+                 : launch_mfma<2, FUSED, false, true>(A, lda, B, ldb, C, ldc, M, N, K, bn, ConvArgs{}, stream);
+}
+
+// Entry points used by the dispatchers.  The callers have validated the arguments.
+bool mfma_path_supports(int64_t K) { return K <= kMfmaMaxAcc; }
+
+int launch_xnor_gemm_mfma(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
+                          int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
+    if (K <= 96) return launch_tiny<false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, stream);
+    return launch_mfma<4, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
+}
+
+int launch_xnor_gemm_mfma_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
+                                int64_t N, int64_t K, BnSignArgs bn, void* stream) {
+    if (K <= 96) return launch_tiny<true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, stream);
+    return launch_mfma<4, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
+}
+
 int launch_xnor_gemm_mfma128(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                              int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
-    if (K <= 96) return launch_mfma<1, false, false, true>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
+    if (K <= 96) return launch_tiny<false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, stream);
     if (wants_half_tiles(M, N))
         return launch_mfma<1, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
     return launch_mfma<2, false, false>(A, lda, B, ldb, C, ldc, M, N, K, BnSignArgs{}, ConvArgs{}, stream);
@@ -345,7 +356,7 @@ int launch_xnor_gemm_mfma128(const uint32_t* A, int64_t lda, const uint32_t* B, 
 
 int launch_xnor_gemm_mfma128_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
                                    int64_t N, int64_t K, BnSignArgs bn, void* stream) {
-    if (K <= 96) return launch_mfma<1, true, false, true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
+    if (K <= 96) return launch_tiny<true>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, stream);
     if (wants_half_tiles(M, N))
         return launch_mfma<1, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);
     return launch_mfma<2, true, false>(A, lda, B, ldb, nullptr, 0, M, N, K, bn, ConvArgs{}, stream);

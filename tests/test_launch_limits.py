@@ -127,3 +127,18 @@ def test_first_layers_of_any_size_stay_below_the_work_item_limit(launches_of, M,
     assert st == 0 and log
     tile_n, tile_m = {256: (256, 64), 512: (512, 128)}[log[0][1]]
     assert covers(log, A, 8 * kw, M, -(-N // tile_n), tile_m)
+
+
+@pytest.mark.parametrize("M,N,K", [(2 ** 25, 4096, 64), (2 ** 31 - 1025, 33, 32), (2 ** 31 - 1025, 64, 96), (2 ** 20, 2 ** 17, 96)])
+def test_fused_products_of_few_words_stay_below_the_work_item_limit(launches_of, M, N, K):
+    """Fused layers with K <= 96 of up to 2^38 outputs: one launch that the runtime takes."""
+    kw = (K + 31) // 32
+    (st, log), = launches_of(("bnn_xnor_gemm_bn_sign_pack", (A, kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
+    assert st == 0 and len(log) == 1
+
+
+@pytest.mark.parametrize("M,N,K", [(2 ** 31 - 1025, 17, 32), (2 ** 31 - 1025, 33, 96)])
+def test_int32_products_of_few_words_stay_below_the_work_item_limit(launches_of, M, N, K):
+    kw = (K + 31) // 32
+    (st, log), = launches_of(("bnn_xnor_gemm", (A, kw, B, kw, C, N, M, N, K, 0)))
+    assert st == 0 and len(log) == 1
