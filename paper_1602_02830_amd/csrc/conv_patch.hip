@@ -150,15 +150,16 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
         }
     };
 
-    // The tile's first output pixel is (image b0, row y0, ...); the patch starts at the padded row its window starts at.
+    // The tile's first output pixel is (image b0, row y0, ...); the patch starts at the padded row its window starts at,
+    // row patch_row0 of image b0 (rows are counted from there: all images' together may be more than 2^31).
     // Output pixel r of the tile as a patch cell: the divisions are done once per pixel here, not once per use.
     const int row_first = pg.by_wo(row0), b0 = pg.by_ho(row_first), y0 = row_first - b0 * cv.Ho;
-    const int patch_row0 = b0 * pg.img_rows + y0 * cv.stride;
+    const int patch_row0 = y0 * cv.stride;
     if (tid < BM) {
         const int m = min(row0 + tid, M - 1);
         const int t = pg.by_wo(m), x = m - t * cv.Wo;
         const int b = pg.by_ho(t), y = t - b * cv.Ho;
-        slot_s[tid] = (b * pg.img_rows + y * cv.stride - patch_row0) * pg.pw + x * cv.stride;
+        slot_s[tid] = ((b - b0) * pg.img_rows + y * cv.stride - patch_row0) * pg.pw + x * cv.stride;
         if (POOL) pixel_s[tid] = ((b - b0) << 22) | (y << 7) | x;           // pooled rows have at most 64 pixels
     }
     // Thresholds and flip words go to registers here and to LDS after the patch loads have been issued: every
@@ -184,13 +185,15 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     }
 
     // ---- patch: every slot once ------------------------------------------------------------
-    // Slot s is column s % pw of row patch_row0 + s / pw of the padded images, which follow each other without a gap.
+    // Slot s is column s % pw of row patch_row0 + s / pw of the padded images from b0 on, which follow each other without a
+    // gap.
     if (WORDS || !FUSED) {
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
         for (int s = tid; s < pg.slots; s += T) {
             const int py = pg.by_pw(s), px = s - py * pg.pw;
-            const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+            const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
+            const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
             const bool inside = b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
             const uint32_t pix = inside ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
             const uint32_t* p = in + size_t(pix) * uint32_t(cv.Cw);
@@ -226,7 +229,8 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
                 const int s = s_base + u * T + tid;
                 live[u] = s < pg.slots;
                 const int py = pg.by_pw(s), px = s - py * pg.pw;
-                const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+                const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
+                const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
                 inside[u] = live[u] && b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
                 const uint32_t pix = inside[u] ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
                 p[u] = in + size_t(pix) * uint32_t(cv.Cw);
@@ -495,11 +499,10 @@ static int64_t patch_rows(const ConvArgs& cv, int64_t BM) {
 }
 
 // Fills the patch geometry for tiles of BM output pixels; false if the patch does not fit.
-static bool patch_geometry(const ConvArgs& cv, int64_t M, int BM, PatchGeom& pg) {
+static bool patch_geometry(const ConvArgs& cv, int BM, PatchGeom& pg) {
     const int64_t img_rows = int64_t(cv.H) + 2 * cv.pad, pw = int64_t(cv.W) + 2 * cv.pad;
     const int64_t slots = patch_rows(cv, BM) * pw;
     if (slots * (int64_t(cv.Cw) * 4 + 4) > kPatchMaxBytes) return false;
-    if (ceil_div(M, int64_t(cv.Ho) * cv.Wo) * img_rows + slots > kMaxDim) return false;      // row numbers are 32-bit
     pg.img_rows = int(img_rows);
     pg.pw = int(pw);
     pg.slots = int(slots);
@@ -576,7 +579,7 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
                                  int64_t M, int64_t N, int64_t K, BnSignArgs bn, ConvArgs cv, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    auto fits = [&](int BM) { return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, M, BM, pg); };
+    auto fits = [&](int BM) { return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg); };
     if (wants_small_tiles(M, N, K) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
     if (wants_big_tiles(M, N) && fits(256))
@@ -613,7 +616,7 @@ int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t 
                                  BnSignArgs bn, ConvArgs cv, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    auto fits = [&](int WM) { return pool_fits(cv, WM) && patch_geometry(cv, M, 64 * WM, pg); };
+    auto fits = [&](int WM) { return pool_fits(cv, WM) && patch_geometry(cv, 64 * WM, pg); };
     if (wants_small_tiles(M, N, K) && fits(2) && fits(1))
         return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
     if (wants_big_tiles(M, N) && fits(4))

@@ -63,6 +63,7 @@ print(json.dumps(out))
 """
 
 A, B, C, THR, FLIP, OUT = (i << 44 for i in range(1, 7))          # operand addresses
+WB = B
 
 
 @pytest.fixture(scope="module")
@@ -142,3 +143,14 @@ def test_int32_products_of_few_words_stay_below_the_work_item_limit(launches_of,
     kw = (K + 31) // 32
     (st, log), = launches_of(("bnn_xnor_gemm", (A, kw, B, kw, C, N, M, N, K, 0)))
     assert st == 0 and len(log) == 1
+
+
+@pytest.mark.parametrize("B,H,W,k,pad", [(2 ** 30, 1, 1, 3, 1), (2 ** 29, 2, 1, 5, 2), (2 ** 28, 2, 2, 7, 3), (2 ** 29 - 300, 1, 2, 5, 2)])
+def test_layers_of_whole_channel_words_take_any_number_of_images(launches_of, B, H, W, k, pad):
+    """Small images in batches whose padded rows are more than 2^31 together."""
+    assert B * (H + 2 * pad) >= 2 ** 31 - 2 ** 8
+    (st, log), (st_pool, log_pool) = launches_of(
+        ("bnn_conv_bn_sign_pack", (A, B, H, W, 32, WB, 256, 32, k, k, 1, pad, THR, FLIP, OUT, 1, 0)),
+        ("bnn_conv_pool_bn_sign_pack", (A, B, H, W, 32, WB, 256, 32, k, k, 1, pad, 2, THR, FLIP, OUT, 1, 0)))
+    assert st == 0 and len(log) == 1
+    assert (st_pool, len(log_pool)) == ((0, 1) if H % 2 == 0 and W % 2 == 0 else (3, 0))
