@@ -52,6 +52,7 @@ struct PatchGeom {
     int img_rows;      // H + 2*pad: rows of a padded image
     int pw;            // W + 2*pad: patch row pitch (pixels)
     int slots;         // cells of the largest patch a tile of this layer has
+    bool trim;         // most tiles need far fewer
     int cqn;           // channel quads per pixel (Cw / 4); unused when a tap is not a whole number of quads
     int kq;            // quads of K per filter row: kh * kw * cqn, or ceil(kwords / 4)
     int kwords;        // words of K per filter row: kh * kw * Cw
@@ -155,6 +156,12 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     // Output pixel r of the tile as a patch cell: the divisions are done once per pixel here, not once per use.
     const int row_first = pg.by_wo(row0), b0 = pg.by_ho(row_first), y0 = row_first - b0 * cv.Ho;
     const int patch_row0 = y0 * cv.stride;
+    // Cells to load: up to the end of the last pixel's window where that may be far fewer than the tile that needs most has.
+    int slots_here = pg.slots;
+    if (pg.trim) {
+        const int row_last = pg.by_wo(min(row0 + BM, M) - 1), b_last = pg.by_ho(row_last), y_last = row_last - b_last * cv.Ho;
+        slots_here = ((b_last - b0) * pg.img_rows + (y_last - y0) * cv.stride + cv.kh) * pg.pw;
+    }
     if (tid < BM) {
         const int m = min(row0 + tid, M - 1);
         const int t = pg.by_wo(m), x = m - t * cv.Wo;
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     if (WORDS || !FUSED) {
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
-        for (int s = tid; s < pg.slots; s += T) {
+        for (int s = tid; s < slots_here; s += T) {
             const int py = pg.by_pw(s), px = s - py * pg.pw;
             const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
             const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
@@ -220,14 +227,14 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
         // of a pass are issued before the first LDS write waits for one.  Slots that do not exist and cells
         // outside the image load input pixel 0 (a valid address) and are not written / written as all ones.
         constexpr int kSlotsPerPass = 2, kQuadsPerPass = 4;
-        for (int s_base = 0; s_base < pg.slots; s_base += kSlotsPerPass * T) {
+        for (int s_base = 0; s_base < slots_here; s_base += kSlotsPerPass * T) {
             const uint32_t* p[kSlotsPerPass];
             bool live[kSlotsPerPass], inside[kSlotsPerPass];
             int pop[kSlotsPerPass];
 #pragma unroll
             for (int u = 0; u < kSlotsPerPass; ++u) {
                 const int s = s_base + u * T + tid;
-                live[u] = s < pg.slots;
+                live[u] = s < slots_here;
                 const int py = pg.by_pw(s), px = s - py * pg.pw;
                 const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
                 const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
@@ -506,6 +513,10 @@ static bool patch_geometry(const ConvArgs& cv, int BM, PatchGeom& pg) {
     pg.img_rows = int(img_rows);
     pg.pw = int(pw);
     pg.slots = int(slots);
+    // The largest patch crosses from image to image and starts in the middle of a row.  Counting a tile's own cells costs
+    // 0.1 - 0.2 us and pays from about 1.4 times (8 images of 112 x 112, 128 -> 128 channels 15.1 -> 13.7 us, 64 of 56 x 56
+    // 19.6 -> 18.7; 100 of 16 x 16, whose patches are all alike, 6.8 -> 6.9).
+    pg.trim = 5 * slots >= 7 * ((ceil_div(BM, cv.Wo) - 1) * cv.stride + cv.kh) * pw;
     pg.cqn = cv.Cw / 4;
     pg.kwords = cv.kh * cv.kw * cv.Cw;
     pg.kq = (pg.kwords + 3) / 4;
@@ -573,13 +584,24 @@ static bool wants_small_tiles(int64_t M, int64_t N, int64_t K) {
            (K <= kResidentKTiles * 512 || (K <= kResidentKTilesAlone * 512 && ceil_div(M, 64) * ceil_div(N, 128) <= kLoneGrid));
 }
 
+// Patches of a few, wide rows hold many cells that no window of the tile reads: stride 1 and a receptive field that the
+// short-K kernel gathers, fused, 300 x 300 x 128 -> 128 14.8 us and 12.4 gathered (1812 cells), 2 images of 200 x 250 15.5 and
+// 14.1 (1512); but 2 of 300 x 160 10.1 and 12.3 (972).  At stride 2 patches of 2034 cells still gain (4 of 224 x 224 9.4 and
+// 10.3), and 256-pixel tiles read more of theirs (4 of 224 x 224 20.9 and 22.2).
+constexpr int64_t kShortField = 1152;     // the longest receptive field of the short-K kernel
+static bool better_gathered(const ConvArgs& cv, int BM, int64_t K, const PatchGeom& pg) {
+    return BM <= 128 && cv.stride == 1 && K <= kShortField && pg.slots > 1280 && !whole_row_tiles(cv, BM);
+}
+
 // BNN_ERR_UNSUPPORTED if the layer is not one this kernel takes (the caller then uses the gathering kernels).
 template <bool FUSED>
 static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                                  int64_t M, int64_t N, int64_t K, BnSignArgs bn, ConvArgs cv, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    auto fits = [&](int BM) { return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg); };
+    auto fits = [&](int BM) {
+        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, K, pg);
+    };
     if (wants_small_tiles(M, N, K) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
     if (wants_big_tiles(M, N) && fits(256))

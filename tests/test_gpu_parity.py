@@ -1167,9 +1167,15 @@ def test_implicit_conv_matches_direct_convolution(shape):
     (20, 16, 16, 256, 256, 3, 3, 1, 1),     # 18 quads, 4 + 5 K-tiles wide halves of 2 and 3
     (3, 20, 20, 640, 64, 2, 2, 1, 1),       # 20 quads, taps that start inside a K-tile
     (2, 40, 400, 128, 20, 3, 3, 1, 1),      # patch too large at 128 pixels and more: the gathering kernels
+    (2, 9, 300, 128, 40, 3, 3, 1, 1),       # wide rows at stride 1: gathered as well
+    (8, 50, 112, 128, 40, 3, 3, 1, 1),      # patches of a few rows, of which a tile loads its own alone; 128 pixels
+    (3, 30, 112, 128, 40, 3, 3, 1, 1),      # the same, 64 pixels
+    (10, 120, 121, 128, 30, 3, 3, 1, 1),    # the same, 256 pixels
+    (5, 23, 200, 128, 20, 3, 3, 2, 1),      # the same at stride 2
+    (70, 3, 64, 128, 20, 2, 5, 1, 2),       # the same, most tiles crossing an image boundary
 ])
 def test_conv_without_im2col_on_any_geometry(shape):
-    """int32 and fused against lowering through the im2col matrix (kernels of their own, held to the oracle elsewhere)."""
+    """int32 and fused against the oracle's direct convolution, and against lowering through the im2col matrix."""
     B, H, W, Cin, Cout, kh, kw, stride, pad = shape
     g = torch.Generator().manual_seed(sum(shape))
     xb = torch.randint(-2 ** 31, 2 ** 31, (B, H, W, Cin // 32), generator=g, dtype=torch.int64).to(torch.int32).to(DEV)
@@ -1178,6 +1184,9 @@ def test_conv_without_im2col_on_any_geometry(shape):
     K = kh * kw * Cin
     cols = bnn.conv_im2col_pack(xb, Cin, kh, kw, stride, pad)
     want = bnn.xnor_gemm(cols, wb, K, kernel=bnn.KERNEL_TILED64)
+    x = oracle.unpack_bits(words_to_host(xb).reshape(-1, Cin // 32), Cin).reshape(B, H, W, Cin)
+    filters = oracle.unpack_bits(words_to_host(wb), K).reshape(Cout, kh, kw, Cin)
+    assert (want.cpu().numpy() == oracle.conv_direct(x, filters, stride=stride, pad=pad).reshape(-1, Cout)).all()
     assert torch.equal(bnn.conv_xnor(xb, Cin, wb, kh, kw, stride, pad), want)
     thr = torch.randint(-40, 40, (Cout,), generator=g, dtype=torch.int32).to(DEV)
     flip = torch.randint(-2 ** 31, 2 ** 31, ((Cout + 31) // 32,), generator=g, dtype=torch.int64).to(torch.int32).to(DEV)
