@@ -578,9 +578,16 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
 // of 8 x 8, 256 -> 128 channels (26 tiles of 128) 8.8 -> 8.0 us, 20 of 16 x 16, 256 -> 256 (80) 9.0 -> 8.4, 128 -> 256 of
 // 16 x 16 at stride 2 (128) 7.8 -> 6.6; but 52 of 16 x 16, 256 -> 256 pooled (208) 9.6 -> 9.9, and filters that stream
 // through LDS (512 channels, 188 tiles) 17.0 -> 20.6: a K-tile of 64 pixels is over before the next one's loads are back.
+//
+// The shortest fields keep to 64 pixels up to 320 tiles of 128 (256 images of 14 x 14, 256 -> 256, 2 x 2 at stride 2, 196
+// tiles, 7.2 -> 6.7 us, gathered 6.8; 128 of 28 x 28, 128 -> 256, 2 x 2 at stride 3, 162 tiles, 6.6 -> 6.0, gathered 6.3; 3 x 3
+// over 128 channels in the int32 form 8.8 -> 7.7, but fused 6.6 -> 6.8).  The int32 form, whose stores take most of its time,
+// gathers faster than 256-pixel tiles and slower than 128-pixel ones where the field is short (128 of 28 x 28, 128 -> 256: 1 x 1
+// 21.4 gathered, 23.3, 18.2; 2 x 2 22.0, 24.2, 19.1; 3 x 3 30.1, 32.9, 25.6); whole-row layers keep the larger tiles.
+constexpr int64_t kShortField = 1152;     // the longest receptive field of the short-K kernel
 static bool wants_big_tiles(int64_t M, int64_t N) { return ceil_div(M, 256) * ceil_div(N, 128) >= 512; }
-static bool wants_small_tiles(int64_t M, int64_t N, int64_t K) {
-    return ceil_div(M, 128) * ceil_div(N, 128) <= 160 &&
+static bool wants_small_tiles(int64_t M, int64_t N, int64_t K, bool fused) {
+    return ceil_div(M, 128) * ceil_div(N, 128) <= (K <= (fused ? 1024 : kShortField) ? 320 : 160) &&
            (K <= kResidentKTiles * 512 || (K <= kResidentKTilesAlone * 512 && ceil_div(M, 64) * ceil_div(N, 128) <= kLoneGrid));
 }
 
@@ -588,7 +595,6 @@ static bool wants_small_tiles(int64_t M, int64_t N, int64_t K) {
 // short-K kernel gathers, fused, 300 x 300 x 128 -> 128 14.8 us and 12.4 gathered (1812 cells), 2 images of 200 x 250 15.5 and
 // 14.1 (1512); but 2 of 300 x 160 10.1 and 12.3 (972).  At stride 2 patches of 2034 cells still gain (4 of 224 x 224 9.4 and
 // 10.3), and 256-pixel tiles read more of theirs (4 of 224 x 224 20.9 and 22.2).
-constexpr int64_t kShortField = 1152;     // the longest receptive field of the short-K kernel
 static bool better_gathered(const ConvArgs& cv, int BM, int64_t K, const PatchGeom& pg) {
     return BM <= 128 && cv.stride == 1 && K <= kShortField && pg.slots > 1280 && !whole_row_tiles(cv, BM);
 }
@@ -602,9 +608,9 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
     auto fits = [&](int BM) {
         return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, K, pg);
     };
-    if (wants_small_tiles(M, N, K) && fits(128) && fits(64))
+    if (wants_small_tiles(M, N, K, FUSED) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
-    if (wants_big_tiles(M, N) && fits(256))
+    if (wants_big_tiles(M, N) && (FUSED || K > kShortField || whole_row_tiles(cv, 256)) && fits(256))
         return launch_patch<4, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
     if (fits(128)) return launch_patch<2, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
     return BNN_ERR_UNSUPPORTED;
@@ -639,7 +645,7 @@ int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t 
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
     auto fits = [&](int WM) { return pool_fits(cv, WM) && patch_geometry(cv, 64 * WM, pg); };
-    if (wants_small_tiles(M, N, K) && fits(2) && fits(1))
+    if (wants_small_tiles(M, N, K, true) && fits(2) && fits(1))
         return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
     if (wants_big_tiles(M, N) && fits(4))
         return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);

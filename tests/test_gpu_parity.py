@@ -1150,7 +1150,11 @@ def test_implicit_conv_matches_direct_convolution(shape):
 @pytest.mark.parametrize("shape", [
     # B, H, W, Cin, Cout, kh, kw, stride, pad: tiles that start and end inside image rows and span images
     (64, 28, 28, 128, 130, 3, 3, 1, 1),     # 256-pixel tiles would leave units idle: 128
-    (176, 28, 28, 128, 128, 3, 3, 1, 1),    # 539 tiles of 256 pixels
+    (176, 28, 28, 128, 128, 3, 3, 1, 1),    # 539 tiles of 256 pixels, int32 on 128
+    (176, 28, 28, 256, 20, 2, 3, 1, 1),     # a longer field: 256 pixels in both forms
+    (80, 14, 14, 256, 200, 2, 2, 2, 0),     # short fields on 64-pixel tiles
+    (60, 28, 28, 128, 33, 3, 3, 1, 1),      # 368 tiles: 128 pixels
+    (52, 28, 28, 128, 33, 3, 3, 1, 1),      # 319 tiles: 64 pixels in the int32 form
     (30, 7, 7, 512, 96, 3, 3, 1, 1),        # several images per tile, filters streamed
     (9, 13, 11, 256, 40, 3, 3, 1, 1),       # 64-pixel tiles, resident filters
     (33, 3, 3, 128, 33, 3, 3, 1, 1),        # 28 image boundaries in a 256-pixel run
