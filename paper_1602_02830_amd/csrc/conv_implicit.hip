@@ -192,14 +192,17 @@ extern "C" int bnn_maxpool_bits(const uint32_t* in, int64_t B, int64_t H, int64_
     const int64_t n_words = B * Hp * Wp * Cw;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (n_words <= kMaxDim) {
-        const int vw = Cw % 4 == 0 ? 4 : 1;
+        // Four words a thread for 2 x 2 windows, and for others where the loads and not the wait for them count: the windows are
+        // walked load by load, longer the wider the loads (64 of 14 x 14 x 512, 7 x 7 6.7 us a word at a time, 7.8 four; 2000 of
+        // 6 x 6 x 128, 6 x 6 4.7 and 6.8; 256 of 28 x 28 x 256, 3 x 3 at stride 2 3.6 and 3.5, at stride 1 4.9 and 3.9).
+        const bool two = ph == 2 && pw == 2;
+        const int vw = Cw % 4 == 0 && (two || n_words >= 1 << 18) ? 4 : 1;
         const int64_t n_units = n_words / vw;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(unsigned(ceil_div(n_units, 256))), dim3(256), 0, s, in, int(H), int(W), int(Cw), ph,
                                pw, stride, int(Hp), int(Wp), fast_div(Cw / vw), fast_div(Wp), fast_div(Hp), flip_bits, out,
                                int(n_units));
         };
-        const bool two = ph == 2 && pw == 2;
         if (vw == 4 && two) launch(maxpool_units_kernel<4, true>);
         else if (vw == 4) launch(maxpool_units_kernel<4, false>);
         else if (two) launch(maxpool_units_kernel<1, true>);

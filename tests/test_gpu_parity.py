@@ -1344,6 +1344,7 @@ def test_maxpool_bits_matches_pooling_of_preactivations(shape):
     (5, 7, 5, 256, 2, 2, 1),        # overlapping windows
     (2, 9, 7, 96, 2, 2, 2),         # three words: units of one
     (2, 9, 8, 384, 3, 2, 3),        # windows of other sizes
+    (2100, 7, 9, 256, 3, 2, 1),     # the same, units of four words
     (1, 2, 2, 32, 2, 2, 2),         # one word
     (300, 3, 3, 40, 3, 1, 1),
 ])
