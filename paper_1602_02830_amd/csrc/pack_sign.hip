@@ -11,6 +11,7 @@
 // take pack_sign_units_kernel (4 words per group, one 16-byte store).
 #include "bit_transpose.h"
 #include "bnn_internal.h"
+#include "gemm_staging.h"
 
 namespace bnn {
 
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_sign_units_kernel(
 //
 // One thread per 32 elements: two 16-byte loads, a 4 x 4 byte transposition (16 v_perm) and an 8 x 8 bit
 // transposition (48 operations) turn 32 bytes into 8 plane words, which leave as two 16-byte stores.  The kernel
-// streams 1 B in and 1 B out per element and is bound by memory: 10000 x 784 4.6 us per launch against 15 when 8 lanes
+// streams 1 B in and 1 B out per element and is bound by memory: 10000 x 784 4.5 us per launch against 10 when 8 lanes
 // shared a word and gathered every plane with a multiply and three lane permutes.
 // A row's last, partial word reads the row's last 32 elements instead and shifts the planes down.
 // ----------------------------------------------------------------------------
@@ -152,6 +153,37 @@ __device__ inline uint4 load_bytes16(const uint8_t* p) {
     typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(1)));
     const quad_t v = *reinterpret_cast<const quad_t*>(p);
     return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// The bytes of a row of 1 .. 31 as eight words, zero past its end: two loads that overlap in its middle, the second one
+// shifted to where its bytes belong.  All conditions are the same for every thread.  (Byte by byte, each load waited for:
+// 4400 rows of 20 3.6 us, 2.5 this way; 1000000 of 27 25.6 and 11.4.)
+__device__ inline void load_short_row(const uint8_t* p, int cols, uint32_t (&w)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = 0u;
+    if (cols >= 16) {
+        const uint4 lo = load_bytes16(p), hi = load_bytes16(p + cols - 16);
+        const int past = 32 - cols;                       // bytes of hi that lo has, 1 .. 16
+        const uint64_t h0 = uint64_t(hi.y) << 32 | hi.x, h1 = uint64_t(hi.w) << 32 | hi.z;
+        const int bits = 8 * (past & 7);
+        const uint64_t low = bits == 0 ? h0 : h0 >> bits | h1 << (64 - bits), high = h1 >> bits;      // past bytes within 8
+        const uint64_t v0 = past < 8 ? low : past < 16 ? high : 0u, v1 = past < 8 ? high : 0u;
+        w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
+        w[4] = uint32_t(v0); w[5] = uint32_t(v0 >> 32); w[6] = uint32_t(v1); w[7] = uint32_t(v1 >> 32);
+    } else if (cols >= 8) {
+        typedef uint32_t pair_t __attribute__((ext_vector_type(2), aligned(1)));
+        const pair_t lo = *reinterpret_cast<const pair_t*>(p), hi = *reinterpret_cast<const pair_t*>(p + cols - 8);
+        const uint64_t v = cols == 8 ? 0u : (uint64_t(hi[1]) << 32 | hi[0]) >> (8 * (16 - cols));
+        w[0] = lo[0]; w[1] = lo[1]; w[2] = uint32_t(v); w[3] = uint32_t(v >> 32);
+    } else if (cols >= 4) {
+        typedef uint32_t word_t __attribute__((aligned(1)));
+        const uint32_t lo = *reinterpret_cast<const word_t*>(p), hi = *reinterpret_cast<const word_t*>(p + cols - 4);
+        w[0] = lo;
+        w[1] = cols == 4 ? 0u : hi >> (8 * (8 - cols));
+    } else {
+        const uint32_t a = p[0], b = p[cols > 1 ? 1 : 0], c = p[cols - 1];
+        w[0] = a | (cols > 1 ? b << 8 : 0u) | (cols > 2 ? c << 16 : 0u);
+    }
 }
 
 __device__ inline void store_words4(uint32_t* p, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
@@ -171,15 +203,15 @@ __device__ inline void transpose_bytes_4x4(uint32_t (&w)[4]) {
 
 __global__ __launch_bounds__(kPackThreads) void pack_bitplanes_kernel(
     const uint8_t* __restrict__ x, int64_t cols, int64_t ld_x, uint32_t* __restrict__ out, int64_t ld_out, int64_t kw,
-    int64_t n_groups) {
+    FastDiv by_kw, int64_t n_groups) {
     for (int64_t base = int64_t(blockIdx.x) * kPackThreads; base < n_groups; base += int64_t(gridDim.x) * kPackThreads) {
         if (base + threadIdx.x >= n_groups) break;
-        // The 64-bit division is the workgroup's, the thread's own is a 32-bit one (kw < 2^26).
-        const int64_t row_base = base / kw;
-        const uint32_t t = uint32_t(base - row_base * kw) + threadIdx.x;
-        const uint32_t d_row = t / uint32_t(kw);
+        // Up to 2^31 groups: a group's row by a multiplication.  More: a 64-bit division for the workgroup, and the thread's
+        // own is within 32 bits (kw < 2^26).
+        const int64_t row_base = n_groups <= kMaxDim ? 0 : base / kw;
+        const int t = int(base - row_base * kw) + int(threadIdx.x), d_row = by_kw(t);
         const int64_t row = row_base + d_row;
-        const int64_t w = t - d_row * uint32_t(kw);
+        const int64_t w = t - d_row * int(kw);
         const int64_t c0 = w * 32;
         const uint8_t* p = x + row * ld_x;
         uint32_t even[4], odd[4];                         // 4-byte groups 0, 2, 4, 6 and 1, 3, 5, 7 of the 32
@@ -190,14 +222,12 @@ __global__ __launch_bounds__(kPackThreads) void pack_bitplanes_kernel(
             even[0] = lo.x; odd[0] = lo.y; even[1] = lo.z; odd[1] = lo.w;
             even[2] = hi.x; odd[2] = hi.y; even[3] = hi.z; odd[3] = hi.w;
         } else {
+            uint32_t v[8];
+            load_short_row(p, int(cols), v);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                even[i] = odd[i] = 0u;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (8 * i + e < cols) even[i] |= uint32_t(p[8 * i + e]) << (8 * e);
-                    if (8 * i + 4 + e < cols) odd[i] |= uint32_t(p[8 * i + 4 + e]) << (8 * e);
-                }
+                even[i] = v[2 * i];
+                odd[i] = v[2 * i + 1];
             }
         }
         transpose_bytes_4x4(even);
@@ -225,7 +255,7 @@ extern "C" int bnn_pack_bitplanes(const uint8_t* x, int64_t rows, int64_t cols, 
     int64_t blocks = ceil_div(n_groups, kPackThreads);
     if (blocks > max_blocks(kPackThreads)) blocks = max_blocks(kPackThreads);      // the kernel loops over the rest
     hipLaunchKernelGGL(pack_bitplanes_kernel, dim3(unsigned(blocks)), dim3(kPackThreads), 0, static_cast<hipStream_t>(stream),
-                       x, cols, ld_x, out, ld_out, kw, n_groups);
+                       x, cols, ld_x, out, ld_out, kw, fast_div(kw), n_groups);
     return check_launch();
 }
 

@@ -1702,7 +1702,8 @@ def test_bitplane_gemm_of_no_inputs(M, N):
     assert (words_to_host(bnn.bitplane_gemm_bn_sign_pack(planes, wb, 0, thr, flip)) == want).all()
 
 
-@pytest.mark.parametrize("rows,cols", [(3, 1), (5, 17), (4, 31), (300, 32), (257, 33), (9, 63), (7, 65), (2, 4097), (70, 1000)])
+@pytest.mark.parametrize("rows,cols", [(3, 1), (5, 17), (4, 31), (300, 32), (257, 33), (9, 63), (7, 65), (2, 4097), (70, 1000)] +
+                         [(37, c) for c in range(2, 31) if c != 17])
 @pytest.mark.parametrize("shift", [0, 1, 3])
 def test_pack_bitplanes_any_byte_alignment(rows, cols, shift):
     """Rows at every byte alignment, last words that are read back from the row's end, canaries behind every row."""
