@@ -591,12 +591,19 @@ static bool wants_small_tiles(int64_t M, int64_t N, int64_t K, bool fused) {
            (K <= kResidentKTiles * 512 || (K <= kResidentKTilesAlone * 512 && ceil_div(M, 64) * ceil_div(N, 128) <= kLoneGrid));
 }
 
-// Patches of a few, wide rows hold many cells that no window of the tile reads: stride 1 and a receptive field that the
-// short-K kernel gathers, fused, 300 x 300 x 128 -> 128 14.8 us and 12.4 gathered (1812 cells), 2 images of 200 x 250 15.5 and
-// 14.1 (1512); but 2 of 300 x 160 10.1 and 12.3 (972).  At stride 2 patches of 2034 cells still gain (4 of 224 x 224 9.4 and
-// 10.3), and 256-pixel tiles read more of theirs (4 of 224 x 224 20.9 and 22.2).
-static bool better_gathered(const ConvArgs& cv, int BM, int64_t K, const PatchGeom& pg) {
-    return BM <= 128 && cv.stride == 1 && K <= kShortField && pg.slots > 1280 && !whole_row_tiles(cv, BM);
+// Layers of other than whole-row tiles that are faster gathered:
+//  - patches of a few, wide rows hold many cells that no window of the tile reads: stride 1 and a receptive field that the
+//    short-K kernel gathers, fused, 300 x 300 x 128 -> 128 14.8 us and 12.4 gathered (1812 cells), 2 images of 200 x 250 15.5 and
+//    14.1 (1512); but 2 of 300 x 160 10.1 and 12.3 (972).  At stride 2 patches of 2034 cells still gain (4 of 224 x 224 9.4 and
+//    10.3), and 256-pixel tiles read more of theirs (4 of 224 x 224 20.9 and 22.2).
+//  - a patch that leaves a compute unit with two workgroups, streamed filters beside it, where three would take all tiles in one
+//    round: 31 images of 28 x 28, 1024 -> 512 (760 tiles) 53.0 and 49.9, int32 57.2 and 50.2, 24 of them (588) 50.2 and 46.1; but
+//    40 (980) 61.9 and 62.8.
+static bool better_gathered(const ConvArgs& cv, int BM, int64_t M, int64_t N, int64_t K, const PatchGeom& pg) {
+    if (BM > 128 || whole_row_tiles(cv, BM)) return false;
+    if (cv.stride == 1 && K <= kShortField && pg.slots > 1280) return true;
+    const int64_t tiles = ceil_div(M, BM) * ceil_div(N, 128);
+    return K > kResidentKTiles * 512 && tiles > 512 && tiles <= 768 && int64_t(pg.slots) * (cv.Cw * 4 + 4) > 32 * 1024;
 }
 
 // BNN_ERR_UNSUPPORTED if the layer is not one this kernel takes (the caller then uses the gathering kernels).
@@ -606,7 +613,7 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
     auto fits = [&](int BM) {
-        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, K, pg);
+        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, M, N, K, pg);
     };
     if (wants_small_tiles(M, N, K, FUSED) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);

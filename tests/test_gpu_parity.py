@@ -1172,6 +1172,7 @@ def test_implicit_conv_matches_direct_convolution(shape):
     (3, 20, 20, 640, 64, 2, 2, 1, 1),       # 20 quads, taps that start inside a K-tile
     (2, 40, 400, 128, 20, 3, 3, 1, 1),      # patch too large at 128 pixels and more: the gathering kernels
     (2, 9, 300, 128, 40, 3, 3, 1, 1),       # wide rows at stride 1: gathered as well
+    (24, 28, 28, 1024, 400, 2, 2, 1, 1),    # 632 tiles with two patches to a compute unit: gathered
     (8, 50, 112, 128, 40, 3, 3, 1, 1),      # patches of a few rows, of which a tile loads its own alone; 128 pixels
     (3, 30, 112, 128, 40, 3, 3, 1, 1),      # the same, 64 pixels
     (10, 120, 121, 128, 30, 3, 3, 1, 1),    # the same, 256 pixels
