@@ -11,7 +11,6 @@
 // take pack_sign_units_kernel (4 words per group, one 16-byte store).
 #include "bit_transpose.h"
 #include "bnn_internal.h"
-#include "gemm_staging.h"
 
 namespace bnn {
 
@@ -201,22 +200,24 @@ __device__ inline void transpose_bytes_4x4(uint32_t (&w)[4]) {
     w[3] = __builtin_amdgcn_perm(d, b, 0x07060302u);
 }
 
+// SHORT: rows of fewer than 32 elements, one group each.
+template <bool SHORT>
 __global__ __launch_bounds__(kPackThreads) void pack_bitplanes_kernel(
     const uint8_t* __restrict__ x, int64_t cols, int64_t ld_x, uint32_t* __restrict__ out, int64_t ld_out, int64_t kw,
-    FastDiv by_kw, int64_t n_groups) {
+    int64_t n_groups) {
     for (int64_t base = int64_t(blockIdx.x) * kPackThreads; base < n_groups; base += int64_t(gridDim.x) * kPackThreads) {
         if (base + threadIdx.x >= n_groups) break;
-        // Up to 2^31 groups: a group's row by a multiplication.  More: a 64-bit division for the workgroup, and the thread's
-        // own is within 32 bits (kw < 2^26).
-        const int64_t row_base = n_groups <= kMaxDim ? 0 : base / kw;
-        const int t = int(base - row_base * kw) + int(threadIdx.x), d_row = by_kw(t);
+        // The 64-bit division is the workgroup's, the thread's own is a 32-bit one (kw < 2^26).
+        const int64_t row_base = SHORT ? base : base / kw;
+        const uint32_t t = uint32_t(base - row_base * kw) + threadIdx.x;
+        const uint32_t d_row = SHORT ? threadIdx.x : t / uint32_t(kw);
         const int64_t row = row_base + d_row;
-        const int64_t w = t - d_row * int(kw);
+        const int64_t w = SHORT ? 0 : t - d_row * uint32_t(kw);
         const int64_t c0 = w * 32;
         const uint8_t* p = x + row * ld_x;
         uint32_t even[4], odd[4];                         // 4-byte groups 0, 2, 4, 6 and 1, 3, 5, 7 of the 32
         int past = 0;                                     // elements of the word that do not exist
-        if (cols >= 32) {
+        if (!SHORT) {
             past = c0 + 32 <= cols ? 0 : int(c0 + 32 - cols);
             const uint4 lo = load_bytes16(p + c0 - past), hi = load_bytes16(p + c0 - past + 16);
             even[0] = lo.x; odd[0] = lo.y; even[1] = lo.z; odd[1] = lo.w;
@@ -254,8 +255,12 @@ extern "C" int bnn_pack_bitplanes(const uint8_t* x, int64_t rows, int64_t cols, 
     const int64_t n_groups = rows * kw;
     int64_t blocks = ceil_div(n_groups, kPackThreads);
     if (blocks > max_blocks(kPackThreads)) blocks = max_blocks(kPackThreads);      // the kernel loops over the rest
-    hipLaunchKernelGGL(pack_bitplanes_kernel, dim3(unsigned(blocks)), dim3(kPackThreads), 0, static_cast<hipStream_t>(stream),
-                       x, cols, ld_x, out, ld_out, kw, fast_div(kw), n_groups);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(kPackThreads), 0, static_cast<hipStream_t>(stream), x, cols, ld_x,
+                           out, ld_out, kw, n_groups);
+    };
+    if (cols < 32) launch(pack_bitplanes_kernel<true>);
+    else launch(pack_bitplanes_kernel<false>);
     return check_launch();
 }
 
