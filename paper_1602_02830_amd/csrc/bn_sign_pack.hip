@@ -94,10 +94,11 @@ __global__ __launch_bounds__(kBnThreads) void bn_sign_pack_kernel(
                 const bool live = g0 + u * kSlice < n_words;
                 row_of[u] = live ? row : ~0u;
                 word_of[u] = w;
+                // unconditional as well; the mask below drops what does not exist
+                const int32_t* p = C + int64_t(live ? row : 0u) * ldc;
                 nib[u] = 0u;
 #pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (live && q == 0 && e < N) nib[u] |= uint32_t(C[int64_t(row) * ldc + e] >= thr[e]) << e;
+                for (int e = 0; e < 3; ++e) nib[u] |= uint32_t(p[min(e, N - 1)] >= thr[min(e, N - 1)]) << e;
                 row += slice_row;
                 w += slice_word;
                 if (w >= nw) {

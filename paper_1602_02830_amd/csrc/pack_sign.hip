@@ -97,10 +97,11 @@ __global__ __launch_bounds__(kPackThreads) void pack_sign_kernel(
                 const bool live = g0 + u * kSlice < n_words;
                 row_of[u] = live ? row : ~0u;
                 word_of[u] = w;
+                const float* p = x + int64_t(live ? row : 0u) * ld_x;          // unconditional loads here too
                 nib[u] = 0u;
 #pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (live && q == 0 && e < cols) nib[u] |= ge_zero(x[int64_t(row) * ld_x + e]) << e;
+                for (int e = 0; e < 3; ++e) nib[u] |= ge_zero(p[min(e, cols - 1)]) << e;
+                nib[u] = q == 0 ? nib[u] & ((1u << cols) - 1u) : 0u;
                 advance(row, w, slice, kw);
             }
         }
