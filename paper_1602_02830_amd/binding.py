@@ -7,12 +7,13 @@ Python, and nothing falls back to the CPU.
 
 Calls that bring their output take a native path first (``_calls``, csrc/python_calls.cpp), which reads the tensors
 and launches without ctypes; whatever it does not take comes back as -1 and goes through the wrapper below it, whose
-checks then say what is wrong.
+checks then say what is wrong.  Where it does not load, a warning says so and all calls go through the wrappers.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -87,10 +88,11 @@ def load_library():
         if _raw_stream is not None:
             try:
                 from . import _calls as calls
-            except ImportError as e:
-                raise ImportError("the native call path is not built; run `python -m paper_1602_02830_amd.build`") from e
-            calls.bind({name: ctypes.cast(getattr(lib, name), _ptr).value for name in _SIGNATURES}, _raw_stream)
-            _calls = calls
+                calls.bind({name: ctypes.cast(getattr(lib, name), _ptr).value for name in _SIGNATURES}, _raw_stream)
+                _calls = calls
+            except ImportError as e:           # absent, or built against another torch: the wrappers below are complete
+                warnings.warn(f"calls go through ctypes, the native call path does not load ({e}); "
+                              "`python -m paper_1602_02830_amd.build` builds it", RuntimeWarning, stacklevel=2)
         _lib = lib
     return _lib
 

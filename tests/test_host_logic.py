@@ -5,6 +5,8 @@ on every admissible pre-activation."""
 import ctypes
 import os
 import re
+import sys
+import warnings
 
 import numpy as np
 import pytest
@@ -212,6 +214,23 @@ def test_fold_rejects_bad_parameters():
         bnn.bn_fold(one, one, one, -one, 1e-4, 16)          # var + eps <= 0
     with pytest.raises(bnn.BnnError):
         bnn.bn_fold(one, one, one, one, 1e-4, 2 ** 31 - 1)  # K too large
+
+
+def test_native_call_path_is_built_and_its_absence_leaves_the_wrappers(monkeypatch):
+    """_calls.so is an optimisation: where it does not load, the package does, with one warning that says why."""
+    bnn.load_library()
+    assert binding._raw_stream is None or binding._calls is not None
+    monkeypatch.setattr(binding, "_raw_stream", lambda index: 0)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setitem(sys.modules, "paper_1602_02830_amd._calls", None)           # the import raises ImportError
+    monkeypatch.delattr(bnn, "_calls", raising=False)
+    with pytest.warns(RuntimeWarning, match="_calls"):
+        lib = binding.load_library()
+    assert binding._calls is None and lib.bnn_version() == 100
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        assert binding.load_library() is lib
 
 
 def test_missing_library_fails_loudly(monkeypatch):
