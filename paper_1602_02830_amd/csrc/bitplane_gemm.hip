@@ -12,7 +12,8 @@
 //   sum_k x (2b - 1) = S + 256 * popcount(B_n) - sum_k x[m][k],      S = sum_k (x - 128) * 2b   (int32 accumulation)
 //
 // The row sums come from the staged bytes (v_dot4), the popcounts from B's words.  Everything is 32-bit integer
-// arithmetic, exact modulo 2^32 and therefore exact for every K with 255*K < 2^31.
+// arithmetic, exact modulo 2^32 and therefore exact for every K with 255*K < 2^31: single terms pass 2^31 from K = 2^23 on, so
+// sums of them are formed in unsigned integers.
 //
 // Two organisations:
 //   tiles   32*WI*WR x 64*WC outputs per workgroup, WI x 2 blocks of 32 x 32 per wavefront: 128 x 512 with 8 wavefronts
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
     }
     const bool sign = FUSED && K <= kSignMaxK;
     if (st_b) {
-        colterm_s[tid] = 256 * cnt_b - (sign ? thr : 0);
+        colterm_s[tid] = int(256u * uint32_t(cnt_b) - uint32_t(sign ? thr : 0));
         if (FUSED) thr_s[tid] = thr;
     }
     __syncthreads();
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int ml = (wr * WI + i) * 32 + 8 * (v / 4) + 4 * fh + (v % 4), m = row0 + ml;
-                    if (m < M && n < N) store_result(&C[int64_t(m) * ldc + n], acc[i][j][v] + ct - rowsum_s[ml]);
+                    if (m < M && n < N) store_result(&C[int64_t(m) * ldc + n], int(uint32_t(acc[i][j][v]) + uint32_t(ct) - uint32_t(rowsum_s[ml])));
                 }
         }
     } else {
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
 #pragma unroll
                         for (int e = 3; e >= 0; --e) {
                             const int c = e == 0 ? ct[g].x : e == 1 ? ct[g].y : e == 2 ? ct[g].z : ct[g].w;
-                            int d = acc[i][j][4 * g + e] + c - r;
+                            int d = int(uint32_t(acc[i][j][4 * g + e]) + uint32_t(c) - uint32_t(r));
                             if (!SIGN) {
                                 const int t = e == 0 ? th[g].x : e == 1 ? th[g].y : e == 2 ? th[g].z : th[g].w;
                                 d = d >= t ? 0 : -1;
@@ -373,8 +374,8 @@ template <bool FUSED>
 __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
-    __shared__ int4 part[kSplitWaves][4][kWave];           // [wavefront][accumulator registers 4g .. 4g + 3][lane]
-    __shared__ __attribute__((aligned(16))) int sum_part[kSplitWaves][kWave];   // [0, 32) row sums of A, [32, 64) 256 * popcounts of B
+    __shared__ uint4 part[kSplitWaves][4][kWave];          // [wavefront][accumulator registers 4g .. 4g + 3][lane]
+    __shared__ __attribute__((aligned(16))) uint32_t sum_part[kSplitWaves][kWave];   // [0, 32) row sums of A, [32, 64) 256 * popcounts of B
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 31, fh = lane >> 5;
     int tm, tn;
@@ -396,7 +397,8 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
     v16i acc[2];
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0;
-    int ca = 0, cb = 0;
+    int ca = 0;
+    uint32_t cb = 0u;
 
     // Of a group of 8 pairs wavefront w takes pairs w and w + 4, lane half fh word fh of each.  Word indices are clamped
     // into the row and what was loaded is masked away where the word does not exist.
@@ -429,7 +431,7 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
 #pragma unroll
             for (int s = 0; s < 8; ++s) ca = add_bytes(p[s], ca);
             ca += kOffsetPerWord;
-            cb += 256 * __popc(b);
+            cb += 256u * uint32_t(__popc(b));
             acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i{int(p[0]), int(p[1]), int(p[2]), int(p[3])}, widen_bits<0>(b),
                                                           acc[0], 0, 0, 0);
             acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i{int(p[4]), int(p[5]), int(p[6]), int(p[7])}, widen_bits<1>(b),
@@ -439,33 +441,37 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
     }
 
     // Lanes 0-31 end up with the sum of A's row fr over both lane halves, lanes 32-63 with that of B's row fr.
-    const auto sw = __builtin_amdgcn_permlane32_swap(uint32_t(ca), uint32_t(cb), false, false);
-    sum_part[wave][lane] = int(sw[0] + sw[1]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(uint32_t(ca), cb, false, false);
+    sum_part[wave][lane] = sw[0] + sw[1];
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-        part[wave][g][lane] = make_int4(acc[0][4 * g] + acc[1][4 * g], acc[0][4 * g + 1] + acc[1][4 * g + 1],
-                                        acc[0][4 * g + 2] + acc[1][4 * g + 2], acc[0][4 * g + 3] + acc[1][4 * g + 3]);
+        part[wave][g][lane] = make_uint4(uint32_t(acc[0][4 * g]) + uint32_t(acc[1][4 * g]),
+                                         uint32_t(acc[0][4 * g + 1]) + uint32_t(acc[1][4 * g + 1]),
+                                         uint32_t(acc[0][4 * g + 2]) + uint32_t(acc[1][4 * g + 2]),
+                                         uint32_t(acc[0][4 * g + 3]) + uint32_t(acc[1][4 * g + 3]));
     __syncthreads();
 
     // Accumulator register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.  This wavefront finishes registers
     // 4*wave .. 4*wave + 3.
-    int dot[4] = {0, 0, 0, 0};
-    int pb = 0;
+    uint32_t sum[4] = {0u, 0u, 0u, 0u}, pb = 0u;
 #pragma unroll
     for (int w = 0; w < kSplitWaves; ++w) {
-        const int4 s4 = part[w][wave][lane];
-        const int4 ra = *reinterpret_cast<const int4*>(&sum_part[w][8 * wave + 4 * fh]);
-        dot[0] += s4.x - ra.x;
-        dot[1] += s4.y - ra.y;
-        dot[2] += s4.z - ra.z;
-        dot[3] += s4.w - ra.w;
+        const uint4 s4 = part[w][wave][lane];
+        const uint4 ra = *reinterpret_cast<const uint4*>(&sum_part[w][8 * wave + 4 * fh]);
+        sum[0] += s4.x - ra.x;
+        sum[1] += s4.y - ra.y;
+        sum[2] += s4.z - ra.z;
+        sum[3] += s4.w - ra.w;
         pb += sum_part[w][32 + fr];
     }
+    int dot[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dot[e] = int(sum[e] + pb);
     if constexpr (!FUSED) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = row0 + 8 * wave + 4 * fh + e;
-            if (row < M && col < N) C[int64_t(row) * ldc + col] = dot[e] + pb;
+            if (row < M && col < N) C[int64_t(row) * ldc + col] = dot[e];
         }
     } else {
         const bool valid = col < N;
@@ -474,7 +480,7 @@ __global__ __launch_bounds__(256) void bitplane_gemm_split_kernel(
         uint32_t word = 0u;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint64_t mask = __ballot(valid && ((dot[e] + pb >= thr) != flip));
+            const uint64_t mask = __ballot(valid && ((dot[e] >= thr) != flip));
             if ((lane & 3) == e) word = (lane & 4) ? uint32_t(mask >> 32) : uint32_t(mask);
         }
         const int row = row0 + 8 * wave + lane;

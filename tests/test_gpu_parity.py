@@ -407,9 +407,9 @@ def test_fused_layer_on_both_sides_of_the_float_compare_limit(K):
         assert (words_to_host(got) == oracle.pack_bits(want)).all(), kernel
 
 
-def test_bitplane_gemm_at_the_exact_accumulation_limit():
-    """255 * K < 2^24 bounds the 8-bit first layer on the matrix engine: K = 65792 with every input 255 and
-    every weight +1 gives 16776960, the largest sum it must represent."""
+def test_bitplane_gemm_with_sums_just_below_2_24():
+    """K = 65792 with every input 255 and every weight +1 gives 16776960: whole numbers of 24 bits, which sums in 32-bit floats
+    would still represent."""
     K = 65792
     rng = np.random.default_rng(65)
     X = synth.uint8_input(rng, (3, K))
@@ -423,10 +423,11 @@ def test_bitplane_gemm_at_the_exact_accumulation_limit():
     assert (bnn.bitplane_gemm(planes, wb, K).cpu().numpy() == S).all()
 
 
-@pytest.mark.parametrize("K", [65794, 65824, 70001])
-def test_bitplane_gemm_past_the_matrix_engine_limit(K):
-    """One step past 255 * K < 2^24 (and a ragged K further out): the product leaves the matrix engine for the
-    and/popcount kernel; int32 sums and fused bits against the oracle, pad bits of both operands poisoned."""
+@pytest.mark.parametrize("K", [65794, 65824, 70001, (1 << 22) + 1, 8421504])
+def test_bitplane_gemm_of_long_rows(K):
+    """Sums past 2^24 (65794 and further), past the last K whose fused form decides by the sign of a difference (2^22), and the
+    largest K there is (255 * K = 2^31 - 128): int32 sums and fused bits against the oracle, pad bits of both operands
+    poisoned."""
     rng = np.random.default_rng(K)
     M, N = 5, 37
     X = synth.uint8_input(rng, (M, K))
@@ -445,6 +446,35 @@ def test_bitplane_gemm_past_the_matrix_engine_limit(K):
     thr, flip = _fold_to_dev(bn, 255 * K)
     got = bnn.bitplane_gemm_bn_sign_pack(planes, wb, K, thr, flip)
     assert (words_to_host(got) == oracle.pack_bits(oracle.bn_sign(S, *bn, eps=EPS))).all()
+
+
+def test_bitplane_gemm_tiles_that_compare_with_their_thresholds():
+    """The larger tiles at K past 2^22, where a result less its threshold may not fit 32 bits and the fused form compares
+    instead: int32 and fused, against the product in 64-bit floats (exact: sums below 2^53)."""
+    M, N, K = 370, 2900, (1 << 22) + 33
+    kw = (K + 31) // 32
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8)
+    x[0] = 255
+    w = torch.randint(-2 ** 31, 2 ** 31 - 1, (N, kw), generator=g, device=DEV, dtype=torch.int32)
+    w[0], w[1] = -1, 0                                       # all +1, all -1: the largest sums of either sign
+    planes = bnn.pack_bitplanes(x)
+    want = torch.zeros(M, N, dtype=torch.float64, device=DEV)
+    shifts = torch.arange(32, device=DEV, dtype=torch.int32)
+    for w0 in range(0, kw, 2048):
+        part = x[:, 32 * w0:32 * (w0 + 2048)].double()
+        bits = ((w[:, w0:w0 + 2048, None] >> shifts) & 1).reshape(N, -1)[:, :part.shape[1]]
+        want += part @ (2 * bits - 1).double().t()
+    want = want.to(torch.int32)
+    assert int(want[0, 0]) == 255 * K and int(want[0, 1]) == -255 * K
+    assert torch.equal(bnn.bitplane_gemm(planes, w, K), want)
+    thr = want[torch.arange(N, device=DEV) % M, torch.arange(N, device=DEV)] + torch.arange(N, device=DEV, dtype=torch.int32) % 3 - 1
+    thr[2:40:2], thr[3:41:2] = 2 ** 31 - 1, -2 ** 31
+    flip = torch.randint(-2 ** 31, 2 ** 31 - 1, ((N + 31) // 32,), generator=g, device=DEV, dtype=torch.int32)
+    flip[-1] &= (1 << (N % 32)) - 1
+    got = words_to_host(bnn.bitplane_gemm_bn_sign_pack(planes, w, K, thr, flip))
+    flips = oracle.unpack_bits(words_to_host(flip[None, :]), N)[0] == 1
+    assert (got == oracle.pack_bits(np.where((want >= thr).cpu().numpy() != flips, 1, -1).astype(np.int8))).all()
 
 
 def test_xnor_gemm_ldc_and_canary():
