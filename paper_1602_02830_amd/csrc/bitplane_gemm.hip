@@ -73,11 +73,9 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
     const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
     constexpr int T = 64 * WR * WC, BM = 32 * WI * WR, BN = 64 * WC;      // the first BN threads stage a column of B each
-    constexpr int L = BM * kWordsPerTile / T;              // A words (32 elements, 8 plane words) a thread stages per tile
-    constexpr int ROWS = T / kWordsPerTile;                // rows of a staging pass: 4 neighbouring lanes take the words of one
     constexpr int PLANE_A = BM + 1;                        // 16-byte slots; odd, so that the 4 words x 2 rows that 8 lanes
                                                            // store fall into eight different bank groups
-    static_assert((L == 1 || L == 2) && L * T == BM * kWordsPerTile, "the tile's words must divide among the threads");
+    static_assert(T == BM * kWordsPerTile, "a thread stages one word (32 elements, 8 plane words) of A per tile");
     __shared__ uint4 lds_a[TINY ? 1 : 2][2 * kWordsPerTile * PLANE_A];    // [word][half of its 32 bytes][row]
     __shared__ uint32_t lds_b[TINY ? 1 : 2][kWordsPerTile * BN];          // [word][column]
     __shared__ int rowsum_s[BM];
@@ -97,25 +95,21 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
     const int n_pairs = (kw + 1) >> 1;
 
     const int st_w = tid & 3, st_r = tid >> 2;
-    const uint32_t* pa[L];
-#pragma unroll
-    for (int l = 0; l < L; ++l) pa[l] = Xp + int64_t(min(row0 + st_r + ROWS * l, M - 1)) * ldx;
+    const uint32_t* pa = Xp + int64_t(min(row0 + st_r, M - 1)) * ldx;
     const bool st_b = WR == 1 || tid < BN;
     const int b_col = min(col0 + (WR == 1 ? tid : tid & (BN - 1)), N - 1);             // rows past the matrix repeat its last one
     const uint32_t* pb = B + int64_t(b_col) * ldb;
 
-    uint4 ra[L][2], rb;
-    int cnt_a[L], cnt_b = 0;
-#pragma unroll
-    for (int l = 0; l < L; ++l) cnt_a[l] = 0;
+    uint4 ra[2], rb;
+    int cnt_a = 0, cnt_b = 0;
 
     // Loads carry no control flow (a branch around them makes the compiler wait for them where the branches meet, which
     // exposes the whole memory latency in every iteration): word indices are clamped into the row, and the last tile's
     // words that do not exist are sorted out when they are staged.  A row has at least one whole quad (the launcher).
-    auto fetch_a = [&](int kt, int l) {
+    auto fetch_a = [&](int kt) {
         const int w = 8 * min(kWordsPerTile * kt + st_w, kw - 1);
-        ra[l][0] = load_quad_any(pa[l] + w);
-        ra[l][1] = load_quad_any(pa[l] + w + 4);
+        ra[0] = load_quad_any(pa + w);
+        ra[1] = load_quad_any(pa + w + 4);
     };
     auto fetch_b = [&](int kt) {
         if (TINY) rb = make_uint4(pb[0], pb[min(1, kw - 1)], pb[min(2, kw - 1)], 0u);
@@ -126,10 +120,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
         const int w = kWordsPerTile * kt + st_w;
         const uint32_t mask = w < kw - 1 ? ~0u : w == kw - 1 ? tmask : 0u;
 #pragma unroll
-        for (int l = 0; l < L; ++l)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                ra[l][h] = make_uint4(ra[l][h].x & mask, ra[l][h].y & mask, ra[l][h].z & mask, ra[l][h].w & mask);
+        for (int h = 0; h < 2; ++h) ra[h] = make_uint4(ra[h].x & mask, ra[h].y & mask, ra[h].z & mask, ra[h].w & mask);
         const int left = kw - kWordsPerTile * kt;
         if (TINY) {
             rb = mask_row_quad(rb, left, tmask);
@@ -141,17 +132,17 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
            : left == 3 ? make_uint4(rb.y, rb.z, last, 0u) : make_uint4(rb.x, rb.y, rb.z, last);
     };
     uint32_t bytes[8];
-    auto transpose_a = [&](int l) {
-        bytes[0] = ra[l][0].x; bytes[1] = ra[l][0].y; bytes[2] = ra[l][0].z; bytes[3] = ra[l][0].w;
-        bytes[4] = ra[l][1].x; bytes[5] = ra[l][1].y; bytes[6] = ra[l][1].z; bytes[7] = ~ra[l][1].w;
+    auto transpose_a = [&] {
+        bytes[0] = ra[0].x; bytes[1] = ra[0].y; bytes[2] = ra[0].z; bytes[3] = ra[0].w;
+        bytes[4] = ra[1].x; bytes[5] = ra[1].y; bytes[6] = ra[1].z; bytes[7] = ~ra[1].w;
         transpose_bits_8x8(bytes);
     };
-    auto store_a = [&](int l, int buf) {
+    auto store_a = [&](int buf) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) cnt_a[l] = add_bytes(bytes[s], cnt_a[l]);
+        for (int s = 0; s < 8; ++s) cnt_a = add_bytes(bytes[s], cnt_a);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-            lds_a[buf][(2 * st_w + u) * PLANE_A + st_r + ROWS * l] =
+            lds_a[buf][(2 * st_w + u) * PLANE_A + st_r] =
                 make_uint4(bytes[4 * u], bytes[4 * u + 1], bytes[4 * u + 2], bytes[4 * u + 3]);
     };
     auto store_b = [&](int buf) {
@@ -197,17 +188,13 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
     const int lim = 255 * K + 1;
     if (FUSED) thr = max(-lim, min(lim, bn.thr[b_col]));
     auto fetch = [&](int kt) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) fetch_a(kt, l);
+        fetch_a(kt);
         fetch_b(kt);
     };
     auto stage = [&](int kt, int buf) {
         if (kt >= n_full) mask_tail(kt);
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-            transpose_a(l);
-            store_a(l, buf);
-        }
+        transpose_a();
+        store_a(buf);
         store_b(buf);
     };
     if (!TINY || n_ktiles > 0) {
@@ -225,22 +212,16 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
         // Slots the scheduler may not cross: it would sink the loads to the end of the iteration and wait for them at
         // the top of the next.
         step(buf, 0, 0);
-        transpose_a(0);
-        fetch_a(kt + 2, 0);
+        transpose_a();
+        fetch_a(kt + 2);
         __builtin_amdgcn_sched_barrier(0);
         step(buf, 0, 1);
-        store_a(0, buf ^ 1);
+        store_a(buf ^ 1);
         store_b(buf ^ 1);
         fetch_b(kt + 2);
         __builtin_amdgcn_sched_barrier(0);
         step(buf, 1, 0);
-        if (L > 1) {
-            transpose_a(L - 1);
-            fetch_a(kt + 2, L - 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
         step(buf, 1, 1);
-        if (L > 1) store_a(L - 1, buf ^ 1);
         __syncthreads();
     }
     // The last full tile and the partial one.
@@ -259,12 +240,11 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
         __syncthreads();
     }
 
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-        int c = cnt_a[l] + kOffsetPerWord * n_ktiles;                       // words past the row's end included
+    {
+        int c = cnt_a + kOffsetPerWord * n_ktiles;                          // words past the row's end included
         c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
         c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
-        if (st_w == 0) rowsum_s[st_r + ROWS * l] = c;
+        if (st_w == 0) rowsum_s[st_r] = c;
     }
     const bool sign = FUSED && K <= kSignMaxK;
     if (st_b) {
