@@ -234,7 +234,7 @@ int bnn_conv_im2col_pack(const uint32_t *in, int64_t B, int64_t H, int64_t W,
 /*
  * A whole binary convolution layer without the intermediate matrix (implicit GEMM): the
  * receptive fields described under bnn_conv_im2col_pack are taken straight from the packed NHWC
- * input - from a patch of it held on chip where the patch of a tile fits, gathered by the
+ * input - from a patch of it held on chip where that fits and is faster, gathered by the
  * product's tile loader otherwise.
  *   S[(b*Ho + oy)*Wo + ox][co] = sum_{ky,kx,ci} in(b, oy*stride+ky-pad, ox*stride+kx-pad, ci) * Wt[co][ky][kx][ci]
  *   in   packed NHWC [B][H][W][Cin/32] uint32, out-of-image taps read as +1

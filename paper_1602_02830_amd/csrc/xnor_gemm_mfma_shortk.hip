@@ -22,7 +22,7 @@
 // of plane (q, h): consecutive lanes, consecutive slots.  Step 2q + s multiplies word s of that
 // pair, i.e. K words 4q + s (h = 0) and 4q + 2 + s (h = 1); the order of the K sum is free.
 //
-// Requirements (checked by the launcher): A, B 16-byte aligned, lda, ldb multiples of 4 words.
+// Rows may start at any 4-byte alignment (kernel id 7, asked for by number, takes 16-byte aligned rows only).
 // The last quad of a row, where it is incomplete or holds pad bits, is loaded from the row's last
 // four words (never past word K/32), moved into place and masked when it is written to LDS.
 //
