@@ -507,6 +507,7 @@ template <bool FUSED, bool TINY>
 static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                          int64_t M, int64_t N, int64_t K, const BnSignArgs& bn, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (ceil_div(M, 256) * ceil_div(N, 128) > kMaxDim) return BNN_ERR_UNSUPPORTED;
     const int64_t small_m = ceil_div(M, 32), small_n = ceil_div(N, 32);
     if (small_m * small_n <= kSplitMaxTiles) {
         hipLaunchKernelGGL(planes::bitplane_gemm_split_kernel<FUSED>, dim3(unsigned(small_m * small_n)), dim3(256), 0, s, Xp,

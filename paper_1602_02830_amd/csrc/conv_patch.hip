@@ -546,7 +546,7 @@ template <int WM, bool FUSED, bool POOL>
 static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc, int64_t M,
                         int64_t N, int64_t K, BnSignArgs bn, ConvArgs cv, PatchGeom pg, void* stream) {
     const int64_t tiles_m = ceil_div(M, 64 * WM), tiles_n = ceil_div(N, 128);
-    if (tiles_m * tiles_n > kMaxDim) return BNN_ERR_UNSUPPORTED;
+    if (tiles_m * tiles_n > max_blocks(256)) return BNN_ERR_UNSUPPORTED;        // (the larger tiles of the gathering kernels)
     const bool words = cv.Cw % 4 != 0;                  // a tap is not a whole number of 16-byte quads
     const size_t patch_bytes = words ? (words_patch_koff_offset(cv.Cw, pg.slots) + size_t(4) * pg.kq) * 4
                                      : size_t(pg.slots) * size_t(cv.Cw) * 4 + size_t((pg.slots + 1) / 2) * 8;

@@ -154,3 +154,13 @@ def test_layers_of_whole_channel_words_take_any_number_of_images(launches_of, B,
         ("bnn_conv_pool_bn_sign_pack", (A, B, H, W, 32, WB, 256, 32, k, k, 1, pad, 2, THR, FLIP, OUT, 1, 0)))
     assert st == 0 and len(log) == 1
     assert (st_pool, len(log_pool)) == ((0, 1) if H % 2 == 0 and W % 2 == 0 else (3, 0))
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_convolutions_whose_patch_tiles_do_not_fit_one_launch_are_gathered(launches_of, fused):
+    """171000 images of 28 x 28 x 1024, 2176 filters: 17.8 million tiles of 128 pixels, half as many of 256."""
+    B, Cin, Cout, words = 171000, 1024, 2176, 9 * 32
+    call = (("bnn_conv_bn_sign_pack", (A, B, 28, 28, Cin, WB, words, Cout, 3, 3, 1, 1, THR, FLIP, OUT, Cout // 32, 0)) if fused else
+            ("bnn_conv_xnor", (A, B, 28, 28, Cin, WB, words, Cout, 3, 3, 1, 1, C, Cout, 0)))
+    (st, log), = launches_of(call)
+    assert st == 0 and len(log) == 1
