@@ -72,6 +72,7 @@ __host__ __device__ inline size_t words_patch_koff_offset(int Cw, int slots) {
 // covers (52 images of 8 x 8, 512 -> 512 pooled 13.9 -> 12.8 us, 20 of 16 x 16, 384 -> 256 11.5 -> 10.7).
 constexpr int kResidentKTiles = 5, kResidentKTilesAlone = 9;
 constexpr int64_t kLoneGrid = 224;        // workgroups that leave no compute unit with two
+constexpr int64_t kComputeUnits = 256;
 
 // KS = 2: eight wavefronts, the second four taking the second half of K of the same tile; their sums join the first
 // four's in LDS.  For grids that give a compute unit one workgroup at most: a wavefront alone on its SIMD waits for every
@@ -552,10 +553,23 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
                                      : size_t(pg.slots) * size_t(cv.Cw) * 4 + size_t((pg.slots + 1) / 2) * 8;
     const int n_ktiles = (pg.kq + 3) / 4;
     const bool alone = WM <= 2 && n_ktiles > kResidentKTiles && n_ktiles <= kResidentKTilesAlone && tiles_m * tiles_n <= kLoneGrid;
-    const bool resident = n_ktiles <= kResidentKTiles || alone;
+    const bool few = n_ktiles <= kResidentKTiles;
+    // Filters stay resident unless a compute unit then holds fewer workgroups than streaming them would leave it with, and the
+    // grid needs more than it holds: 30 images of 100 x 100, 256 -> 256, stride 2 43.6 us resident, 30.5 streamed, 10 of 70 x 70
+    // 17.9 and 14.7, 151 of 14 x 124, 256 -> 512 (256-pixel tiles, one resident workgroup) 179 and 119, 255 of 16 x 16, 256 ->
+    // 256 (1020 tiles, three and four workgroups) 19.4 and 17.7; but 10 of 70 x 70 at stride 2 (192 tiles) 9.1 and 10.3, 100 of
+    // 28 x 28 on 256 pixels (two either way) 24.9 and 24.8.
+    const size_t tile_bytes = size_t(8) * (128 + 2) * sizeof(uint2);
+    auto per_unit = [&](size_t filters) {
+        const int64_t fit = int64_t(size_t(160) * 1024 / (patch_bytes + filters + (2 + WM) * 1024)), most = WM >= 4 ? 2 : 4;
+        return fit < most ? fit : most;
+    };
+    const bool streams = !words && few && tiles_m * tiles_n > kComputeUnits * per_unit(n_ktiles * tile_bytes) &&
+                         per_unit(n_ktiles * tile_bytes) < per_unit(2 * tile_bytes);
+    const bool resident = (few && !streams) || alone;
     const bool split = WM <= 2 && resident && !words && tiles_m * tiles_n <= kLoneGrid &&
                        n_ktiles >= (WM == 1 ? 2 : 4);
-    const size_t filter_bytes = resident ? size_t(n_ktiles) * 8 * (128 + 2) * sizeof(uint2) : 0;
+    const size_t filter_bytes = resident ? n_ktiles * tile_bytes : 0;
     const size_t sum_bytes = split ? size_t(4) * WM * 2 * 4 * kWave * sizeof(float4) + 16 : 0;   // of the second half of K
     const size_t lds_bytes = patch_bytes + (filter_bytes > sum_bytes ? filter_bytes : sum_bytes);
     const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
@@ -569,7 +583,7 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     if (words) launch(conv_patch_mfma_kernel<WM, FUSED, POOL, kResidentKTiles, true, 1>, 256);   // resident: words_layer_fits
     else if (alone) launch(conv_patch_mfma_kernel<WS, FUSED, POOL, kResidentKTilesAlone, false, 2>, 512);
     else if (split) launch(conv_patch_mfma_kernel<WS, FUSED, POOL, kResidentKTiles, false, 2>, 512);
-    else if (n_ktiles <= kResidentKTiles) launch(conv_patch_mfma_kernel<WM, FUSED, POOL, kResidentKTiles, false, 1>, 256);
+    else if (resident) launch(conv_patch_mfma_kernel<WM, FUSED, POOL, kResidentKTiles, false, 1>, 256);
     else launch(conv_patch_mfma_kernel<WM, FUSED, POOL, 0, false, 1>, 256);
     return check_launch();
 }
@@ -600,8 +614,12 @@ static bool wants_small_tiles(int64_t M, int64_t N, int64_t K, bool fused) {
 //  - a patch that leaves a compute unit with two workgroups, streamed filters beside it, where three would take all tiles in one
 //    round: 31 images of 28 x 28, 1024 -> 512 (760 tiles) 53.0 and 49.9, int32 57.2 and 50.2, 24 of them (588) 50.2 and 46.1; but
 //    40 (980) 61.9 and 62.8.
-static bool better_gathered(const ConvArgs& cv, int BM, int64_t M, int64_t N, int64_t K, const PatchGeom& pg) {
-    if (BM > 128 || whole_row_tiles(cv, BM)) return false;
+//  - 1 x 1 windows over many channels, which reuse nothing: 200 images of 14 x 14, 1024 -> 512 19.4 and 14.4, int32 23.9 and
+//    19.9, 768 channels int32 22.0 and 19.6; but fused 512 -> 256 over 64 of 28 x 28 8.6 and 9.6.
+static bool better_gathered(const ConvArgs& cv, int BM, int64_t M, int64_t N, int64_t K, const PatchGeom& pg, bool fused) {
+    if (whole_row_tiles(cv, BM)) return false;
+    if (cv.kh * cv.kw == 1 && cv.Cw >= (fused ? 32 : 20)) return true;
+    if (BM > 128) return false;
     if (cv.stride == 1 && K <= kShortField && pg.slots > 1280) return true;
     const int64_t tiles = ceil_div(M, BM) * ceil_div(N, 128);
     return K > kResidentKTiles * 512 && tiles > 512 && tiles <= 768 && int64_t(pg.slots) * (cv.Cw * 4 + 4) > 32 * 1024;
@@ -614,7 +632,7 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
     auto fits = [&](int BM) {
-        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, M, N, K, pg);
+        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, M, N, K, pg, FUSED);
     };
     if (wants_small_tiles(M, N, K, FUSED) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);

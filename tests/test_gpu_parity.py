@@ -1203,6 +1203,10 @@ def test_implicit_conv_matches_direct_convolution(shape):
     (2, 40, 400, 128, 20, 3, 3, 1, 1),      # patch too large at 128 pixels and more: the gathering kernels
     (2, 9, 300, 128, 40, 3, 3, 1, 1),       # wide rows at stride 1: gathered as well
     (24, 28, 28, 1024, 400, 2, 2, 1, 1),    # 632 tiles with two patches to a compute unit: gathered
+    (16, 100, 100, 256, 200, 3, 3, 2, 1),   # filters that would fit are streamed: two workgroups to a compute unit with them
+    (20, 60, 60, 256, 33, 3, 3, 1, 1),      # the same, 558 tiles in the first round of three
+    (40, 14, 14, 1024, 70, 1, 1, 1, 0),     # 1 x 1 windows over many channels: gathered
+    (40, 14, 14, 640, 70, 1, 1, 1, 0),      # the same in the int32 form alone
     (8, 50, 112, 128, 40, 3, 3, 1, 1),      # patches of a few rows, of which a tile loads its own alone; 128 pixels
     (3, 30, 112, 128, 40, 3, 3, 1, 1),      # the same, 64 pixels
     (10, 120, 121, 128, 30, 3, 3, 1, 1),    # the same, 256 pixels
