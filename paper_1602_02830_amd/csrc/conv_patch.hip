@@ -196,16 +196,17 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     // ---- patch: every slot once ------------------------------------------------------------
     // Slot s is column s % pw of row patch_row0 + s / pw of the padded images from b0 on, which follow each other without a
     // gap.
+    const uint32_t* in_b0 = in + size_t(b0) * uint32_t(cv.H * cv.W) * uint32_t(cv.Cw);
+    const int images_left = n_images - b0;
     if (WORDS || !FUSED) {
         // Slot by slot (the word-granular patch, and the int32 form, whose epilogue leaves no registers for
         // more loads in flight).
         for (int s = tid; s < slots_here; s += T) {
             const int py = pg.by_pw(s), px = s - py * pg.pw;
-            const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
-            const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
-            const bool inside = b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
+            const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+            const bool inside = b < images_left && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
             const uint32_t pix = inside ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
-            const uint32_t* p = in + size_t(pix) * uint32_t(cv.Cw);
+            const uint32_t* p = in_b0 + size_t(pix) * uint32_t(cv.Cw);
             int pop = 0;
             if (WORDS) {
                 for (int cw = 0; cw < cv.Cw; ++cw) {
@@ -238,11 +239,10 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
                 const int s = s_base + u * T + tid;
                 live[u] = s < slots_here;
                 const int py = pg.by_pw(s), px = s - py * pg.pw;
-                const int db = pg.by_img_rows(patch_row0 + py), b = b0 + db;
-                const int y = patch_row0 + py - db * pg.img_rows - cv.pad, x = px - cv.pad;
-                inside[u] = live[u] && b < n_images && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
+                const int b = pg.by_img_rows(patch_row0 + py), y = patch_row0 + py - b * pg.img_rows - cv.pad, x = px - cv.pad;
+                inside[u] = live[u] && b < images_left && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
                 const uint32_t pix = inside[u] ? uint32_t((b * cv.H + y) * cv.W + x) : 0u;
-                p[u] = in + size_t(pix) * uint32_t(cv.Cw);
+                p[u] = in_b0 + size_t(pix) * uint32_t(cv.Cw);
                 pop[u] = 0;
             }
             for (int cq0 = 0; cq0 < pg.cqn; cq0 += kQuadsPerPass) {
