@@ -438,7 +438,7 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 // 169 -> 147); with 257 .. 511 rows a strip is one tile and a bit, and the second start-up costs what the
 // kernel gains (20000 x 1024 x 2048 19.3 vs 21.0, 10000 x 2048 x 4096 32.8 vs 33.1).
 static int choose_kernel(int64_t M, int64_t N, int64_t K, bool fused, bool short_ok, bool whole_ok, bool walk_ok,
-                         bool big_ok, bool splitk_ok) {
+                         bool big_ok, bool splitk_ok, bool aligned_rows) {
     // Small outputs: 32 x 32 tiles with K split inside the workgroup, while the tiles are few enough for the
     // workgroup dispatch rate.  Launches replayed from a graph, fused, rows of ceil(K / 32) words, against the 64 x 128
     // tiles below, us: 64 x 1000 (64 tiles) K = 128 3.0 vs 4.0, 1000 3.2 vs 4.6, 4097 4.4 vs 8.7, 16384 6.2 vs 22.6;
@@ -465,7 +465,20 @@ static int choose_kernel(int64_t M, int64_t N, int64_t K, bool fused, bool short
         if (K >= 4096 && tiles256 >= 1024) return KERNEL_MFMA;
         // fused, K = 2048, N = 4096: M = 8192 27.4 vs 28.0 (128 x 128 tiles), 12288 39.4 vs 40.7, 20000 62.4 vs 65.5
         if (fused && K >= 2048 && tiles256 >= 768) return KERNEL_MFMA;
-        if (short_ok && tiles128 >= 768) return KERNEL_MFMA_SHORTK;
+        if (short_ok && tiles128 >= 768) {
+            // Rows at any 4-byte alignment: the short-K kernel stages word by word, so its lead is smaller and K of
+            // exactly one 512-bit step of the 128 x 128 tiles is theirs (us, short-K vs 128 x 128 tiles: fused
+            // 98304 x 128 7.2 vs 6.0, 12783 x 992 9.4 vs 8.3, 30000 x 4000 41.7 vs 40.8; fused K = 640 17.2 vs 22.1 and
+            // K = 1024 20.4 vs 21.7 at 10000 x 4096).  In int32 so is K >= 993 (98304 x 130, K = 1024 23.8 vs 20.3;
+            // 40000 x 1024, K = 1152 42.7 vs 41.1), unless a few tiles are left over after full rounds of three
+            // workgroups per compute unit (12783 x 992, K = 1024, 800 tiles: 14.5 vs 16.5; 200000 x 128 24.3 vs 25.6).
+            const int64_t kw = ceil_div(K, 32), left_over = tiles128 % 768;
+            const bool few_left = left_over > 0 && left_over < 96;
+            if (!aligned_rows && tiles128 <= max_blocks(256) &&
+                (fused ? kw == 16 : (kw == 16 || kw >= 32) && !few_left))
+                return KERNEL_MFMA128;
+            return KERNEL_MFMA_SHORTK;
+        }
         // Small grids, measured against the 64 x 64 vector-ALU tiles (fused / int32): 200 x 1000 x 520 4.6 vs 7.0 /
         // 5.0 vs 6.2 us, 1500 x 1000 x 2100 6.7 vs 15.5 / 7.0 vs 14.6.  Rows of fewer than 4 words: the int32 form
         // only from a few dozen tiles on.
@@ -503,7 +516,7 @@ static int xnor_gemm_dispatch(const uint32_t* A, int64_t lda, const uint32_t* B,
         kernel_id = choose_kernel(M, N, K, /*fused=*/false, mfma_shortk_supports(K),
                                   mfma_persist_supports(A, lda, B, ldb, ldc, M, N, K, false, false),
                                   mfma_persist_supports(A, lda, B, ldb, ldc, M, N, K, false, true), false,
-                                  mfma_splitk_supports(M, N, K));
+                                  mfma_splitk_supports(M, N, K), aligned_rows);
 
     switch (kernel_id) {
         case KERNEL_NAIVE: {
@@ -607,7 +620,7 @@ static int xnor_gemm_bn_sign_pack_dispatch(const uint32_t* A, int64_t lda, const
                                   mfma_persist_supports(A, lda, B, ldb, 0, M, N, K, true, false),
                                   mfma_persist_supports(A, lda, B, ldb, 0, M, N, K, true, true),
                                   mfma_big_supports(A, lda, B, ldb, M, N, K, bn),
-                                  mfma_splitk_supports(M, N, K));
+                                  mfma_splitk_supports(M, N, K), aligned_rows);
     if (kernel_id == KERNEL_MFMA_SHORTK) return launch_xnor_gemm_mfma_shortk_fused(A, lda, B, ldb, M, N, K, bn, stream);
     if (kernel_id == KERNEL_MFMA_PERSIST)
         return launch_xnor_gemm_mfma_persist(A, lda, B, ldb, nullptr, 0, M, N, K, true, true, bn, stream);

@@ -729,7 +729,10 @@ ANY_ROW_SHAPES = [(33, 65, 97), (64, 100, 128), (31, 32, 129), (65, 33, 255), (4
                   (1000, 1000, 511), (1000, 1000, 513), (1025, 1024, 777), (300, 4000, 1153), (700, 700, 3001), (130, 257, 96),
                   (130, 257, 33), (1500, 260, 2049), (1300, 1290, 96), (2049, 1030, 1600), (4100, 1027, 2085),
                   # rows of fewer than 4 words, on both sides of the fused form's 256 tiles of 128 x 128
-                  (2048, 2048, 96), (2049, 2047, 33), (32640, 127, 64), (32641, 129, 31), (33000, 1, 65), (2048, 1920, 1)]
+                  (2048, 2048, 96), (2049, 2047, 33), (32640, 127, 64), (32641, 129, 31), (33000, 1, 65), (2048, 1920, 1),
+                  # 768 tiles of 128 x 128, on both sides of the words that leave the short-K kernel where rows are not aligned
+                  (6100, 2040, 480), (6100, 2040, 481), (6144, 2048, 512), (6100, 2040, 513), (6100, 2040, 992), (6100, 2040, 1100),
+                  (12783, 992, 1024)]
 
 
 @pytest.mark.parametrize("M,N,K", ANY_ROW_SHAPES)

@@ -164,3 +164,23 @@ def test_convolutions_whose_patch_tiles_do_not_fit_one_launch_are_gathered(launc
             ("bnn_conv_xnor", (A, B, 28, 28, Cin, WB, words, Cout, 3, 3, 1, 1, C, Cout, 0)))
     (st, log), = launches_of(call)
     assert st == 0 and len(log) == 1
+
+
+@pytest.mark.parametrize("M,N,K,fused,id_", [
+    (12783, 992, 480, True, 7), (12783, 992, 481, True, 6), (12783, 992, 512, True, 6), (12783, 992, 513, True, 7),
+    (30000, 4000, 512, True, 6), (10000, 4096, 1024, True, 7), (30000, 4000, 1152, True, 7),
+    (98304, 130, 480, False, 7), (98304, 130, 512, False, 6), (98304, 130, 992, False, 7), (98304, 130, 1000, False, 6),
+    (40000, 1024, 1152, False, 6), (12783, 992, 1024, False, 7), (12783, 992, 512, False, 7), (200000, 128, 1100, False, 7),
+    (2 ** 26, 4096, 512, True, 7), (2 ** 26 - 128, 4096, 512, True, 6)])
+def test_short_rows_at_any_alignment_take_the_tiles_that_fit_them(launches_of, M, N, K, fused, id_):
+    """Rows that do not start at 16 bytes: K of one 512-bit step, and long int32 rows over whole rounds of tiles, take a
+    workgroup per 128 x 128 tile (kernel 6, while one launch holds them); the rest, and aligned rows, the short-K kernel."""
+    def call(kernel, ld):
+        if fused:
+            return ("bnn_xnor_gemm_bn_sign_pack_kernel", (A, ld, B, ld, M, N, K, THR, FLIP, OUT, (N + 31) // 32, kernel, 0))
+        return ("bnn_xnor_gemm_kernel", (A, ld, B, ld, C, N, M, N, K, kernel, 0))
+    kw = (K + 31) // 32
+    odd, aligned = kw | 1, kw + 3 & ~3
+    (st, log), (st7, log7), (st_aligned, log_aligned) = launches_of(call(0, odd), call(7, aligned), call(0, aligned))
+    assert st == st7 == st_aligned == 0 and log_aligned == log7 != [[-(-M // 128) * -(-N // 128), 256, A]]
+    assert log == (log7 if id_ == 7 else [[-(-M // 128) * -(-N // 128), 256, A]])
