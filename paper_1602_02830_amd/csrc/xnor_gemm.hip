@@ -381,6 +381,7 @@ bool mfma_big_prefers(int64_t M, int64_t N);
 // 32 x 32 output tiles with K split over the wavefronts of a workgroup (xnor_gemm_mfma_splitk.hip), for small
 // outputs with a long K: BNN_ERR_UNSUPPORTED, with nothing launched, for the products it does not take.
 bool mfma_splitk_supports(int64_t M, int64_t N, int64_t K);
+bool mfma_splitk_prefers(int64_t M, int64_t N, int64_t K, bool fused);
 int launch_xnor_gemm_mfma_splitk(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C,
                                  int64_t ldc, int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn,
                                  void* stream);
@@ -439,17 +440,13 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 // kernel gains (20000 x 1024 x 2048 19.3 vs 21.0, 10000 x 2048 x 4096 32.8 vs 33.1).
 static int choose_kernel(int64_t M, int64_t N, int64_t K, bool fused, bool short_ok, bool whole_ok, bool walk_ok,
                          bool big_ok, bool splitk_ok, bool aligned_rows) {
-    // Small outputs: 32 x 32 tiles with K split inside the workgroup, while the tiles are few enough for the
-    // workgroup dispatch rate.  Launches replayed from a graph, fused, rows of ceil(K / 32) words, against the 64 x 128
+    // Small outputs: K split inside the workgroup, while the tiles are few enough for the workgroup dispatch rate
+    // (mfma_splitk_prefers).  Launches replayed from a graph, fused, rows of ceil(K / 32) words, 32 x 32 tiles against the 64 x 128
     // tiles below, us: 64 x 1000 (64 tiles) K = 128 3.0 vs 4.0, 1000 3.2 vs 4.6, 4097 4.4 vs 8.7, 16384 6.2 vs 22.6;
-    // 500 x 1000 (512 tiles) K = 128 3.4 vs 4.1, 1000 3.5 vs 4.7, 4097 5.8 vs 8.8; 1000 x 1000 (1024 tiles) K = 300 4.2 vs
-    // 4.1, 520 4.2 vs 4.7, 2100 5.7 vs 6.5, 8192 10.8 vs 13.1; 1500 x 1000 (1504 tiles) K = 1000 5.7 vs 4.8, 4096 9.3 vs
-    // 8.4.  The int32 form alike, skinny outputs included (against the lane-group kernel: 10000 x 10, K = 4096, 4.3 vs
+    // 500 x 1000 (512 tiles) K = 128 3.4 vs 4.1, 1000 3.5 vs 4.7, 4097 5.2 vs 8.8; 1000 x 1000 (1024 tiles) K = 300 4.2 vs
+    // 4.1.  The int32 form alike, skinny outputs included (against the lane-group kernel: 10000 x 10, K = 4096, 4.3 vs
     // 5.1 us, 16384 x 16 4.6 vs 6.8, 1 x 4096 3.2 vs 3.6, 4 x 1024, K = 8192, 4.6 vs 4.3).
-    if (splitk_ok) {
-        const int64_t tiles32 = ceil_div(M, 32) * ceil_div(N, 32);
-        if (tiles32 <= 512 || (tiles32 <= 1024 && K >= 512)) return KERNEL_MFMA_SPLITK;
-    }
+    if (splitk_ok && mfma_splitk_prefers(M, N, K, fused)) return KERNEL_MFMA_SPLITK;
     if (!fused && (N <= 16 || M <= 4)) return KERNEL_KSPLIT;
     if (fused && big_ok && mfma_big_prefers(M, N)) return KERNEL_MFMA_BIG;
     const int64_t tiles128 = ceil_div(M, 128) * ceil_div(N, 128);

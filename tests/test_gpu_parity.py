@@ -781,6 +781,20 @@ def test_int32_rows_of_every_alignment(M, N, K, pad, first):
         assert (flat == 0x6B6B6B6B).all(), kernel
 
 
+# The forms of the split-K kernel that the automatic choice takes by size: 64 x 32 tiles from 897 tiles of 32 x 32 on, K staged
+# in rounds of 32 quads whose last one is shared out in 2, 4, 6 or 8 quads per wavefront, both sides of every limit.
+@pytest.mark.parametrize("M,N,K", [
+    (300, 1000, 3456), (300, 1000, 3457), (290, 999, 4097), (290, 1000, 4225), (300, 1000, 8192), (300, 1000, 8193),
+    (33, 8000, 4096), (1, 32000, 4097), (896, 1024, 1000), (897, 1000, 520), (961, 990, 777), (993, 1024, 3585),
+    (1000, 1000, 4225), (1000, 1000, 5300), (1000, 1000, 6500), (1000, 1001, 8190), (1249, 1000, 999), (1249, 1000, 1000),
+    (1506, 1023, 4100), (1537, 1024, 4096), (40000, 10, 1500), (4, 40000, 1500)])
+@pytest.mark.parametrize("extra,first", [(0, 0), (3, 1)])
+def test_k_split_kernel_forms(M, N, K, extra, first):
+    test_products_of_rows_at_any_alignment(M, N, K, extra, first)
+    if M * N * K < 1 << 33:
+        test_int32_rows_of_every_alignment(M, N, K, extra, first)
+
+
 def test_k_split_matrix_engine_kernel_refuses_what_it_does_not_take():
     """Kernel id 10 answers BNN_ERR_UNSUPPORTED, launching nothing, outside its shapes: K not a multiple of
     128 (or zero), operands that do not allow 16-byte loads."""
