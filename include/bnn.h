@@ -280,6 +280,15 @@ int bnn_conv_pool_bn_sign_pack(const uint32_t *in, int64_t B, int64_t H, int64_t
                                uint32_t *out, int64_t ld_out, void *stream);
 
 /*
+ * The same pooled layer on any map: pool = 2, even Ho and Wo, any window, stride and padding, Cin a multiple of 128 and an
+ * input patch that fits the compute unit's local memory.  Anything else returns BNN_ERR_UNSUPPORTED before any launch.
+ */
+int bnn_conv_pool_windows_bn_sign_pack(const uint32_t *in, int64_t B, int64_t H, int64_t W, int64_t Cin,
+                                       const uint32_t *Wb, int64_t ldw, int64_t Cout, int kh, int kw, int stride,
+                                       int pad, int pool, const int32_t *thr, const uint32_t *flip_bits,
+                                       uint32_t *out, int64_t ld_out, void *stream);
+
+/*
  * Max pooling for binarized layers.  In the architecture Sec. 2.2 refers to (the cited BinaryConnect
  * ConvNet, as this library reads it) the pre-activations are pooled between a convolution and its
  * BatchNorm + Sign; since Sign(BatchNorm(.)) is monotone per channel, the bit

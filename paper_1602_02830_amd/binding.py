@@ -50,6 +50,8 @@ _SIGNATURES = {
                                      _ptr, _ptr, _i64, _ptr]),
     "bnn_conv_pool_bn_sign_pack": (_int, [_ptr, _i64, _i64, _i64, _i64, _ptr, _i64, _i64, _int, _int, _int, _int, _int,
                                           _ptr, _ptr, _ptr, _i64, _ptr]),
+    "bnn_conv_pool_windows_bn_sign_pack": (_int, [_ptr, _i64, _i64, _i64, _i64, _ptr, _i64, _i64, _int, _int, _int, _int, _int,
+                                                  _ptr, _ptr, _ptr, _i64, _ptr]),
     "bnn_maxpool_bits": (_int, [_ptr, _i64, _i64, _i64, _i64, _int, _int, _int, _ptr, _ptr, _ptr]),
     "bnn_gemm_i8_mfma": (_int, [_ptr, _i64, _ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr]),
     "bnn_unpack_i8": (_int, [_ptr, _i64, _i64, _i64, _ptr, _i64, _ptr]),
@@ -447,9 +449,20 @@ def conv_pool_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor,
     """bnn_conv_pool_bn_sign_pack: binary conv + max pooling + Sign(BatchNorm) in one launch ->
     packed bits [B*(Ho/pool)*(Wo/pool)][ceil(Cout/32)].  Raises BnnError with status 3 (unsupported)
     for geometries the fused kernel does not take."""
+    return _conv_pool("conv_pool_bn_sign_pack", x_bits, Cin, w_bits, thr, flip_bits, kh, kw, stride, pad, pool, out)
+
+
+def conv_pool_windows_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor, thr: torch.Tensor,
+                                   flip_bits: torch.Tensor, kh: int = 3, kw: int = 3, stride: int = 1, pad: int = 1,
+                                   pool: int = 2, out: torch.Tensor | None = None) -> torch.Tensor:
+    """bnn_conv_pool_windows_bn_sign_pack: the same on any even map (Cin % 128 == 0)."""
+    return _conv_pool("conv_pool_windows_bn_sign_pack", x_bits, Cin, w_bits, thr, flip_bits, kh, kw, stride, pad, pool, out)
+
+
+def _conv_pool(name, x_bits, Cin, w_bits, thr, flip_bits, kh, kw, stride, pad, pool, out):
     if out is not None and _calls is not None:
-        st = _calls.conv_pool_bn_sign_pack(x_bits, Cin, w_bits, kh, kw, stride, pad, thr, flip_bits, out, pool)
-        if st == 0 or _took("bnn_conv_pool_bn_sign_pack", st):
+        st = getattr(_calls, name)(x_bits, Cin, w_bits, kh, kw, stride, pad, thr, flip_bits, out, pool)
+        if st == 0 or _took("bnn_" + name, st):
             return out
     lib = load_library()
     _check_nhwc_bits(x_bits, Cin)
@@ -470,10 +483,10 @@ def conv_pool_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch.Tensor,
     _holds(w_bits, Cout if B * max(Ho, 0) * max(Wo, 0) else 0, words_per_row(kh * kw * Cin), "w_bits")
     if out.shape[0] != B * (Ho // pool) * (Wo // pool) or out.shape[1] != nw:
         raise ValueError("out must be [B*(Ho/pool)*(Wo/pool)][ceil(Cout/32)]")
-    _check("bnn_conv_pool_bn_sign_pack",
-           lib.bnn_conv_pool_bn_sign_pack(x_bits.data_ptr(), B, H, W, Cin, w_bits.data_ptr(), _ld(w_bits), Cout, kh,
-                                          kw, stride, pad, pool, thr.data_ptr(), flip_bits.data_ptr(),
-                                          out.data_ptr(), _ld(out), _stream(out)))
+    _check("bnn_" + name,
+           getattr(lib, "bnn_" + name)(x_bits.data_ptr(), B, H, W, Cin, w_bits.data_ptr(), _ld(w_bits), Cout, kh, kw, stride,
+                                       pad, pool, thr.data_ptr(), flip_bits.data_ptr(), out.data_ptr(), _ld(out),
+                                       _stream(out)))
     return out
 
 

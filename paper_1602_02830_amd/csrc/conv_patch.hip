@@ -19,9 +19,9 @@
 // Pooled layers (POOL = true): the paper's ConvNets max-pool the pre-activations 2 x 2 between a
 // convolution and its BatchNorm + Sign.  Sign(BatchNorm(.)) is monotone per channel, so the pooled
 // output bit is the OR of the window's four output bits where the folded flip bit is 0 and their
-// AND where it is 1.  A tile holds whole (even numbers of) image rows, so every window lies inside
-// one wavefront's rows: the horizontal neighbour is the next lane, the vertical one W lanes away
-// (W < 32) or in the accumulator block W / 32 further on, and only the pooled words are stored.
+// AND where it is 1.  The rows of a pooled layer are its pixels window by window (row 4 * window + 2 * dy + dx), so a
+// window is four neighbouring lanes of one accumulator block whatever the size of the image, and only the pooled words are
+// stored.  Nothing but the cell of a row depends on that order.
 //
 // Channel counts that are multiples of 32 but not of 128 (WORDS = true; the 64-channel block of the
 // half-width SVHN net of Sec. 2.3): a tap is then not a whole number of 16-byte quads, so the patch is
@@ -42,23 +42,17 @@
 // us, 200 of 13 x 13, 128 -> 396 17.8 -> 13.9, 100 of 14 x 14, 256 -> 256 13.4 -> 11.7, 256 of 32 x 32, 128 -> 256 at
 // stride 2 15.5 -> 13.0, 128 of 56 x 56, 128 -> 128 37.0 -> 31.6.
 #include "bnn_internal.h"
+#include "conv_patch_geometry.h"
 #include "gemm_staging.h"
 #include "mfma_fp4.h"
 
 namespace bnn {
 
-constexpr int kPatchMaxBytes = 40 * 1024;
+// Layers that fill the chip (conv_strip.hip): BNN_ERR_UNSUPPORTED, with nothing launched, for those it leaves to this kernel.
+int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                            BnSignArgs bn, ConvArgs cv, bool pool, void* stream);
 
-struct PatchGeom {
-    int img_rows;      // H + 2*pad: rows of a padded image
-    int pw;            // W + 2*pad: patch row pitch (pixels)
-    int slots;         // cells of the largest patch a tile of this layer has
-    bool trim;         // most tiles need far fewer
-    int cqn;           // channel quads per pixel (Cw / 4); unused when a tap is not a whole number of quads
-    int kq;            // quads of K per filter row: kh * kw * cqn, or ceil(kwords / 4)
-    int kwords;        // words of K per filter row: kh * kw * Cw
-    FastDiv by_wo, by_ho, by_img_rows, by_pw;
-};
+constexpr int kPatchMaxBytes = 40 * 1024;
 
 // Word offset of the K-word table behind the word-granular patch ([Cw][slots] words + slots pixel popcounts).
 __host__ __device__ inline size_t words_patch_koff_offset(int Cw, int slots) {
@@ -102,7 +96,6 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     __shared__ uint32_t flip_s[FUSED ? BN / 32 : 1];
     __shared__ float colfix_s[FUSED ? BN : 1];
     __shared__ int slot_s[BM];
-    __shared__ int pixel_s[POOL ? BM : 1];              // POOL: (image of the tile, y, x) in 7 + 15 + 7 bits
     uint32_t* patchw = reinterpret_cast<uint32_t*>(patch);
     int* pix_pop = WORDS ? reinterpret_cast<int*>(patchw + size_t(cv.Cw) * pg.slots)
                          : reinterpret_cast<int*>(patch + size_t(2) * pg.cqn * pg.slots);
@@ -156,20 +149,23 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     // The tile's first output pixel is (image b0, row y0, ...); the patch starts at the padded row its window starts at,
     // row patch_row0 of image b0 (rows are counted from there: all images' together may be more than 2^31).
     // Output pixel r of the tile as a patch cell: the divisions are done once per pixel here, not once per use.
-    const int row_first = pg.by_wo(row0), b0 = pg.by_ho(row_first), y0 = row_first - b0 * cv.Ho;
-    const int patch_row0 = y0 * cv.stride;
+    // POOL: cv.Wo, cv.Ho and the divisions are those of the map of windows (pooled_units).
+    constexpr int PF = POOL ? 2 : 1;
+    const int row_first = pg.by_wo(POOL ? row0 >> 2 : row0), b0 = pg.by_ho(row_first), y0 = row_first - b0 * cv.Ho;
+    const int patch_row0 = PF * y0 * cv.stride;
     // Cells to load: up to the end of the last pixel's window where that may be far fewer than the tile that needs most has.
     int slots_here = pg.slots;
     if (pg.trim) {
-        const int row_last = pg.by_wo(min(row0 + BM, M) - 1), b_last = pg.by_ho(row_last), y_last = row_last - b_last * cv.Ho;
-        slots_here = ((b_last - b0) * pg.img_rows + (y_last - y0) * cv.stride + cv.kh) * pg.pw;
+        const int last = min(row0 + BM, M) - 1;
+        const int row_last = pg.by_wo(POOL ? last >> 2 : last), b_last = pg.by_ho(row_last), y_last = row_last - b_last * cv.Ho;
+        slots_here = ((b_last - b0) * pg.img_rows + PF * (y_last - y0) * cv.stride + (PF - 1) * cv.stride + cv.kh) * pg.pw;
     }
     if (tid < BM) {
-        const int m = min(row0 + tid, M - 1);
-        const int t = pg.by_wo(m), x = m - t * cv.Wo;
+        const int m = min(row0 + tid, M - 1), unit = POOL ? m >> 2 : m;
+        const int t = pg.by_wo(unit), x = unit - t * cv.Wo;
         const int b = pg.by_ho(t), y = t - b * cv.Ho;
-        slot_s[tid] = ((b - b0) * pg.img_rows + y * cv.stride - patch_row0) * pg.pw + x * cv.stride;
-        if (POOL) pixel_s[tid] = ((b - b0) << 22) | (y << 7) | x;           // pooled rows have at most 64 pixels
+        const int dy = POOL ? (m >> 1) & 1 : 0, dx = POOL ? m & 1 : 0;
+        slot_s[tid] = ((b - b0) * pg.img_rows + (PF * y + dy) * cv.stride - patch_row0) * pg.pw + (PF * x + dx) * cv.stride;
     }
     // Thresholds and flip words go to registers here and to LDS after the patch loads have been issued: every
     // global load of the prologue (these, the filters, the patch) is in flight before the first one is waited for.
@@ -304,15 +300,49 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
     __syncthreads();                                    // patch, pixel popcounts and the first (or every) B tile are in LDS
 
     // Row popcounts: sum of the pixel popcounts under the kh x kw window (read before the epilogue,
-    // which follows at least one more barrier).
+    // which follows at least one more barrier).  Nine taps at a time, their loads in flight together and their offsets
+    // stepped in scalar registers: one tap after the other, nine round trips to LDS stood between staging and the first
+    // product (of the 31200 cycles of a 256-pixel tile of 256 x 16 x 16 x 256, 256 -> 256, this phase took 2050).
     if (tid < BM) {
-        const int s0 = slot_s[tid];
-        int sum = 0;
-        for (int ky = 0; ky < cv.kh; ++ky)
-            for (int kx = 0; kx < cv.kw; ++kx) sum += pix_pop[s0 + ky * pg.pw + kx];
+        constexpr int kTaps = 9;
+        const int* at = pix_pop + slot_s[tid];
+        const int taps = cv.kh * cv.kw;
+        int sum = 0, off = 0, kx = 0;
+        if (taps == 1) sum = at[0];
+        for (int t0 = 0; t0 < taps && taps > 1; t0 += kTaps) {
+            int v[kTaps];
+#pragma unroll
+            for (int u = 0; u < kTaps; ++u) {
+                v[u] = at[off];                         // past the last tap: the last one again
+                if (t0 + u + 1 < taps) {
+                    ++off;
+                    if (++kx == cv.kw) {
+                        kx = 0;
+                        off += pg.pw - cv.kw;
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kTaps; ++u) sum += t0 + u < taps ? v[u] : 0;
+        }
         pop_a[tid] = 2 * sum;
         if (FUSED) pop_af[tid] = 0.5f * float(sum);
     }
+
+    // Column popcounts and column terms of the epilogue, once every filter word has been staged.
+    auto publish_columns = [&] {
+#pragma unroll
+        for (int l = 0; l < LOADS_B; ++l) {
+            int c = cnt_b[l];
+            c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
+            c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
+            if (st_q == 0) {
+                pop_b[st_r + l * ST_ROWS] = 2 * c;
+                if (FUSED) colfix_s[st_r + l * ST_ROWS] = fold_column_term(thr_s[st_r + l * ST_ROWS], K, 2 * c);
+            }
+        }
+    };
+    if (BRES) publish_columns();
 
     // This lane's A operands: pixel wm*32*WM + i*32 + fr, words of lane half fh.
     const uint2* rd_a[WM];
@@ -435,16 +465,7 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
         }
     }
 
-#pragma unroll
-    for (int l = 0; l < LOADS_B; ++l) {
-        int c = cnt_b[l];
-        c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
-        c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
-        if (st_q == 0) {
-            pop_b[st_r + l * ST_ROWS] = 2 * c;
-            if (FUSED) colfix_s[st_r + l * ST_ROWS] = fold_column_term(thr_s[st_r + l * ST_ROWS], K, 2 * c);
-        }
-    }
+    if (!BRES) publish_columns();
     __syncthreads();
     if (KS > 1 && kg > 0) return;                       // no barrier follows
 
@@ -455,78 +476,20 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 2 : RES > kResidentKTiles ? 1 : 
         const uint32_t flip_word = flip_s[wn * WN + fh];
         const int64_t nw = (int64_t(N) + 31) >> 5;
         const int64_t w = ((int64_t(col0) + wn * 32 * WN) >> 5) + fh;
-        uint32_t any[WM], all[WM];
+        // Lane i of the four that hold a window stores block i's word.
+        uint32_t pooled = 0u;
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
-            // horizontal neighbour (x ^ 1): the next lane; vertical one for W < 32: W lanes away
-            const uint32_t h = uint32_t(__shfl_xor(int(words[i]), 1));
-            any[i] = words[i] | h;
-            all[i] = words[i] & h;
-            if (cv.W < 32) {
-                any[i] |= uint32_t(__shfl_xor(int(any[i]), cv.W));
-                all[i] &= uint32_t(__shfl_xor(int(all[i]), cv.W));
-            }
+            const uint32_t p = pool_words(words[i], flip_word);              // by every lane
+            pooled = (fr & 3) == i ? p : pooled;
         }
-        const int blocks_per_row = cv.W >> 5;           // W >= 32: image row y and y + 1 are blocks i and i + W / 32
-        const int hp = cv.H >> 1, wp = cv.W >> 1;
-#pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            uint32_t a = any[i], l = all[i];
-            if (cv.W >= 32) {
-#pragma unroll
-                for (int i2 = 0; i2 < WM; ++i2)
-                    if (i2 == i + blocks_per_row) {
-                        a |= any[i2];
-                        l &= all[i2];
-                    }
-            }
-            const int rl = wm * 32 * WM + i * 32 + fr, m = row0 + rl;
-            const int c = pixel_s[rl];
-            const int b = b0 + (c >> 22), y = (c >> 7) & 32767, x = c & 127;
-            const uint32_t pooled = (a & ~flip_word) | (l & flip_word);
-            if (m < M && w < nw && !(y & 1) && !(x & 1))
-                bn.out[(int64_t(b) * hp + (y >> 1)) * wp * bn.ld_out + int64_t(x >> 1) * bn.ld_out + w] = pooled;
-        }
+        const int m = row0 + wm * 32 * WM + (fr & 3) * 32 + (fr & 28);
+        if ((fr & 3) < WM && m < M && w < nw) bn.out[int64_t(m >> 2) * bn.ld_out + w] = pooled;
     } else if constexpr (FUSED)
         mfma_epilogue_bits<WM, WN>(acc, pop_a, pop_af, pop_b, thr_s, flip_s, colfix_s, bn, M, N, K, row0, col0, wm, wn,
                                    fr, fh);
     else
         mfma_epilogue<WM, WN>(acc, pop_a, pop_b, C, ldc, M, N, K, row0, col0, wm, wn, fr, fh);
-}
-
-// Rows of the padded images that the windows of BM consecutive output pixels can span, at most.
-static int64_t patch_rows(const ConvArgs& cv, int64_t BM) {
-    const int64_t rows = BM % cv.Wo == 0 ? BM / cv.Wo : (BM - 2) / cv.Wo + 2;    // output rows a tile touches
-    // Image boundaries among them: none or rows / Ho - 1 where tiles are whole rows that divide into images or the reverse.
-    int64_t cross = ceil_div(rows - 1, cv.Ho);
-    if (BM % cv.Wo == 0 && cv.Ho % rows == 0) cross = 0;
-    else if (BM % cv.Wo == 0 && rows % cv.Ho == 0) cross = rows / cv.Ho - 1;
-    // From one output row to the next the window moves by `stride` rows, across a boundary by what is left of the image.
-    const int64_t over = int64_t(cv.H) + 2 * cv.pad - int64_t(cv.Ho - 1) * cv.stride;
-    const int64_t within = (rows - 1) * cv.stride, crossing = (rows - 1 - cross) * cv.stride + cross * over;
-    return (within > crossing ? within : crossing) + cv.kh;
-}
-
-// Fills the patch geometry for tiles of BM output pixels; false if the patch does not fit.
-static bool patch_geometry(const ConvArgs& cv, int BM, PatchGeom& pg) {
-    const int64_t img_rows = int64_t(cv.H) + 2 * cv.pad, pw = int64_t(cv.W) + 2 * cv.pad;
-    const int64_t slots = patch_rows(cv, BM) * pw;
-    if (slots * (int64_t(cv.Cw) * 4 + 4) > kPatchMaxBytes) return false;
-    pg.img_rows = int(img_rows);
-    pg.pw = int(pw);
-    pg.slots = int(slots);
-    // The largest patch crosses from image to image and starts in the middle of a row.  Counting a tile's own cells costs
-    // 0.1 - 0.2 us and pays from about 1.4 times (8 images of 112 x 112, 128 -> 128 channels 15.1 -> 13.7 us, 64 of 56 x 56
-    // 19.6 -> 18.7; 100 of 16 x 16, whose patches are all alike, 6.8 -> 6.9).
-    pg.trim = 5 * slots >= 7 * ((ceil_div(BM, cv.Wo) - 1) * cv.stride + cv.kh) * pw;
-    pg.cqn = cv.Cw / 4;
-    pg.kwords = cv.kh * cv.kw * cv.Cw;
-    pg.kq = (pg.kwords + 3) / 4;
-    pg.by_wo = fast_div(cv.Wo);
-    pg.by_ho = fast_div(cv.Ho);
-    pg.by_img_rows = fast_div(img_rows);
-    pg.by_pw = fast_div(pw);
-    return true;
 }
 
 // Same-size stride-1 layers whose tiles of BM pixels are whole image rows that divide into images, or whole images.
@@ -572,7 +535,7 @@ static int launch_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int3
     const size_t filter_bytes = resident ? n_ktiles * tile_bytes : 0;
     const size_t sum_bytes = split ? size_t(4) * WM * 2 * 4 * kWave * sizeof(float4) + 16 : 0;   // of the second half of K
     const size_t lds_bytes = patch_bytes + (filter_bytes > sum_bytes ? filter_bytes : sum_bytes);
-    const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
+    const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo * (POOL ? 4 : 1)));
     const dim3 grid(unsigned(tiles_m * tiles_n));
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto launch = [&](auto kernel, int threads) {
@@ -632,7 +595,7 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
     auto fits = [&](int BM) {
-        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, pg) && !better_gathered(cv, BM, M, N, K, pg, FUSED);
+        return (cv.Cw % 4 == 0 || words_layer_fits(cv, BM)) && patch_geometry(cv, BM, BM, kPatchMaxBytes, false, pg) && !better_gathered(cv, BM, M, N, K, pg, FUSED);
     };
     if (wants_small_tiles(M, N, K, FUSED) && fits(128) && fits(64))
         return launch_patch<1, FUSED, false>(in, B, ldb, C, ldc, M, N, K, bn, cv, pg, stream);
@@ -642,8 +605,8 @@ static int launch_conv_patch_any(const uint32_t* in, const uint32_t* B, int64_t 
     return BNN_ERR_UNSUPPORTED;
 }
 
-// 2 x 2 pooling inside a tile of BM = 64 * WM pixels: whole-row tiles, even H and W, W a power of two below 32 or 32 * k
-// with the row pair inside one wavefront's WM blocks, and an even number of image rows per tile.
+// What bnn_conv_pool_bn_sign_pack takes: tiles of 64 * WM pixels that are whole image rows, even H and W, W a power of two
+// below 32 or 32 * k with k <= WM / 2, and an even number of image rows per tile.
 static bool pool_fits(const ConvArgs& cv, int WM) {
     const int BM = 64 * WM;
     if (!whole_row_tiles(cv, BM) || (cv.Cw % 4 != 0 && !words_layer_fits(cv, BM))) return false;
@@ -660,23 +623,35 @@ int launch_conv_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_
 
 int launch_conv_patch_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             BnSignArgs bn, ConvArgs cv, void* stream) {
+    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, false, stream);
+    if (st != BNN_ERR_UNSUPPORTED) return st;
     return launch_conv_patch_any<true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, stream);
 }
 
 // Convolution, 2 x 2 max pooling (stride 2), BatchNorm, Sign in one launch; bn.out is the pooled
-// packed NHWC map [B][H/2][W/2][ld_out].  BNN_ERR_UNSUPPORTED where the pooling windows do not fit
-// the tiles (the caller then pools the unpooled output bits with bnn_maxpool_bits).
+// packed NHWC map [B][Ho/2][Wo/2][ld_out].  BNN_ERR_UNSUPPORTED for what it does not take (the caller then pools the unpooled
+// output bits with bnn_maxpool_bits).  any_map: any even map of whole channel quads whose patch fits, not only the layers of
+// pool_fits.
 int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                                 BnSignArgs bn, ConvArgs cv, void* stream) {
+                                 BnSignArgs bn, ConvArgs cv, bool any_map, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    auto fits = [&](int WM) { return pool_fits(cv, WM) && patch_geometry(cv, 64 * WM, pg); };
+    if (any_map ? cv.Cw % 4 != 0 || ((cv.Ho | cv.Wo) & 1)
+                : !((pool_fits(cv, 2) && patch_geometry(cv, 128, 128, kPatchMaxBytes, false, pg)) ||
+                    (pool_fits(cv, 4) && patch_geometry(cv, 256, 256, kPatchMaxBytes, false, pg))))
+        return BNN_ERR_UNSUPPORTED;
+    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, true, stream);
+    if (st != BNN_ERR_UNSUPPORTED) return st;
+    const ConvArgs units = pooled_units(cv);
+    auto fits = [&](int WM) {
+        return (any_map || pool_fits(cv, WM)) && patch_geometry(units, 64 * WM, 64 * WM, kPatchMaxBytes, true, pg);
+    };
     if (wants_small_tiles(M, N, K, true) && fits(2) && fits(1))
-        return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
+        return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
     if (wants_big_tiles(M, N) && fits(4))
-        return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
-    if (fits(2)) return launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
-    if (fits(4)) return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, pg, stream);
+        return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    if (fits(2)) return launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    if (fits(4)) return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
     return BNN_ERR_UNSUPPORTED;
 }
 

@@ -1,0 +1,539 @@
+// Binary convolution layers on bits (fused with Sign(BatchNorm), with or without 2 x 2 max pooling) that fill the chip:
+// one workgroup of eight wavefronts per compute unit, 128 filters resident in LDS, a strip of output pixels walked in tiles
+// of 512.
+//
+// Arithmetic, patch and filter layout are those of conv_patch.hip (an input patch in LDS, the A operand of tap (ky, kx) read at
+// slot(pixel) + ky * PW + kx; pooled layers in window order).  What differs is how the work is cut, because at batch 256 these
+// layers are bound by what surrounds their products: of the 34500 cycles of a workgroup of 256 pixels x 128 filters (256 -> 256
+// channels of 16 x 16, two workgroups per compute unit, all starting together) 18400 were matrix cycles.
+//   - Filters are staged once per compute unit instead of once per 256 pixels: loads go through the unit at 64 bytes a
+//     cycle, so staging them twice beside two patches took 1500 of the 7500 cycles before the first product, and filters of
+//     up to nine K-tiles (3 x 3 over 512 channels) fit instead of streaming.
+//   - Strips are equal: the N / 128 column tiles times `groups` strips are at most one workgroup per compute unit, and
+//     every workgroup has the same pixels, where whole tiles left the last round of workgroups half empty (392 tiles of 256
+//     pixels over 512 slots).  A strip's last tile holds what is left, in block rows of 32 dealt to the wavefronts in turn.
+//   - While a tile is multiplied the next one's patch is loaded into registers and stored to another of three buffers, with
+//     one barrier per tile, so that a wavefront's epilogue and start of the next tile run under the other wavefront's products.
+//   - Everything a wavefront needs for its own rows (patch cells, window popcounts) it computes itself, and the
+//     accumulators START as the folded threshold, a product of bf16 pairs (a quarter of the rank-2 fp32 update that
+//     conv_patch.hip adds at the end, and neither zeros nor a pass of its own).
+//   - The K loop is one quad of channels (two steps of 64) long: the operands of a step are widened between the products of
+//     the step before, LDS is read half a step ahead (BNN_STRIP_SCHEDULE).  The two wavefronts of a SIMD take 39 cycles per
+//     product together, 36 where one runs alone: alternating operands cost the engine more than the issue of both does.
+// Batch 256, us, tiles of conv_patch.hip before and strips now: 128 -> 128 of 32 x 32 pooled 19.3 and 17.3, 128 -> 256 of
+// 16 x 16 10.9 and 10.3, 256 -> 256 16.3 and 14.9, 256 -> 512 of 8 x 8 11.3 and 10.2, 512 -> 512 pooled 18.3 and 16.3; 128 images
+// of 28 x 28, 128 -> 256 pooled (then two launches) 21.7 and 15.1; the ConvNet body 88.0 and 78.9.
+// Four wavefronts of 4 x 4 blocks (one per SIMD) were slower at every size (256 -> 256 of 16 x 16 21.4): the allocator does not
+// fit 256 accumulators and the next patch's registers, and nothing covers the phases between the tiles.
+#include <numeric>
+
+#include "bnn_internal.h"
+#include "conv_patch_geometry.h"
+#include "gemm_staging.h"
+#include "mfma_fp4.h"
+
+namespace bnn {
+namespace strip {
+
+constexpr int T = 512, BN = 128, PLANE_B = BN + 2;     // 8-byte slots per filter plane (2 pad slots)
+constexpr int WAVE_ROWS = 4;                           // wavefronts along the pixels, two along the filters
+constexpr int NB_MAX = 4;                              // block rows of 32 pixels per wavefront
+constexpr int BM = 32 * WAVE_ROWS * NB_MAX;            // 512 pixels
+constexpr int PF_SLOTS = 2, PF_QUADS = 2;              // patch cells per thread and quads per cell that are loaded ahead
+constexpr int FIRST = 4;                               // quads of the first patch that a thread loads before it stores one
+
+// How the layer is cut.
+struct Cut {
+    FastDiv by_tiles_n;
+    int tiles_n, per_die;      // column tiles; workgroups / 8
+    int rows;                  // pixels per strip, a multiple of 32
+    int ahead;                 // whether the next patch is loaded under the products, into another of up to three buffers
+};
+
+// After every product: VALU vector operations and, with READ, one LDS read.
+#define BNN_STRIP_SCHEDULE(MFMAS, READ, VALU)                               \
+    do {                                                                    \
+        _Pragma("unroll") for (int g_ = 0; g_ < (MFMAS); ++g_) {            \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              \
+            __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);           \
+            if (READ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    \
+        }                                                                   \
+        __builtin_amdgcn_sched_barrier(0);                                  \
+    } while (0)
+
+// A tile and its patch: unit row and column (in the image) and image of the tile's first unit, first padded row of the patch in
+// that image, cells up to the end of the tile's last window, first row of the image that can be among them, and that row's
+// address.  Units: pixels, or (POOL) pooling
+// windows, whose maps cv.Wo, cv.Ho and the divisions then describe.
+struct Origin {
+    int y, x, b, row0, slots, top;
+    const uint32_t* at;
+};
+
+template <bool POOL>
+__device__ __forceinline__ Origin origin_of(const uint32_t* in, const PatchGeom& pg, const ConvArgs& cv, int row0, int rows) {
+    constexpr int PF = POOL ? 2 : 1;
+    const int u0 = POOL ? row0 >> 2 : row0, u1 = POOL ? (row0 + rows - 1) >> 2 : row0 + rows - 1;
+    const int first = pg.by_wo(u0), last = pg.by_wo(u1);
+    const int b0 = pg.by_ho(first), b1 = pg.by_ho(last), y0 = first - b0 * cv.Ho, y1 = last - b1 * cv.Ho;
+    const int row_first = PF * y0 * cv.stride, top = max(min(row_first - cv.pad, cv.H - 1), 0);
+    return Origin{y0, u0 - first * cv.Wo, b0, row_first,
+                  ((b1 - b0) * pg.img_rows + PF * (y1 - y0) * cv.stride + (PF - 1) * cv.stride + cv.kh) * pg.pw,
+                  top, in + (size_t(b0) * uint32_t(cv.H) + uint32_t(top)) * uint32_t(cv.W) * uint32_t(cv.Cw)};
+}
+
+// Cells and offsets below are counted from there, hence at most a patch's: products of 24 bits, in a quarter of the time of 32.
+__device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
+
+// Byte offset of cell s of a patch from o.at, 0 for a cell outside the images.
+__device__ __forceinline__ uint32_t cell_of(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o, int s, bool& inside) {
+    const int py = pg.by_pw(s), px = s - mul24(py, pg.pw);
+    const int b = pg.by_img_rows(o.row0 + py), y = o.row0 + py - mul24(b, pg.img_rows) - cv.pad, x = px - cv.pad;
+    inside = s < o.slots && b < n_images - o.b && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
+    return inside ? uint32_t(mul24(mul24(mul24(b, cv.H) + y - o.top, cv.W) + x, 4 * cv.Cw)) : 0u;
+}
+
+__device__ __forceinline__ uint4 ones_unless(bool keep, uint4 v) {
+    return make_uint4(keep ? v.x : ~0u, keep ? v.y : ~0u, keep ? v.z : ~0u, keep ? v.w : ~0u);
+}
+
+__device__ __forceinline__ void put_quad(uint2* patch, int slots, int s, int cq, uint4 v) {
+    patch[(2 * cq) * slots + s] = make_uint2(v.x, v.y);
+    patch[(2 * cq + 1) * slots + s] = make_uint2(v.z, v.w);
+}
+
+// Quad cq of the cell at byte offset `at`.
+__device__ __forceinline__ uint4 load_at(const uint32_t* image, uint32_t at, int cq) {
+    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(image) + 16 * cq + at);
+}
+
+// Cells s0, s0 + T, ... (FIRST / C of them) of a patch, C quads each, on their way into registers ...
+template <int C>
+__device__ __forceinline__ void load_cells(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o, int s0, int cq0, uint4 (&v)[FIRST], uint32_t& inside) {
+    inside = 0u;
+#pragma unroll
+    for (int u = 0; u < FIRST / C; ++u) {
+        bool in_image;
+        const uint32_t at = cell_of(pg, cv, n_images, o, s0 + u * T, in_image);
+        inside |= in_image ? 1u << u : 0u;
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[u * C + c] = load_at(o.at, at, min(cq0 + c, pg.cqn - 1));
+    }
+}
+
+// ... and from there to LDS; pop: set bits of the cells' quads before cq0, and afterwards with these.
+template <int C>
+__device__ __forceinline__ void store_cells(const PatchGeom& pg, Origin o, int s0, int cq0, const uint4 (&v)[FIRST], uint32_t inside,
+                                            int (&pop)[FIRST / C], uint2* patch) {
+    const int slots = pg.slots, cqn = pg.cqn;
+#pragma unroll
+    for (int u = 0; u < FIRST / C; ++u) {
+        const int s = s0 + u * T;
+        const bool keep = (inside >> u) & 1u;
+        if (s < o.slots) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (cq0 + c >= cqn) break;
+                const uint4 w = ones_unless(keep, v[u * C + c]);
+                patch[(2 * (cq0 + c)) * slots + s] = make_uint2(w.x, w.y);
+                patch[(2 * (cq0 + c) + 1) * slots + s] = make_uint2(w.z, w.w);
+                pop[u] += popc4(w);
+            }
+            if (cq0 + C >= cqn) reinterpret_cast<int*>(patch + 2 * cqn * slots)[s] = pop[u];
+        }
+    }
+}
+
+// A whole patch but for what load_cells(s0 = tid, cq0 = 0) took.
+template <int C>
+__device__ __forceinline__ void load_rest(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o,
+                                          int (&pop)[FIRST / C], uint2* patch) {
+    for (int base = 0; base < o.slots; base += FIRST / C * T) {
+        if (base > 0) {
+#pragma unroll
+            for (int u = 0; u < FIRST / C; ++u) pop[u] = 0;
+        }
+        for (int cq0 = base == 0 ? C : 0; cq0 < pg.cqn; cq0 += C) {
+            uint4 v[FIRST];
+            uint32_t inside;
+            load_cells<C>(pg, cv, n_images, o, base + int(threadIdx.x), cq0, v, inside);
+            store_cells<C>(pg, o, base + int(threadIdx.x), cq0, v, inside, pop, patch);
+        }
+    }
+}
+
+// Integers n / 8 of at most 16 bits as two bf16 numbers: the upper eight bits and the rest, both exact.
+typedef short v4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void split_bf16(float v, short& hi, short& lo) {
+    const uint32_t top = __float_as_uint(v) & 0xFFFF0000u;
+    hi = short(top >> 16);
+    lo = short(__float_as_uint(v - __uint_as_float(top)) >> 16);
+}
+
+// C: quads per cell and load of the first patch.
+template <bool POOL, int RES, int C>
+__global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
+    const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, int M, int N, int K, BnSignArgs bn,
+    ConvArgs cv, PatchGeom pg, Cut cut, int n_images) {
+    constexpr int WN = 2, PF = POOL ? 2 : 1;           // POOL: rows are the pixels of one pooling window after the other
+    extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // filters, then one or two patches with their pixel popcounts
+    __shared__ float colfix_s[BN];
+    __shared__ uint32_t flip_s[BN / 32];
+    const int cqn = pg.cqn, slots = pg.slots, kq = pg.kq;
+    const int patch_size = 2 * cqn * slots + (slots + 1) / 2;     // in 8-byte slots
+    uint2* patches = dyn + 2 * kq * PLANE_B;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wn = wave & 1;
+    const int fr = lane & 31, fh = lane >> 5;
+
+    // Consecutive workgroups go to the 8 dies in turn: a die takes neighbouring strips, with all their column tiles.
+    int logical = int(blockIdx.x);
+    if (logical < 8 * cut.per_die) logical = (logical & 7) * cut.per_die + (logical >> 3);
+    const int group = cut.by_tiles_n(logical), col0 = (logical - group * cut.tiles_n) * BN;
+    const int row_begin = group * cut.rows, row_end = min(M, row_begin + cut.rows);
+
+    // ---- filters: every load of the start is in flight before the first one is waited for -----------------
+    const int st_q = tid & 3, st_r = tid >> 2;
+    const uint32_t* pb = B + int64_t(min(col0 + st_r, N - 1)) * ldb;
+    uint4 all_b[RES];
+#pragma unroll
+    for (int kt = 0; kt < RES; ++kt) all_b[kt] = *reinterpret_cast<const uint4*>(pb + 4 * min(4 * kt + st_q, kq - 1));
+    const int thr = bn.thr[min(col0 + st_r, N - 1)];
+    uint32_t flip_reg = 0u;
+    if (tid < BN / 32 && col0 + 32 * tid < N) flip_reg = bn.flip_bits[(col0 >> 5) + tid];
+
+    // ---- patches -------------------------------------------------------------------------------------------
+    // Loaded ahead (cut.ahead: at most PF_SLOTS cells per thread of at most PF_QUADS quads): cell u * T + tid of a patch.
+    uint4 ahead[PF_QUADS];
+    bool ahead_inside = false;
+    auto load_ahead = [&](Origin o, int u) __attribute__((always_inline)) {
+        const uint32_t at = cell_of(pg, cv, n_images, o, u * T + tid, ahead_inside);
+#pragma unroll
+        for (int c = 0; c < PF_QUADS; ++c) ahead[c] = load_at(o.at, at, min(c, cqn - 1));
+    };
+    auto store_ahead = [&](Origin o, int u, uint2* patch) __attribute__((always_inline)) {
+        const int s = u * T + tid;
+        if (s < o.slots) {
+            const uint4 v0 = ones_unless(ahead_inside, ahead[0]);
+            put_quad(patch, slots, s, 0, v0);
+            int pop = popc4(v0);
+            if (cqn > 1) {
+                const uint4 v1 = ones_unless(ahead_inside, ahead[1]);
+                put_quad(patch, slots, s, 1, v1);
+                pop += popc4(v1);
+            }
+            reinterpret_cast<int*>(patch + 2 * cqn * slots)[s] = pop;
+        }
+    };
+
+    Origin here = origin_of<POOL>(in, pg, cv, row_begin, min(BM, row_end - row_begin));
+    uint4 first[FIRST];
+    uint32_t first_inside;
+    load_cells<C>(pg, cv, n_images, here, tid, 0, first, first_inside);
+
+    // The lane's rows as patch cells: row (i * WAVE_ROWS + wr) * 32 + fr of the tile.
+    int slot[NB_MAX];
+    auto find_slots = [&](int row0, Origin o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NB_MAX; ++i) {
+            const int r = min((i * WAVE_ROWS + wr) * 32 + fr, row_end - 1 - row0), u = o.x + (POOL ? r >> 2 : r);
+            const int t = pg.by_wo(u), x = u - mul24(t, cv.Wo);
+            const int b = pg.by_ho(o.y + t), y = o.y + t - mul24(b, cv.Ho);
+            const int dy = POOL ? (r >> 1) & 1 : 0, dx = POOL ? r & 1 : 0;
+            slot[i] = mul24(mul24(b, pg.img_rows) + mul24(PF * y + dy, cv.stride) - o.row0, pg.pw) + mul24(PF * x + dx, cv.stride);
+        }
+    };
+    find_slots(row_begin, here);
+
+    // Filters to LDS, planes [quad][half] of 8-byte slots, with their popcounts and column terms.
+    {
+        int c = 0;
+#pragma unroll
+        for (int kt = 0; kt < RES; ++kt)
+            if (4 * kt + st_q < kq) {
+                const uint4 v = all_b[kt];
+                c += popc4(v);
+                uint2* to = dyn + (2 * (4 * kt + st_q)) * PLANE_B + st_r;
+                to[0] = make_uint2(v.x, v.y);
+                to[PLANE_B] = make_uint2(v.z, v.w);
+            }
+        c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
+        c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
+        if (st_q == 0) colfix_s[st_r] = fold_column_term(max(-K - 1, min(K + 1, thr)), K, 2 * c);
+        if (tid < BN / 32) flip_s[tid] = flip_reg;
+    }
+    {
+        int pop[FIRST / C] = {};
+        store_cells<C>(pg, here, tid, 0, first, first_inside, pop, patches);
+        load_rest<C>(pg, cv, n_images, here, pop, patches);
+    }
+    __syncthreads();
+
+    // Left factors of the accumulators' start, start = (column term) x 1 + 1 x (row term), each term in two bf16 parts:
+    // lane half 0 holds (column hi, column lo, 1, 1) and, on the right, (1, 1, row hi, row lo); half 1 zeros.
+    constexpr short kOne = 0x3F80;
+    v4s left[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+        short hi, lo;
+        split_bf16(colfix_s[wn * 32 * WN + j * 32 + fr], hi, lo);
+        left[j] = fh == 0 ? v4s{hi, lo, kOne, kOne} : v4s{0, 0, 0, 0};
+    }
+    const uint32_t flip_word = flip_s[wn * WN + fh];
+    const int cols_left = N - (col0 + wn * 64 + fh * 32);
+    const uint32_t live_word = cols_left >= 32 ? ~0u : cols_left <= 0 ? 0u : ((1u << cols_left) - 1u);
+    uint32_t* out = bn.out + ((col0 + wn * 64) >> 5) + fh;                  // this lane's word column
+    const uint2* rd_b0 = dyn + fh * PLANE_B + wn * 64 + fr;
+
+    // One tile: rows [row0, row0 + rows), the wavefront's NB block rows (block i * WAVE_ROWS + wr).
+    auto run = [&](auto nb_tag, int row0, uint2* patch, bool more_tiles, Origin next, uint2* next_patch) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb_tag)::value;
+        constexpr int VALU = (5 * NB + 6 * WN + NB * WN - 1) / (NB * WN);      // widening of a step, per product
+        const bool more = NB == NB_MAX && more_tiles;                          // a tile before the last one is whole
+        const uint2* rd_a[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) rd_a[i] = patch + fh * slots + slot[i];
+        v16f acc[NB][WN];
+        {
+            // Popcounts under the windows: lane half h sums block rows i with i % 2 = h, nine taps at a time.
+            const int* pops = reinterpret_cast<int*>(patch + 2 * cqn * slots);
+            constexpr int NP = (NB + 1) / 2;
+            const int* at[NP];
+            int sum[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int odd = slot[2 * p + 1 < NB ? 2 * p + 1 : 2 * p];
+                at[p] = pops + (fh == 0 ? slot[2 * p] : odd);
+                sum[p] = 0;
+            }
+            for (int ky = 0; ky < cv.kh; ky += 3)
+                for (int kx = 0; kx < cv.kw; kx += 3) {
+                    int v[NP][9];
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+#pragma unroll
+                        for (int e = 0; e < 9; ++e)
+                            v[p][e] = at[p][min(ky + e / 3, cv.kh - 1) * pg.pw + min(kx + e % 3, cv.kw - 1)];
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+#pragma unroll
+                        for (int e = 0; e < 9; ++e) sum[p] += ky + e / 3 < cv.kh && kx + e % 3 < cv.kw ? v[p][e] : 0;
+                }
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                short hi, lo;
+                split_bf16(-0.5f * float(sum[p]), hi, lo);                 // block row 2p + fh
+                const uint32_t mine = uint32_t(uint16_t(hi)) | (uint32_t(uint16_t(lo)) << 16);
+                const auto sw = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+                const uint32_t odd = sw[1];                                // lanes 0-31: what lanes 32-63 have
+                const v4s right_even = {kOne, kOne, short(mine & 0xFFFFu), short(mine >> 16)};
+                const v4s right_odd = {kOne, kOne, short(odd & 0xFFFFu), short(odd >> 16)};
+                v16f zero;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) zero[v] = 0.0f;
+#pragma unroll
+                for (int j = 0; j < WN; ++j) {
+                    acc[2 * p][j] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(left[j], right_even, zero, 0, 0, 0);
+                    if (2 * p + 1 < NB)
+                        acc[2 * p + 1 < NB ? 2 * p + 1 : 0][j] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(left[j], right_odd, zero, 0, 0, 0);
+                }
+            }
+        }
+        const bool piped = more && cut.ahead;
+        if (piped) load_ahead(next, 0);
+
+        // K loop over quads of channels; (ky, kx, cq) of the quad that is read next, stepped with carries.
+        int kx = 0, cq = 0, off = 0, q = 0;
+        const int row_step = pg.pw - cv.kw + 1, plane_step = 2 * slots;
+        auto step_quad = [&]() __attribute__((always_inline)) {
+            if (++cq < cqn) {
+                off += plane_step;
+            } else {
+                cq = 0;
+                off -= (cqn - 1) * plane_step;
+                if (++kx < cv.kw) {
+                    ++off;
+                } else {
+                    kx = 0;
+                    off += row_step;
+                }
+            }
+        };
+        const uint2* rd_b = rd_b0;
+        uint2 aw[NB], bw[WN];
+        auto read_words = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) aw[i] = rd_a[i][off];
+#pragma unroll
+            for (int j = 0; j < WN; ++j) bw[j] = rd_b[j * 32];
+        };
+        v4i fa[NB], fb[WN], ha[NB], hb[WN];
+        read_words();
+#pragma unroll
+        for (int i = 0; i < NB; ++i) fa[i] = widen4_a(aw[i].x);
+#pragma unroll
+        for (int j = 0; j < WN; ++j) fb[j] = widen4_b(bw[j].x);
+        auto multiply = [&](const v4i (&a)[NB], const v4i (&b)[WN]) __attribute__((always_inline)) {
+            // operands swapped: the accumulators hold the transposed blocks, a lane 16 columns of one output row
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand8(b[j]), operand8(a[i]), acc[i][j], 4, 4, 0, 0, 0, 0);
+        };
+        for (int part = piped ? 0 : 2; part < 3; ++part) {
+            const int q_end = part == 0 ? kq / 3 : part == 1 ? 2 * kq / 3 : kq;
+            for (; q < q_end; ++q) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (q + 1 < kq) {                    // past the end the last quad again, whose products are not taken
+                    step_quad();
+                    rd_b += 2 * PLANE_B;
+                }
+#pragma unroll
+                for (int i = 0; i < NB; ++i) ha[i] = widen4_a(aw[i].y);
+#pragma unroll
+                for (int j = 0; j < WN; ++j) hb[j] = widen4_b(bw[j].y);
+                read_words();
+                multiply(fa, fb);
+                BNN_STRIP_SCHEDULE(NB * WN, true, VALU);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) fa[i] = widen4_a(aw[i].x);
+#pragma unroll
+                for (int j = 0; j < WN; ++j) fb[j] = widen4_b(bw[j].x);
+                multiply(ha, hb);
+                BNN_STRIP_SCHEDULE(NB * WN, false, VALU);
+            }
+            // The next patch, half of the cells, then the rest (the loop has registers for one cell's quads, not for two).  A
+            // buffer is written two tiles after it was read, behind the barrier of the tile in between.
+            if (part == 0) {
+                store_ahead(next, 0, next_patch);
+                load_ahead(next, 1);
+            } else if (part == 1) {
+                store_ahead(next, 1, next_patch);
+                __syncthreads();
+            }
+        }
+        if (more && !cut.ahead) {
+            __syncthreads();
+            int pop[FIRST / C] = {};
+            load_cells<C>(pg, cv, n_images, next, tid, 0, first, first_inside);
+            store_cells<C>(pg, next, tid, 0, first, first_inside, pop, next_patch);
+            load_rest<C>(pg, cv, n_images, next, pop, next_patch);
+            __syncthreads();
+        }
+
+        // The output bit is the complement of the accumulator's sign (mfma_output_words).
+        uint32_t words[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            uint32_t part[WN];
+#pragma unroll
+            for (int j = 0; j < WN; ++j) {
+                uint32_t neg = 0u;
+#pragma unroll
+                for (int v = 3; v >= 0; --v) {
+#pragma unroll
+                    for (int e = 3; e >= 0; --e)
+                        neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[i][j][4 * v + e]), 31);
+                    if (v > 0) neg <<= 4;
+                }
+                part[j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
+            }
+            const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
+            words[i] = ((sw[0] | sw[1]) ^ flip_word) & live_word;
+        }
+        if (cols_left <= 0) return;
+        if constexpr (POOL) {
+            // Lane i of the four that hold a window stores block row i's word.
+            uint32_t pooled = 0u;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const uint32_t w = pool_words(words[i], flip_word);
+                pooled = (fr & 3) == i ? w : pooled;
+            }
+            const int m = row0 + ((fr & 3) * WAVE_ROWS + wr) * 32 + (fr & 28);
+            if ((fr & 3) < NB && m < row_end) out[int64_t(m >> 2) * bn.ld_out] = pooled;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int m = row0 + (i * WAVE_ROWS + wr) * 32 + fr;
+                if (m < row_end) out[int64_t(m) * bn.ld_out] = words[i];
+            }
+        }
+    };
+
+    int buf = 0;
+    for (int row0 = row_begin; row0 < row_end; row0 += BM) {
+        const int rows = min(BM, row_end - row0), left_rows = row_end - row0 - BM;
+        const bool more = left_rows > 0;
+        Origin next = here;
+        if (more) next = origin_of<POOL>(in, pg, cv, row0 + BM, min(BM, left_rows));
+        uint2* patch = patches + buf * patch_size;
+        if (cut.ahead) buf = buf == 2 ? 0 : buf + 1;
+        uint2* next_patch = patches + buf * patch_size;
+        const int blocks = (rows + 31) / 32, mine = (blocks - wr + WAVE_ROWS - 1) / WAVE_ROWS;
+        if (mine == 4) run(std::integral_constant<int, 4>{}, row0, patch, more, next, next_patch);
+        else if (mine == 3) run(std::integral_constant<int, 3>{}, row0, patch, more, next, next_patch);
+        else if (mine == 2) run(std::integral_constant<int, 2>{}, row0, patch, more, next, next_patch);
+        else if (mine == 1) run(std::integral_constant<int, 1>{}, row0, patch, more, next, next_patch);
+        if (more) find_slots(row0 + BM, next);
+        here = next;
+    }
+}
+
+}  // namespace strip
+
+constexpr int kStripResident = 5, kStripResidentMost = 9;     // K-tiles of 512 bits of the resident filters
+constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, beside what the kernel declares itself
+constexpr int64_t kStripUnits = 256;                          // compute units
+// Strips of more than 128 rows, a block row for each of the four wavefronts along the pixels and more.  us, conv_patch.hip and
+// strips: 192 rows 48 of 32 x 32, 128 -> 128 7.8 and 6.8, 96 of 16 x 16, 256 -> 256 11.3 and 9.0, 160 of 8 x 8, 512 -> 512 (160
+// rows) 18.2 and 14.6; with 128 rows 64 of 16 x 16, 256 -> 256 8.65 and 8.6, 128 -> 256 6.5 and 6.7.  Windows that do not overlap
+// reuse nothing of a patch: 1 x 1, 64 of 32 x 32, 256 -> 256 6.6 and 7.4, 256 of 28 x 28, 512 -> 256 21.4 and 23.0, 2 x 2 at
+// stride 2, 233 of 16 x 16, 128 -> 512 7.7 and 7.95; but 2 x 2 at stride 1, 128 of 28 x 28, 256 -> 256 17.3 and 14.9.
+constexpr int64_t kStripMinRows = 160;
+
+// BNN_ERR_UNSUPPORTED, with nothing launched, for a layer that this kernel does not take or that is faster elsewhere.
+int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                            BnSignArgs bn, ConvArgs cv, bool pool, void* stream) {
+    using namespace strip;
+    if (!aligned_to(B, 16) || ldb % 4 != 0 || cv.Cw % 4 != 0 || K > kStripResidentMost * 512) return BNN_ERR_UNSUPPORTED;
+    if (pool && ((cv.Ho | cv.Wo) & 1)) return BNN_ERR_UNSUPPORTED;
+    const int64_t tiles_n = ceil_div(N, BN);
+    if (tiles_n > kStripUnits) return BNN_ERR_UNSUPPORTED;
+    const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
+    PatchGeom pg;
+    Cut cut;
+    const int64_t rows = ceil_div(ceil_div(M, kStripUnits / tiles_n), 32) * 32, groups = ceil_div(M, rows);
+    if (rows < kStripMinRows || (cv.kh <= cv.stride && cv.kw <= cv.stride)) return BNN_ERR_UNSUPPORTED;
+    if (pool) cv = pooled_units(cv);
+    // Tiles start at multiples of the strips' rows, and 512 pixels further on.
+    const int64_t tile = rows < BM ? rows : BM, align = rows <= BM ? rows : std::gcd(rows, int64_t(BM));
+    if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg)) return BNN_ERR_UNSUPPORTED;
+    const int64_t filters = int64_t(2) * pg.kq * PLANE_B * 8, patch = (int64_t(2) * pg.cqn * pg.slots + (pg.slots + 1) / 2) * 8;
+    if (filters + patch > kStripLdsBytes) return BNN_ERR_UNSUPPORTED;
+    const int64_t tiles = ceil_div(rows, BM), buffers = tiles < 3 ? tiles : 3;
+    cut.ahead = tiles > 1 && pg.slots <= PF_SLOTS * T && pg.cqn <= PF_QUADS && filters + buffers * patch <= kStripLdsBytes;
+    cut.tiles_n = int(tiles_n);
+    cut.by_tiles_n = fast_div(tiles_n);
+    cut.per_die = int(groups * tiles_n / 8);
+    cut.rows = int(rows);
+    const size_t lds = size_t(filters + (cut.ahead ? buffers : 1) * patch);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(groups * tiles_n)), dim3(T), lds, static_cast<hipStream_t>(stream), in, B, ldb,
+                           int(M), int(N), int(K), bn, cv, pg, cut, n_images);
+        return check_launch();
+    };
+    auto of_size = [&](auto pool_tag, auto res_tag) {
+        constexpr bool POOL = decltype(pool_tag)::value;
+        constexpr int RES = decltype(res_tag)::value;
+        return pg.cqn <= 2 ? launch(conv_strip_mfma_kernel<POOL, RES, 2>) : launch(conv_strip_mfma_kernel<POOL, RES, 4>);
+    };
+    using Few = std::integral_constant<int, kStripResident>;
+    using Most = std::integral_constant<int, kStripResidentMost>;
+    if (K <= kStripResident * 512) return pool ? of_size(std::true_type{}, Few{}) : of_size(std::false_type{}, Few{});
+    return pool ? of_size(std::true_type{}, Most{}) : of_size(std::false_type{}, Most{});
+}
+
+}  // namespace bnn

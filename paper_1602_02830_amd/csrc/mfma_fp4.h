@@ -29,6 +29,17 @@ __device__ inline v8i widen_fp4_b(uint32_t w) {
     return f;
 }
 
+// The four fp4 operand registers of a word alone; the MFMA's operand type has eight, of which the fp4 format reads four.
+typedef int v4i __attribute__((ext_vector_type(4)));
+__device__ inline v4i widen4_a(uint32_t w) {
+    return v4i{int(w & 0x11111111u), int(w & 0x22222222u), int(w & 0x44444444u), int((w >> 2) & 0x22222222u)};
+}
+__device__ inline v4i widen4_b(uint32_t w) {
+    const uint32_t r = w >> 2;
+    return v4i{int((w << 2) & 0x44444444u), int(w & 0x22222222u), int(r & 0x11111111u), int(r & 0x22222222u)};
+}
+__device__ inline v8i operand8(v4i f) { return v8i{f[0], f[1], f[2], f[3], 0, 0, 0, 0}; }
+
 __device__ inline int popc4(uint4 v) { return __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w); }
 
 __device__ inline uint32_t quad_word(const uint4& q, int s) { return s == 0 ? q.x : s == 1 ? q.y : s == 2 ? q.z : q.w; }
@@ -245,6 +256,17 @@ __device__ inline void mfma_epilogue_bits(v16f (&acc)[WM][WN], const int* pop_a,
         const int m = row0 + wm * 32 * WM + i * 32 + fr;
         if (m < M && w < nw) bn.out[int64_t(m) * bn.ld_out + w] = words[i];
     }
+}
+
+// 2 x 2 pooling of output words whose windows are four neighbouring lanes (every lane active): OR where the channel's flip
+// bit is 0, AND where it is 1, in all four lanes.
+__device__ inline uint32_t pool_words(uint32_t word, uint32_t flip_word) {
+    uint32_t any = word, all = word;
+    any |= uint32_t(__builtin_amdgcn_update_dpp(0, int(any), 0xB1, 0xF, 0xF, true));      // lane ^ 1
+    all &= uint32_t(__builtin_amdgcn_update_dpp(0, int(all), 0xB1, 0xF, 0xF, true));
+    any |= uint32_t(__builtin_amdgcn_update_dpp(0, int(any), 0x4E, 0xF, 0xF, true));      // lane ^ 2
+    all &= uint32_t(__builtin_amdgcn_update_dpp(0, int(all), 0x4E, 0xF, 0xF, true));
+    return (any & ~flip_word) | (all & flip_word);
 }
 
 }  // namespace bnn

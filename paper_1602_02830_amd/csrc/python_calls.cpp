@@ -41,6 +41,8 @@ struct EntryPoints {
                              const int32_t*, Words, uint32_t*, int64_t, void*);
     int (*conv_pool_bn_sign_pack)(Words, int64_t, int64_t, int64_t, int64_t, Words, int64_t, int64_t, int, int, int, int, int,
                                   const int32_t*, Words, uint32_t*, int64_t, void*);
+    int (*conv_pool_windows_bn_sign_pack)(Words, int64_t, int64_t, int64_t, int64_t, Words, int64_t, int64_t, int, int, int, int, int,
+                                          const int32_t*, Words, uint32_t*, int64_t, void*);
     int (*conv_im2col_pack)(Words, int64_t, int64_t, int64_t, int64_t, int, int, int, int, uint32_t*, int64_t, void*);
     int (*maxpool_bits)(Words, int64_t, int64_t, int64_t, int64_t, int, int, int, Words, uint32_t*, void*);
 };
@@ -311,7 +313,8 @@ PyObject* conv_bn_sign_pack(PyObject* const* a) {
 }
 
 // (x_bits, Cin, w_bits, kh, kw, stride, pad, thr, flip, out, pool)
-PyObject* conv_pool_bn_sign_pack(PyObject* const* a) {
+template <auto EntryPoints::*POOLED>
+PyObject* conv_pool_of(PyObject* const* a) {
     Conv c;
     Matrix out;
     int pool;
@@ -323,10 +326,14 @@ PyObject* conv_pool_bn_sign_pack(PyObject* const* a) {
     const int64_t Ho = dh / c.stride + 1, Wo = dw / c.stride + 1;
     if (out.rows != c.x.B * (Ho / pool) * (Wo / pool) || out.cols != words(c.w.rows)) return long_way();
     return launch(*out.t, [&](void* s) {
-        return entry.conv_pool_bn_sign_pack(c.x.data, c.x.B, c.x.H, c.x.W, c.Cin, c.w.as<uint32_t>(), c.w.ld, c.w.rows, c.kh,
-                                            c.kw, c.stride, c.pad, pool, static_cast<const int32_t*>(thr),
-                                            static_cast<Words>(flip), out.as<uint32_t>(), out.ld, s);
+        return (entry.*POOLED)(c.x.data, c.x.B, c.x.H, c.x.W, c.Cin, c.w.as<uint32_t>(), c.w.ld, c.w.rows, c.kh, c.kw,
+                               c.stride, c.pad, pool, static_cast<const int32_t*>(thr), static_cast<Words>(flip),
+                               out.as<uint32_t>(), out.ld, s);
     });
+}
+PyObject* conv_pool_bn_sign_pack(PyObject* const* a) { return conv_pool_of<&EntryPoints::conv_pool_bn_sign_pack>(a); }
+PyObject* conv_pool_windows_bn_sign_pack(PyObject* const* a) {
+    return conv_pool_of<&EntryPoints::conv_pool_windows_bn_sign_pack>(a);
 }
 
 // (x_bits, Cin, kh, kw, stride, pad, out)
@@ -388,6 +395,7 @@ PyObject* bind(PyObject*, PyObject* args) {
     set(e.conv_xnor, "bnn_conv_xnor");
     set(e.conv_bn_sign_pack, "bnn_conv_bn_sign_pack");
     set(e.conv_pool_bn_sign_pack, "bnn_conv_pool_bn_sign_pack");
+    set(e.conv_pool_windows_bn_sign_pack, "bnn_conv_pool_windows_bn_sign_pack");
     set(e.conv_im2col_pack, "bnn_conv_im2col_pack");
     set(e.maxpool_bits, "bnn_maxpool_bits");
     if (!ok || !PyCallable_Check(stream)) {
@@ -418,6 +426,7 @@ PyMethodDef methods[] = {
     fast<conv_xnor, 8>("conv_xnor"),
     fast<conv_bn_sign_pack, 10>("conv_bn_sign_pack"),
     fast<conv_pool_bn_sign_pack, 11>("conv_pool_bn_sign_pack"),
+    fast<conv_pool_windows_bn_sign_pack, 11>("conv_pool_windows_bn_sign_pack"),
     fast<conv_im2col_pack, 7>("conv_im2col_pack"),
     fast<maxpool_bits, 7>("maxpool_bits"),
     {nullptr, nullptr, 0, nullptr},

@@ -48,19 +48,6 @@ constexpr int ST_ROWS = 256 / kMfmaKQ;             // rows covered by one stagin
 constexpr int LOADS_B = BN / ST_ROWS;              // staging passes of B
 static_assert(BN == BM_MAX && kMfmaKQ == 4, "square large tile, 4 staging lanes per row");
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-// The four fp4 operand registers of a word (see widen_fp4_a / widen_fp4_b); the MFMA's operand type has
-// eight, of which the fp4 format reads four.
-__device__ inline v4i widen4_a(uint32_t w) {
-    return v4i{int(w & 0x11111111u), int(w & 0x22222222u), int(w & 0x44444444u), int((w >> 2) & 0x22222222u)};
-}
-__device__ inline v4i widen4_b(uint32_t w) {
-    const uint32_t r = w >> 2;
-    return v4i{int((w << 2) & 0x44444444u), int(w & 0x22222222u), int(r & 0x11111111u), int(r & 0x22222222u)};
-}
-__device__ inline v8i operand8(v4i f) { return v8i{f[0], f[1], f[2], f[3], 0, 0, 0, 0}; }
-
 __device__ inline uint4 load16_at(const uint32_t* uniform_base, uint32_t lane_byte_offset) {
     return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(uniform_base) + lane_byte_offset);
 }

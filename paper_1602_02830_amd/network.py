@@ -158,20 +158,22 @@ class BinaryConvLayer:
         # Pooled, fused, implicit layers try the one-launch form first; the library refuses geometries whose
         # pooling windows do not fit its tiles (before launching anything), and the layer then keeps to
         # conv -> bnn_maxpool_bits.
+        # Other even maps take its form for any map, which the library refuses likewise.
         self.pool_in_conv = bool(pool) and fused and implicit and self.Ho % pool == 0 and self.Wo % pool == 0
+        self.pool_windows = self.pool_in_conv
 
     def forward(self, x_bits: torch.Tensor) -> torch.Tensor:
         """x_bits: packed NHWC int32 [B][H][W][Cin/32].  Returns packed NHWC [B][Ho][Wo][ceil(Cout/32)]."""
-        if self.pool_in_conv:
-            try:
-                B.conv_pool_bn_sign_pack(x_bits, self.Cin, self.w_bits, self.thr, self.flip, self.kh, self.kw,
-                                         self.stride, self.pad, self.pool,
-                                         out=self.pooled.view(self.B * self.Hp * self.Wp, -1))
-                return self.pooled
-            except B.BnnError as e:
-                if e.status != 3:
-                    raise
-                self.pool_in_conv = False
+        for form, call in (("pool_in_conv", B.conv_pool_bn_sign_pack), ("pool_windows", B.conv_pool_windows_bn_sign_pack)):
+            if getattr(self, form):
+                try:
+                    call(x_bits, self.Cin, self.w_bits, self.thr, self.flip, self.kh, self.kw, self.stride, self.pad,
+                         self.pool, out=self.pooled.view(self.B * self.Hp * self.Wp, -1))
+                    return self.pooled
+                except B.BnnError as e:
+                    if e.status != 3:
+                        raise
+                    setattr(self, form, False)
         if self.implicit:
             try:
                 if self.fused:

@@ -1479,6 +1479,50 @@ def test_conv_pool_layer_refuses_what_does_not_fit_its_tiles():
     assert (out == oracle.pack_bits(a_want.reshape(-1, 128))).all() and not conv.pool_in_conv
 
 
+@pytest.mark.parametrize("shape", [
+    # B, H, W, Cin, Cout, window, stride, pad: the rows of a strip (one per compute unit and column tile) in the comment
+    (90, 12, 10, 128, 500, 3, 1, 1),      # 192 of one tile: one or two blocks of 32 per wavefront
+    (41, 30, 30, 128, 450, 3, 1, 1),      # 608 = 512 + 96: a wavefront without rows in the last tile
+    (130, 30, 30, 128, 500, 3, 1, 1),     # 1856 = 3 x 512 + 320: every patch buffer used twice
+    (60, 32, 30, 256, 385, 3, 1, 1),      # 928, two quads per cell, a column tile of one column
+    (100, 20, 22, 384, 390, 3, 1, 1),     # 704, three quads per cell: one patch buffer
+    (26, 24, 26, 512, 512, 3, 1, 1),      # 256, filters of nine K-tiles
+    (50, 40, 36, 128, 300, 5, 2, 2),      # stride 2
+    (4000, 2, 2, 128, 600, 3, 1, 1),      # images smaller than a block
+    (3, 1030, 34, 128, 64, 3, 1, 1),      # rows far down a tall image
+    (9, 14, 18, 384, 99, 3, 1, 1),        # too few rows for strips: small tiles, pooled in window order
+    (2, 6, 6, 128, 70, 3, 1, 1),
+])
+def test_fused_convolutions_of_any_map_in_strips_and_windows(shape):
+    """The fused layer, and the same layer pooled 2 x 2 in one launch on any even map, against its im2col matrix through the
+    vector-ALU product and the pooling of its output bits: every word."""
+    B, H, W, Cin, Cout, k, stride, pad = shape
+    g = torch.Generator(device=DEV).manual_seed(sum(shape))
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    x, K, nw = words(B, H, W, Cin // 32), k * k * Cin, (Cout + 31) // 32
+    w, flip = words(Cout, K // 32), words(nw)
+    if Cout % 32:
+        flip[-1] &= (1 << Cout % 32) - 1
+    thr = torch.randint(-60, 60, (Cout,), generator=g, device=DEV, dtype=torch.int32)
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    cols = bnn.conv_im2col_pack(x, Cin, k, k, stride, pad)
+    want = bnn.xnor_gemm_bn_sign_pack(cols, w, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    assert torch.equal(bnn.conv_bn_sign_pack(x, Cin, w, thr, flip, k, k, stride, pad), want)
+    pooled = bnn.maxpool_bits(want.view(B, Ho, Wo, nw), Cout, flip, 2, 2, 2).reshape(-1, nw)
+    got = bnn.conv_pool_windows_bn_sign_pack(x, Cin, w, thr, flip, k, k, stride, pad)
+    assert torch.equal(got, pooled)
+
+
+def test_pooled_convolution_of_any_map_refuses_odd_maps_and_partial_quads():
+    thr, flip = torch.zeros(8, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    for (H, W, Cin, pool) in ((7, 6, 128, 2), (6, 7, 128, 2), (6, 6, 96, 2), (6, 6, 128, 3)):
+        x = torch.zeros((2, H, W, Cin // 32), dtype=torch.int32, device=DEV)
+        w = torch.zeros((8, 9 * Cin // 32 + 3 & ~3), dtype=torch.int32, device=DEV)[:, :9 * Cin // 32]
+        with pytest.raises(bnn.BnnError) as e:
+            bnn.conv_pool_windows_bn_sign_pack(x, Cin, w, thr, flip, 3, 3, 1, 1, pool)
+        assert e.value.status == 3, (H, W, Cin, pool)
+
+
 def test_conv_pool_layers_full_batch_every_image():
     """conv -> max pool -> BatchNorm -> Sign at batch 256 with the implicit, fused layer and the pooling
     inside the launch: every output bit of all 256 images."""
