@@ -15,20 +15,26 @@
 // arithmetic, exact modulo 2^32 and therefore exact for every K with 255*K < 2^31: single terms pass 2^31 from K = 2^23 on, so
 // sums of them are formed in unsigned integers.
 //
-// Two organisations:
+// Three organisations:
+//   strips  128 x 512 tiles, WI = 4 x 2 blocks of 32 x 32 for each of 8 wavefronts, walked by one workgroup per compute unit
+//           with all of K of its 512 columns in LDS (large fused products up to K = 1536).
 //   tiles   32*WI*WR x 64*WC outputs per workgroup, WI x 2 blocks of 32 x 32 per wavefront: 128 x 512 with 8 wavefronts
-//           (the large fused products), 64 x 256 with 4, or 64 x 128 with 2 x 2 (few columns).  A's rows are transposed once per workgroup while they are
-//           staged into LDS; B stays bits in LDS and is widened by the wavefront that multiplies it (as bytes it would
-//           double the LDS traffic, which is what holds the plain int8 product at a third of the matrix rate).  The wide,
-//           flat tile keeps both cheap: 4.4 vector operations per MFMA in all on 128 x 512 (a 2 x 2 arrangement of
-//           wavefronts on 128 x 256 needs 8).
+//           (large fused products of longer K), 64 x 256 with 4, or 64 x 128 with 2 x 2 (few columns).  A's rows are transposed
+//           once per workgroup while they are staged into LDS; B stays bits in LDS and is widened by the wavefront that
+//           multiplies it (as bytes it would double the LDS traffic, which is what holds the plain int8 product at a third of
+//           the matrix rate).  The wide, flat tile keeps both cheap: 4.4 vector operations per MFMA in all on 128 x 512 (a 2 x 2
+//           arrangement of wavefronts on 128 x 256 needs 8).
 //   split   32 x 32 outputs per workgroup, K split over its four wavefronts, operands straight from memory into
 //           registers: for small grids, where the tiles above leave most compute units without work.
 //
-// What bounds the tiles: the matrix engine's power.  A workgroup's tile of 128 bits of K (32 MFMAs per wavefront, 1024
-// cycles each way) takes 1.2 us on constant operands or on a quarter of the chip, 1.7 us on random bytes with every
-// compute unit at work: 2.3 POP/s sustained on random pixels, 2.9 on constant ones, whatever the tile shape.
-// 10000 x 4096 x 784 fused: 42 us (85 us plane by plane on the fp4 engine); 100 x 4096 x 784: 5.2 us (22 us).
+// What bounds them.  Tiles: a K-tile of 128 bits (64 MFMAs per SIMD, 2048 cycles) took 3400 - 3700 cycles.  A lane per column
+// loads 16 bytes of every line of B per K-tile, and 512 lines do not stay in the first-level cache until the next one: 64 KB
+// per K-tile through a path of 64 bytes a cycle.  Strips read B once, in whole lines: 2630 cycles, 41 per MFMA.  A loop of these
+// MFMAs alone on random bytes takes 32.6 cycles and 15.0 ns with the bytes as first operand, 17.7 ns as second: the clock
+// falls with the engine's power, 1.85 against 2.2 GHz.  Strips have them first; their accumulators are then columns by lane,
+// and the output words are turned by a 32 x 32 bit transposition over the lanes (16 operations per pair of blocks).
+// 10000 x 4096 x 784 fused: 85 us plane by plane on the fp4 engine, 40 - 43 in tiles, 31 - 35 in strips (K = 1536: 64 and 52);
+// 100 x 4096 x 784: 5.2 us (22 us).
 #include <type_traits>
 
 #include "bit_transpose.h"
@@ -345,6 +351,326 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void bitplane_gemm_kernel(
 }
 
 // ----------------------------------------------------------------------------
+// strips: 128 x 512 tiles of the large fused products, walked by one workgroup per compute unit
+//
+// The N / 512 column tiles times equal strips of rows are at most one workgroup per compute unit (10000 x 4096: 2.5 tiles
+// each, where whole tiles need three rounds).  A K-tile is four steps of 8 MFMAs; the operands of a step are read and widened
+// under the step before, the K-tile two further on is transposed under steps 0 and 1 and stored under step 2, into the third
+// of three buffers, with one barrier in between; the stream of K-tiles runs on across the strip's tiles.  Nothing in a K-tile
+// branches, so that the compiler can keep to the order given (BNN_PLANES_SCHEDULE): partial words are zero bytes of A, whatever
+// B holds there.
+// ----------------------------------------------------------------------------
+constexpr int kStripT = 512, kStripBM = 128, kStripBN = 512, kStripBuffers = 3;
+constexpr int kStripPitchB = kStripBN + 2;     // words per plane of B: 8 lanes' quads of 8 columns fall into 64 different banks
+constexpr int kStripWords = 48;                // K-words of B beside three buffers of A: 96 of 160 KB
+
+struct StripCut {
+    FastDiv by_tiles_n;
+    int tiles_n, per_die;      // column tiles; workgroups / 8
+    int rows;                  // rows per strip, a multiple of 32
+};
+
+// After every product: one LDS read with READ, VALU vector operations, one LDS write with WRITE, one load with LOAD.
+#define BNN_PLANES_SCHEDULE(MFMAS, READ, VALU, WRITE, LOAD)                           \
+    do {                                                                              \
+        _Pragma("unroll") for (int g_ = 0; g_ < (MFMAS); ++g_) {                      \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        \
+            if (READ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);              \
+            if (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);              \
+            __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);                     \
+            if (WRITE) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);             \
+        }                                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                            \
+    } while (0)
+
+__global__ __launch_bounds__(kStripT, 2) void bitplane_gemm_strip_kernel(
+    const uint32_t* __restrict__ Xp, int64_t ldx, const uint32_t* __restrict__ B, int64_t ldb, int M, int N, int K,
+    StripCut cut, BnSignArgs bn) {
+    constexpr int T = kStripT, BM = kStripBM, BN = kStripBN, WI = 4;
+    constexpr int PLANE_A = BM + 1;                        // 16-byte slots, odd (see above)
+    constexpr int A_BUF = 2 * kWordsPerTile * PLANE_A;
+    constexpr int PITCH_B = kStripPitchB;
+    static_assert(T == BN && T == BM * kWordsPerTile, "a thread stages a column of B and a word of A per K-tile");
+    __shared__ uint4 lds_a[kStripBuffers * A_BUF];         // [word][half of its 32 bytes][row]
+    extern __shared__ uint32_t lds_b[];                    // [word][column]: all of K, for the workgroup's life
+    __shared__ __attribute__((aligned(16))) int rowsum_s[2][BM];           // minus the sums of the rows' bytes
+    __shared__ __attribute__((aligned(16))) int colterm_s[BN];
+    __shared__ __attribute__((aligned(16))) int thr_s[BN];
+
+    int logical = int(blockIdx.x);
+    if (logical < kDies * cut.per_die) logical = (logical % kDies) * cut.per_die + logical / kDies;
+    const int group = cut.by_tiles_n(logical), col0 = (logical - group * cut.tiles_n) * BN;
+    const int row_begin = group * cut.rows, row_end = min(M, row_begin + cut.rows);
+
+    const int tid = threadIdx.x, lane = tid & 63, wc = tid >> 6;
+    const int fr = lane & 31, fh = lane >> 5;
+    const int kw = (K + 31) >> 5;
+    const uint32_t tmask = tail_mask(K);
+    const int n_ktiles = (kw + kWordsPerTile - 1) / kWordsPerTile;         // at least 3 (the launcher)
+    const bool short_end = kw - kWordsPerTile * (n_ktiles - 1) <= 2;       // the last K-tile has one pair of words
+
+    const int st_w = tid & 3, st_r = tid >> 2;
+    auto row_at = [&](int row0) __attribute__((always_inline)) { return Xp + int64_t(min(row0 + st_r, row_end - 1)) * ldx; };
+
+    uint4 ra[2];
+    uint32_t bytes[8];
+    int cnt_a = 0;
+    // K-tile kt of the row at p / of B.  Nothing here carries control flow (a branch around loads makes the compiler wait for
+    // them where it ends, and the code between two branches is scheduled by itself): word indices are clamped into the row.
+    auto fetch_a = [&](const uint32_t* p, int kt) __attribute__((always_inline)) {
+        const int w = 8 * min(kWordsPerTile * kt + st_w, kw - 1);
+        ra[0] = load_quad_any(p + w);
+        ra[1] = load_quad_any(p + w + 4);
+    };
+    // Bytes of K-tile kt: x - 128, and 0 past the row's end, whatever B has there.
+    auto take = [&](int kt) __attribute__((always_inline)) {
+        const int w = kWordsPerTile * kt + st_w;
+        const uint32_t mask = w < kw - 1 ? ~0u : w == kw - 1 ? tmask : 0u;
+        const uint32_t p[8] = {ra[0].x, ra[0].y, ra[0].z, ra[0].w, ra[1].x, ra[1].y, ra[1].z, ~ra[1].w};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) bytes[s] = p[s] & mask;
+    };
+    auto store_a = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            lds_a[buf * A_BUF + (2 * st_w + u) * PLANE_A + st_r] =
+                make_uint4(bytes[4 * u], bytes[4 * u + 1], bytes[4 * u + 2], bytes[4 * u + 3]);
+    };
+    // Row sums so far of the K-tile's rows (complete with the last one, two K-tiles before they are read).
+    auto sum_rows = [&](int kt, int parity) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) cnt_a = add_bytes(bytes[s], cnt_a);
+        int c = cnt_a;
+        c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
+        c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
+        rowsum_s[parity][st_r] = -c;
+        cnt_a = kt == n_ktiles - 1 ? 0 : cnt_a;
+    };
+
+    // Start: K-tiles 0 and 1 of the first row tile, and all of B, into LDS; K-tile 2 in flight.  8 lanes take a column's 128
+    // bytes at a time (a lane per column fetched every line of B once per K-tile: 512 lines do not stay in the first-level
+    // cache, and 64 KB per K-tile through it were what the loop waited for).
+    const uint32_t* pa = row_at(row_begin);
+    fetch_a(pa, 0);
+    const uint4 first_a[2] = {ra[0], ra[1]};
+    fetch_a(pa, 1);
+    const int lim = 255 * K + 1;
+    constexpr int COLS = T / 8;                            // columns per pass
+    const int bq = tid & 7, bc = tid >> 3;
+    const int last_quad = kw - kWordsPerTile;              // of a row: the quad at its end (K > 96)
+    constexpr int PASSES = BN / COLS;
+    int th[PASSES], pop[PASSES] = {};
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) th[p] = bn.thr[min(col0 + p * COLS + bc, N - 1)];
+    for (int q = bq; q - bq < (kw + 3) >> 2; q += 8) {     // 32 words of every column at a time
+        uint4 v[PASSES];
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p)
+            v[p] = load_quad_any(B + int64_t(min(col0 + p * COLS + bc, N - 1)) * ldb + min(4 * q, last_quad));
+        if (4 * q < kw) {
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) {
+                const uint4 w = place_row_quad(v[p], q, kw, tmask);
+                pop[p] += __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
+                uint32_t* to = lds_b + 4 * q * PITCH_B + p * COLS + bc;
+                to[0] = w.x;
+                to[PITCH_B] = w.y;
+                to[2 * PITCH_B] = w.z;
+                to[3 * PITCH_B] = w.w;
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int c = p * COLS + bc;
+        int sum = pop[p];
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0xB1, 0xF, 0xF, true);       // lane ^ 1
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x4E, 0xF, 0xF, true);       // lane ^ 2
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x141, 0xF, 0xF, true);      // the other four of eight
+        const int thr = max(-lim, min(lim, th[p]));
+        if (bq == 0) {
+            colterm_s[c] = int(256u * uint32_t(sum) - uint32_t(K <= kSignMaxK ? thr : 0));
+            thr_s[c] = thr;
+        }
+    }
+    {
+        const uint4 second_a[2] = {ra[0], ra[1]};
+        ra[0] = first_a[0]; ra[1] = first_a[1];
+        take(0);
+        transpose_bits_8x8(bytes);
+        store_a(0);
+        sum_rows(0, 0);
+        ra[0] = second_a[0]; ra[1] = second_a[1];
+        take(1);
+        transpose_bits_8x8(bytes);
+        store_a(1);
+        sum_rows(1, 0);
+    }
+    fetch_a(pa, 2);
+    __syncthreads();
+
+    // This lane's output word: column block 2 * wc + fh.
+    const int64_t nw = (int64_t(N) + 31) >> 5, word = (int64_t(col0) >> 5) + 2 * wc + fh;
+    const int64_t cols_left = N - 32 * word;
+    const uint32_t live = cols_left >= 32 ? ~0u : cols_left <= 0 ? 0u : ((1u << cols_left) - 1u);
+    const uint32_t flip = bn.flip_bits[word < nw ? word : nw - 1] & live;
+
+    v16i acc[WI][2];
+    int buf = 0;                                           // LDS buffer of the K-tile that is multiplied
+    // Step s = 2t + u of a K-tile: lane half fh takes word 2t + fh, half u of its 32 bytes.
+    v4i fa[WI], ga[WI], fb[2], gb[2];
+    uint32_t wb[2];
+    const uint4* rd_a = lds_a + 2 * fh * PLANE_A + fr;
+    const uint32_t* rd_b = lds_b + fh * PITCH_B + wc * 64 + fr;
+    auto run = [&](auto nb_tag, int row0, int parity) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb_tag)::value;
+        auto read_a = [&](int b, int s, v4i (&f)[WI]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const uint4 q = rd_a[b * A_BUF + (4 * (s >> 1) + (s & 1)) * PLANE_A + i * 32];
+                f[i] = v4i{int(q.x), int(q.y), int(q.z), int(q.w)};
+            }
+        };
+        auto read_b = [&](int kt, int t) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) wb[j] = rd_b[(kWordsPerTile * kt + 2 * t) * PITCH_B + j * 32];
+        };
+        auto multiply = [&](const v4i (&a)[WI], const v4i (&b)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+        };
+        const uint32_t* pa_next = row_at(min(row0 + BM, row_end - 1));     // past the strip: rows that nothing reads
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+        // The operands of a step are read and widened during the step before.
+        read_a(buf, 0, fa);
+        read_b(0, 0);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j] = widen_bits<0>(wb[j]);
+        constexpr int P = 2 * NB;                          // products per step
+        auto k_tile = [&](int kt, auto pair_tag) __attribute__((always_inline)) {
+            constexpr bool ONE_PAIR = decltype(pair_tag)::value;
+            const int buf1 = buf == kStripBuffers - 1 ? 0 : buf + 1, buf2 = buf1 == kStripBuffers - 1 ? 0 : buf1 + 1;
+            // K-tile that is staged (in registers; its row tile's parity), and the one that is loaded.
+            const bool over = kt + 2 >= n_ktiles, over3 = kt + 3 >= n_ktiles;
+            const int s_kt = over ? kt + 2 - n_ktiles : kt + 2, f_kt = over3 ? kt + 3 - n_ktiles : kt + 3;
+            const uint32_t* f_row = over3 ? pa_next : pa;
+            __builtin_amdgcn_sched_barrier(0);
+            // step 0
+            read_a(buf, 1, ga);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) gb[j] = widen_bits<1>(wb[j]);
+            take(s_kt);
+            exchange_fields<4, 0x0F0F0F0Fu>(bytes);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(bytes[s]));
+            multiply(fa, fb);
+            BNN_PLANES_SCHEDULE(P, 1, (16 + 30 + P - 1) / P, 0, 0);
+            // step 1
+            if constexpr (!ONE_PAIR) {
+                read_a(buf, 2, fa);
+                read_b(kt, 1);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[j] = widen_bits<0>(wb[j]);
+            }
+            fetch_a(f_row, f_kt);
+            exchange_fields<2, 0x33333333u>(bytes);
+            exchange_fields<1, 0x55555555u>(bytes);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(bytes[s]));
+            if constexpr (!ONE_PAIR) {
+                multiply(ga, gb);
+                BNN_PLANES_SCHEDULE(P, 1, (16 + 36 + P - 1) / P, 0, 1);
+            }
+            // Every wavefront has left the K-tile before, whose buffer is written now, and has written the next one's.
+            __syncthreads();
+            // step 2
+            if constexpr (!ONE_PAIR) {
+                read_a(buf, 3, ga);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) gb[j] = widen_bits<1>(wb[j]);
+            }
+            store_a(buf2);
+            sum_rows(s_kt, over ? parity ^ 1 : parity);
+            if constexpr (!ONE_PAIR) {
+                multiply(fa, fb);
+                BNN_PLANES_SCHEDULE(P, 1, (16 + 14 + P - 1) / P, 1, 0);
+            }
+            // step 3, under which the next K-tile's (or row tile's) first operands are read
+            read_a(buf1, 0, fa);
+            read_b(kt + 1 == n_ktiles ? 0 : kt + 1, 0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) fb[j] = widen_bits<0>(wb[j]);
+            multiply(ga, gb);
+            BNN_PLANES_SCHEDULE(P, 1, (16 + 4 + P - 1) / P, 0, 0);
+            buf = buf1;
+        };
+        const int whole = n_ktiles - (short_end ? 1 : 0);
+        for (int kt = 0; kt < whole; ++kt) k_tile(kt, std::false_type{});
+        if (short_end) k_tile(n_ktiles - 1, std::true_type{});
+        pa = pa_next;
+
+        // Register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.  The output bit is the complement of the sign of
+        // result - threshold: an add of three, and an alignbit that shifts the sign into the lane's word of rows.
+        auto collect = [&](auto sign_tag) __attribute__((always_inline)) {
+            constexpr bool SIGN = decltype(sign_tag)::value;
+            int ct[2], th[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                ct[j] = int(uint32_t(colterm_s[(wc * 2 + j) * 32 + fr]) - 128u * uint32_t(K));      // (sum x = the bytes' sum + 128 K)
+                th[j] = thr_s[(wc * 2 + j) * 32 + fr];
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                int4 rs[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) rs[g] = *reinterpret_cast<const int4*>(&rowsum_s[parity][i * 32 + 8 * g + 4 * fh]);
+                uint32_t part[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    uint32_t neg = 0u;
+#pragma unroll
+                    for (int g = 3; g >= 0; --g) {
+#pragma unroll
+                        for (int e = 3; e >= 0; --e) {
+                            const int r = e == 0 ? rs[g].x : e == 1 ? rs[g].y : e == 2 ? rs[g].z : rs[g].w;
+                            int d = int(uint32_t(acc[i][j][4 * g + e]) + uint32_t(ct[j]) + uint32_t(r));
+                            if (!SIGN) d = d >= th[j] ? 0 : -1;
+                            neg = __builtin_amdgcn_alignbit(neg, uint32_t(d), 31);
+                        }
+                        if (g > 0) neg <<= 4;
+                    }
+                    part[j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
+                }
+                // One v_permlane32_swap brings the two lane halves' nibbles together: lane l holds the rows of column l % 32
+                // of block l / 32, and after the transposition the columns of row l % 32.
+                const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
+                const uint32_t bits = transpose_bits_32_lanes(sw[0] | sw[1]);
+                const int m = row0 + i * 32 + fr;
+                if (m < row_end && word < nw) bn.out[int64_t(m) * bn.ld_out + word] = (bits & live) ^ flip;
+            }
+        };
+        if (K <= kSignMaxK) collect(std::true_type{});
+        else collect(std::false_type{});
+    };
+
+    int parity = 0;
+    for (int row0 = row_begin; row0 < row_end; row0 += BM, parity ^= 1) {
+        const int blocks = (min(BM, row_end - row0) + 31) / 32;
+        if (blocks == 4) run(std::integral_constant<int, 4>{}, row0, parity);
+        else if (blocks == 3) run(std::integral_constant<int, 3>{}, row0, parity);
+        else if (blocks == 2) run(std::integral_constant<int, 2>{}, row0, parity);
+        else run(std::integral_constant<int, 1>{}, row0, parity);
+    }
+}
+
+// ----------------------------------------------------------------------------
 // split: 32 x 32 outputs, K split over the wavefronts
 // ----------------------------------------------------------------------------
 constexpr int kSplitWaves = 4;
@@ -495,10 +821,14 @@ static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int6
 //  - 64 x 128 up to 128 columns, which wider tiles would multiply as 256 or 512: 262144 x 128 x 27 12.6 vs 19.7 on 64 x 256
 //    and 35.6 on 128 x 512, 262144 x 128 x 147 17.7 vs 24.5 and 49.3, 1000000 x 32 x 75 43.6 vs 75 and 151.  With 129 columns
 //    and more the 64 x 256 tile is level or better (100000 x 300 x 200 20.8 vs 21.3, 40000 x 640 x 784 36.7 vs 33.5).
+//  - strips with at most a quarter of columns that do not exist, strips of more than one tile, at least three K-tiles (the
+//    stream runs three ahead) and K that fits LDS beside A: 10000 x 4096 x 784 43.0 on 128 x 512 tiles and 35.1, x 1536 65.6 and
+//    53.8, 16384 x 4096 x 784 57.1 and 49.2, 6000 x 4096 x 784 26.3 and 23.9, 5000 x 4096 x 784 (160 rows) 23.3 and 21.9, 8192 x 4096
+//    x 300 17.2 and 16.4; but of one tile, 4000 x 4096 x 784 (128 rows, one round of tiles) 15.4 and 16.3.
 //  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5 with at most a quarter of columns that do
-//    not exist, and K > 96: 4000 x 4096 x 784 21.5 vs 24.3 on 64 x 256, 10000 x 4096 x 784 51.5 vs 52.9 (K = 4096: 173 vs
-//    194); but 6000 x 4096 (1.47 rounds) 34.8 vs 32.9, 262144 x 256 x 147 (half of the columns) 50.4 vs 25.2, 10000 x 4096 x
-//    64 (one K-tile) 15.3 vs 13.7.  Its int32 form does not fit the registers.
+//    not exist, and K > 256 or one round: 4000 x 4096 x 784 21.5 vs 24.3 on 64 x 256; but 262144 x 256 x 147 (half of the columns)
+//    50.4 vs 25.2, 10000 x 4096 x 129 18.9 vs 15.9, 4096 x 4096 x 160 (one round) 7.1 vs 7.6.  Its int32 form does not fit the
+//    registers.
 //  - 64 x 256 (four workgroups per compute unit) otherwise: 2000 x 4096 x 784 15.4 vs 18.0, 3280 x 1152 x 2394 30 vs 39.
 constexpr int64_t kSplitMaxTiles = 1024;
 constexpr int64_t kComputeUnits = 256;
@@ -516,9 +846,20 @@ static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int
     }
     if (N <= 128) return launch_tiles<1, 2, 2, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
     if constexpr (FUSED && !TINY) {
-        const int64_t tiles_n = ceil_div(N, 512), tiles = ceil_div(M, 128) * tiles_n;
-        const int64_t rounds = ceil_div(tiles, kComputeUnits);
-        if (5 * tiles >= 4 * rounds * kComputeUnits && 4 * N >= 3 * 512 * tiles_n)
+        const int64_t tiles_n = ceil_div(N, planes::kStripBN);
+        const bool wide = 4 * N >= 3 * planes::kStripBN * tiles_n;           // at most a quarter of columns that do not exist
+        if (wide && tiles_n <= kComputeUnits && K > 256 && K <= 32 * planes::kStripWords) {
+            const int64_t rows = ceil_div(ceil_div(M, kComputeUnits / tiles_n), 32) * 32, groups = ceil_div(M, rows);
+            if (rows > planes::kStripBM) {
+                const planes::StripCut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
+                hipLaunchKernelGGL(planes::bitplane_gemm_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(planes::kStripT),
+                                   size_t(4) * planes::kStripPitchB * (4 * ceil_div(K, 128)), s, Xp, ldx, B, ldb, int(M), int(N),
+                                   int(K), cut, bn);
+                return check_launch();
+            }
+        }
+        const int64_t tiles = ceil_div(M, 128) * tiles_n, rounds = ceil_div(tiles, kComputeUnits);
+        if ((K > 256 || rounds == 1) && 5 * tiles >= 4 * rounds * kComputeUnits && wide)
             return launch_tiles<4, 1, 8, true, false>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);
     }
     return launch_tiles<2, 1, 4, FUSED, TINY>(Xp, ldx, B, ldb, C, ldc, M, N, K, bn, s);

@@ -1479,6 +1479,39 @@ def test_conv_pool_layer_refuses_what_does_not_fit_its_tiles():
     assert (out == oracle.pack_bits(a_want.reshape(-1, 128))).all() and not conv.pool_in_conv
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (2070, 8192, 784),       # strips of 160 rows: 128 + 32, a last K-tile of one word
+    (2400, 8192, 257),       # three K-tiles, the last of one bit
+    (2500, 7930, 384),       # 160: K of whole K-tiles, columns that do not exist
+    (3300, 8192, 448),       # 224 = 128 + 96, a last K-tile of two words
+    (3000, 8150, 470),       # 192, of three words
+    (6170, 8192, 1000),      # 416 = 3 x 128 + 32: every buffer and both sets of row sums reused
+    (4200, 4096, 1536),      # the longest K
+    (2049, 8192, 800),       # rows past the matrix in the last strip
+])
+@pytest.mark.parametrize("bytes_", ["random", "extreme"])
+def test_first_layer_on_bytes_in_strips(M, N, K, bytes_):
+    """The fused 8-bit layer against the int32 product (other kernels) and the thresholds applied to it, every word."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    x = torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8)
+    if bytes_ == "extreme":
+        x = torch.where(x < 128, 0, 255).to(torch.uint8)
+        x[::3] = 255
+        x[1::7] = 0
+    kw, nw = (K + 31) // 32, (N + 31) // 32
+    w, flip = words(N, kw), words(nw)
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    w[::5] = -1                                            # whole rows of +1: the largest sums, pad bits set
+    w[1::5] = 0
+    thr = torch.randint(-4000, 4000, (N,), generator=g, device=DEV, dtype=torch.int32)
+    thr[::11], thr[5::11] = 2 ** 31 - 1, -2 ** 31          # no sum and every sum
+    planes = bnn.pack_bitplanes(x)
+    sums = bnn.bitplane_gemm(planes, w, K)
+    assert torch.equal(bnn.bitplane_gemm_bn_sign_pack(planes, w, K, thr, flip), bnn.bn_sign_pack(sums, thr, flip))
+
+
 @pytest.mark.parametrize("shape", [
     # B, H, W, Cin, Cout, window, stride, pad: the rows of a strip (one per compute unit and column tile) in the comment
     (90, 12, 10, 128, 500, 3, 1, 1),      # 192 of one tile: one or two blocks of 32 per wavefront
