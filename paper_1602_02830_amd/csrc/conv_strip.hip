@@ -162,14 +162,6 @@ __device__ __forceinline__ void load_rest(const PatchGeom& pg, const ConvArgs& c
     }
 }
 
-// Integers n / 8 of at most 16 bits as two bf16 numbers: the upper eight bits and the rest, both exact.
-typedef short v4s __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void split_bf16(float v, short& hi, short& lo) {
-    const uint32_t top = __float_as_uint(v) & 0xFFFF0000u;
-    hi = short(top >> 16);
-    lo = short(__float_as_uint(v - __uint_as_float(top)) >> 16);
-}
-
 // C: quads per cell and load of the first patch.
 template <bool POOL, int RES, int C>
 __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(

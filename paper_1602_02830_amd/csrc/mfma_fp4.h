@@ -269,4 +269,12 @@ __device__ inline uint32_t pool_words(uint32_t word, uint32_t flip_word) {
     return (any & ~flip_word) | (all & flip_word);
 }
 
+// Integers n / 8 of at most 16 bits as two bf16 numbers: the upper eight bits and the rest, both exact.
+typedef short v4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void split_bf16(float v, short& hi, short& lo) {
+    const uint32_t top = __float_as_uint(v) & 0xFFFF0000u;
+    hi = short(top >> 16);
+    lo = short(__float_as_uint(v - __uint_as_float(top)) >> 16);
+}
+
 }  // namespace bnn

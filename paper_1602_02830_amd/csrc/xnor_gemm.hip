@@ -391,6 +391,9 @@ int launch_xnor_gemm_mfma_shortk(const uint32_t* A, int64_t lda, const uint32_t*
                                  int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream);
 int launch_xnor_gemm_mfma_shortk_fused(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M,
                                        int64_t N, int64_t K, BnSignArgs bn, void* stream);
+// Short rows on grids that fill the chip (xnor_gemm_mfma_strip.hip): BNN_ERR_UNSUPPORTED, with nothing launched, for others.
+int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                                const BnSignArgs& bn, void* stream);
 // First layer on 8-bit inputs (bitplane_gemm.hip).
 int launch_bitplane_gemm(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                          int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn, void* stream);
@@ -612,6 +615,10 @@ static int xnor_gemm_bn_sign_pack_dispatch(const uint32_t* A, int64_t lda, const
     hipStream_t s = static_cast<hipStream_t>(stream);
     const BnSignArgs bn{thr, flip_bits, out, ld_out};
     if (kernel_id == KERNEL_MFMA_SPLITK && !(K % 128 == 0 && aligned_rows)) return BNN_ERR_UNSUPPORTED;
+    if (kernel_id == KERNEL_AUTO && !(mfma_splitk_supports(M, N, K) && mfma_splitk_prefers(M, N, K, true))) {
+        const int st = launch_xnor_gemm_mfma_strip(A, lda, B, ldb, M, N, K, bn, stream);
+        if (st != BNN_ERR_UNSUPPORTED) return st;
+    }
     if (kernel_id == KERNEL_AUTO)
         kernel_id = choose_kernel(M, N, K, /*fused=*/true, mfma_shortk_supports(K),
                                   mfma_persist_supports(A, lda, B, ldb, 0, M, N, K, true, false),

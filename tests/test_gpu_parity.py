@@ -1480,6 +1480,32 @@ def test_conv_pool_layer_refuses_what_does_not_fit_its_tiles():
 
 
 @pytest.mark.parametrize("M,N,K", [
+    (638, 8192, 577),        # strips of 160 rows, a K of one bit in its last word and quad
+    (1000, 8100, 640),       # 256, whole quads, columns that do not exist
+    (1500, 8192, 784),       # 384, a last quad of one word
+    (2047, 8192, 1024),      # 512, the longest K, a row less than the strips hold
+    (4500, 8192, 785),       # 1152 = 512 + 512 + 128, both buffers
+    (4097, 8160, 896),       # 1056 = 2 x 512 + 32: three wavefronts without rows in the last tile
+    (8300, 8192, 600),       # 2080 = 4 x 512 + 32
+])
+@pytest.mark.parametrize("tight", [False, True])
+def test_fused_products_of_short_rows_in_strips(M, N, K, tight):
+    """Against the vector-ALU tiles, every word; rows padded to 16 bytes (with set bits in the padding) and not."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    kw, nw = (K + 31) // 32, (N + 31) // 32
+    ld = kw if tight else kw + 3 & ~3
+    a, w, flip = words(M, ld)[:, :kw], words(N, ld)[:, :kw], words(nw)
+    a[::7], w[::5] = -1, -1
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    thr = torch.randint(-50, 50, (N,), generator=g, device=DEV, dtype=torch.int32)
+    thr[::11], thr[5::11] = 2 ** 31 - 1, -2 ** 31          # no sum and every sum
+    want = bnn.xnor_gemm_bn_sign_pack(a, w, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    assert torch.equal(bnn.xnor_gemm_bn_sign_pack(a, w, K, thr, flip), want)
+
+
+@pytest.mark.parametrize("M,N,K", [
     (2070, 8192, 784),       # strips of 160 rows: 128 + 32, a last K-tile of one word
     (2400, 8192, 257),       # three K-tiles, the last of one bit
     (2500, 7930, 384),       # 160: K of whole K-tiles, columns that do not exist
