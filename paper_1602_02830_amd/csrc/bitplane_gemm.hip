@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kStripT, 2) void bitplane_gemm_strip_kernel(
     extern __shared__ uint32_t lds_b[];                    // [word][column]: all of K, for the workgroup's life
     __shared__ __attribute__((aligned(16))) int rowsum_s[2][BM];           // minus the sums of the rows' bytes
     __shared__ __attribute__((aligned(16))) int colterm_s[BN];
-    __shared__ __attribute__((aligned(16))) int thr_s[BN];
+    static_assert(32 * kStripWords <= kSignMaxK, "the difference of a result and a clamped threshold fits int32");
 
     int logical = int(blockIdx.x);
     if (logical < kDies * cut.per_die) logical = (logical % kDies) * cut.per_die + logical / kDies;
@@ -489,8 +489,7 @@ __global__ __launch_bounds__(kStripT, 2) void bitplane_gemm_strip_kernel(
         sum += __builtin_amdgcn_update_dpp(0, sum, 0x141, 0xF, 0xF, true);      // the other four of eight
         const int thr = max(-lim, min(lim, th[p]));
         if (bq == 0) {
-            colterm_s[c] = int(256u * uint32_t(sum) - uint32_t(K <= kSignMaxK ? thr : 0));
-            thr_s[c] = thr;
+            colterm_s[c] = int(256u * uint32_t(sum) - uint32_t(thr));
         }
     }
     {
@@ -618,46 +617,38 @@ __global__ __launch_bounds__(kStripT, 2) void bitplane_gemm_strip_kernel(
 
         // Register v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.  The output bit is the complement of the sign of
         // result - threshold: an add of three, and an alignbit that shifts the sign into the lane's word of rows.
-        auto collect = [&](auto sign_tag) __attribute__((always_inline)) {
-            constexpr bool SIGN = decltype(sign_tag)::value;
-            int ct[2], th[2];
+        int ct[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            ct[j] = int(uint32_t(colterm_s[(wc * 2 + j) * 32 + fr]) - 128u * uint32_t(K));      // (sum x = the bytes' sum + 128 K)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            int4 rs[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) rs[g] = *reinterpret_cast<const int4*>(&rowsum_s[parity][i * 32 + 8 * g + 4 * fh]);
+            uint32_t part[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                ct[j] = int(uint32_t(colterm_s[(wc * 2 + j) * 32 + fr]) - 128u * uint32_t(K));      // (sum x = the bytes' sum + 128 K)
-                th[j] = thr_s[(wc * 2 + j) * 32 + fr];
-            }
+                uint32_t neg = 0u;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                int4 rs[4];
+                for (int g = 3; g >= 0; --g) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) rs[g] = *reinterpret_cast<const int4*>(&rowsum_s[parity][i * 32 + 8 * g + 4 * fh]);
-                uint32_t part[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    uint32_t neg = 0u;
-#pragma unroll
-                    for (int g = 3; g >= 0; --g) {
-#pragma unroll
-                        for (int e = 3; e >= 0; --e) {
-                            const int r = e == 0 ? rs[g].x : e == 1 ? rs[g].y : e == 2 ? rs[g].z : rs[g].w;
-                            int d = int(uint32_t(acc[i][j][4 * g + e]) + uint32_t(ct[j]) + uint32_t(r));
-                            if (!SIGN) d = d >= th[j] ? 0 : -1;
-                            neg = __builtin_amdgcn_alignbit(neg, uint32_t(d), 31);
-                        }
-                        if (g > 0) neg <<= 4;
+                    for (int e = 3; e >= 0; --e) {
+                        const int r = e == 0 ? rs[g].x : e == 1 ? rs[g].y : e == 2 ? rs[g].z : rs[g].w;
+                        const uint32_t d = uint32_t(acc[i][j][4 * g + e]) + uint32_t(ct[j]) + uint32_t(r);
+                        neg = __builtin_amdgcn_alignbit(neg, d, 31);
                     }
-                    part[j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
+                    if (g > 0) neg <<= 4;
                 }
-                // One v_permlane32_swap brings the two lane halves' nibbles together: lane l holds the rows of column l % 32
-                // of block l / 32, and after the transposition the columns of row l % 32.
-                const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
-                const uint32_t bits = transpose_bits_32_lanes(sw[0] | sw[1]);
-                const int m = row0 + i * 32 + fr;
-                if (m < row_end && word < nw) bn.out[int64_t(m) * bn.ld_out + word] = (bits & live) ^ flip;
+                part[j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
             }
-        };
-        if (K <= kSignMaxK) collect(std::true_type{});
-        else collect(std::false_type{});
+            // One v_permlane32_swap brings the two lane halves' nibbles together: lane l holds the rows of column l % 32
+            // of block l / 32, and after the transposition the columns of row l % 32.
+            const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
+            const uint32_t bits = transpose_bits_32_lanes(sw[0] | sw[1]);
+            const int m = row0 + i * 32 + fr;
+            if (m < row_end && word < nw) bn.out[int64_t(m) * bn.ld_out + word] = (bits & live) ^ flip;
+        }
     };
 
     int parity = 0;
