@@ -40,6 +40,7 @@
 #include "bit_transpose.h"
 #include "bnn_internal.h"
 #include "gemm_staging.h"
+#include "strip_cut.h"
 
 namespace bnn {
 namespace planes {
@@ -400,7 +401,8 @@ __global__ __launch_bounds__(kStripT, 2) void bitplane_gemm_strip_kernel(
     int logical = int(blockIdx.x);
     if (logical < kDies * cut.per_die) logical = (logical % kDies) * cut.per_die + logical / kDies;
     const int group = cut.by_tiles_n(logical), col0 = (logical - group * cut.tiles_n) * BN;
-    const int row_begin = group * cut.rows, row_end = min(M, row_begin + cut.rows);
+    const StripRows strip = strip_rows(group, cut.rows, M);
+    const int row_begin = strip.begin, row_end = strip.end;
 
     const int tid = threadIdx.x, lane = tid & 63, wc = tid >> 6;
     const int fr = lane & 31, fh = lane >> 5;
@@ -839,8 +841,9 @@ static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int
     if constexpr (FUSED && !TINY) {
         const int64_t tiles_n = ceil_div(N, planes::kStripBN);
         const bool wide = 4 * N >= 3 * planes::kStripBN * tiles_n;           // at most a quarter of columns that do not exist
-        if (wide && tiles_n <= kComputeUnits && K > 256 && K <= 32 * planes::kStripWords) {
-            const int64_t rows = ceil_div(ceil_div(M, kComputeUnits / tiles_n), 32) * 32, groups = ceil_div(M, rows);
+        if (wide && tiles_n <= kStripUnits && K > 256 && K <= 32 * planes::kStripWords) {
+            const StripPlan plan = strip_plan(M, tiles_n);
+            const int64_t rows = plan.rows, groups = plan.groups;
             if (rows > planes::kStripBM) {
                 const planes::StripCut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
                 hipLaunchKernelGGL(planes::bitplane_gemm_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(planes::kStripT),

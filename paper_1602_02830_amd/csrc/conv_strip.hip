@@ -31,6 +31,7 @@
 #include "conv_patch_geometry.h"
 #include "gemm_staging.h"
 #include "mfma_fp4.h"
+#include "strip_cut.h"
 
 namespace bnn {
 namespace strip {
@@ -183,7 +184,8 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     int logical = int(blockIdx.x);
     if (logical < 8 * cut.per_die) logical = (logical & 7) * cut.per_die + (logical >> 3);
     const int group = cut.by_tiles_n(logical), col0 = (logical - group * cut.tiles_n) * BN;
-    const int row_begin = group * cut.rows, row_end = min(M, row_begin + cut.rows);
+    const StripRows strip = strip_rows(group, cut.rows, M);
+    const int row_begin = strip.begin, row_end = strip.end;
 
     // ---- filters: every load of the start is in flight before the first one is waited for -----------------
     const int st_q = tid & 3, st_r = tid >> 2;
@@ -478,7 +480,6 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
 
 constexpr int kStripResident = 5, kStripResidentMost = 9;     // K-tiles of 512 bits of the resident filters
 constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, beside what the kernel declares itself
-constexpr int64_t kStripUnits = 256;                          // compute units
 // Strips of more than 128 rows, a block row for each of the four wavefronts along the pixels and more.  us, conv_patch.hip and
 // strips: 192 rows 48 of 32 x 32, 128 -> 128 7.8 and 6.8, 96 of 16 x 16, 256 -> 256 11.3 and 9.0, 160 of 8 x 8, 512 -> 512 (160
 // rows) 18.2 and 14.6; with 128 rows 64 of 16 x 16, 256 -> 256 8.65 and 8.6, 128 -> 256 6.5 and 6.7.  Windows that do not overlap
@@ -497,7 +498,8 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     const int n_images = int(M / (int64_t(cv.Ho) * cv.Wo));
     PatchGeom pg;
     Cut cut;
-    const int64_t rows = ceil_div(ceil_div(M, kStripUnits / tiles_n), 32) * 32, groups = ceil_div(M, rows);
+    const StripPlan plan = strip_plan(M, tiles_n);
+    const int64_t rows = plan.rows, groups = plan.groups;
     if (rows < kStripMinRows || (cv.kh <= cv.stride && cv.kw <= cv.stride)) return BNN_ERR_UNSUPPORTED;
     if (pool) cv = pooled_units(cv);
     // Tiles start at multiples of the strips' rows, and 512 pixels further on.

@@ -15,6 +15,7 @@
 #include "bnn_internal.h"
 #include "gemm_staging.h"
 #include "mfma_fp4.h"
+#include "strip_cut.h"
 
 namespace bnn {
 namespace row_strip {
@@ -62,7 +63,8 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     int logical = int(blockIdx.x);
     if (logical < kDies * cut.per_die) logical = (logical % kDies) * cut.per_die + logical / kDies;
     const int group = cut.by_tiles_n(logical), col0 = (logical - group * cut.tiles_n) * BN;
-    const int row_begin = group * cut.rows, row_end = min(M, row_begin + cut.rows);
+    const StripRows strip = strip_rows(group, cut.rows, M);
+    const int row_begin = strip.begin, row_end = strip.end;
 
     // Lane q of 8 takes quad q of a row (lanes past the row's end the last one again, which they do not store).
     const int st_q = tid & 7, st_r = tid >> 3;
@@ -244,7 +246,6 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 
 }  // namespace row_strip
 
-constexpr int64_t kRowStripUnits = 256;                // compute units
 // Strips of more than one block row per wavefront; K from 577 on (shorter rows have kernels 6 and 7, chosen by alignment); at most
 // an eighth of columns that do not exist (16384 x 300 x 900 6.4 us before, 6.7 in strips); strips of one tile, or of two
 // tiles and more whose two buffers are refilled under K loops of at most 7 quads: 5000 x 4096 x 784 (640 rows, the second tile of one
@@ -257,8 +258,9 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
                                 const BnSignArgs& bn, void* stream) {
     using namespace row_strip;
     const int64_t tiles_n = ceil_div(N, BN);
-    if (K <= 576 || K > 128 * MAX_QUADS || tiles_n > kRowStripUnits || 8 * N < 7 * BN * tiles_n) return BNN_ERR_UNSUPPORTED;
-    const int64_t rows = ceil_div(ceil_div(M, kRowStripUnits / tiles_n), 32) * 32, groups = ceil_div(M, rows);
+    if (K <= 576 || K > 128 * MAX_QUADS || tiles_n > kStripUnits || 8 * N < 7 * BN * tiles_n) return BNN_ERR_UNSUPPORTED;
+    const StripPlan plan = strip_plan(M, tiles_n);
+    const int64_t rows = plan.rows, groups = plan.groups;
     if (rows < kRowStripMinRows || (rows <= BM / 2 && K > 832) || (rows > BM && (rows < 2 * BM || K > 128 * (MAX_QUADS - 1)))) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
     const int64_t kq = ceil_div(K, 128);

@@ -1,0 +1,72 @@
+"""CPU-only tests of how the strip kernels cut an output (csrc/strip_cut.h): the function that gives a workgroup its rows, built by
+the host compiler with every signed overflow an error, and the launches of the entry points at the sizes where the strips' ends lie
+beyond 2^31."""
+import os
+import subprocess
+
+import pytest
+
+from test_launch_limits import A, B, FLIP, OUT, THR, WB, launches_of  # noqa: F401
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1602_02830_amd", "csrc")
+
+COVER = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#define __host__
+#define __device__
+#include "strip_cut.h"
+int main(int argc, char** argv) {                   /* M tiles_n ...: the strips of each, in order, cover [0, M) */
+    for (int a = 1; a + 1 < argc; a += 2) {
+        const int64_t M = atoll(argv[a]), tiles_n = atoll(argv[a + 1]);
+        const bnn::StripPlan plan = bnn::strip_plan(M, tiles_n);
+        if (plan.groups * tiles_n > bnn::kStripUnits || plan.rows % bnn::kStripStep != 0 || plan.rows > M + 31) return 1;
+        int64_t next = 0;
+        for (int group = 0; group < int(plan.groups); ++group) {
+            const bnn::StripRows r = bnn::strip_rows(group, int(plan.rows), int(M));
+            if (r.begin != next || r.end <= r.begin || r.end - r.begin > plan.rows || r.end > M) {
+                fprintf(stderr, "M %lld, %lld column tiles: strip %d is [%d, %d)\n", (long long)M, (long long)tiles_n, group, r.begin, r.end);
+                return 2;
+            }
+            next = r.end;
+        }
+        if (next != M) return 3;
+    }
+    return 0;
+}
+"""
+
+# The last strip's unclamped end reaches 2^31 from here on.
+PAST_INT = {1: 2147475457, 2: 2147479553, 4: 2147481601}
+LARGEST = 2 ** 31 - 1025
+
+
+@pytest.fixture(scope="module")
+def cover(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("strips")
+    src, exe = folder / "cover.cpp", folder / "cover"
+    src.write_text(COVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}", str(src),
+                    "-o", str(exe)], check=True)
+    return lambda sizes: subprocess.run([str(exe), *(str(v) for pair in sizes for v in pair)], stderr=subprocess.PIPE, text=True)
+
+
+def test_strips_cover_the_rows_of_every_size(cover):
+    sizes = [(M + d, t) for t, M in PAST_INT.items() for d in (-1, 0, 1)] + [(LARGEST, t) for t in (1, 2, 3, 4, 52, 129, 256)]
+    sizes += [(M, t) for M in (1, 31, 32, 33, 8191, 8192, 8193, 40960, 100001) for t in (1, 3, 8, 31, 128, 129, 255, 256)]
+    r = cover(sizes)
+    assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("tiles_n,M", sorted(PAST_INT.items()) + [(t, LARGEST) for t in PAST_INT])
+def test_strip_kernels_take_rows_up_to_the_limit(launches_of, tiles_n, M):  # noqa: F811
+    """One workgroup of 512 threads per strip and column tile: a convolution of 2 x 2 maps (window 3 x 3, padding 2, 16 outputs an
+    image), the same with its pooling, and a fused layer of K = 600 (whose call refuses four column tiles of that many rows)."""
+    N, K = 128 * tiles_n, 600
+    images = min(-(-M // 16), LARGEST // 16)
+    conv = (A, images, 2, 2, 128, WB, 36, N, 3, 3, 1, 2)
+    runs = launches_of(("bnn_conv_bn_sign_pack", (*conv, THR, FLIP, OUT, N // 32, 0)),
+                       ("bnn_conv_pool_windows_bn_sign_pack", (*conv, 2, THR, FLIP, OUT, N // 32, 0)),
+                       ("bnn_xnor_gemm_bn_sign_pack", (A, 19, B, 19, M, N, K, THR, FLIP, OUT, N // 32, 0)))
+    for st, log in runs if tiles_n <= 2 else runs[:2]:
+        assert st == 0 and log == [[256, 512, A]]
