@@ -20,6 +20,12 @@ inline StripPlan strip_plan(int64_t M, int64_t tiles_n) {
     return StripPlan{rows, (M + rows - 1) / rows};
 }
 
+// Whether the strips keep at least `percent` of the chip at work: the rows there are against kStripUnits strips of `rows` rows.
+// (kStripUnits / tiles_n is rounded down and rows up: 129 column tiles leave 127 units without a strip, 52 leave 48.)
+inline bool strips_fill(int64_t M, int64_t tiles_n, int64_t rows, int percent) {
+    return 100 * M * tiles_n >= percent * kStripUnits * rows;
+}
+
 // Rows [begin, end) of strip `group`.  `rows` is rounded up for every strip, so begin + rows can pass M by thousands of rows and,
 // near the largest M, 2^31: what is left of the matrix is compared instead.
 struct StripRows {

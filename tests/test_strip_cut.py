@@ -70,3 +70,20 @@ def test_strip_kernels_take_rows_up_to_the_limit(launches_of, tiles_n, M):  # no
                        ("bnn_xnor_gemm_bn_sign_pack", (A, 19, B, 19, M, N, K, THR, FLIP, OUT, N // 32, 0)))
     for st, log in runs if tiles_n <= 2 else runs[:2]:
         assert st == 0 and log == [[256, 512, A]]
+
+
+def strips(M, N, tile_n):
+    """Workgroups of 512 threads that an M x N output in strips has."""
+    t = -(-N // tile_n)
+    rows = -(-(-(-M // (256 // t))) // 32) * 32
+    return [[-(-M // rows) * t, 512, A]]
+
+
+@pytest.mark.parametrize("M,N,K,taken", [
+    (2000, 6656, 784, True), (2000, 5504, 600, True), (1164, 19579, 600, False), (3060, 16512, 600, False), (1853, 4224, 1002, False),
+    (1853, 4224, 800, True), (10000, 4096, 784, True), (10000, 3000, 700, True), (4000, 6656, 784, True), (4000, 12000, 784, False), (10000, 6656, 784, False), (10000, 12000, 600, False),
+    (4000, 16512, 784, False), (10000, 16640, 784, False), (4141, 7168, 810, False), (4112, 15104, 784, True), (4000, 32768, 784, True)])
+def test_row_strips_are_taken_where_they_fill_the_chip(launches_of, M, N, K, taken):  # noqa: F811
+    kw = (K + 31) // 32
+    (st, log), = launches_of(("bnn_xnor_gemm_bn_sign_pack", (A, kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
+    assert st == 0 and (log == strips(M, N, 128)) == taken
