@@ -253,10 +253,10 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 // 6.6 and 6.9, 1583 x 4096 x 907 6.5 and 6.7, 1853 x 4224 x 1002 (288 rows) 6.8 and 7.4, but 2940 x 3000 x 671 (320 rows) 7.9 and
 // 6.4, 2924 x 2048 x 784 (192) 6.5 and 6.0.
 // Strips that keep most of the chip at work, where the tiles taken otherwise fill it by themselves: 65 % of it with strips of one
-// tile (2000 x 6656 x 784, 79 %, 10.1 and 8.3; 1164 x 19579 x 600, 59 %, 13.1 and 15.7), 76 % of two to four (4000 x 6656 x 784, 79 %,
+// tile (2000 x 6656 x 784, 79 %, 10.1 and 8.3; 1164 x 19579 x 600, 59 %, 13.1 and 15.7), 74 % of two to four (4000 x 6656 x 784, 79 %,
 // 15.6 and 14.3; 4000 x 12000 x 784, 73 %, 25.1 and 26.0), 82 % with longer ones (10000 x 6656 x 784, 80 %, 31.2 and 32.0, 10000 x 12000
 // x 784, 72 %, 53.7 and 60.9, 10000 x 16512 x 784, 50 %, 82 and 116; 10000 x 5504 x 784, 83 %, level, 4000 x 32768 x 784, 98 %, 53.3
-// and 49.4).  A last tile counts as a quarter of one at least (4141 x 7168 x 810, 1056 rows, 15.9 and 17.6).
+// and 49.4).  A last tile counts as half of one at least (4141 x 7168 x 810, 1056 rows, 15.9 and 17.6).
 constexpr int64_t kRowStripMinRows = 160;
 
 // BNN_ERR_UNSUPPORTED, with nothing launched, for a product that this kernel does not take or that is faster elsewhere.
@@ -268,8 +268,8 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
     const StripPlan plan = strip_plan(M, tiles_n);
     const int64_t rows = plan.rows, groups = plan.groups;
     if (rows < kRowStripMinRows || (rows <= 288 && K > 832) || (rows > BM && (rows < 2 * BM || K > 128 * (MAX_QUADS - 1)))) return BNN_ERR_UNSUPPORTED;
-    const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 4 ? rows - last + BM / 4 : rows;
-    if (!strips_fill(M, tiles_n, cost, rows <= BM ? 65 : rows <= 4 * BM ? 76 : 82)) return BNN_ERR_UNSUPPORTED;
+    const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 2 ? rows - last + BM / 2 : rows;
+    if (!strips_fill(M, tiles_n, cost, rows <= BM ? 65 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
     const int64_t kq = ceil_div(K, 128);
     hipLaunchKernelGGL(xnor_gemm_mfma_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(T),
