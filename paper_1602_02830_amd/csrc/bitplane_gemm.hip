@@ -817,7 +817,12 @@ static int launch_tiles(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int6
 //  - strips with at most a quarter of columns that do not exist, strips of more than one tile, at least three K-tiles (the
 //    stream runs three ahead) and K that fits LDS beside A: 10000 x 4096 x 784 43.0 on 128 x 512 tiles and 35.1, x 1536 65.6 and
 //    53.8, 16384 x 4096 x 784 57.1 and 49.2, 6000 x 4096 x 784 26.3 and 23.9, 5000 x 4096 x 784 (160 rows) 23.3 and 21.9, 8192 x 4096
-//    x 300 17.2 and 16.4; but of one tile, 4000 x 4096 x 784 (128 rows, one round of tiles) 15.4 and 16.3.
+//    x 300 17.2 and 16.4; but of one tile, 4000 x 4096 x 784 (128 rows, one round of tiles) 15.4 and 16.3.  They also have to
+//    keep the chip at work: a strip's last tile costs as much staging as a whole one, which short K-loops do not cover, and
+//    256 / (N / 512) strips are rounded down.  Outputs there are against whole tiles on 256 units, least share taken: 70 % up to
+//    K = 384 (12300 x 1226 x 440 11.6 and 14.5, 5190 x 3247 x 258 11.4 and 12.5, strips of 160 rows each; 16412 x 3697 x 309, 72 %,
+//    37.8 and 29.9), 63 % up to K = 512 (2539 x 8192 x 496, 62 %, 14.7 and 15.3), 50 % above (9101 x 1701 x 743, 46 %, 16.9 and 18.8;
+//    9633 x 1920 x 788, 55 %, 21.7 and 20.0; 1500 x 66048 x 784, 49 %, 93.6 and 122).
 //  - 128 x 512 where its tiles fill whole rounds of the 256 compute units to 4/5 with at most a quarter of columns that do
 //    not exist, and K > 256 or one round: 4000 x 4096 x 784 21.5 vs 24.3 on 64 x 256; but 262144 x 256 x 147 (half of the columns)
 //    50.4 vs 25.2, 10000 x 4096 x 129 18.9 vs 15.9, 4096 x 4096 x 160 (one round) 7.1 vs 7.6.  Its int32 form does not fit the
@@ -844,7 +849,9 @@ static int launch_planes(const uint32_t* Xp, int64_t ldx, const uint32_t* B, int
         if (wide && tiles_n <= kStripUnits && K > 256 && K <= 32 * planes::kStripWords) {
             const StripPlan plan = strip_plan(M, tiles_n);
             const int64_t rows = plan.rows, groups = plan.groups;
-            if (rows > planes::kStripBM) {
+            // Whole tiles; the share of the chip that works on columns that exist.
+            const int64_t cost = ceil_div(rows, planes::kStripBM) * planes::kStripBM * planes::kStripBN;
+            if (rows > planes::kStripBM && strips_fill(M, N, cost, K <= 384 ? 70 : K <= 512 ? 63 : 50)) {
                 const planes::StripCut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
                 hipLaunchKernelGGL(planes::bitplane_gemm_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(planes::kStripT),
                                    size_t(4) * planes::kStripPitchB * (4 * ceil_div(K, 128)), s, Xp, ldx, B, ldb, int(M), int(N),

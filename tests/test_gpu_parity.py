@@ -1514,6 +1514,9 @@ def test_fused_products_of_short_rows_in_strips(M, N, K, tight):
     (6170, 8192, 1000),      # 416 = 3 x 128 + 32: every buffer and both sets of row sums reused
     (4200, 4096, 1536),      # the longest K
     (2049, 8192, 800),       # rows past the matrix in the last strip
+    (3700, 8192, 257),       # 256 rows: three K-tiles, the last of one bit
+    (3700, 7930, 384),       # 256: K of whole K-tiles, columns that do not exist
+    (7000, 6600, 300),       # 384, a K-tile of two words and one of a part
 ])
 @pytest.mark.parametrize("bytes_", ["random", "extreme"])
 def test_first_layer_on_bytes_in_strips(M, N, K, bytes_):

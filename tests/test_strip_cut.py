@@ -87,3 +87,13 @@ def test_row_strips_are_taken_where_they_fill_the_chip(launches_of, M, N, K, tak
     kw = (K + 31) // 32
     (st, log), = launches_of(("bnn_xnor_gemm_bn_sign_pack", (A, kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
     assert st == 0 and (log == strips(M, N, 128)) == taken
+
+
+@pytest.mark.parametrize("M,N,K,taken", [
+    (10000, 4096, 784, True), (10000, 4096, 300, True), (2400, 8192, 257, False), (12300, 1226, 440, False), (5190, 3247, 258, False),
+    (8192, 4096, 300, True), (16412, 3697, 309, True), (2539, 8192, 496, False), (2539, 8192, 513, True), (9101, 1701, 743, False),
+    (9633, 1920, 788, True), (1500, 66048, 300, False), (6000, 16640, 784, True)])
+def test_byte_layer_strips_are_taken_where_they_fill_the_chip(launches_of, M, N, K, taken):  # noqa: F811
+    kw = (K + 31) // 32
+    (st, log), = launches_of(("bnn_bitplane_gemm_bn_sign_pack", (A, 8 * kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
+    assert st == 0 and (log == strips(M, N, 512)) == taken
