@@ -487,6 +487,29 @@ constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, besi
 // stride 2, 233 of 16 x 16, 128 -> 512 7.7 and 7.95; but 2 x 2 at stride 1, 128 of 28 x 28, 256 -> 256 17.3 and 14.9.
 constexpr int64_t kStripMinRows = 160;
 
+// Which of the layers that fit are faster here than on the tiles of conv_patch.hip and the gathering kernels.  Measured on 3600
+// layers, pooled and not, of 1 to 25 taps, 128 to 1024 channels and 32 to 32768 filters; us, tiles and strips:
+//  - enough of the chip at work: 60 % with strips of one tile, 80 % up to four, 86 % beyond (41 images of 16 x 16, 256 -> 8576,
+//    78 %, 75.5 and 79.1; 47 of 14 x 14, 512 -> 12288, 75 %, 169 and 190), 93 % with K <= 1152, whose tiles are short (40 of 28 x 28,
+//    128 -> 9984, 91 %, 138 and 148; 58 of 32 x 32, 128 -> 4700 pooled, 87 %, 123 and 139);
+//  - K <= 1152 not with 577 to 768 rows: two and a half to three tiles of 256 pixels per compute unit, which hold two at a time and
+//    the third alone (3 x 3, 185 of 16 x 16, 128 -> 512, 740 rows, 13.7 and 14.9; 73 of 14 x 51, 256 -> 512, 1 x 4, 12.6 and 14.8; but
+//    544 rows, 272 of 14 x 14, 128 -> 1159 at stride 2 19.6 and 14.5, 800 rows and more 1.1 to 1.25 times faster);
+//  - fewer than nine taps reuse little of a patch.  Their tiles win where most of the strip's patch is not read (more than eight
+//    cells per pixel: 571 of 32 x 32, 384 -> 128, 1 x 4 at stride 3 8.8 and 10.9), in strips of more than two tiles with K < 1152
+//    (145 of 89 x 89, 128 -> 128, 7 x 1 65.3 and 75.2), two taps (189 of 56 x 56, 1024 -> 128, 2 x 1 64.5 and 74.2) or up to four of
+//    K <= 1536 on dense patches (493 of 28 x 28, 384 -> 384, 4 x 1 93.8 and 109), and in the shortest strips with K <= 512 (64 of
+//    32 x 32, 128 -> 128, 1 x 4 5.7 and 6.0).
+static bool strips_preferred(const ConvArgs& cv, int64_t M, int64_t K, int64_t tiles_n, int64_t rows, int64_t cells, int64_t pixels) {
+    const int64_t tiles = ceil_div(rows, strip::BM), taps = int64_t(cv.kh) * cv.kw;
+    if (!strips_fill(M, tiles_n, rows, tiles == 1 ? 60 : tiles <= 4 ? 80 : K <= 1152 ? 93 : 86)) return false;
+    if (K <= 1152 && rows > 576 && rows <= 768) return false;
+    if (taps >= 9) return true;
+    if (K <= 1536 && cells > 8 * pixels) return false;
+    if (tiles > 2 && (K < 1152 || taps <= 2 || (taps <= 4 && K <= 1536 && 2 * cells < 3 * pixels))) return false;
+    return K > 512 || rows > 256;
+}
+
 // BNN_ERR_UNSUPPORTED, with nothing launched, for a layer that this kernel does not take or that is faster elsewhere.
 int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             BnSignArgs bn, ConvArgs cv, bool pool, void* stream) {
@@ -504,7 +527,8 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     if (pool) cv = pooled_units(cv);
     // Tiles start at multiples of the strips' rows, and 512 pixels further on.
     const int64_t tile = rows < BM ? rows : BM, align = rows <= BM ? rows : std::gcd(rows, int64_t(BM));
-    if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg)) return BNN_ERR_UNSUPPORTED;
+    if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg) || !strips_preferred(cv, M, K, tiles_n, rows, pg.slots, tile))
+        return BNN_ERR_UNSUPPORTED;
     const int64_t filters = int64_t(2) * pg.kq * PLANE_B * 8, patch = (int64_t(2) * pg.cqn * pg.slots + (pg.slots + 1) / 2) * 8;
     if (filters + patch > kStripLdsBytes) return BNN_ERR_UNSUPPORTED;
     const int64_t tiles = ceil_div(rows, BM), buffers = tiles < 3 ? tiles : 3;

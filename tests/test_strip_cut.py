@@ -97,3 +97,25 @@ def test_byte_layer_strips_are_taken_where_they_fill_the_chip(launches_of, M, N,
     kw = (K + 31) // 32
     (st, log), = launches_of(("bnn_bitplane_gemm_bn_sign_pack", (A, 8 * kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
     assert st == 0 and (log == strips(M, N, 512)) == taken
+
+
+@pytest.mark.parametrize("B_,H,W,Cin,Cout,window,stride,pad,taken", [
+    (256, 16, 16, 256, 256, (3, 3), 1, 1, True), (256, 32, 32, 128, 128, (3, 3), 1, 1, True), (128, 28, 28, 128, 256, (3, 3), 1, 1, True),
+    (256, 16, 16, 128, 256, (3, 3), 1, 1, True),                                                       # the ConvNet's layers
+    (47, 14, 14, 512, 12288, (3, 3), 1, 1, False), (54, 14, 14, 256, 5632, (3, 3), 1, 1, False), (18, 14, 14, 512, 8448, (3, 3), 1, 1, False),
+    (5, 14, 14, 512, 8704, (3, 3), 1, 1, True), (40, 28, 28, 128, 9984, (3, 3), 1, 1, False), (29, 28, 28, 512, 3840, (3, 3), 1, 1, True),
+    (185, 16, 16, 128, 512, (3, 3), 1, 1, False), (140, 16, 16, 128, 512, (3, 3), 1, 1, True), (200, 16, 16, 128, 512, (3, 3), 1, 1, True),
+    (185, 16, 16, 256, 512, (3, 3), 1, 1, True), (73, 14, 51, 256, 512, (1, 4), 1, 0, False),
+    (571, 32, 32, 384, 128, (1, 4), 3, 0, False), (145, 89, 89, 128, 128, (7, 1), 1, 3, False), (189, 56, 56, 1024, 128, (2, 1), 1, 0, False),
+    (493, 28, 28, 384, 384, (4, 1), 1, 2, False), (64, 32, 32, 128, 128, (1, 4), 1, 0, False), (100, 32, 32, 256, 128, (1, 4), 1, 0, True)])
+def test_convolution_strips_are_taken_where_they_are_faster(launches_of, B_, H, W, Cin, Cout, window, stride, pad, taken):  # noqa: F811
+    kh, kw = window
+    Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
+    args = (A, B_, H, W, Cin, WB, kh * kw * Cin // 32, Cout, kh, kw, stride, pad)
+    tail = (THR, FLIP, OUT, (Cout + 31) // 32, 0)
+    (st, log), (st_pool, log_pool) = launches_of(("bnn_conv_bn_sign_pack", (*args, *tail)),
+                                                 ("bnn_conv_pool_windows_bn_sign_pack", (*args, 2, *tail)))
+    want = strips(B_ * Ho * Wo, Cout, 128)
+    assert st == 0 and (log == want) == taken
+    if (Ho | Wo) % 2 == 0:
+        assert (st_pool, log_pool == want) in ((0, taken), (3, False))
