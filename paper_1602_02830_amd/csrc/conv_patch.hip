@@ -616,6 +616,32 @@ static bool pool_fits(const ConvArgs& cv, int WM) {
     return cv.W % 32 == 0 && 2 * (cv.W / 32) <= WM;
 }
 
+// Pooled layers of other than the maps of pool_fits that are faster as a convolution and a pooling of its output bits (2 to 3 us):
+//  - windows lie in two image rows at least, so a pooled patch has more rows than the plain one; where a compute unit holds fewer
+//    workgroups of 128 pixels with it (beside two K-tiles of streamed filters) and the grid then takes another round of them: one image
+//    of 56 x 56, 512 -> 21028 (3795 tiles, 8 rounds and 5) 117 us, apart 103, 93 of 28 x 28, 768 -> 32 (570) 38.2 and 34.4, 5 of 56 x
+//    183, 128 -> 17696 at stride 2 218 and 160; but 77 of 28 x 28, 768 -> 32 (472, one round) 25.1 and 27.4, and 1 x 1
+//    windows win all the same (45 of 28 x 28, 768 -> 384 11.7 and 12.6);
+//  - patches that only tiles of 256 pixels can hold (their windows fill whole rows) on fewer than 192 of those: 1, 3, 7 images of 32 x
+//    128, 512 -> 128 19.3 and 14.5 to 15.5, 14 of 16 x 128, 128 -> 128, 7 x 7 25.2 and 21.6; but 30 (240 tiles) 25.3 and 27.4;
+//  - what better_gathered says of 1 x 1 windows, beyond one round: 59 of 26 x 26, 1024 -> 384 14.8 and 13.6; but 15 of 28 x 14,
+//    1024 -> 1718 (644 tiles) 10.4 and 12.0.
+static bool better_pooled_apart(const ConvArgs& cv, const ConvArgs& units, int64_t M, int64_t N) {
+    const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), tiles256 = ceil_div(M, 256) * ceil_div(N, 128);
+    if (cv.kh * cv.kw == 1) return cv.Cw >= 32 && tiles > 3 * kComputeUnits && !whole_row_tiles(cv, 128);
+    PatchGeom pooled, plain;
+    const bool fits256 = patch_geometry(units, 256, 256, kPatchMaxBytes, true, pooled);
+    if (wants_big_tiles(M, N) && fits256) return false;
+    if (!patch_geometry(units, 128, 128, kPatchMaxBytes, true, pooled)) return fits256 && tiles256 < 192;
+    if (!patch_geometry(cv, 128, 128, kPatchMaxBytes, false, plain)) return false;
+    auto rounds = [&](const PatchGeom& pg) {
+        const int64_t bytes = pg.slots * (int64_t(cv.Cw) * 4 + 4) + 2 * 8 * (128 + 2) * int64_t(sizeof(uint2)) + 4 * 1024;
+        const int64_t fit = 160 * 1024 / bytes;
+        return ceil_div(tiles, kComputeUnits * (fit < 4 ? fit : 4));
+    };
+    return rounds(pooled) > rounds(plain);
+}
+
 int launch_conv_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc, int64_t M,
                       int64_t N, int64_t K, ConvArgs cv, void* stream) {
     return launch_conv_patch_any<false>(in, B, ldb, C, ldc, M, N, K, BnSignArgs{}, cv, stream);
@@ -636,15 +662,15 @@ int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t 
                                  BnSignArgs bn, ConvArgs cv, bool any_map, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
-    if (any_map ? cv.Cw % 4 != 0 || ((cv.Ho | cv.Wo) & 1)
-                : !((pool_fits(cv, 2) && patch_geometry(cv, 128, 128, kPatchMaxBytes, false, pg)) ||
-                    (pool_fits(cv, 4) && patch_geometry(cv, 256, 256, kPatchMaxBytes, false, pg))))
-        return BNN_ERR_UNSUPPORTED;
+    const bool whole_rows = (pool_fits(cv, 2) && patch_geometry(cv, 128, 128, kPatchMaxBytes, false, pg)) ||
+                            (pool_fits(cv, 4) && patch_geometry(cv, 256, 256, kPatchMaxBytes, false, pg));
+    if (any_map ? cv.Cw % 4 != 0 || ((cv.Ho | cv.Wo) & 1) : !whole_rows) return BNN_ERR_UNSUPPORTED;
     const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, true, stream);
     if (st != BNN_ERR_UNSUPPORTED) return st;
     const ConvArgs units = pooled_units(cv);
+    if (!whole_rows && better_pooled_apart(cv, units, M, N)) return BNN_ERR_UNSUPPORTED;
     auto fits = [&](int WM) {
-        if (!any_map && !pool_fits(cv, WM)) return false;
+        if (whole_rows && !pool_fits(cv, WM)) return false;
         // Eight windows side by side read 16 cells of a row and 16 of the next: in different banks if rows are 16 cells modulo 32
         // apart.
         const int64_t pw = int64_t(cv.W) + 2 * cv.pad, pitch = pw + (48 - pw % 32) % 32;
