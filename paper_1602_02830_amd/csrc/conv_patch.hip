@@ -671,10 +671,6 @@ int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t 
     if (!whole_rows && better_pooled_apart(cv, units, M, N)) return BNN_ERR_UNSUPPORTED;
     auto fits = [&](int WM) {
         if (whole_rows && !pool_fits(cv, WM)) return false;
-        // Eight windows side by side read 16 cells of a row and 16 of the next: in different banks if rows are 16 cells modulo 32
-        // apart.
-        const int64_t pw = int64_t(cv.W) + 2 * cv.pad, pitch = pw + (48 - pw % 32) % 32;
-        if (WM <= 2 && units.Wo >= 16 && patch_geometry(units, 64 * WM, 64 * WM, kPatchMaxBytes, true, pg, pitch)) return true;
         return patch_geometry(units, 64 * WM, 64 * WM, kPatchMaxBytes, true, pg);
     };
     if (wants_small_tiles(M, N, K, true) && fits(2) && fits(1))

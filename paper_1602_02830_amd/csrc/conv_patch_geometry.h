@@ -43,10 +43,8 @@ inline ConvArgs pooled_units(ConvArgs cv) {
 
 // Fills the patch geometry for tiles of BM output pixels that start at multiples of align; false if the patch takes more than
 // max_bytes.  windows: cv is pooled_units of the layer and a tile BM / 4 pooling windows.
-// pitch: cells from row to row, at least W + 2 * pad (more are loaded as cells outside the image); 0 for that.
-inline bool patch_geometry(const ConvArgs& cv, int64_t BM, int64_t align, int64_t max_bytes, bool windows, PatchGeom& pg,
-                           int64_t pitch = 0) {
-    const int64_t img_rows = int64_t(cv.H) + 2 * cv.pad, pw = pitch > 0 ? pitch : int64_t(cv.W) + 2 * cv.pad;
+inline bool patch_geometry(const ConvArgs& cv, int64_t BM, int64_t align, int64_t max_bytes, bool windows, PatchGeom& pg) {
+    const int64_t img_rows = int64_t(cv.H) + 2 * cv.pad, pw = int64_t(cv.W) + 2 * cv.pad;
     ConvArgs unit = cv;
     if (windows) {
         unit.stride *= 2;

@@ -1,12 +1,14 @@
 """CPU-only tests of how the strip kernels cut an output (csrc/strip_cut.h): the function that gives a workgroup its rows, built by
 the host compiler with every signed overflow an error, and the launches of the entry points at the sizes where the strips' ends lie
 beyond 2^31."""
+import json
 import os
 import subprocess
+import sys
 
 import pytest
 
-from test_launch_limits import A, B, FLIP, OUT, THR, WB, launches_of  # noqa: F401
+from test_launch_limits import A, B, CHILD, FLIP, LIB, OUT, RUNTIME, THR, WB, launches_of  # noqa: F401
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1602_02830_amd", "csrc")
 
@@ -141,3 +143,30 @@ def test_pooled_maps_of_whole_rows_keep_their_call(launches_of, B_, H, W, Cin): 
     (st, log), (st_any, log_any) = launches_of(("bnn_conv_pool_bn_sign_pack", args), ("bnn_conv_pool_windows_bn_sign_pack", args))
     assert st == 0 and len(log) == 1
     assert (st_any, log_any) == ((0, log) if Cin % 128 == 0 else (3, []))
+
+
+@pytest.fixture(scope="module")
+def local_memory_of(tmp_path_factory):
+    """calls -> bytes of local memory that each one's launch asks for beside what the kernel declares."""
+    folder = tmp_path_factory.mktemp("local_memory")
+    src, so = folder / "runtime.c", folder / "runtime.so"
+    assert "launch_log[launches][2] = *(uint64_t*)args[0];" in RUNTIME
+    src.write_text(RUNTIME.replace("launch_log[launches][2] = *(uint64_t*)args[0];", "launch_log[launches][2] = shared;"))
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+
+    def run(*calls):
+        r = subprocess.run([sys.executable, "-c", CHILD, str(so), LIB], input=json.dumps([[n, list(a)] for n, a in calls]),
+                           stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+        assert r.returncode == 0, r.stderr
+        return [log[0][2] for status, log in json.loads(r.stdout) if status == 0]
+
+    return run
+
+
+@pytest.mark.parametrize("B_,HW,Cin", [(100, 32, 768), (168, 32, 1024), (22, 32, 256), (8, 16, 512)])
+def test_pooled_patches_of_whole_rows_are_no_larger_than_plain_ones(local_memory_of, B_, HW, Cin):
+    """Tiles of pooling windows that are whole image rows cover the same rows as the tiles of the unpooled layer."""
+    args = (A, B_, HW, HW, Cin, WB, 9 * Cin // 32, 64, 3, 3, 1, 1)
+    plain, pooled = local_memory_of(("bnn_conv_bn_sign_pack", (*args, THR, FLIP, OUT, 2, 0)),
+                                    ("bnn_conv_pool_bn_sign_pack", (*args, 2, THR, FLIP, OUT, 2, 0)))
+    assert 0 < pooled <= plain
