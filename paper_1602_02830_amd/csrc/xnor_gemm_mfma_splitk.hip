@@ -413,20 +413,27 @@ static int launch_splitk_rows(const uint32_t* A, int64_t lda, const uint32_t* B,
 }
 
 // Which products with t tiles of 32 x 32 the automatic choice sends here (fused and int32 alike), and in which form.
-// Launches replayed from a graph, us, rows of ceil(K / 32) words; "before": 32 x 32 direct up to 1024 tiles, then 64 x 128
-// tiles with K in one piece:
-//  - staged from 28 quads on, more than 256 tiles, where the last round of 32 quads is nearly full, or one quad of unaligned rows
-//    (t = 512 fused K = 4096 4.3 vs 5.0, K = 8192 5.7 vs 6.3, K = 4097 5.2 vs 5.5; but K = 5000, of 8 quads in the last round,
-//    5.2 vs 4.9, and t = 296 aligned K = 4097 5.5 vs 5.1) and there are two rounds at most (t = 288 K = 20000 10.0 vs 9.6), or there are more than 896 tiles (t = 1024 int32
-//    K = 4097 6.8 vs 8.0 direct, K = 6000 7.6 vs 7.8); not where many rows repeat the last one, which are loaded once
-//    directly (1 x 32000, K = 4097 6.6 vs 7.3 staged, 33 x 8000, K = 4097 5.1 vs 5.6);
+// Launches replayed from a graph, us; "tiles": the 64 x 128 tiles with K in one piece that take what is not sent here.  1750
+// products were measured in both forms.
 //  - 64 x 32 tiles above 896 tiles of 32 x 32 (t = 704 fused K = 4096 5.5 vs 5.4 on 32 x 32, t = 1024 5.5 vs 6.1) where that
-//    multiplies no more than an eighth of rows that do not exist;
-//  - so up to 1536 tiles with K >= 1000 instead of 1024 tiles with K >= 512: t = 1250 fused K = 1000 4.4 vs 4.6 before,
+//    multiplies no more than an eighth of rows that do not exist, and only in as many as two of them fill a compute unit, three
+//    above t = 1024: one more leaves most units waiting for a few (416 x 2368 x 4580, t = 962 in 518, 7.8 vs 6.4 on 32 x 32, 672 x
+//    2235 x 4480, t = 1470 in 770, 9.6 vs 8.4 on tiles);
+//  - so up to t = 1536 with K >= 1000 instead of t = 1024 with K >= 512: t = 1250 fused K = 1000 4.4 vs 4.6 on tiles,
 //    K = 3000 6.2 vs 7.0, K = 8192 9.7 vs 12.6, t = 1504 int32 K = 4096 7.0 vs 8.1; but K = 512 4.2 vs 3.8 and t = 1824
-//    K = 4096 8.3 vs 8.0.
+//    K = 4096 8.3 vs 8.0;
+//  - staged above t = 256, not where many rows repeat the last one, which are loaded once directly (1 x 32000, K = 4097 6.6 vs 7.3
+//    staged, 33 x 8000, K = 4097 5.1 vs 5.6):
+//      rows that are whole 128-byte lines apart but for a word, from 32 quads on: what 32 rows of a direct load want then lies at
+//      the same place of their lines, and staged is 1.04 to 1.3 times faster at every t and form (t = 512 fused K = 4096 4.3
+//      vs 5.0, t = 1024 int32 K = 4097 6.8 vs 8.0, t = 485 K = 10212 6.4 vs 7.9);
+//      other rows only where the last round of 32 quads is well filled: 49 to 64 quads (t = 776 int32 K = 7680 1.08 times faster; fused
+//      up to t = 896 from 57 on; 64 x 32 fused from 41 on, and above t = 1024 from 34 on without end), 89 to 96, 121 to 128 and so
+//      on above t = 512 (1.03), and 24 to 30, one round, int32 up to t = 896 (1.02).  With 33 to 40 quads staged takes 1.05 to 1.15 times as long (t = 750 fused K = 4160 5.9 vs 5.4),
+//      with 65 to 88 as well (1003 tiles, int32 K = 8704 11.5 vs 10.2).
 static bool splitk_two_rows(int64_t M, int64_t N) {
-    return ceil_div(M, 32) * ceil_div(N, 32) > 896 && 16 * ceil_div(M, 64) <= 9 * ceil_div(M, 32);
+    const int64_t t = ceil_div(M, 32) * ceil_div(N, 32), t64 = ceil_div(M, 64) * ceil_div(N, 32);
+    return t > 896 && t64 <= (t <= 1024 ? 512 : 768) && 16 * ceil_div(M, 64) <= 9 * ceil_div(M, 32);
 }
 
 bool mfma_splitk_prefers(int64_t M, int64_t N, int64_t K, bool fused) {
@@ -446,9 +453,12 @@ int launch_xnor_gemm_mfma_splitk(const uint32_t* A, int64_t lda, const uint32_t*
     const int64_t t = ceil_div(M, 32) * ceil_div(N, 32);
     const int64_t quads = ceil_div(K, 128), last = (quads - 1) % 32;        // quads of the last round, less one
     const bool two_rows = splitk_two_rows(M, N);
-    const bool aligned = rows_16_byte_aligned(A, lda) && rows_16_byte_aligned(B, ldb);
     const bool few_repeated = 4 * M >= 96 * ceil_div(M, 32) && 4 * N >= 96 * ceil_div(N, 32);
-    const bool staged = t > 256 && quads >= 28 && few_repeated && (t > 896 || (quads <= 64 && (last >= 24 || (last == 0 && !aligned))));
+    auto whole_lines = [](int64_t ld) { return (ld + 1) % 32 <= 2; };        // but for a word
+    const int64_t first = two_rows && fused ? (t > 1024 ? 34 : 41) : fused && t <= 896 ? 57 : 49;
+    const bool filled = quads >= first ? quads <= 64 || (last >= 24 && t > 512) || (fused && t > 1024)
+                                       : !fused && t <= 896 && quads >= 24 && quads <= 30;
+    const bool staged = t > 256 && few_repeated && (whole_lines(lda) && whole_lines(ldb) ? quads >= 32 : filled);
     if (staged)
         return two_rows ? launch_splitk_rows<2, true>(A, lda, B, ldb, C, ldc, M, N, K, fused, bn, s)
                         : launch_splitk_rows<1, true>(A, lda, B, ldb, C, ldc, M, N, K, fused, bn, s);

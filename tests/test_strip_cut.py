@@ -8,7 +8,7 @@ import sys
 
 import pytest
 
-from test_launch_limits import A, B, CHILD, FLIP, LIB, OUT, RUNTIME, THR, WB, launches_of  # noqa: F401
+from test_launch_limits import A, B, C, CHILD, FLIP, LIB, OUT, RUNTIME, THR, WB, launches_of  # noqa: F401
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1602_02830_amd", "csrc")
 
@@ -146,27 +146,62 @@ def test_pooled_maps_of_whole_rows_keep_their_call(launches_of, B_, H, W, Cin): 
 
 
 @pytest.fixture(scope="module")
-def local_memory_of(tmp_path_factory):
-    """calls -> bytes of local memory that each one's launch asks for beside what the kernel declares."""
-    folder = tmp_path_factory.mktemp("local_memory")
-    src, so = folder / "runtime.c", folder / "runtime.so"
-    assert "launch_log[launches][2] = *(uint64_t*)args[0];" in RUNTIME
-    src.write_text(RUNTIME.replace("launch_log[launches][2] = *(uint64_t*)args[0];", "launch_log[launches][2] = shared;"))
-    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+def seen_by_launch(tmp_path_factory):
+    """(what, calls) -> that expression of the stand-in for every call's launch: its local memory beside what the kernel declares, its
+    kernel, its workgroups."""
+    folder = tmp_path_factory.mktemp("seen")
+    line = "launch_log[launches][2] = *(uint64_t*)args[0];"
+    assert line in RUNTIME and "(void)f; (void)shared;" in RUNTIME
 
-    def run(*calls):
+    def run(what, *calls):
+        src, so = folder / f"{what}.c", folder / f"{what}.so"
+        if not so.exists():
+            expression = {"local_memory": "shared", "kernel": "(uint64_t)f", "workgroups": "g.x"}[what]
+            src.write_text(RUNTIME.replace(line, f"launch_log[launches][2] = {expression};"))
+            subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
         r = subprocess.run([sys.executable, "-c", CHILD, str(so), LIB], input=json.dumps([[n, list(a)] for n, a in calls]),
                            stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
         assert r.returncode == 0, r.stderr
-        return [log[0][2] for status, log in json.loads(r.stdout) if status == 0]
+        return [log[0][2] for status, log in json.loads(r.stdout) if status == 0 and len(log) == 1]
 
     return run
 
 
 @pytest.mark.parametrize("B_,HW,Cin", [(100, 32, 768), (168, 32, 1024), (22, 32, 256), (8, 16, 512)])
-def test_pooled_patches_of_whole_rows_are_no_larger_than_plain_ones(local_memory_of, B_, HW, Cin):
+def test_pooled_patches_of_whole_rows_are_no_larger_than_plain_ones(seen_by_launch, B_, HW, Cin):
     """Tiles of pooling windows that are whole image rows cover the same rows as the tiles of the unpooled layer."""
     args = (A, B_, HW, HW, Cin, WB, 9 * Cin // 32, 64, 3, 3, 1, 1)
-    plain, pooled = local_memory_of(("bnn_conv_bn_sign_pack", (*args, THR, FLIP, OUT, 2, 0)),
-                                    ("bnn_conv_pool_bn_sign_pack", (*args, 2, THR, FLIP, OUT, 2, 0)))
+    plain, pooled = seen_by_launch("local_memory", ("bnn_conv_bn_sign_pack", (*args, THR, FLIP, OUT, 2, 0)),
+                                   ("bnn_conv_pool_bn_sign_pack", (*args, 2, THR, FLIP, OUT, 2, 0)))
     assert 0 < pooled <= plain
+
+
+def product(fused, M, N, K, ld=0):
+    ld = ld or (K + 31) // 32
+    return (("bnn_xnor_gemm_bn_sign_pack", (A, ld, B, ld, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)) if fused else
+            ("bnn_xnor_gemm", (A, ld, B, ld, C, N, M, N, K, 0)))
+
+
+@pytest.mark.parametrize("fused,M,N,K,ld,staged", [
+    (True, 512, 1024, 4096, 128, True), (False, 512, 1024, 4096, 128, True), (True, 512, 1024, 4097, 129, True), (True, 512, 1024, 4064, 127, True),
+    (True, 800, 960, 4160, 130, False), (False, 800, 960, 4160, 130, False), (True, 800, 960, 4168, 131, False),     # 33 quads
+    (True, 800, 960, 4097, 132, False), (True, 800, 960, 5120, 160, True), (True, 800, 960, 3968, 124, False),
+    (False, 512, 640, 6200, 194, True), (True, 512, 640, 6200, 194, False), (True, 512, 640, 7300, 229, True), (False, 512, 640, 8704, 272, False),
+    (False, 800, 960, 12000, 375, True), (False, 512, 640, 12000, 375, False), (True, 200, 1000, 4096, 128, False),
+    (False, 512, 640, 3500, 110, True), (True, 512, 640, 3500, 110, False), (False, 512, 640, 3900, 122, False)])
+def test_k_split_products_are_staged_where_that_is_faster(seen_by_launch, fused, M, N, K, ld, staged):
+    got, direct, lines = seen_by_launch("kernel", product(fused, M, N, K, ld), product(fused, 512, 640, 2000), product(fused, 512, 640, 4096))
+    assert direct != lines and got == (lines if staged else direct)
+
+
+@pytest.mark.parametrize("fused,M,N,K,workgroups", [
+    (True, 416, 2368, 4580, 13 * 74), (False, 539, 1883, 8704, 17 * 59), (False, 1000, 1000, 4097, 16 * 32), (True, 1000, 1000, 4097, 16 * 32),
+    (True, 1280, 1200, 4352, 20 * 38), (True, 672, 2235, 4480, None), (True, 1292, 1184, 4352, None), (False, 800, 1947, 6528, None)])
+def test_k_split_tiles_of_two_rows_fill_the_compute_units(seen_by_launch, fused, M, N, K, workgroups):
+    """As many 64 x 32 tiles as two (three, with more than 1024 tiles of 32 x 32) fill every compute unit; else 32 x 32 tiles up to 1024
+    of them, and the tiles with K in one piece above."""
+    (got,) = seen_by_launch("workgroups", product(fused, M, N, K))
+    if workgroups is None:
+        assert got <= -(-M // 64) * -(-N // 128)
+    else:
+        assert got == workgroups
