@@ -280,13 +280,24 @@ int bnn_conv_pool_bn_sign_pack(const uint32_t *in, int64_t B, int64_t H, int64_t
                                uint32_t *out, int64_t ld_out, void *stream);
 
 /*
- * The same pooled layer on any map: pool = 2, even Ho and Wo, any window, stride and padding, Cin a multiple of 128 and an
- * input patch that fits the compute unit's local memory.  Anything else returns BNN_ERR_UNSUPPORTED before any launch.
+ * The same pooled layer on any map: pool = 2, even Ho and Wo, any window, stride and padding, Cin a multiple of 128, Wb 16-byte
+ * aligned with ldw % 4 == 0, and an input patch that fits the compute unit's local memory.  Anything else returns
+ * BNN_ERR_UNSUPPORTED before any launch.  Not every layer that it takes is faster in one launch: see bnn_conv_pool_form.
  */
 int bnn_conv_pool_windows_bn_sign_pack(const uint32_t *in, int64_t B, int64_t H, int64_t W, int64_t Cin,
                                        const uint32_t *Wb, int64_t ldw, int64_t Cout, int kh, int kw, int stride,
                                        int pad, int pool, const int32_t *thr, const uint32_t *flip_bits,
                                        uint32_t *out, int64_t ld_out, void *stream);
+
+/*
+ * The fastest form of a pooled layer whose input and filters are 16-byte aligned (ldw % 4 == 0).  Host only: nothing is launched.
+ * BNN_POOL_IN_CONV, BNN_POOL_WINDOWS: bnn_conv_pool_bn_sign_pack, bnn_conv_pool_windows_bn_sign_pack;
+ * BNN_POOL_APART: neither takes it, or bnn_conv_bn_sign_pack followed by bnn_maxpool_bits is faster.
+ */
+#define BNN_POOL_APART 0
+#define BNN_POOL_IN_CONV 1
+#define BNN_POOL_WINDOWS 2
+int bnn_conv_pool_form(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int kh, int kw, int stride, int pad, int pool);
 
 /*
  * Max pooling for binarized layers.  In the architecture Sec. 2.2 refers to (the cited BinaryConnect

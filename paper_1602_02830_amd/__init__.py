@@ -22,12 +22,16 @@ from .binding import (  # noqa: F401
     conv_bn_sign_pack,
     conv_pool_bn_sign_pack,
     conv_pool_windows_bn_sign_pack,
+    conv_pool_form,
     maxpool_bits,
     pack_bitplanes,
     bitplane_gemm,
     bitplane_gemm_bn_sign_pack,
     gemm_i8_mfma,
     unpack_i8,
+    POOL_APART,
+    POOL_IN_CONV,
+    POOL_WINDOWS,
     KERNEL_AUTO,
     KERNEL_NAIVE,
     KERNEL_TILED128,

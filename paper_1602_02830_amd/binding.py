@@ -21,6 +21,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libbnn_hip.so")
 
+POOL_APART, POOL_IN_CONV, POOL_WINDOWS = range(3)
 (KERNEL_AUTO, KERNEL_NAIVE, KERNEL_TILED128, KERNEL_KSPLIT, KERNEL_TILED64, KERNEL_MFMA, KERNEL_MFMA128,
  KERNEL_MFMA_SHORTK, KERNEL_MFMA_PERSIST, KERNEL_MFMA_BIG, KERNEL_MFMA_SPLITK) = range(11)
 
@@ -52,6 +53,7 @@ _SIGNATURES = {
                                           _ptr, _ptr, _ptr, _i64, _ptr]),
     "bnn_conv_pool_windows_bn_sign_pack": (_int, [_ptr, _i64, _i64, _i64, _i64, _ptr, _i64, _i64, _int, _int, _int, _int, _int,
                                                   _ptr, _ptr, _ptr, _i64, _ptr]),
+    "bnn_conv_pool_form": (_int, [_i64, _i64, _i64, _i64, _i64, _int, _int, _int, _int, _int]),
     "bnn_maxpool_bits": (_int, [_ptr, _i64, _i64, _i64, _i64, _int, _int, _int, _ptr, _ptr, _ptr]),
     "bnn_gemm_i8_mfma": (_int, [_ptr, _i64, _ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr]),
     "bnn_unpack_i8": (_int, [_ptr, _i64, _i64, _i64, _ptr, _i64, _ptr]),
@@ -457,6 +459,13 @@ def conv_pool_windows_bn_sign_pack(x_bits: torch.Tensor, Cin: int, w_bits: torch
                                    pool: int = 2, out: torch.Tensor | None = None) -> torch.Tensor:
     """bnn_conv_pool_windows_bn_sign_pack: the same on any even map (Cin % 128 == 0)."""
     return _conv_pool("conv_pool_windows_bn_sign_pack", x_bits, Cin, w_bits, thr, flip_bits, kh, kw, stride, pad, pool, out)
+
+
+def conv_pool_form(B: int, H: int, W: int, Cin: int, Cout: int, kh: int = 3, kw: int = 3, stride: int = 1, pad: int = 1,
+                   pool: int = 2) -> int:
+    """bnn_conv_pool_form: the fastest form of a pooled layer, POOL_IN_CONV (conv_pool_bn_sign_pack), POOL_WINDOWS
+    (conv_pool_windows_bn_sign_pack) or POOL_APART (conv_bn_sign_pack, then maxpool_bits)."""
+    return load_library().bnn_conv_pool_form(B, H, W, Cin, Cout, kh, kw, stride, pad, pool)
 
 
 def _conv_pool(name, x_bits, Cin, w_bits, thr, flip_bits, kh, kw, stride, pad, pool, out):

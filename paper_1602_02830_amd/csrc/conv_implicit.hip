@@ -26,7 +26,7 @@ int launch_conv_mfma(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t
 int launch_conv_mfma_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
                            BnSignArgs bn, ConvArgs cv, void* stream);
 int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                                 BnSignArgs bn, ConvArgs cv, bool any_map, void* stream);
+                                 BnSignArgs bn, ConvArgs cv, bool any_map, ConvUse use, void* stream);
 // Vector-ALU form for receptive fields beyond the matrix engine's exact range (valu_fallbacks.hip).
 int launch_conv_xnor_valu(const uint32_t* in, const uint32_t* Wb, int64_t ldw, int32_t* S, int64_t lds, int64_t M,
                           int64_t N, int64_t K, ConvArgs cv, bool fused, BnSignArgs bn, void* stream);
@@ -175,7 +175,8 @@ static int conv_pool(const uint32_t* in, int64_t B, int64_t H, int64_t W, int64_
     if (M == 0 || Cout == 0) return BNN_OK;
     if (!thr || !flip_bits || !out) return BNN_ERR_INVALID_ARG;
     if (!aligned_to(thr, 4) || !aligned_to(flip_bits, 4) || !aligned_to(out, 4)) return BNN_ERR_ALIGNMENT;
-    return launch_conv_patch_pool_fused(in, Wb, ldw, M, Cout, K, BnSignArgs{thr, flip_bits, out, ld_out}, cv, any_map, stream);
+    return launch_conv_patch_pool_fused(in, Wb, ldw, M, Cout, K, BnSignArgs{thr, flip_bits, out, ld_out}, cv, any_map,
+                                        ConvUse::faster, stream);
 }
 
 extern "C" int bnn_conv_pool_bn_sign_pack(const uint32_t* in, int64_t B, int64_t H, int64_t W, int64_t Cin,
@@ -190,6 +191,22 @@ extern "C" int bnn_conv_pool_windows_bn_sign_pack(const uint32_t* in, int64_t B,
                                                   int stride, int pad, int pool, const int32_t* thr,
                                                   const uint32_t* flip_bits, uint32_t* out, int64_t ld_out, void* stream) {
     return conv_pool(in, B, H, W, Cin, Wb, ldw, Cout, kh, kw, stride, pad, pool, thr, flip_bits, out, ld_out, true, stream);
+}
+
+extern "C" int bnn_conv_pool_form(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int kh, int kw, int stride, int pad,
+                                  int pool) {
+    using namespace bnn;
+    // Buffers of any alignment and filters of any length that the calls can ask for: nothing is read.
+    const uint32_t* const aligned = reinterpret_cast<const uint32_t*>(uintptr_t(256));
+    const int64_t ldw = ceil_div(kMaxK, 128) * 4;
+    ConvArgs cv;
+    int64_t M, K;
+    if (conv_geometry(aligned, B, H, W, Cin, aligned, ldw, Cout, kh, kw, stride, pad, cv, M, K) != BNN_OK) return BNN_POOL_APART;
+    if (pool != 2 || !mfma_path_supports(K) || M == 0 || Cout == 0) return BNN_POOL_APART;
+    auto takes = [&](bool any_map) {
+        return launch_conv_patch_pool_fused(aligned, aligned, ldw, M, Cout, K, BnSignArgs{}, cv, any_map, ConvUse::ask, nullptr) == BNN_OK;
+    };
+    return takes(false) ? BNN_POOL_IN_CONV : takes(true) ? BNN_POOL_WINDOWS : BNN_POOL_APART;
 }
 
 extern "C" int bnn_maxpool_bits(const uint32_t* in, int64_t B, int64_t H, int64_t W, int64_t C, int ph, int pw,

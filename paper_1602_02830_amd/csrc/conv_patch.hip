@@ -50,7 +50,7 @@ namespace bnn {
 
 // Layers that fill the chip (conv_strip.hip): BNN_ERR_UNSUPPORTED, with nothing launched, for those it leaves to this kernel.
 int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                            BnSignArgs bn, ConvArgs cv, bool pool, void* stream);
+                            BnSignArgs bn, ConvArgs cv, bool pool, ConvUse use, void* stream);
 
 constexpr int kPatchMaxBytes = 40 * 1024;
 
@@ -649,37 +649,47 @@ int launch_conv_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_
 
 int launch_conv_patch_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             BnSignArgs bn, ConvArgs cv, void* stream) {
-    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, false, stream);
+    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, false, ConvUse::faster, stream);
     if (st != BNN_ERR_UNSUPPORTED) return st;
-    return launch_conv_patch_any<true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, stream);
+    const int st_patch = launch_conv_patch_any<true>(in, B, ldb, nullptr, 0, M, N, K, bn, cv, stream);
+    if (st_patch != BNN_ERR_UNSUPPORTED || ceil_div(M, 256) * ceil_div(N, 128) <= max_blocks(256)) return st_patch;
+    // More tiles than the gathering kernels can launch: strips, whatever part of the chip they leave idle.
+    return launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, false, ConvUse::any, stream);
 }
 
 // Convolution, 2 x 2 max pooling (stride 2), BatchNorm, Sign in one launch; bn.out is the pooled
 // packed NHWC map [B][Ho/2][Wo/2][ld_out].  BNN_ERR_UNSUPPORTED for what it does not take (the caller then pools the unpooled
 // output bits with bnn_maxpool_bits).  any_map: any even map of whole channel quads whose patch fits, not only the layers of
-// pool_fits.
+// pool_fits.  ConvUse::ask: BNN_OK, with nothing launched, for what it takes and is no slower than the two launches.
 int launch_conv_patch_pool_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                                 BnSignArgs bn, ConvArgs cv, bool any_map, void* stream) {
+                                 BnSignArgs bn, ConvArgs cv, bool any_map, ConvUse use, void* stream) {
     if (!aligned_to(B, 16) || ldb % 4 != 0) return BNN_ERR_UNSUPPORTED;
     PatchGeom pg;
     const bool whole_rows = (pool_fits(cv, 2) && patch_geometry(cv, 128, 128, kPatchMaxBytes, false, pg)) ||
                             (pool_fits(cv, 4) && patch_geometry(cv, 256, 256, kPatchMaxBytes, false, pg));
     if (any_map ? cv.Cw % 4 != 0 || ((cv.Ho | cv.Wo) & 1) : !whole_rows) return BNN_ERR_UNSUPPORTED;
-    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, true, stream);
+    const bool ask = use == ConvUse::ask;
+    const int st = launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, true, use, stream);
     if (st != BNN_ERR_UNSUPPORTED) return st;
     const ConvArgs units = pooled_units(cv);
-    if (!whole_rows && better_pooled_apart(cv, units, M, N)) return BNN_ERR_UNSUPPORTED;
+    if (ask && !whole_rows && better_pooled_apart(cv, units, M, N)) return BNN_ERR_UNSUPPORTED;
     auto fits = [&](int WM) {
         if (whole_rows && !pool_fits(cv, WM)) return false;
         return patch_geometry(units, 64 * WM, 64 * WM, kPatchMaxBytes, true, pg);
     };
+    if (ask) return fits(2) || fits(4) ? BNN_OK : BNN_ERR_UNSUPPORTED;
+    int st_patch = BNN_ERR_UNSUPPORTED;
     if (wants_small_tiles(M, N, K, true) && fits(2) && fits(1))
-        return launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
-    if (wants_big_tiles(M, N) && fits(4))
-        return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
-    if (fits(2)) return launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
-    if (fits(4)) return launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
-    return BNN_ERR_UNSUPPORTED;
+        st_patch = launch_patch<1, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    else if (wants_big_tiles(M, N) && fits(4))
+        st_patch = launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    else if (fits(2))
+        st_patch = launch_patch<2, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    else if (fits(4))
+        st_patch = launch_patch<4, true, true>(in, B, ldb, nullptr, 0, M, N, K, bn, units, pg, stream);
+    if (st_patch != BNN_ERR_UNSUPPORTED) return st_patch;
+    // A patch that only the strips' share of local memory holds, or more tiles than one launch does.
+    return launch_conv_strip_fused(in, B, ldb, M, N, K, bn, cv, true, ConvUse::any, stream);
 }
 
 }  // namespace bnn

@@ -510,9 +510,10 @@ static bool strips_preferred(const ConvArgs& cv, int64_t M, int64_t K, int64_t t
     return K > 512 || rows > 256;
 }
 
-// BNN_ERR_UNSUPPORTED, with nothing launched, for a layer that this kernel does not take or that is faster elsewhere.
+// BNN_ERR_UNSUPPORTED, with nothing launched, for a layer that this kernel does not take or, but for ConvUse::any, that is faster
+// elsewhere.
 int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                            BnSignArgs bn, ConvArgs cv, bool pool, void* stream) {
+                            BnSignArgs bn, ConvArgs cv, bool pool, ConvUse use, void* stream) {
     using namespace strip;
     if (!aligned_to(B, 16) || ldb % 4 != 0 || cv.Cw % 4 != 0 || K > kStripResidentMost * 512) return BNN_ERR_UNSUPPORTED;
     if (pool && ((cv.Ho | cv.Wo) & 1)) return BNN_ERR_UNSUPPORTED;
@@ -527,10 +528,11 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     if (pool) cv = pooled_units(cv);
     // Tiles start at multiples of the strips' rows, and 512 pixels further on.
     const int64_t tile = rows < BM ? rows : BM, align = rows <= BM ? rows : std::gcd(rows, int64_t(BM));
-    if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg) || !strips_preferred(cv, M, K, tiles_n, rows, pg.slots, tile))
-        return BNN_ERR_UNSUPPORTED;
+    if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg)) return BNN_ERR_UNSUPPORTED;
+    if (use != ConvUse::any && !strips_preferred(cv, M, K, tiles_n, rows, pg.slots, tile)) return BNN_ERR_UNSUPPORTED;
     const int64_t filters = int64_t(2) * pg.kq * PLANE_B * 8, patch = (int64_t(2) * pg.cqn * pg.slots + (pg.slots + 1) / 2) * 8;
     if (filters + patch > kStripLdsBytes) return BNN_ERR_UNSUPPORTED;
+    if (use == ConvUse::ask) return BNN_OK;
     const int64_t tiles = ceil_div(rows, BM), buffers = tiles < 3 ? tiles : 3;
     cut.ahead = tiles > 1 && pg.slots <= PF_SLOTS * T && pg.cqn <= PF_QUADS && filters + buffers * patch <= kStripLdsBytes;
     cut.tiles_n = int(tiles_n);

@@ -143,4 +143,8 @@ struct ConvArgs {
     int H, W, Cw, kh, kw, stride, pad, Ho, Wo;
 };
 
+// What a launcher of one of several kernels is to do: launch if it takes the layer and is the faster one (for whom this is asked),
+// launch if it takes the layer at all, or answer only, with nothing launched.
+enum class ConvUse { faster, any, ask };
+
 }  // namespace bnn

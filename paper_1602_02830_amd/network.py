@@ -158,9 +158,10 @@ class BinaryConvLayer:
         # Pooled, fused, implicit layers try the one-launch form first; the library refuses geometries whose
         # pooling windows do not fit its tiles (before launching anything), and the layer then keeps to
         # conv -> bnn_maxpool_bits.
-        # Other even maps take its form for any map, which the library refuses likewise.
+        # Other even maps take its form for any map where the library finds that faster than the two launches.
         self.pool_in_conv = bool(pool) and fused and implicit and self.Ho % pool == 0 and self.Wo % pool == 0
-        self.pool_windows = self.pool_in_conv
+        self.pool_windows = self.pool_in_conv and B.conv_pool_form(batch, H, W, self.Cin, self.Cout, self.kh, self.kw, stride, pad,
+                                                                   pool) == B.POOL_WINDOWS
 
     def forward(self, x_bits: torch.Tensor) -> torch.Tensor:
         """x_bits: packed NHWC int32 [B][H][W][Cin/32].  Returns packed NHWC [B][Ho][Wo][ceil(Cout/32)]."""

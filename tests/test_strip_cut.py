@@ -120,19 +120,35 @@ def test_convolution_strips_are_taken_where_they_are_faster(launches_of, B_, H, 
     want = strips(B_ * Ho * Wo, Cout, 128)
     assert st == 0 and (log == want) == taken
     if (Ho | Wo) % 2 == 0:
-        assert (st_pool, log_pool == want) in ((0, taken), (3, False))
+        assert st_pool in (0, 3) and (log_pool != want or taken)
 
 
-@pytest.mark.parametrize("B_,H,W,Cin,Cout,k,stride,pad,taken", [
+@pytest.mark.parametrize("B_,H,W,Cin,Cout,stride", [(38836, 96, 96, 384, 5410, 1), (131071, 64, 64, 256, 11136, 1),
+                                                    (280956, 14, 84, 128, 21632, 1), (44239, 96, 172, 128, 16640, 2)])
+def test_convolutions_of_more_tiles_than_one_launch_holds_take_strips(launches_of, B_, H, W, Cin, Cout, stride):  # noqa: F811
+    """Strips that leave much of the chip idle, and no tiled kernel that could launch."""
+    args = (A, B_, H, W, Cin, WB, 9 * Cin // 32, Cout, 3, 3, stride, 1)
+    tail = (THR, FLIP, OUT, (Cout + 31) // 32, 0)
+    want = strips(B_ * (H // stride) * (W // stride), Cout, 128)
+    plain, pooled, windows = launches_of(("bnn_conv_bn_sign_pack", (*args, *tail)), ("bnn_conv_pool_bn_sign_pack", (*args, 2, *tail)),
+                                         ("bnn_conv_pool_windows_bn_sign_pack", (*args, 2, *tail)))
+    assert plain == windows == [0, want] and pooled == ([0, want] if H == W == 64 else [3, []])
+
+
+@pytest.mark.parametrize("B_,H,W,Cin,Cout,k,stride,pad,faster", [
     (93, 28, 28, 768, 32, 3, 1, 1, False), (77, 28, 28, 768, 32, 3, 1, 1, True), (1, 56, 56, 512, 21028, 3, 1, 0, False),
     (5, 56, 183, 128, 17696, 3, 2, 1, False), (3, 32, 128, 512, 128, 3, 1, 1, False), (14, 16, 128, 128, 128, 7, 1, 3, False),
     (30, 16, 128, 128, 128, 7, 1, 3, True), (59, 26, 26, 1024, 384, 1, 1, 0, False), (15, 28, 14, 1024, 1718, 1, 1, 0, True),
-    (2, 6, 6, 128, 70, 3, 1, 1, True), (8, 64, 64, 96, 64, 3, 1, 1, False)])
-def test_pooled_maps_are_taken_in_one_launch_where_that_is_faster(launches_of, B_, H, W, Cin, Cout, k, stride, pad, taken):  # noqa: F811
+    (2, 6, 6, 128, 70, 3, 1, 1, True), (8, 60, 60, 96, 64, 3, 1, 1, False)])
+def test_pooled_maps_are_taken_and_advised_where_one_launch_is_faster(launches_of, B_, H, W, Cin, Cout, k, stride, pad, faster):  # noqa: F811
+    """The call takes any even map of whole channel quads; bnn_conv_pool_form names it where it is the faster form."""
     words = -(-k * k * Cin // 128) * 4
-    (st, log), = launches_of(("bnn_conv_pool_windows_bn_sign_pack", (A, B_, H, W, Cin, WB, words, Cout, k, k, stride, pad, 2, THR,
-                                                                     FLIP, OUT, (Cout + 31) // 32, 0)))
-    assert (st, len(log)) == ((0, 1) if taken else (3, 0))
+    (st, log), (form, none) = launches_of(
+        ("bnn_conv_pool_windows_bn_sign_pack", (A, B_, H, W, Cin, WB, words, Cout, k, k, stride, pad, 2, THR, FLIP, OUT,
+                                                (Cout + 31) // 32, 0)),
+        ("bnn_conv_pool_form", (B_, H, W, Cin, Cout, k, k, stride, pad, 2)))
+    assert (st, len(log)) == ((0, 1) if Cin % 128 == 0 else (3, 0))
+    assert (form, none) == (2 if faster else 0, [])
 
 
 @pytest.mark.parametrize("B_,H,W,Cin", [(4, 32, 32, 96), (3, 8, 8, 64), (40, 32, 32, 768), (2, 64, 64, 128)])
@@ -140,7 +156,10 @@ def test_pooled_maps_of_whole_rows_keep_their_call(launches_of, B_, H, W, Cin): 
     """What bnn_conv_pool_bn_sign_pack takes, the call for any map takes as well with the same launch where Cin is a multiple of 128."""
     words = -(-9 * Cin // 128) * 4
     args = (A, B_, H, W, Cin, WB, words, 64, 3, 3, 1, 1, 2, THR, FLIP, OUT, 2, 0)
-    (st, log), (st_any, log_any) = launches_of(("bnn_conv_pool_bn_sign_pack", args), ("bnn_conv_pool_windows_bn_sign_pack", args))
+    (st, log), (st_any, log_any), (form, _) = launches_of(("bnn_conv_pool_bn_sign_pack", args),
+                                                          ("bnn_conv_pool_windows_bn_sign_pack", args),
+                                                          ("bnn_conv_pool_form", (B_, H, W, Cin, 64, 3, 3, 1, 1, 2)))
+    assert form == 1
     assert st == 0 and len(log) == 1
     assert (st_any, log_any) == ((0, log) if Cin % 128 == 0 else (3, []))
 
