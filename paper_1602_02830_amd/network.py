@@ -155,13 +155,14 @@ class BinaryConvLayer:
             self.Hp, self.Wp = (self.Ho - pool) // pool + 1, (self.Wo - pool) // pool + 1
             self.pooled = torch.empty((batch, self.Hp, self.Wp, B.words_per_row(self.Cout)), dtype=torch.int32,
                                       device=dev)
-        # Pooled, fused, implicit layers try the one-launch form first; the library refuses geometries whose
-        # pooling windows do not fit its tiles (before launching anything), and the layer then keeps to
-        # conv -> bnn_maxpool_bits.
-        # Other even maps take its form for any map where the library finds that faster than the two launches.
-        self.pool_in_conv = bool(pool) and fused and implicit and self.Ho % pool == 0 and self.Wo % pool == 0
-        self.pool_windows = self.pool_in_conv and B.conv_pool_form(batch, H, W, self.Cin, self.Cout, self.kh, self.kw, stride, pad,
-                                                                   pool) == B.POOL_WINDOWS
+        # Pooled, fused, implicit layers run in one launch where the library has a form for them that is not slower than
+        # conv -> bnn_maxpool_bits.  A call that refuses its buffers all the same (an input that is not 16-byte aligned), which it does
+        # before launching anything, turns its form off.
+        form = B.POOL_APART
+        if pool and fused and implicit:
+            form = B.conv_pool_form(batch, H, W, self.Cin, self.Cout, self.kh, self.kw, stride, pad, pool)
+        self.pool_in_conv = form == B.POOL_IN_CONV
+        self.pool_windows = form == B.POOL_WINDOWS
 
     def forward(self, x_bits: torch.Tensor) -> torch.Tensor:
         """x_bits: packed NHWC int32 [B][H][W][Cin/32].  Returns packed NHWC [B][Ho][Wo][ceil(Cout/32)]."""

@@ -9,6 +9,7 @@ import torch
 
 import oracle
 import paper_1602_02830_amd as bnn
+from paper_1602_02830_amd import network
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
@@ -1479,6 +1480,30 @@ def test_conv_pool_layer_refuses_what_does_not_fit_its_tiles():
     assert (out == oracle.pack_bits(a_want.reshape(-1, 128))).all() and not conv.pool_in_conv
 
 
+@pytest.mark.parametrize("H,Cin,pool,form", [(6, 128, 2, "windows"), (8, 128, 2, "rows"), (7, 128, 2, "apart"), (12, 128, 3, "apart"),
+                                             (12, 64, 2, "apart"), (12, 96, 2, "apart")])
+def test_conv_layer_pools_in_the_form_that_takes_its_map(H, Cin, pool, form, monkeypatch):
+    """One pooled call per forward, never one that is known to refuse; conv and bnn_maxpool_bits for what neither takes."""
+    rng = np.random.default_rng(H + Cin + pool)
+    Bt, Cout = 3, 70
+    x, Wt = synth.pm1(rng, (Bt, H, H, Cin)), synth.pm1(rng, (Cout, 3, 3, Cin))
+    bn = synth.bn_params(rng, Cout, 9 * Cin, adversarial=True)
+    conv = bnn.BinaryConvLayer(torch.from_numpy(Wt.astype(np.float32)).to(DEV), bn, EPS, Bt, H, H, fused=True, implicit=True, pool=pool)
+    assert (conv.pool_in_conv, conv.pool_windows) == (form == "rows", form == "windows")
+    calls = []
+    for name in ("conv_pool_bn_sign_pack", "conv_pool_windows_bn_sign_pack", "maxpool_bits"):
+        def counted(*a, _call=getattr(network.B, name), _name=name, **k):
+            calls.append(_name)
+            return _call(*a, **k)
+        monkeypatch.setattr(network.B, name, counted)
+    xb = words_to_dev(_pack_nhwc(x).reshape(-1, Cin // 32)).view(Bt, H, H, Cin // 32)
+    _P, a_want = oracle.conv_pool_layer(x, Wt, bn, pool=pool, eps=EPS)
+    for _ in range(2):
+        out = words_to_host(conv.forward(xb).reshape(-1, (Cout + 31) // 32))
+        assert (out == oracle.pack_bits(a_want.reshape(-1, Cout))).all()
+    assert calls == 2 * [{"rows": "conv_pool_bn_sign_pack", "windows": "conv_pool_windows_bn_sign_pack"}.get(form, "maxpool_bits")]
+
+
 @pytest.mark.parametrize("M,N,K", [
     (638, 8192, 577),        # strips of 160 rows, a K of one bit in its last word and quad
     (1000, 8100, 640),       # 256, whole quads, columns that do not exist
@@ -1544,7 +1569,9 @@ def test_first_layer_on_bytes_in_strips(M, N, K, bytes_):
 @pytest.mark.parametrize("shape", [
     # B, H, W, Cin, Cout, window, stride, pad: the rows of a strip (one per compute unit and column tile) in the comment
     (90, 12, 10, 128, 500, 3, 1, 1),      # 192 of one tile: one or two blocks of 32 per wavefront
-    (41, 30, 30, 128, 450, 3, 1, 1),      # 608 = 512 + 96: a wavefront without rows in the last tile
+    (41, 30, 30, 128, 450, 3, 1, 1),      # tiles of 256 pixels, in any order and in window order
+    (41, 30, 30, 256, 450, 3, 1, 1),      # 608 = 512 + 96: a wavefront without rows in the last tile
+    (3, 8, 96, 128, 40, 3, 1, 1),         # wide even maps in few small tiles
     (130, 30, 30, 128, 500, 3, 1, 1),     # 1856 = 3 x 512 + 320: every patch buffer used twice
     (60, 32, 30, 256, 385, 3, 1, 1),      # 928, two quads per cell, a column tile of one column
     (100, 20, 22, 384, 390, 3, 1, 1),     # 704, three quads per cell: one patch buffer
