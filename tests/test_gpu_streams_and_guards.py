@@ -223,6 +223,59 @@ def test_entry_point_on_two_streams_with_guards_around_the_output(cases, name):
     assert (got2 == want).all(), f"{name}: second stream"
 
 
+def _large_case(name):
+    """(rows, words or columns of the output, launch, expected): sizes that the strip kernels, the long-K tiles and the windows form of
+    the pooled convolution take, against other kernels."""
+    g = torch.Generator(device=DEV).manual_seed(len(name))
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    kind, *sizes = name.split()
+    sizes = [int(v) for v in sizes]
+    N = sizes[4] if kind in ("conv", "pooled") else sizes[1]
+    nw = (N + 31) // 32
+    thr = torch.randint(-60, 60, (N,), generator=g, device=DEV, dtype=torch.int32)
+    flip = words(nw)
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    if kind in ("conv", "pooled"):
+        B, H, W, Cin, _ = sizes
+        x, w = words(B, H, W, Cin // 32), words(N, 9 * Cin // 32)
+        want = bnn.xnor_gemm_bn_sign_pack(bnn.conv_im2col_pack(x, Cin), w, 9 * Cin, thr, flip, kernel=bnn.KERNEL_TILED64)
+        if kind == "conv":
+            return B * H * W, nw, lambda o: bnn.conv_bn_sign_pack(x, Cin, w, thr, flip, out=o), want
+        want = bnn.maxpool_bits(want.view(B, H, W, nw), N, flip).reshape(-1, nw)
+        return B * H * W // 4, nw, lambda o: bnn.conv_pool_windows_bn_sign_pack(x, Cin, w, thr, flip, out=o), want
+    M, _, K = sizes
+    w = words(N, (K + 31) // 32)
+    if kind == "bytes":
+        x = bnn.pack_bitplanes(torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8))
+        thr *= 60
+        want = bnn.bn_sign_pack(bnn.bitplane_gemm(x, w, K), thr, flip)
+        return M, nw, lambda o: bnn.bitplane_gemm_bn_sign_pack(x, w, K, thr, flip, out=o), want
+    x = words(M, (K + 31) // 32)
+    if kind == "int32":
+        return M, N, lambda o: bnn.xnor_gemm(x, w, K, out=o), bnn.xnor_gemm(x, w, K, kernel=bnn.KERNEL_TILED64)
+    want = bnn.xnor_gemm_bn_sign_pack(x, w, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    return M, nw, lambda o: bnn.xnor_gemm_bn_sign_pack(x, w, K, thr, flip, out=o), want
+
+
+@pytest.mark.parametrize("name", [
+    "fused 638 8192 577", "fused 4097 8160 896",                    # row strips of one tile and of three
+    "bytes 2070 8192 784",                                          # 8-bit strips
+    "conv 41 30 30 256 450", "pooled 41 30 30 256 450",             # convolution strips of 608 rows
+    "pooled 2 12 40 128 70", "pooled 1 6 96 256 33", "pooled 3 6 6 128 97",       # pooling windows of few tiles
+    "int32 1000 1000 4225", "fused 1000 1000 4225", "int32 130 700 8260", "fused 100 1000 8192"])
+def test_large_forms_on_two_streams_with_guards_around_the_output(name):
+    rows, cols, launch, want = _large_case(name)
+    want = want.cpu().numpy()
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        g = Guarded(rows, cols)
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            launch(g.view)
+        stream.synchronize()
+        assert (g.result_and_check() == want).all(), name
+
+
 def test_unpack_i8_with_guards_on_two_streams():
     """bnn_unpack_i8 allocates its int8 output itself in the binding, so it is called through the C ABI here:
     rows of K = 1000 values inside a guarded int8 array with ld_out = 1008."""
@@ -297,6 +350,12 @@ def _call_forms():
         ("conv layer, transposed map", bnn.conv_bn_sign_pack, (maps.transpose(1, 2), 128, filt, thr, flip), lambda: out(128, 3)),
         ("pooled layer", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(32, 3)),
         ("pooled layer, wrong rows", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(31, 3)),
+        ("windows layer", bnn.conv_pool_windows_bn_sign_pack, (maps[:, :6], 128, filt, thr, flip), lambda: out(24, 3)),
+        ("windows layer, even map", bnn.conv_pool_windows_bn_sign_pack, (maps[:1, :6], 128, filt, thr, flip), lambda: out(12, 3)),
+        ("windows layer, odd map", bnn.conv_pool_windows_bn_sign_pack, (maps[:1, :7], 128, filt, thr, flip), lambda: out(12, 3)),
+        ("windows layer, wrong rows", bnn.conv_pool_windows_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(31, 3)),
+        ("windows layer, short thresholds", bnn.conv_pool_windows_bn_sign_pack, (maps, 128, filt, thr[1:], flip), lambda: out(32, 3)),
+        ("windows layer, window 3", bnn.conv_pool_windows_bn_sign_pack, (maps, 128, filt, thr, flip, 3, 3, 1, 1, 3), lambda: out(8, 3)),
         ("pooled layer, window 3", bnn.conv_pool_bn_sign_pack, (maps, 128, filt, thr, flip, 3, 3, 1, 1, 3), lambda: out(8, 3)),
         ("pooling", bnn.maxpool_bits, (maps, 128, None), lambda: out(32, 4).view(2, 4, 4, 4)),
         ("pooling, flips", bnn.maxpool_bits, (maps, 128, bits(1, 4)[0]), lambda: out(32, 4).view(2, 4, 4, 4)),
@@ -322,6 +381,9 @@ def _call_forms():
         ("refused: bytes layer, narrow weights", bnn.bitplane_gemm_bn_sign_pack, (planes, w[:, :5], K, thr, flip), lambda: out(M, 3)),
         ("refused: conv, narrow filters", bnn.conv_xnor, (maps, 128, filt[:, :35]), lambda: out(128, N)),
         ("refused: conv layer, narrow filters", bnn.conv_bn_sign_pack, (maps, 128, filt[:, :35], thr, flip), lambda: out(128, 3)),
+        ("refused: windows layer, narrow filters", bnn.conv_pool_windows_bn_sign_pack, (maps, 128, filt[:, :35], thr, flip),
+         lambda: out(32, 3)),
+        ("refused: windows layer, a narrow output", bnn.conv_pool_windows_bn_sign_pack, (maps, 128, filt, thr, flip), lambda: out(32, 2)),
         ("refused: pooled layer, narrow filters", bnn.conv_pool_bn_sign_pack, (maps, 128, filt[:, :35], thr, flip), lambda: out(32, 3)),
     ]
     return forms

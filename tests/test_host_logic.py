@@ -144,6 +144,23 @@ def test_argument_validation_of_the_fused_bitplane_and_conv_entry_points():
     assert lib.bnn_conv_pool_bn_sign_pack(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == UNSUPPORTED
     assert lib.bnn_conv_pool_bn_sign_pack(p, 1, 4, 4, 128, p, 36, 4, 3, 3, 2, 1, 2, p, p, p, 1, None) == UNSUPPORTED
     assert lib.bnn_conv_pool_bn_sign_pack(p, 0, 4, 4, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == 0
+    windows = lib.bnn_conv_pool_windows_bn_sign_pack       # even maps of any size, whole channel quads, 16-byte aligned operands
+    assert windows(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 0, p, p, p, 1, None) == INVALID
+    assert windows(p, 1, 6, 6, 128, p, 36, 40, 3, 3, 1, 1, 2, p, p, p, 1, None) == INVALID
+    assert windows(p, 1, 6, 6, 128, p, 35, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == INVALID
+    assert windows(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 2, None, p, p, 1, None) == INVALID
+    assert windows(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, None, 1, None) == INVALID
+    assert windows(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, p + 2, 1, None) == ALIGN
+    assert windows(p, 1, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 3, p, p, p, 1, None) == UNSUPPORTED
+    assert windows(p, 1, 6, 7, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == UNSUPPORTED
+    assert windows(p, 1, 6, 6, 64, p, 20, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == UNSUPPORTED
+    assert windows(p, 1, 6, 6, 128, p, 38, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == UNSUPPORTED
+    assert windows(p, 0, 6, 6, 128, p, 36, 4, 3, 3, 1, 1, 2, p, p, p, 1, None) == 0
+    # which form of a pooled layer is the fastest: no buffers, no launch, nothing refused
+    form = bnn.conv_pool_form
+    assert [form(1, n, n, c, 4) for n, c in ((8, 128), (8, 64), (6, 128), (6, 64), (7, 128))] == [1, 1, 2, 0, 0]
+    assert form(2, 8, 8, 128, 4, pool=3) == form(2, 8, 8, 128, 4, stride=0) == form(0, 8, 8, 128, 4) == form(1, 8, 8, 2 ** 31, 4) == 0
+    assert form(2, 8, 8, 128, 4, 2 ** 31 - 1, 2 ** 31 - 1, 1, 2 ** 30) == form(2, 8, 8, 128, -1) == form(2, 8, 8, 96, 2 ** 31) == 0
     # pooling on bits: window larger than the map, zero stride, empty batch
     assert lib.bnn_maxpool_bits(p, 1, 2, 2, 32, 3, 3, 1, None, p, None) == INVALID
     assert lib.bnn_maxpool_bits(p, 1, 4, 4, 32, 2, 2, 0, None, p, None) == INVALID
