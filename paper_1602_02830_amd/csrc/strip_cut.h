@@ -27,13 +27,14 @@ inline bool strips_fill(int64_t M, int64_t tiles_n, int64_t rows, int percent) {
 }
 
 // Rows [begin, end) of strip `group`.  `rows` is rounded up for every strip, so begin + rows can pass M by thousands of rows and,
-// near the largest M, 2^31: what is left of the matrix is compared instead.
+// near the largest M, 2^31 (not 2^32): that sum is unsigned.
 struct StripRows {
     int begin, end;
 };
 __host__ __device__ inline StripRows strip_rows(int group, int rows, int M) {
-    const int begin = group * rows, left = M - begin;
-    return StripRows{begin, begin + (rows < left ? rows : left)};
+    const int begin = group * rows;
+    const uint32_t past = uint32_t(begin) + uint32_t(rows);
+    return StripRows{begin, int(past < uint32_t(M) ? past : uint32_t(M))};
 }
 
 }  // namespace bnn
