@@ -3,12 +3,15 @@
 // bnn_conv_xnor / bnn_conv_bn_sign_pack: a kh x kw binary convolution (3 x 3 in the paper's
 // nets, Sec. 3.3) as the XnorDotProduct of Alg. 4 over receptive fields that the GEMM's tile
 // loader gathers straight from the packed NHWC input (taps outside the image are +1: zero
-// padding through Eq. (1)).  The kernels: the LDS-patch kernel (conv_patch.hip) wherever the
-// input patch of a tile fits, else the conv modes of the matrix-engine
+// padding through Eq. (1)).  The kernels: fused layers that fill the chip in equal strips of pixels, filters resident
+// (conv_strip.hip); the LDS-patch kernel (conv_patch.hip) wherever the
+// input patch of a tile fits; else the conv modes of the matrix-engine
 // GEMMs (xnor_gemm_mfma.hip, xnor_gemm_mfma_shortk.hip); launch_conv_mfma chooses.
 //
 // bnn_conv_pool_bn_sign_pack: the same layer with the paper's 2 x 2 max pooling between the
-// convolution and BatchNorm + Sign, in one launch (LDS-patch kernel only).
+// convolution and BatchNorm + Sign, in one launch (strips and the LDS-patch kernel), on tiles of whole image rows.
+// bnn_conv_pool_windows_bn_sign_pack: on any even map whose patch fits.  bnn_conv_pool_form: which of the two, or
+// neither, is the fastest form of a layer.
 //
 // bnn_maxpool_bits: the paper's ConvNets pool the integer pre-activations before BatchNorm and
 // Sign.  Sign(BatchNorm(.)) is monotone per channel - non-decreasing where the folded flip bit

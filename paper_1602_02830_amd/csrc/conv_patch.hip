@@ -38,9 +38,10 @@
 // with ldb % 4 == 0, a patch within kPatchMaxBytes of LDS, and Cin % 128 == 0 - or Cin % 32 == 0 for same-size stride-1
 // layers whose tiles are whole image rows or images, with a receptive field of at most kResidentKTiles * 512 bits.
 // Some layers that would fit are faster gathered (better_gathered).
-// Against gathering the receptive fields K-tile by K-tile, fused: 128 images of 28 x 28, 128 -> 256 channels 22.4 -> 18.9
-// us, 200 of 13 x 13, 128 -> 396 17.8 -> 13.9, 100 of 14 x 14, 256 -> 256 13.4 -> 11.7, 256 of 32 x 32, 128 -> 256 at
-// stride 2 15.5 -> 13.0, 128 of 56 x 56, 128 -> 128 37.0 -> 31.6.
+// Fused layers that fill the chip in strips leave before these tiles are chosen (conv_strip.hip).
+// Against gathering the receptive fields K-tile by K-tile, fused, on layers that now run in strips: 128 images of 28 x 28, 128 -> 256
+// channels 22.4 -> 18.9 us, 200 of 13 x 13, 128 -> 396 17.8 -> 13.9, 100 of 14 x 14, 256 -> 256 13.4 -> 11.7, 256 of 32 x 32, 128 -> 256
+// at stride 2 15.5 -> 13.0, 128 of 56 x 56, 128 -> 128 37.0 -> 31.6; as int32, which stays here, 128 of 28 x 28, 128 -> 256 30.1 -> 25.6.
 #include "bnn_internal.h"
 #include "conv_patch_geometry.h"
 #include "gemm_staging.h"

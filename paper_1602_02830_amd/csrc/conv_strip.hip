@@ -51,17 +51,6 @@ struct Cut {
     int ahead;                 // whether the next patch is loaded under the products, into another of up to three buffers
 };
 
-// After every product: VALU vector operations and, with READ, one LDS read.
-#define BNN_STRIP_SCHEDULE(MFMAS, READ, VALU)                               \
-    do {                                                                    \
-        _Pragma("unroll") for (int g_ = 0; g_ < (MFMAS); ++g_) {            \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              \
-            __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);           \
-            if (READ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    \
-        }                                                                   \
-        __builtin_amdgcn_sched_barrier(0);                                  \
-    } while (0)
-
 // A tile and its patch: unit row and column (in the image) and image of the tile's first unit, first padded row of the patch in
 // that image, cells up to the end of the tile's last window, first row of the image that can be among them, and that row's
 // address.  Units: pixels, or (POOL) pooling
@@ -169,7 +158,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, int M, int N, int K, BnSignArgs bn,
     ConvArgs cv, PatchGeom pg, Cut cut, int n_images) {
     constexpr int WN = 2, PF = POOL ? 2 : 1;           // POOL: rows are the pixels of one pooling window after the other
-    extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // filters, then one or two patches with their pixel popcounts
+    extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // filters, then up to three patches with their pixel popcounts
     __shared__ float colfix_s[BN];
     __shared__ uint32_t flip_s[BN / 32];
     const int cqn = pg.cqn, slots = pg.slots, kq = pg.kq;
@@ -480,6 +469,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
 
 constexpr int kStripResident = 5, kStripResidentMost = 9;     // K-tiles of 512 bits of the resident filters
 constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, beside what the kernel declares itself
+static_assert(starts_in_bf16_pairs(kStripResidentMost * 512));
 // Strips of more than 128 rows, a block row for each of the four wavefronts along the pixels and more.  us, conv_patch.hip and
 // strips: 192 rows 48 of 32 x 32, 128 -> 128 7.8 and 6.8, 96 of 16 x 16, 256 -> 256 11.3 and 9.0, 160 of 8 x 8, 512 -> 512 (160
 // rows) 18.2 and 14.6; with 128 rows 64 of 16 x 16, 256 -> 256 8.65 and 8.6, 128 -> 256 6.5 and 6.7.  Windows that do not overlap

@@ -269,12 +269,25 @@ __device__ inline uint32_t pool_words(uint32_t word, uint32_t flip_word) {
     return (any & ~flip_word) | (all & flip_word);
 }
 
-// Integers n / 8 of at most 16 bits as two bf16 numbers: the upper eight bits and the rest, both exact.
+// Integers n / 8 of at most 16 bits as two bf16 numbers: the upper eight bits and the rest, both exact.  The largest that start an
+// accumulator, in eighths: 4K + 3, the column term of a threshold -K - 1 or K + 1 (fold_column_term); -pa / 2 has 4K.
+constexpr bool starts_in_bf16_pairs(int K) { return 4 * K + 3 < 1 << 16; }
 typedef short v4s __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void split_bf16(float v, short& hi, short& lo) {
     const uint32_t top = __float_as_uint(v) & 0xFFFF0000u;
     hi = short(top >> 16);
     lo = short(__float_as_uint(v - __uint_as_float(top)) >> 16);
 }
+
+// The K loops of the strip kernels.  After every product: VALU vector operations and, with READ, one LDS read.
+#define BNN_STRIP_SCHEDULE(MFMAS, READ, VALU)                               \
+    do {                                                                    \
+        _Pragma("unroll") for (int g_ = 0; g_ < (MFMAS); ++g_) {            \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              \
+            __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);           \
+            if (READ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    \
+        }                                                                   \
+        __builtin_amdgcn_sched_barrier(0);                                  \
+    } while (0)
 
 }  // namespace bnn

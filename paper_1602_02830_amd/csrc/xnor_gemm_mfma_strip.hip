@@ -33,16 +33,6 @@ struct Cut {
     int rows;                  // rows per strip, a multiple of 32
 };
 
-#define BNN_ROW_STRIP_SCHEDULE(MFMAS, READ, VALU)                           \
-    do {                                                                    \
-        _Pragma("unroll") for (int g_ = 0; g_ < (MFMAS); ++g_) {            \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              \
-            __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);           \
-            if (READ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    \
-        }                                                                   \
-        __builtin_amdgcn_sched_barrier(0);                                  \
-    } while (0)
-
 __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32_t* __restrict__ A, int64_t lda,
                                                                     const uint32_t* __restrict__ B, int64_t ldb, int M, int N,
                                                                     int K, BnSignArgs bn, Cut cut) {
@@ -188,14 +178,14 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
                 for (int j = 0; j < WN; ++j) hb[j] = widen4_b(bw[j].y);
                 read_words();
                 multiply(fa, fb);
-                BNN_ROW_STRIP_SCHEDULE(NB * WN, true, VALU);
+                BNN_STRIP_SCHEDULE(NB * WN, true, VALU);
                 if (q + 1 == kq && half_end) continue;
 #pragma unroll
                 for (int i = 0; i < NB; ++i) fa[i] = widen4_a(aw[i].x);
 #pragma unroll
                 for (int j = 0; j < WN; ++j) fb[j] = widen4_b(bw[j].x);
                 multiply(ha, hb);
-                BNN_ROW_STRIP_SCHEDULE(NB * WN, false, VALU);
+                BNN_STRIP_SCHEDULE(NB * WN, false, VALU);
             }
             if (more) {                                // the other buffer: left by every wavefront before this tile's barrier
                 store_a(next[0], 2 * part, buf ^ 1);
@@ -258,6 +248,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 // x 784, 72 %, 53.7 and 60.9, 10000 x 16512 x 784, 50 %, 82 and 116; 10000 x 5504 x 784, 83 %, level, 4000 x 32768 x 784, 98 %, 53.3
 // and 49.4).  A last tile counts as half of one at least (4141 x 7168 x 810, 1056 rows, 15.9 and 17.6).
 constexpr int64_t kRowStripMinRows = 160;
+static_assert(starts_in_bf16_pairs(128 * row_strip::MAX_QUADS));
 
 // BNN_ERR_UNSUPPORTED, with nothing launched, for a product that this kernel does not take or that is faster elsewhere.
 int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
