@@ -1532,8 +1532,8 @@ def test_fused_products_of_short_rows_in_strips(M, N, K, tight):
 
 @pytest.mark.parametrize("M,N,K", [
     (2070, 8192, 784),       # strips of 160 rows: 128 + 32, a last K-tile of one word
-    (2400, 8192, 257),       # three K-tiles, the last of one bit
-    (2500, 7930, 384),       # 160: K of whole K-tiles, columns that do not exist
+    (2400, 8192, 257),       # tiles: K of one bit past two K-tiles
+    (2500, 7930, 384),       # tiles: K of whole K-tiles, columns that do not exist
     (3300, 8192, 448),       # 224 = 128 + 96, a last K-tile of two words
     (3000, 8150, 470),       # 192, of three words
     (6170, 8192, 1000),      # 416 = 3 x 128 + 32: every buffer and both sets of row sums reused
