@@ -643,6 +643,18 @@ static bool better_pooled_apart(const ConvArgs& cv, const ConvArgs& units, int64
     return rounds(pooled) > rounds(plain);
 }
 
+// Whether three tiles of 256 pixels share a compute unit's local memory beside their resident filters (512 bits of K are 8 KB), four
+// of 128 where the patch of 256 does not fit; layers that are gathered have no patch.  cv: the layer, its pooled_units if pool.
+bool conv_patch_tiles_fill(const ConvArgs& cv, bool pool, int64_t K) {
+    PatchGeom pg;
+    auto fit = [&](int WM) {
+        const int64_t patch = int64_t(pg.slots) * cv.Cw * 4 + (pg.slots + 1) / 2 * 8;
+        return 160 * 1024 / (patch + ceil_div(K, 512) * 8 * (128 + 2) * int64_t(sizeof(uint2)) + (2 + WM) * 1024);
+    };
+    if (patch_geometry(cv, 256, 256, kPatchMaxBytes, pool, pg)) return fit(4) >= 3;
+    return !patch_geometry(cv, 128, 128, kPatchMaxBytes, pool, pg) || fit(2) >= 4;
+}
+
 int launch_conv_patch(const uint32_t* in, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc, int64_t M,
                       int64_t N, int64_t K, ConvArgs cv, void* stream) {
     return launch_conv_patch_any<false>(in, B, ldb, C, ldc, M, N, K, BnSignArgs{}, cv, stream);

@@ -467,6 +467,9 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
 
 }  // namespace strip
 
+// Whether the tiles of conv_patch.hip that the layer would take fill a compute unit (there).
+bool conv_patch_tiles_fill(const ConvArgs& cv, bool pool, int64_t K);
+
 constexpr int kStripResident = 5, kStripResidentMost = 9;     // K-tiles of 512 bits of the resident filters
 constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, beside what the kernel declares itself
 static_assert(starts_in_bf16_pairs(kStripResidentMost * 512));
@@ -482,17 +485,24 @@ constexpr int64_t kStripMinRows = 160;
 //  - enough of the chip at work: 60 % with strips of one tile, 80 % up to four, 86 % beyond (41 images of 16 x 16, 256 -> 8576,
 //    78 %, 75.5 and 79.1; 47 of 14 x 14, 512 -> 12288, 75 %, 169 and 190), 93 % with K <= 1152, whose tiles are short (40 of 28 x 28,
 //    128 -> 9984, 91 %, 138 and 148; 58 of 32 x 32, 128 -> 4700 pooled, 87 %, 123 and 139);
-//  - K <= 1152 not with 577 to 768 rows: two and a half to three tiles of 256 pixels per compute unit, which hold two at a time and
-//    the third alone (3 x 3, 185 of 16 x 16, 128 -> 512, 740 rows, 13.7 and 14.9; 73 of 14 x 51, 256 -> 512, 1 x 4, 12.6 and 14.8; but
-//    544 rows, 272 of 14 x 14, 128 -> 1159 at stride 2 19.6 and 14.5, 800 rows and more 1.1 to 1.25 times faster);
+//  - K <= 1536: whatever follows holds only for layers whose tiles fill a compute unit (conv_patch_tiles_fill: three of 256 pixels or
+//    four of 128; gathered layers).  Of 5700 layers, those whose larger patches leave it with fewer are 1.02 to 1.45 times faster in
+//    strips (225 of 28 x 28, 128 -> 512 at stride 2, two tiles, 19.6 and 16.1; 228 of 34 x 92, 256 -> 512, 3 x 1, pooled 154 and 130),
+//    but for K <= 512 with a patch that is mostly not read (14685 of 28 x 19, 128 -> 64, 4 x 1 at stride 3 0.82 times as fast);
+//  - K <= 1152 not with 577 to 768 rows: the three tiles of a compute unit are one round (3 x 3, 185 of 16 x 16, 128 -> 512, 740 rows,
+//    13.7 and 14.9; 73 of 14 x 51, 256 -> 512, 1 x 4, 12.6 and 14.8; 800 rows and more 1.1 to 1.25 times faster in strips);
 //  - fewer than nine taps reuse little of a patch.  Their tiles win where most of the strip's patch is not read (more than eight
 //    cells per pixel: 571 of 32 x 32, 384 -> 128, 1 x 4 at stride 3 8.8 and 10.9), in strips of more than two tiles with K < 1152
 //    (145 of 89 x 89, 128 -> 128, 7 x 1 65.3 and 75.2), two taps (189 of 56 x 56, 1024 -> 128, 2 x 1 64.5 and 74.2) or up to four of
 //    K <= 1536 on dense patches (493 of 28 x 28, 384 -> 384, 4 x 1 93.8 and 109), and in the shortest strips with K <= 512 (64 of
 //    32 x 32, 128 -> 128, 1 x 4 5.7 and 6.0).
-static bool strips_preferred(const ConvArgs& cv, int64_t M, int64_t K, int64_t tiles_n, int64_t rows, int64_t cells, int64_t pixels) {
+// cv: the layer, its pooled_units if pool.
+static bool strips_preferred(const ConvArgs& cv, bool pool, int64_t M, int64_t K, int64_t tiles_n, int64_t rows, int64_t cells,
+                             int64_t pixels) {
     const int64_t tiles = ceil_div(rows, strip::BM), taps = int64_t(cv.kh) * cv.kw;
     if (!strips_fill(M, tiles_n, rows, tiles == 1 ? 60 : tiles <= 4 ? 80 : K <= 1152 ? 93 : 86)) return false;
+    if (taps < 9 && K <= 512 && cells > 8 * pixels) return false;
+    if (K <= 1536 && !conv_patch_tiles_fill(cv, pool, K)) return true;
     if (K <= 1152 && rows > 576 && rows <= 768) return false;
     if (taps >= 9) return true;
     if (K <= 1536 && cells > 8 * pixels) return false;
@@ -519,7 +529,7 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     // Tiles start at multiples of the strips' rows, and 512 pixels further on.
     const int64_t tile = rows < BM ? rows : BM, align = rows <= BM ? rows : std::gcd(rows, int64_t(BM));
     if (!patch_geometry(cv, tile, align, kStripLdsBytes, pool, pg)) return BNN_ERR_UNSUPPORTED;
-    if (use != ConvUse::any && !strips_preferred(cv, M, K, tiles_n, rows, pg.slots, tile)) return BNN_ERR_UNSUPPORTED;
+    if (use != ConvUse::any && !strips_preferred(cv, pool, M, K, tiles_n, rows, pg.slots, tile)) return BNN_ERR_UNSUPPORTED;
     const int64_t filters = int64_t(2) * pg.kq * PLANE_B * 8, patch = (int64_t(2) * pg.cqn * pg.slots + (pg.slots + 1) / 2) * 8;
     if (filters + patch > kStripLdsBytes) return BNN_ERR_UNSUPPORTED;
     if (use == ConvUse::ask) return BNN_OK;

@@ -109,7 +109,9 @@ def test_byte_layer_strips_are_taken_where_they_fill_the_chip(launches_of, M, N,
     (185, 16, 16, 128, 512, (3, 3), 1, 1, False), (140, 16, 16, 128, 512, (3, 3), 1, 1, True), (200, 16, 16, 128, 512, (3, 3), 1, 1, True),
     (185, 16, 16, 256, 512, (3, 3), 1, 1, True), (73, 14, 51, 256, 512, (1, 4), 1, 0, False),
     (571, 32, 32, 384, 128, (1, 4), 3, 0, False), (145, 89, 89, 128, 128, (7, 1), 1, 3, False), (189, 56, 56, 1024, 128, (2, 1), 1, 0, False),
-    (493, 28, 28, 384, 384, (4, 1), 1, 2, False), (64, 32, 32, 128, 128, (1, 4), 1, 0, False), (100, 32, 32, 256, 128, (1, 4), 1, 0, True)])
+    (493, 28, 28, 384, 384, (4, 1), 1, 2, False), (64, 32, 32, 128, 128, (1, 4), 1, 0, False), (100, 32, 32, 256, 128, (1, 4), 1, 0, True),
+    (225, 28, 28, 128, 512, (3, 3), 2, 1, True), (356, 32, 32, 128, 256, (3, 3), 2, 1, False), (17, 96, 96, 128, 512, (3, 3), 2, 0, True),
+    (283, 34, 74, 256, 256, (3, 1), 2, 0, True), (1520, 12, 20, 128, 512, (4, 1), 3, 1, False), (14685, 28, 19, 128, 64, (4, 1), 3, 1, False)])
 def test_convolution_strips_are_taken_where_they_are_faster(launches_of, B_, H, W, Cin, Cout, window, stride, pad, taken):  # noqa: F811
     kh, kw = window
     Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
@@ -121,6 +123,15 @@ def test_convolution_strips_are_taken_where_they_are_faster(launches_of, B_, H, 
     assert st == 0 and (log == want) == taken
     if (Ho | Wo) % 2 == 0:
         assert st_pool in (0, 3) and (log_pool != want or taken)
+
+
+def test_pooled_strips_are_taken_where_pooled_tiles_leave_units_unfilled(launches_of):  # noqa: F811
+    """228 images of 34 x 92, 256 -> 512, 3 x 1: three plain tiles share a compute unit, of the pooled ones not."""
+    args, tail = (A, 228, 34, 92, 256, WB, 24, 512, 3, 1, 1, 0), (THR, FLIP, OUT, 16, 0)
+    (st, log), (st_pool, log_pool) = launches_of(("bnn_conv_bn_sign_pack", (*args, *tail)),
+                                                 ("bnn_conv_pool_windows_bn_sign_pack", (*args, 2, *tail)))
+    want = strips(228 * 32 * 92, 512, 128)
+    assert (st, st_pool) == (0, 0) and log != want and log_pool == want
 
 
 @pytest.mark.parametrize("B_,H,W,Cin,Cout,stride", [(38836, 96, 96, 384, 5410, 1), (131071, 64, 64, 256, 11136, 1),
