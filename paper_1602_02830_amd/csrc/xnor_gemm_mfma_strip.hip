@@ -239,9 +239,10 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 // Strips of more than one block row per wavefront; K from 577 on (shorter rows have kernels 6 and 7, chosen by alignment); at most
 // an eighth of columns that do not exist (16384 x 300 x 900 6.4 us before, 6.7 in strips); strips of one tile, or of two
 // tiles and more whose two buffers are refilled under K loops of at most 7 quads: 5000 x 4096 x 784 (640 rows, the second tile of one
-// block row) 10.9 and 11.4, 10000 x 4096 x 1024 20.1 and 20.8; and strips of at most 288 rows only up to K = 832: 15227 x 512 x 987
-// 6.6 and 6.9, 1583 x 4096 x 907 6.5 and 6.7, 1853 x 4224 x 1002 (288 rows) 6.8 and 7.4, but 2940 x 3000 x 671 (320 rows) 7.9 and
-// 6.4, 2924 x 2048 x 784 (192) 6.5 and 6.0.
+// block row) 10.9 and 11.4, 10000 x 4096 x 1024 20.1 and 20.8; and with K > 832 only where the 128 x 128 tiles are more than two to a
+// compute unit: 15227 x 512 x 987 (476 tiles) 6.6 and 6.9, 1853 x 4224 x 1002 (495) 6.8 and 7.4, 609 x 12519 x 912 (490) 6.7 and 7.2,
+// but 5105 x 1732 x 862 (560) 8.0 and 7.1, 36308 x 238 x 926 (568) 8.0 and 7.2; shorter K 2940 x 3000 x 671 (552) 7.9 and 6.4, 2924 x
+// 2048 x 784 (368) 6.5 and 6.0.
 // Strips that keep most of the chip at work, where the tiles taken otherwise fill it by themselves: 65 % of it with strips of one
 // tile (2000 x 6656 x 784, 79 %, 10.1 and 8.3; 1164 x 19579 x 600, 59 %, 13.1 and 15.7), 74 % of two to four (4000 x 6656 x 784, 79 %,
 // 15.6 and 14.3; 4000 x 12000 x 784, 73 %, 25.1 and 26.0), 82 % with longer ones (10000 x 6656 x 784, 80 %, 31.2 and 32.0, 10000 x 12000
@@ -258,7 +259,8 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
     if (K <= 576 || K > 128 * MAX_QUADS || tiles_n > kStripUnits || 8 * N < 7 * BN * tiles_n) return BNN_ERR_UNSUPPORTED;
     const StripPlan plan = strip_plan(M, tiles_n);
     const int64_t rows = plan.rows, groups = plan.groups;
-    if (rows < kRowStripMinRows || (rows <= 288 && K > 832) || (rows > BM && (rows < 2 * BM || K > 128 * (MAX_QUADS - 1)))) return BNN_ERR_UNSUPPORTED;
+    if (K > 832 && ceil_div(M, 128) * tiles_n <= 512) return BNN_ERR_UNSUPPORTED;
+    if (rows < kRowStripMinRows || (rows > BM && (rows < 2 * BM || K > 128 * (MAX_QUADS - 1)))) return BNN_ERR_UNSUPPORTED;
     const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 2 ? rows - last + BM / 2 : rows;
     if (!strips_fill(M, tiles_n, cost, rows <= BM ? 65 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
