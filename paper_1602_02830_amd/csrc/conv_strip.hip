@@ -20,9 +20,15 @@
 //   - The K loop is one quad of channels (two steps of 64) long: the operands of a step are widened between the products of
 //     the step before, LDS is read half a step ahead (BNN_STRIP_SCHEDULE).  The two wavefronts of a SIMD take 39 cycles per
 //     product together, 36 where one runs alone: alternating operands cost the engine more than the issue of both does.
-// Batch 256, us, tiles of conv_patch.hip before and strips now: 128 -> 128 of 32 x 32 pooled 19.3 and 17.3, 128 -> 256 of
-// 16 x 16 10.9 and 10.3, 256 -> 256 16.3 and 14.9, 256 -> 512 of 8 x 8 11.3 and 10.2, 512 -> 512 pooled 18.3 and 16.3; 128 images
-// of 28 x 28, 128 -> 256 pooled (then two launches) 21.7 and 15.1; the ConvNet body 88.0 and 78.9.
+//   - What comes before the first product is bound by the number of its instructions (two wavefronts of a SIMD take about eight
+//     cycles for each): 900 of them, 8000 cycles of 31000, for 256 -> 256 of 16 x 16, 5300 now.  Hence the divisions in float32
+//     (strip_cells.h), a kernel for each way of walking a strip (Walk) and for 3 x 3 windows, the arguments that the first loads
+//     need in the first line of the argument block, and the pixels' cells held before the barrier, while the loads are in flight.
+// Batch 256, us, tiles of conv_patch.hip, strips before that and now: 128 -> 128 of 32 x 32 pooled 19.3, 17.0, 15.7, 128 -> 256 of
+// 16 x 16 10.9, 10.1, 9.0, 256 -> 256 16.3, 15.0, 13.6, 256 -> 512 of 8 x 8 11.3, 10.0, 9.5, 512 -> 512 pooled 18.3, 16.2, 15.6;
+// 128 images of 28 x 28, 128 -> 256 pooled (on tiles two launches) 21.7, 15.1, 13.6.
+// Signs (+-1) for the filters' bits would need no popcounts of the pixels (2600 cycles less before the first product), but operands
+// that change sign cost the engine more power than bits: 2.11 GHz where bits hold 2.36, and no gain (15.0 us for 256 -> 256).
 // Four wavefronts of 4 x 4 blocks (one per SIMD) were slower at every size (256 -> 256 of 16 x 16 21.4): the allocator does not
 // fit 256 accumulators and the next patch's registers, and nothing covers the phases between the tiles.
 #include <numeric>
@@ -31,6 +37,7 @@
 #include "conv_patch_geometry.h"
 #include "gemm_staging.h"
 #include "mfma_fp4.h"
+#include "strip_cells.h"
 #include "strip_cut.h"
 
 namespace bnn {
@@ -48,13 +55,12 @@ struct Cut {
     FastDiv by_tiles_n;
     int tiles_n, per_die;      // column tiles; workgroups / 8
     int rows;                  // pixels per strip, a multiple of 32
-    int ahead;                 // whether the next patch is loaded under the products, into another of up to three buffers
 };
 
 // A tile and its patch: unit row and column (in the image) and image of the tile's first unit, first padded row of the patch in
-// that image, cells up to the end of the tile's last window, first row of the image that can be among them, and that row's
-// address.  Units: pixels, or (POOL) pooling
-// windows, whose maps cv.Wo, cv.Ho and the divisions then describe.
+// that image, cells to load (up to the end of the tile's last window where that may be far fewer than the largest patch has), first row
+// of the image that can be among them, and that row's address.  Units: pixels, or (POOL) pooling windows, whose maps cv.Wo, cv.Ho and
+// the divisions then describe.
 struct Origin {
     int y, x, b, row0, slots, top;
     const uint32_t* at;
@@ -63,24 +69,23 @@ struct Origin {
 template <bool POOL>
 __device__ __forceinline__ Origin origin_of(const uint32_t* in, const PatchGeom& pg, const ConvArgs& cv, int row0, int rows) {
     constexpr int PF = POOL ? 2 : 1;
-    const int u0 = POOL ? row0 >> 2 : row0, u1 = POOL ? (row0 + rows - 1) >> 2 : row0 + rows - 1;
-    const int first = pg.by_wo(u0), last = pg.by_wo(u1);
-    const int b0 = pg.by_ho(first), b1 = pg.by_ho(last), y0 = first - b0 * cv.Ho, y1 = last - b1 * cv.Ho;
+    const int u0 = POOL ? row0 >> 2 : row0;
+    const int first = pg.by_wo(u0), b0 = pg.by_ho(first), y0 = first - b0 * cv.Ho;
     const int row_first = PF * y0 * cv.stride, top = max(min(row_first - cv.pad, cv.H - 1), 0);
-    return Origin{y0, u0 - first * cv.Wo, b0, row_first,
-                  ((b1 - b0) * pg.img_rows + PF * (y1 - y0) * cv.stride + (PF - 1) * cv.stride + cv.kh) * pg.pw,
-                  top, in + (size_t(b0) * uint32_t(cv.H) + uint32_t(top)) * uint32_t(cv.W) * uint32_t(cv.Cw)};
+    int slots = pg.slots;
+    if (pg.trim) {
+        const int last = pg.by_wo(POOL ? (row0 + rows - 1) >> 2 : row0 + rows - 1), b1 = pg.by_ho(last), y1 = last - b1 * cv.Ho;
+        slots = ((b1 - b0) * pg.img_rows + PF * (y1 - y0) * cv.stride + (PF - 1) * cv.stride + cv.kh) * pg.pw;
+    }
+    return Origin{y0, u0 - first * cv.Wo, b0, row_first, slots, top,
+                  in + (size_t(b0) * uint32_t(cv.H) + uint32_t(top)) * uint32_t(cv.W) * uint32_t(cv.Cw)};
 }
 
-// Cells and offsets below are counted from there, hence at most a patch's: products of 24 bits, in a quarter of the time of 32.
-__device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
-
 // Byte offset of cell s of a patch from o.at, 0 for a cell outside the images.
-__device__ __forceinline__ uint32_t cell_of(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o, int s, bool& inside) {
-    const int py = pg.by_pw(s), px = s - mul24(py, pg.pw);
-    const int b = pg.by_img_rows(o.row0 + py), y = o.row0 + py - mul24(b, pg.img_rows) - cv.pad, x = px - cv.pad;
-    inside = s < o.slots && b < n_images - o.b && y >= 0 && y < cv.H && x >= 0 && x < cv.W;
-    return inside ? uint32_t(mul24(mul24(mul24(b, cv.H) + y - o.top, cv.W) + x, 4 * cv.Cw)) : 0u;
+__device__ __forceinline__ uint32_t cell_of(const Maps& maps, const ConvArgs& cv, int n_images, Origin o, int s, bool& inside) {
+    const uint32_t at = input_of_cell(maps, cv.pad, cv.H, cv.W, o.row0, o.top, n_images - o.b, s, inside);
+    inside = inside && s < o.slots;
+    return inside ? at : 0u;
 }
 
 __device__ __forceinline__ uint4 ones_unless(bool keep, uint4 v) {
@@ -99,12 +104,13 @@ __device__ __forceinline__ uint4 load_at(const uint32_t* image, uint32_t at, int
 
 // Cells s0, s0 + T, ... (FIRST / C of them) of a patch, C quads each, on their way into registers ...
 template <int C>
-__device__ __forceinline__ void load_cells(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o, int s0, int cq0, uint4 (&v)[FIRST], uint32_t& inside) {
+__device__ __forceinline__ void load_cells(const PatchGeom& pg, const Maps& maps, const ConvArgs& cv, int n_images, Origin o, int s0,
+                                           int cq0, uint4 (&v)[FIRST], uint32_t& inside) {
     inside = 0u;
 #pragma unroll
     for (int u = 0; u < FIRST / C; ++u) {
         bool in_image;
-        const uint32_t at = cell_of(pg, cv, n_images, o, s0 + u * T, in_image);
+        const uint32_t at = cell_of(maps, cv, n_images, o, s0 + u * T, in_image);
         inside |= in_image ? 1u << u : 0u;
 #pragma unroll
         for (int c = 0; c < C; ++c) v[u * C + c] = load_at(o.at, at, min(cq0 + c, pg.cqn - 1));
@@ -136,7 +142,7 @@ __device__ __forceinline__ void store_cells(const PatchGeom& pg, Origin o, int s
 
 // A whole patch but for what load_cells(s0 = tid, cq0 = 0) took.
 template <int C>
-__device__ __forceinline__ void load_rest(const PatchGeom& pg, const ConvArgs& cv, int n_images, Origin o,
+__device__ __forceinline__ void load_rest(const PatchGeom& pg, const Maps& maps, const ConvArgs& cv, int n_images, Origin o,
                                           int (&pop)[FIRST / C], uint2* patch) {
     for (int base = 0; base < o.slots; base += FIRST / C * T) {
         if (base > 0) {
@@ -146,17 +152,24 @@ __device__ __forceinline__ void load_rest(const PatchGeom& pg, const ConvArgs& c
         for (int cq0 = base == 0 ? C : 0; cq0 < pg.cqn; cq0 += C) {
             uint4 v[FIRST];
             uint32_t inside;
-            load_cells<C>(pg, cv, n_images, o, base + int(threadIdx.x), cq0, v, inside);
+            load_cells<C>(pg, maps, cv, n_images, o, base + int(threadIdx.x), cq0, v, inside);
             store_cells<C>(pg, o, base + int(threadIdx.x), cq0, v, inside, pop, patch);
         }
     }
 }
 
-// C: quads per cell and load of the first patch.
-template <bool POOL, int RES, int C>
+// Strips of one tile, or longer ones whose next patch is loaded under the products (AHEAD: into another of up to three buffers) or
+// between the tiles.  One kernel for all of them keeps up to 51 scalars in lanes of a vector register (none for one tile): 256 -> 256
+// of 16 x 16 14.5 us with it, 13.6 with these.
+enum class Walk { ONE, AHEAD, BETWEEN };
+
+// C: quads per cell and load of the first patch.  K3: windows of 3 x 3.
+template <bool POOL, int RES, int C, Walk WALK, bool K3>
 __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
-    const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, int M, int N, int K, BnSignArgs bn,
-    ConvArgs cv, PatchGeom pg, Cut cut, int n_images) {
+    const uint32_t* __restrict__ in, const uint32_t* __restrict__ B, int64_t ldb, Cut cut, int M, int N, int K, int n_images,
+    BnSignArgs bn, ConvArgs cv, PatchGeom pg, Maps maps) {
+    if constexpr (K3) cv.kh = cv.kw = 3;
+    constexpr bool MANY = WALK != Walk::ONE;
     constexpr int WN = 2, PF = POOL ? 2 : 1;           // POOL: rows are the pixels of one pooling window after the other
     extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // filters, then up to three patches with their pixel popcounts
     __shared__ float colfix_s[BN];
@@ -181,7 +194,8 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     const uint32_t* pb = B + int64_t(min(col0 + st_r, N - 1)) * ldb;
     uint4 all_b[RES];
 #pragma unroll
-    for (int kt = 0; kt < RES; ++kt) all_b[kt] = *reinterpret_cast<const uint4*>(pb + 4 * min(4 * kt + st_q, kq - 1));
+    for (int kt = 0; kt < RES; ++kt)
+        if (4 * kt < kq) all_b[kt] = *reinterpret_cast<const uint4*>(pb + 4 * min(4 * kt + st_q, kq - 1));
     const int thr = bn.thr[min(col0 + st_r, N - 1)];
     uint32_t flip_reg = 0u;
     if (tid < BN / 32 && col0 + 32 * tid < N) flip_reg = bn.flip_bits[(col0 >> 5) + tid];
@@ -191,7 +205,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     uint4 ahead[PF_QUADS];
     bool ahead_inside = false;
     auto load_ahead = [&](Origin o, int u) __attribute__((always_inline)) {
-        const uint32_t at = cell_of(pg, cv, n_images, o, u * T + tid, ahead_inside);
+        const uint32_t at = cell_of(maps, cv, n_images, o, u * T + tid, ahead_inside);
 #pragma unroll
         for (int c = 0; c < PF_QUADS; ++c) ahead[c] = load_at(o.at, at, min(c, cqn - 1));
     };
@@ -213,21 +227,22 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     Origin here = origin_of<POOL>(in, pg, cv, row_begin, min(BM, row_end - row_begin));
     uint4 first[FIRST];
     uint32_t first_inside;
-    load_cells<C>(pg, cv, n_images, here, tid, 0, first, first_inside);
+    load_cells<C>(pg, maps, cv, n_images, here, tid, 0, first, first_inside);
 
     // The lane's rows as patch cells: row (i * WAVE_ROWS + wr) * 32 + fr of the tile.
     int slot[NB_MAX];
+    const int in_window = POOL ? (fr & 2 ? cv.stride * pg.pw : 0) + (fr & 1 ? cv.stride : 0) : 0;
     auto find_slots = [&](int row0, Origin o) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NB_MAX; ++i) {
-            const int r = min((i * WAVE_ROWS + wr) * 32 + fr, row_end - 1 - row0), u = o.x + (POOL ? r >> 2 : r);
-            const int t = pg.by_wo(u), x = u - mul24(t, cv.Wo);
-            const int b = pg.by_ho(o.y + t), y = o.y + t - mul24(b, cv.Ho);
-            const int dy = POOL ? (r >> 1) & 1 : 0, dx = POOL ? r & 1 : 0;
-            slot[i] = mul24(mul24(b, pg.img_rows) + mul24(PF * y + dy, cv.stride) - o.row0, pg.pw) + mul24(PF * x + dx, cv.stride);
+            const int r = min((i * WAVE_ROWS + wr) * 32 + fr, row_end - 1 - row0);
+            slot[i] = cell_of_unit(maps, o.y, o.x, o.row0, PF * cv.stride, POOL ? r >> 2 : r) + in_window;
         }
     };
     find_slots(row_begin, here);
+    // Here, while the loads are in flight: the compiler would move it behind the barrier, to its first use.
+#pragma unroll
+    for (int i = 0; i < NB_MAX; ++i) asm volatile("" : "+v"(slot[i]));
 
     // Filters to LDS, planes [quad][half] of 8-byte slots, with their popcounts and column terms.
     {
@@ -249,7 +264,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     {
         int pop[FIRST / C] = {};
         store_cells<C>(pg, here, tid, 0, first, first_inside, pop, patches);
-        load_rest<C>(pg, cv, n_images, here, pop, patches);
+        load_rest<C>(pg, maps, cv, n_images, here, pop, patches);
     }
     __syncthreads();
 
@@ -273,7 +288,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     auto run = [&](auto nb_tag, int row0, uint2* patch, bool more_tiles, Origin next, uint2* next_patch) __attribute__((always_inline)) {
         constexpr int NB = decltype(nb_tag)::value;
         constexpr int VALU = (5 * NB + 6 * WN + NB * WN - 1) / (NB * WN);      // widening of a step, per product
-        const bool more = NB == NB_MAX && more_tiles;                          // a tile before the last one is whole
+        const bool more = MANY && NB == NB_MAX && more_tiles;                          // a tile before the last one is whole
         const uint2* rd_a[NB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) rd_a[i] = patch + fh * slots + slot[i];
@@ -290,19 +305,31 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
                 at[p] = pops + (fh == 0 ? slot[2 * p] : odd);
                 sum[p] = 0;
             }
-            for (int ky = 0; ky < cv.kh; ky += 3)
-                for (int kx = 0; kx < cv.kw; kx += 3) {
-                    int v[NP][9];
+            if constexpr (K3) {
+                int v[NP][9];
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
+                for (int p = 0; p < NP; ++p)
 #pragma unroll
-                        for (int e = 0; e < 9; ++e)
-                            v[p][e] = at[p][min(ky + e / 3, cv.kh - 1) * pg.pw + min(kx + e % 3, cv.kw - 1)];
+                    for (int e = 0; e < 9; ++e) v[p][e] = at[p][(e / 3) * pg.pw + e % 3];
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
+                for (int p = 0; p < NP; ++p)
 #pragma unroll
-                        for (int e = 0; e < 9; ++e) sum[p] += ky + e / 3 < cv.kh && kx + e % 3 < cv.kw ? v[p][e] : 0;
-                }
+                    for (int e = 0; e < 9; ++e) sum[p] += v[p][e];
+            } else {
+                for (int ky = 0; ky < cv.kh; ky += 3)
+                    for (int kx = 0; kx < cv.kw; kx += 3) {
+                        int v[NP][9];
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+#pragma unroll
+                            for (int e = 0; e < 9; ++e)
+                                v[p][e] = at[p][min(ky + e / 3, cv.kh - 1) * pg.pw + min(kx + e % 3, cv.kw - 1)];
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+#pragma unroll
+                            for (int e = 0; e < 9; ++e) sum[p] += ky + e / 3 < cv.kh && kx + e % 3 < cv.kw ? v[p][e] : 0;
+                    }
+            }
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
                 short hi, lo;
@@ -323,7 +350,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
                 }
             }
         }
-        const bool piped = more && cut.ahead;
+        const bool piped = WALK == Walk::AHEAD && more;
         if (piped) load_ahead(next, 0);
 
         // K loop over quads of channels; (ky, kx, cq) of the quad that is read next, stepped with carries.
@@ -366,7 +393,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
                     acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand8(b[j]), operand8(a[i]), acc[i][j], 4, 4, 0, 0, 0, 0);
         };
         for (int part = piped ? 0 : 2; part < 3; ++part) {
-            const int q_end = part == 0 ? kq / 3 : part == 1 ? 2 * kq / 3 : kq;
+            const int q_end = WALK != Walk::AHEAD || part == 2 ? kq : part == 0 ? kq / 3 : 2 * kq / 3;
             for (; q < q_end; ++q) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (q + 1 < kq) {                    // past the end the last quad again, whose products are not taken
@@ -389,20 +416,20 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
             }
             // The next patch, half of the cells, then the rest (the loop has registers for one cell's quads, not for two).  A
             // buffer is written two tiles after it was read, behind the barrier of the tile in between.
-            if (part == 0) {
+            if (WALK == Walk::AHEAD && part == 0) {
                 store_ahead(next, 0, next_patch);
                 load_ahead(next, 1);
-            } else if (part == 1) {
+            } else if (WALK == Walk::AHEAD && part == 1) {
                 store_ahead(next, 1, next_patch);
                 __syncthreads();
             }
         }
-        if (more && !cut.ahead) {
+        if (WALK == Walk::BETWEEN && more) {
             __syncthreads();
             int pop[FIRST / C] = {};
-            load_cells<C>(pg, cv, n_images, next, tid, 0, first, first_inside);
+            load_cells<C>(pg, maps, cv, n_images, next, tid, 0, first, first_inside);
             store_cells<C>(pg, next, tid, 0, first, first_inside, pop, next_patch);
-            load_rest<C>(pg, cv, n_images, next, pop, next_patch);
+            load_rest<C>(pg, maps, cv, n_images, next, pop, next_patch);
             __syncthreads();
         }
 
@@ -446,22 +473,28 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
         }
     };
 
-    int buf = 0;
-    for (int row0 = row_begin; row0 < row_end; row0 += BM) {
-        const int rows = min(BM, row_end - row0), left_rows = row_end - row0 - BM;
-        const bool more = left_rows > 0;
-        Origin next = here;
-        if (more) next = origin_of<POOL>(in, pg, cv, row0 + BM, min(BM, left_rows));
-        uint2* patch = patches + buf * patch_size;
-        if (cut.ahead) buf = buf == 2 ? 0 : buf + 1;
-        uint2* next_patch = patches + buf * patch_size;
-        const int blocks = (rows + 31) / 32, mine = (blocks - wr + WAVE_ROWS - 1) / WAVE_ROWS;
-        if (mine == 4) run(std::integral_constant<int, 4>{}, row0, patch, more, next, next_patch);
+    auto tile = [&](int row0, uint2* patch, bool more, Origin next, uint2* next_patch) __attribute__((always_inline)) {
+        const int blocks = (min(BM, row_end - row0) + 31) / 32, mine = (blocks - wr + WAVE_ROWS - 1) / WAVE_ROWS;
+        if (__builtin_expect(mine == 4, 1)) run(std::integral_constant<int, 4>{}, row0, patch, more, next, next_patch);
         else if (mine == 3) run(std::integral_constant<int, 3>{}, row0, patch, more, next, next_patch);
         else if (mine == 2) run(std::integral_constant<int, 2>{}, row0, patch, more, next, next_patch);
         else if (mine == 1) run(std::integral_constant<int, 1>{}, row0, patch, more, next, next_patch);
-        if (more) find_slots(row0 + BM, next);
-        here = next;
+    };
+    if constexpr (!MANY) {
+        tile(row_begin, patches, false, here, patches);
+    } else {
+        int buf = 0;
+        for (int row0 = row_begin; row0 < row_end; row0 += BM) {
+            const int left_rows = row_end - row0 - BM;
+            const bool more = left_rows > 0;
+            Origin next = here;
+            if (more) next = origin_of<POOL>(in, pg, cv, row0 + BM, min(BM, left_rows));
+            uint2* patch = patches + buf * patch_size;
+            if (WALK == Walk::AHEAD) buf = buf == 2 ? 0 : buf + 1;
+            tile(row0, patch, more, next, patches + buf * patch_size);
+            if (more) find_slots(row0 + BM, next);
+            here = next;
+        }
     }
 }
 
@@ -534,26 +567,40 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     if (filters + patch > kStripLdsBytes) return BNN_ERR_UNSUPPORTED;
     if (use == ConvUse::ask) return BNN_OK;
     const int64_t tiles = ceil_div(rows, BM), buffers = tiles < 3 ? tiles : 3;
-    cut.ahead = tiles > 1 && pg.slots <= PF_SLOTS * T && pg.cqn <= PF_QUADS && filters + buffers * patch <= kStripLdsBytes;
+    const bool ahead = tiles > 1 && pg.slots <= PF_SLOTS * T && pg.cqn <= PF_QUADS && filters + buffers * patch <= kStripLdsBytes;
     cut.tiles_n = int(tiles_n);
     cut.by_tiles_n = fast_div(tiles_n);
     cut.per_die = int(groups * tiles_n / 8);
     cut.rows = int(rows);
-    const size_t lds = size_t(filters + (cut.ahead ? buffers : 1) * patch);
+    const Maps maps = maps_of(cv.Wo, cv.Ho, pg.img_rows, pg.pw, cv.H, cv.W, cv.Cw);
+    const size_t lds = size_t(filters + (ahead ? buffers : 1) * patch);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(unsigned(groups * tiles_n)), dim3(T), lds, static_cast<hipStream_t>(stream), in, B, ldb,
-                           int(M), int(N), int(K), bn, cv, pg, cut, n_images);
+        hipLaunchKernelGGL(kernel, dim3(unsigned(groups * tiles_n)), dim3(T), lds, static_cast<hipStream_t>(stream), in, B, ldb, cut,
+                           int(M), int(N), int(K), n_images, bn, cv, pg, maps);
         return check_launch();
     };
-    auto of_size = [&](auto pool_tag, auto res_tag) {
+    auto of_size = [&](auto pool_tag, auto res_tag, auto c_tag) {
         constexpr bool POOL = decltype(pool_tag)::value;
-        constexpr int RES = decltype(res_tag)::value;
-        return pg.cqn <= 2 ? launch(conv_strip_mfma_kernel<POOL, RES, 2>) : launch(conv_strip_mfma_kernel<POOL, RES, 4>);
+        constexpr int RES = decltype(res_tag)::value, C = decltype(c_tag)::value;
+        constexpr bool K3 = RES == kStripResident || C != 2;            // two quads of 3 x 3 taps are at most 4.5 K-tiles
+        const bool three = K3 && cv.kh == 3 && cv.kw == 3;
+        if constexpr (C == PF_QUADS) {
+            if (ahead) return three ? launch(conv_strip_mfma_kernel<POOL, RES, C, Walk::AHEAD, K3>)
+                                    : launch(conv_strip_mfma_kernel<POOL, RES, C, Walk::AHEAD, false>);
+        }
+        if (!three) return launch(conv_strip_mfma_kernel<POOL, RES, C, Walk::BETWEEN, false>);
+        return tiles > 1 ? launch(conv_strip_mfma_kernel<POOL, RES, C, Walk::BETWEEN, K3>)
+                         : launch(conv_strip_mfma_kernel<POOL, RES, C, K3 ? Walk::ONE : Walk::BETWEEN, K3>);
     };
+    using Two = std::integral_constant<int, PF_QUADS>;
+    using Four = std::integral_constant<int, 4>;
     using Few = std::integral_constant<int, kStripResident>;
     using Most = std::integral_constant<int, kStripResidentMost>;
-    if (K <= kStripResident * 512) return pool ? of_size(std::true_type{}, Few{}) : of_size(std::false_type{}, Few{});
-    return pool ? of_size(std::true_type{}, Most{}) : of_size(std::false_type{}, Most{});
+    auto launch_as = [&](auto pool_tag) {
+        if (K > kStripResident * 512) return pg.cqn <= 2 ? of_size(pool_tag, Most{}, Two{}) : of_size(pool_tag, Most{}, Four{});
+        return pg.cqn <= 2 ? of_size(pool_tag, Few{}, Two{}) : of_size(pool_tag, Few{}, Four{});
+    };
+    return pool ? launch_as(std::true_type{}) : launch_as(std::false_type{});
 }
 
 }  // namespace bnn

@@ -1,6 +1,6 @@
-"""CPU-only tests of how the strip kernels cut an output (csrc/strip_cut.h): the function that gives a workgroup its rows, built by
-the host compiler with every signed overflow an error, and the launches of the entry points at the sizes where the strips' ends lie
-beyond 2^31."""
+"""CPU-only tests of how the strip kernels cut an output (csrc/strip_cut.h, csrc/strip_cells.h): the functions that give a workgroup
+its rows and a pixel its patch cell, built by the host compiler with every signed overflow an error, and the launches of the entry
+points at the sizes where the strips' ends lie beyond 2^31."""
 import json
 import os
 import subprocess
@@ -38,6 +38,46 @@ int main(int argc, char** argv) {                   /* M tiles_n ...: the strips
 }
 """
 
+CELLS = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#define __host__
+#define __device__
+#include "strip_cells.h"
+/* Wo Ho H W pad stride channel_words units: float divisions against integer ones, for tiles of 512 units that start anywhere */
+int main(int, char** argv) {
+    int a[8];
+    for (int i = 0; i < 8; ++i) a[i] = atoi(argv[1 + i]);
+    const int Wo = a[0], Ho = a[1], H = a[2], W = a[3], pad = a[4], step = a[5], cw = a[6], tile = a[7];
+    const int img_rows = H + 2 * pad, pw = W + 2 * pad;
+    const bnn::strip::Maps maps = bnn::strip::maps_of(Wo, Ho, img_rows, pw, H, W, cw);
+    unsigned seed = 12345u;
+    auto below = [&](int n) { seed = seed * 1664525u + 1013904223u; return int((uint64_t(seed) * uint64_t(n)) >> 32); };
+    for (int trial = 0; trial < 400; ++trial) {
+        const int y = trial < 2 ? (trial ? Ho - 1 : 0) : below(Ho), x = trial < 4 ? (trial & 2 ? Wo - 1 : 0) : below(Wo);
+        const int row0 = y * step, images = trial % 3 ? 1 + below(600) : 1, top = row0 - pad < 0 ? 0 : row0 - pad < H ? row0 - pad : H - 1;
+        int cells = 1;
+        for (int n = 0; n < tile; ++n) {
+            const int t = (x + n) / Wo, ux = (x + n) % Wo, b = (y + t) / Ho, uy = (y + t) % Ho;
+            const int want = (b * img_rows + uy * step - row0) * pw + ux * step;
+            if (bnn::strip::cell_of_unit(maps, y, x, row0, step, n) != want) return 1;
+            if (want > cells) cells = want;
+        }
+        cells = cells + 3 * pw < 16384 ? cells + 3 * pw : 16384;             /* more cells than that do not fit LDS */
+        for (int s = 0; s < cells; ++s) {
+            const int r = row0 + s / pw, b = r / img_rows, cy = r % img_rows - pad, cx = s % pw - pad;
+            const bool there = b < images && cy >= 0 && cy < H && cx >= 0 && cx < W;
+            bool inside;
+            const uint32_t at = bnn::strip::input_of_cell(maps, pad, H, W, row0, top, images, s, inside);
+            if (inside != there) return 2;
+            if (there && b == 0 && cy < top) continue;                        /* before the patch's first row: never asked for */
+            if (at != (there ? 4u * cw * ((uint32_t(b) * H + cy - top) * W + cx) : 0u)) return 3;
+        }
+    }
+    return 0;
+}
+"""
+
 # The last strip's unclamped end reaches 2^31 from here on.
 PAST_INT = {1: 2147475457, 2: 2147479553, 4: 2147481601}
 LARGEST = 2 ** 31 - 1025
@@ -51,6 +91,19 @@ def cover(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}", str(src),
                     "-o", str(exe)], check=True)
     return lambda sizes: subprocess.run([str(exe), *(str(v) for pair in sizes for v in pair)], stderr=subprocess.PIPE, text=True)
+
+
+def test_cells_in_float32_are_the_integer_ones(tmp_path):
+    src, exe = tmp_path / "cells.cpp", tmp_path / "cells"
+    src.write_text(CELLS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}", str(src),
+                    "-o", str(exe)], check=True)
+    # Wo, Ho, H, W, pad, step, channel words, units of a tile: the ConvNet's maps, single pixels, the tallest and widest maps and
+    # paddings that are admitted, strides of pooling windows
+    for sizes in ((16, 16, 16, 16, 1, 1, 8, 512), (14, 14, 28, 28, 1, 2, 4, 128), (1, 1, 1, 1, 0, 1, 144, 512), (3, 1, 2, 4, 1, 2, 4, 512),
+                  (30, 1030, 1030, 34, 1, 1, 4, 512), (7, 32767, 32767, 9, 0, 1, 4, 512), (5, 32767, 32767, 7, 0, 1, 4, 512),
+                  (8000, 3, 3, 8000, 1, 1, 4, 512), (2670, 13589, 32767, 5, 4000, 3, 4, 32), (333, 127, 1000, 2667, 3, 8, 36, 128)):
+        assert subprocess.run([str(exe), *map(str, sizes)]).returncode == 0, sizes
 
 
 def test_strips_cover_the_rows_of_every_size(cover):
