@@ -170,7 +170,18 @@ int bnn_xnor_gemm_bn_sign_pack(const uint32_t *A, int64_t lda, const uint32_t *B
                                const uint32_t *flip_bits, uint32_t *out, int64_t ld_out,
                                void *stream);
 
-/* Same contract with the kernel chosen by the caller: 0 = automatic, 2, 4, 5, 6, 7, 8 as
+/*
+ * The first hidden layer on real inputs, bnn_pack_sign(x -> a_bits) followed by
+ * bnn_xnor_gemm_bn_sign_pack(a_bits, B -> out), in one launch where that is faster
+ * (small batches, K <= 1024), else in two.  Same arguments, results and status as
+ * those calls; x [M][ldx] float32, ldx >= K; a_bits [M][ld_a] receives the packed input.
+ */
+int bnn_sign_gemm_bn_sign_pack(const float *x, int64_t ldx, const uint32_t *B, int64_t ldb,
+                               int64_t M, int64_t N, int64_t K, const int32_t *thr,
+                               const uint32_t *flip_bits, uint32_t *a_bits, int64_t ld_a,
+                               uint32_t *out, int64_t ld_out, void *stream);
+
+/* bnn_xnor_gemm_bn_sign_pack with the kernel chosen by the caller: 0 = automatic, 2, 4, 5, 6, 7, 8 as
  * in bnn_xnor_gemm_kernel (the other kernels have no fused form), 9 = the arithmetic of
  * kernel 5 on 256x256 tiles with one wavefront per SIMD and one workgroup per compute
  * unit, which takes a strip of rows of one 256-column tile as 256-row tiles and at most

@@ -17,6 +17,7 @@ from .binding import (  # noqa: F401
     bn_fold,
     bn_sign_pack,
     xnor_gemm_bn_sign_pack,
+    sign_gemm_bn_sign_pack,
     conv_im2col_pack,
     conv_xnor,
     conv_bn_sign_pack,

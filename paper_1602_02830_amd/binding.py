@@ -40,6 +40,8 @@ _SIGNATURES = {
     "bnn_xnor_gemm_bn_sign_pack": (_int, [_ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr, _ptr, _ptr, _i64, _ptr]),
     "bnn_xnor_gemm_bn_sign_pack_kernel": (_int, [_ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr, _ptr, _ptr, _i64,
                                                  _int, _ptr]),
+    "bnn_sign_gemm_bn_sign_pack": (_int, [_ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr, _ptr, _ptr, _i64, _ptr, _i64,
+                                          _ptr]),
     "bnn_pack_bitplanes": (_int, [_ptr, _i64, _i64, _i64, _ptr, _i64, _ptr]),
     "bnn_bitplane_gemm": (_int, [_ptr, _i64, _ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr]),
     "bnn_bitplane_gemm_bn_sign_pack": (_int, [_ptr, _i64, _ptr, _i64, _i64, _i64, _i64, _ptr, _ptr, _ptr, _i64, _ptr]),
@@ -285,6 +287,18 @@ def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
                                                    _ld(out), kernel, _stream(out))
     _check("bnn_xnor_gemm_bn_sign_pack", st)
     return out
+
+
+def sign_gemm_bn_sign_pack(x: torch.Tensor, B: torch.Tensor, K: int, thr: torch.Tensor, flip_bits: torch.Tensor,
+                           a_bits: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
+    """pack_sign(x, out=a_bits), then xnor_gemm_bn_sign_pack(a_bits, B, K, thr, flip_bits, out=out): one launch where the
+    library has one for these sizes (bnn_sign_gemm_bn_sign_pack)."""
+    if _calls is not None:
+        st = _calls.sign_gemm_bn_sign_pack(x, B, K, thr, flip_bits, a_bits, out)
+        if st == 0 or _took("bnn_sign_gemm_bn_sign_pack", st):
+            return out
+    pack_sign(x, out=a_bits)
+    return xnor_gemm_bn_sign_pack(a_bits, B, K, thr, flip_bits, out=out)
 
 
 def pack_bitplanes(x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:

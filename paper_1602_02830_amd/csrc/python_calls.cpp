@@ -31,6 +31,8 @@ struct EntryPoints {
                                   int64_t, void*);
     int (*xnor_gemm_bn_sign_pack_kernel)(Words, int64_t, Words, int64_t, int64_t, int64_t, int64_t, const int32_t*, Words,
                                          uint32_t*, int64_t, int, void*);
+    int (*sign_gemm_bn_sign_pack)(const float*, int64_t, Words, int64_t, int64_t, int64_t, int64_t, const int32_t*, Words, uint32_t*,
+                                  int64_t, uint32_t*, int64_t, void*);
     int (*pack_bitplanes)(const uint8_t*, int64_t, int64_t, int64_t, uint32_t*, int64_t, void*);
     int (*bitplane_gemm)(Words, int64_t, Words, int64_t, int32_t*, int64_t, int64_t, int64_t, int64_t, void*);
     int (*bitplane_gemm_bn_sign_pack)(Words, int64_t, Words, int64_t, int64_t, int64_t, int64_t, const int32_t*, Words,
@@ -224,6 +226,24 @@ PyObject* xnor_gemm_bn_sign_pack(PyObject* const* a) {
     });
 }
 
+// (x, B, K, thr, flip, a_bits, out): every row of x is a row of a_bits, and K elements long
+PyObject* sign_gemm_bn_sign_pack(PyObject* const* a) {
+    Matrix x, B, bits, out;
+    int64_t K;
+    if (!x.read(a[0], at::kFloat) || !B.read(a[1], at::kInt) || !integer(a[2], K) || K <= 0 || x.cols != K || B.cols < words(K))
+        return long_way();
+    const void* thr = vector_of(a[3], B.rows);
+    const void* flip = vector_of(a[4], words(B.rows));
+    if (!thr || !flip || !bits.read(a[5], at::kInt) || bits.rows != x.rows || bits.cols < words(K) || !out.read(a[6], at::kInt) ||
+        !out.holds(x.rows, words(B.rows)))
+        return long_way();
+    return launch(*out.t, [&](void* s) {
+        return entry.sign_gemm_bn_sign_pack(x.as<float>(), x.ld, B.as<uint32_t>(), B.ld, x.rows, B.rows, K,
+                                            static_cast<const int32_t*>(thr), static_cast<Words>(flip), bits.as<uint32_t>(), bits.ld,
+                                            out.as<uint32_t>(), out.ld, s);
+    });
+}
+
 // (x, out)
 PyObject* pack_bitplanes(PyObject* const* a) {
     Matrix x, out;
@@ -389,6 +409,7 @@ PyObject* bind(PyObject*, PyObject* args) {
     set(e.bn_sign_pack, "bnn_bn_sign_pack");
     set(e.xnor_gemm_bn_sign_pack, "bnn_xnor_gemm_bn_sign_pack");
     set(e.xnor_gemm_bn_sign_pack_kernel, "bnn_xnor_gemm_bn_sign_pack_kernel");
+    set(e.sign_gemm_bn_sign_pack, "bnn_sign_gemm_bn_sign_pack");
     set(e.pack_bitplanes, "bnn_pack_bitplanes");
     set(e.bitplane_gemm, "bnn_bitplane_gemm");
     set(e.bitplane_gemm_bn_sign_pack, "bnn_bitplane_gemm_bn_sign_pack");
@@ -420,6 +441,7 @@ PyMethodDef methods[] = {
     fast<xnor_gemm, 5>("xnor_gemm"),
     fast<bn_sign_pack, 4>("bn_sign_pack"),
     fast<xnor_gemm_bn_sign_pack, 7>("xnor_gemm_bn_sign_pack"),
+    fast<sign_gemm_bn_sign_pack, 7>("sign_gemm_bn_sign_pack"),
     fast<pack_bitplanes, 2>("pack_bitplanes"),
     fast<bitplane_gemm, 4>("bitplane_gemm"),
     fast<bitplane_gemm_bn_sign_pack, 6>("bitplane_gemm_bn_sign_pack"),

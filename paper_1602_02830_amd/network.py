@@ -84,12 +84,15 @@ class BinaryMLP:
         stream before the GEMM launch of first_layer and one right after that of last_layer:
         dict["start"], dict["end"] (created here unless the caller put events there already).
         """
+        n_layers, first = len(self.w_bits), 0
         if self.input_uint8:
             B.pack_bitplanes(x, out=self.a_bits[0])
+        elif self.fused and n_layers > 1 and self.kernel == B.KERNEL_AUTO and span_events is None:
+            B.sign_gemm_bn_sign_pack(x, self.w_bits[0], self.K[0], self.thr[0], self.flip[0], self.a_bits[0], self.a_bits[1])
+            first = 1
         else:
             B.pack_sign(x, out=self.a_bits[0])
-        n_layers = len(self.w_bits)
-        for l in range(n_layers):
+        for l in range(first, n_layers):
             if span_events is not None and l == span_events[0]:
                 if "start" not in span_events[2]:
                     span_events[2]["start"] = torch.cuda.Event(enable_timing=True)

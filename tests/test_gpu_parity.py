@@ -1602,6 +1602,43 @@ def test_fused_convolutions_of_any_map_in_strips_and_windows(shape):
     assert torch.equal(got, pooled)
 
 
+@pytest.mark.parametrize("M,N,K,tight", [
+    (100, 4096, 784, False),     # 13 pieces of 64, the last a quarter full; seven steps of 128
+    (1, 1, 33, True),            # the shortest rows, one column
+    (16, 128, 64, True),         # a whole tile, one piece
+    (17, 129, 65, True),         # one row, one column and one element more
+    (31, 143, 832, False),       # 13 whole pieces; half a word of columns but one
+    (33, 160, 833, True),        # the longer form; five columns' words
+    (5, 300, 1024, False),       # the longest rows of one launch
+    (200, 256, 1025, True),      # and of two
+    (129, 8192, 97, True),       # 576 tiles: two launches
+])
+def test_first_layer_on_reals_in_one_call(M, N, K, tight):
+    """bnn_sign_gemm_bn_sign_pack against pack_sign followed by the fused product on the vector ALU: the packed input, every output
+    word, and nothing beside them.  Zeros of both signs, infinities and NaN among the reals; thresholds that no sum and every
+    sum reaches; words past the filters' rows that are not zero."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    kw, nw, pad = (K + 31) // 32, (N + 31) // 32, 0 if tight else 3
+    x = torch.randn(M, K + 2 * pad, generator=g, device=DEV)[:, :K]
+    x[::3, ::5], x[1::3, 1::7], x[::4, 3::11], x[::5, 2::13], x[2::5, 2::13] = 0.0, -0.0, float("nan"), float("inf"), -float("inf")
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    w, flip = words(N, kw + pad)[:, :kw], words(nw)
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    thr = torch.randint(-int(2 * K ** .5), int(2 * K ** .5), (N,), generator=g, device=DEV, dtype=torch.int32)
+    thr[::9], thr[4::9] = 2 ** 31 - 1, -2 ** 31
+    a_want, w_clean = bnn.pack_sign(x), w.clone()
+    if K % 32:
+        w_clean[:, -1] &= (1 << K % 32) - 1
+    want = bnn.xnor_gemm_bn_sign_pack(a_want, w_clean.contiguous(), K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    a_all, out_all = words(M + 1, kw + 1), words(M + 1, nw + 1)
+    a_kept, out_kept = a_all.clone(), out_all.clone()
+    assert bnn.sign_gemm_bn_sign_pack(x, w, K, thr, flip, a_all[:M, :kw], out_all[:M, :nw]).data_ptr() == out_all.data_ptr()
+    assert torch.equal(a_all[:M, :kw], a_want) and torch.equal(out_all[:M, :nw], want)
+    for now, kept, c in ((a_all, a_kept, kw), (out_all, out_kept, nw)):
+        assert torch.equal(now[M], kept[M]) and torch.equal(now[:, c], kept[:, c])
+
+
 def test_pooled_convolution_of_any_map_refuses_odd_maps_and_partial_quads():
     thr, flip = torch.zeros(8, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
     for (H, W, Cin, pool) in ((7, 6, 128, 2), (6, 7, 128, 2), (6, 6, 96, 2), (6, 6, 128, 3)):
