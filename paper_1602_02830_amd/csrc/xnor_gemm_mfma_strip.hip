@@ -6,10 +6,12 @@
 // loaded and stored under the products of the current one, a row's 128 bytes by 8 lanes; accumulators start as the folded
 // threshold; the operands of a step are widened between the products of the step before.
 //
-// What bounds it: with 10 - 16 steps of K a wavefront has 8 x 13 products (K = 784, 3500 cycles at 34) beside a start of 2 - 3 us,
-// so what counts is that everything is loaded once and by every compute unit alike.  us, the tiles taken before (128 x 128, whole
-// rounds of workgroups) and strips: 16000 x 1000 x 800 11.2 and 9.1, 2000 x 8000 x 600 9.7 and 7.6, 3000 x 3000 x 784 7.9 and 6.8, 6000 x
-// 2048 x 784 8.5 and 7.6, 10000 x 4096 x 784 20.6 and 19.9, 16384 x 4096 x 784 28.4 and 26.7.
+// What bounds it is the issue of vector operations, two wavefronts to a SIMD: a wavefront's 8 x 13 products (K = 784) bring 510 of them
+// for widening, so the staging of the next tile's rows beside them is kept to 20 per 64 rows: addresses are 32-bit offsets that a pass
+// steps, a row's last quad is masked where it was loaded instead of shifted into place, and planes for all eight quads are written
+// whatever K is.  (With 64-bit addresses, shifts and stores under a mask, 65, a tile took 14000 cycles for 6700 of products.)  us, before
+// that and now: 10000 x 4096 x 784 18.4 and 15.9, 16384 x 4096 x 784 26.4 and 22.9, 3000 x 3000 x 784 6.7 and 6.2, 16000 x 1000 x 800
+// 8.3 and 7.7; on the 128 x 128 tiles 20.6, 28.4, 7.9 and 11.2.
 #include <type_traits>
 
 #include "bnn_internal.h"
@@ -25,6 +27,7 @@ constexpr int WAVE_ROWS = 4, NB_MAX = 4, BM = 32 * WAVE_ROWS * NB_MAX;
 constexpr int PLANE_A = BM + 4;                        // 8-byte slots per plane of A: the quads that 8 lanes store of 8 rows fall into different banks
 constexpr int MAX_QUADS = 8;                           // K <= 1024: a row is one line
 constexpr int PASS_ROWS = T / MAX_QUADS, PASSES = BM / PASS_ROWS;      // 64 rows per pass, 8 passes
+constexpr int TILE_A = 2 * MAX_QUADS * PLANE_A;
 constexpr int PARTS = 4;                               // of a tile's K loop, two passes of the next tile in flight under each
 
 struct Cut {
@@ -37,14 +40,13 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
                                                                     const uint32_t* __restrict__ B, int64_t ldb, int M, int N,
                                                                     int K, BnSignArgs bn, Cut cut) {
     constexpr int WN = 2;
-    extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // B [kq][2][PLANE_B], then two buffers of A [kq][2][PLANE_A]
+    extern __shared__ __attribute__((aligned(16))) uint2 dyn[];            // B [MAX_QUADS][2][PLANE_B], then one or two buffers of A [MAX_QUADS][2][PLANE_A]
     __shared__ float colfix_s[BN];
     __shared__ uint32_t flip_s[BN / 32];
     __shared__ float pop_s[2][BM];                     // minus popcount / 2 of a tile's rows
     const int kw = (K + 31) >> 5, kq = (kw + 3) >> 2;
     const uint32_t tmask = tail_mask(K);
-    const int tile_size = 2 * kq * PLANE_A;
-    uint2* tiles_a = dyn + 2 * kq * PLANE_B;
+    uint2* tiles_a = dyn + 2 * MAX_QUADS * PLANE_B;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave >> 1, wn = wave & 1;
@@ -56,29 +58,44 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     const StripRows strip = strip_rows(group, cut.rows, M);
     const int row_begin = strip.begin, row_end = strip.end;
 
-    // Lane q of 8 takes quad q of a row (lanes past the row's end the last one again, which they do not store).
+    // Lane q of 8 takes quad q of a row.  The quad at a row's end that is not whole is the row's last four words with those that
+    // belong to the quad before zeroed, not shifted: the same for A and B, whose K may run in any order.  Past it zeros.
     const int st_q = tid & 7, st_r = tid >> 3;
-    const bool st_live = st_q < kq;
-    auto load_row = [&](const uint32_t* P, int64_t ld, int row) __attribute__((always_inline)) {
-        return load_row_quad(P + int64_t(row) * ld, min(st_q, kq - 1), kw);
+    const int words_left = kw - 4 * st_q;
+    uint32_t mask[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) mask[p] = words_left <= 0 || p < 4 - words_left ? 0u : p == 3 && words_left <= 4 ? tmask : ~0u;
+    const uint32_t quad_at = 4u * uint32_t(min(4 * st_q, kw - 4));
+    // 16 bytes at `offset` (below 2^31) from a uniform address.
+    auto load_at = [&](const uint32_t* P, uint32_t offset) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(offset));               // or it becomes a 64-bit address per lane
+        return load_quad_any(reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(P) + offset));
     };
     // Words to LDS, set bits of the row in every one of its 8 lanes.
     auto store_row = [&](uint4 v, uint2* to, int plane) __attribute__((always_inline)) {
-        v = place_row_quad(v, st_q, kw, tmask);
-        if (st_live) {
-            to[(2 * st_q) * plane] = make_uint2(v.x, v.y);
-            to[(2 * st_q + 1) * plane] = make_uint2(v.z, v.w);
-        }
+        v = make_uint4(v.x & mask[0], v.y & mask[1], v.z & mask[2], v.w & mask[3]);
+        to[0] = make_uint2(v.x, v.y);
+        to[plane] = make_uint2(v.z, v.w);
         int c = popc4(v);
         c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);       // lane ^ 1
         c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);       // lane ^ 2
         c += __builtin_amdgcn_update_dpp(0, c, 0x141, 0xF, 0xF, true);      // the other four of eight
         return c;
     };
-    auto load_a = [&](int row0, int pass) __attribute__((always_inline)) { return load_row(A, lda, min(row0 + pass * PASS_ROWS + st_r, row_end - 1)); };
+    // Rows from the strip's first on, pass by pass, through all its tiles; past the strip's end its last row again.
+    const uint32_t* strip_a = A + int64_t(row_begin) * lda;
+    const uint32_t pass_bytes = uint32_t(PASS_ROWS) * uint32_t(lda) * 4u;
+    const uint32_t last_row_at = uint32_t(row_end - 1 - row_begin) * uint32_t(lda) * 4u + quad_at;
+    uint32_t row_at = uint32_t(st_r) * uint32_t(lda) * 4u + quad_at;
+    auto load_a = [&]() __attribute__((always_inline)) {
+        const uint4 v = load_at(strip_a, min(row_at, last_row_at));
+        row_at += pass_bytes;
+        return v;
+    };
+    uint2* put_a = tiles_a + 2 * st_q * PLANE_A + st_r;
     auto store_a = [&](uint4 v, int pass, int buf) __attribute__((always_inline)) {
-        const int r = pass * PASS_ROWS + st_r, c = store_row(v, tiles_a + buf * tile_size + r, PLANE_A);
-        if (st_q == 0) pop_s[buf][r] = -0.5f * float(c);
+        const int c = store_row(v, put_a + buf * TILE_A + pass * PASS_ROWS, PLANE_A);
+        if (st_q == 0) pop_s[buf][pass * PASS_ROWS + st_r] = -0.5f * float(c);
     };
 
     // Start: B, thresholds and the first tile, all in flight before the first of them is waited for.
@@ -87,16 +104,16 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
         int thr[BN / PASS_ROWS];
 #pragma unroll
         for (int p = 0; p < BN / PASS_ROWS; ++p) {
-            const int n = min(col0 + p * PASS_ROWS + st_r, N - 1);
-            vb[p] = load_row(B, ldb, n);
-            thr[p] = bn.thr[n];
+            const int n = min(p * PASS_ROWS + st_r, N - 1 - col0);
+            vb[p] = load_at(B + int64_t(col0) * ldb, uint32_t(n) * uint32_t(ldb) * 4u + quad_at);
+            thr[p] = bn.thr[col0 + n];
         }
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) va[p] = load_a(row_begin, p);
+        for (int p = 0; p < PASSES; ++p) va[p] = load_a();
         if (tid < BN / 32) flip_s[tid] = col0 + 32 * tid < N ? bn.flip_bits[(col0 >> 5) + tid] : 0u;
 #pragma unroll
         for (int p = 0; p < BN / PASS_ROWS; ++p) {
-            const int c = store_row(vb[p], dyn + p * PASS_ROWS + st_r, PLANE_B);
+            const int c = store_row(vb[p], dyn + 2 * st_q * PLANE_B + p * PASS_ROWS + st_r, PLANE_B);
             if (st_q == 0) colfix_s[p * PASS_ROWS + st_r] = fold_column_term(max(-K - 1, min(K + 1, thr[p])), K, 2 * c);
         }
 #pragma unroll
@@ -116,15 +133,17 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     const uint32_t flip_word = flip_s[wn * WN + fh];
     const int cols_left = N - (col0 + wn * 64 + fh * 32);
     const uint32_t live_word = cols_left >= 32 ? ~0u : cols_left <= 0 ? 0u : ((1u << cols_left) - 1u);
-    uint32_t* out = bn.out + ((col0 + wn * 64) >> 5) + fh;                  // this lane's word column
     const uint2* rd_b0 = dyn + fh * PLANE_B + wn * 64 + fr;
-    const bool half_end = kw - 4 * (kq - 1) < 2;       // the last quad's second step would multiply words that do not exist
+    const int half_end = kw - 4 * (kq - 1) == 1;       // the last quad's one word is its fourth: no products of its first step
+    // Bytes from the strip's first output word of the wavefront's columns to this lane's.
+    char* strip_out = reinterpret_cast<char*>(bn.out + (int64_t(row_begin) * bn.ld_out + ((col0 + wn * 64) >> 5)));
+    const uint32_t out_row = uint32_t(bn.ld_out) * 4u;
 
     auto run = [&](auto nb_tag, int row0, int buf, bool more_tiles) __attribute__((always_inline)) {
         constexpr int NB = decltype(nb_tag)::value;
         constexpr int VALU = (5 * NB + 6 * WN + NB * WN - 1) / (NB * WN);      // widening of a step, per product
         const bool more = NB == NB_MAX && more_tiles;                          // a tile before the last one is whole
-        const uint2* rd_a = tiles_a + buf * tile_size + fh * PLANE_A + wr * 32 + fr;       // + i * 32 * WAVE_ROWS
+        const uint2* rd_a = tiles_a + buf * TILE_A + fh * PLANE_A + wr * 32 + fr;       // + i * 32 * WAVE_ROWS
         v16f acc[NB][WN];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -139,8 +158,8 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
         }
         uint4 next[2];
         if (more) {
-            next[0] = load_a(row0 + BM, 0);
-            next[1] = load_a(row0 + BM, 1);
+            next[0] = load_a();
+            next[1] = load_a();
         }
         const uint2* rd_b = rd_b0;
         uint2 aw[NB], bw[WN];
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
         };
         int q = 0;
         for (int part = more ? 0 : PARTS - 1; part < PARTS; ++part) {
-            const int q_end = (part + 1) * kq / PARTS;
+            const int q_end = (part + 1) * (kq - half_end) / PARTS;
             for (; q < q_end; ++q) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (q + 1 < kq) {                      // past the end the last quad again, whose products are not taken
@@ -179,7 +198,6 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
                 read_words();
                 multiply(fa, fb);
                 BNN_STRIP_SCHEDULE(NB * WN, true, VALU);
-                if (q + 1 == kq && half_end) continue;
 #pragma unroll
                 for (int i = 0; i < NB; ++i) fa[i] = widen4_a(aw[i].x);
 #pragma unroll
@@ -191,10 +209,18 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
                 store_a(next[0], 2 * part, buf ^ 1);
                 store_a(next[1], 2 * part + 1, buf ^ 1);
                 if (part + 1 < PARTS) {
-                    next[0] = load_a(row0 + BM, 2 * part + 2);
-                    next[1] = load_a(row0 + BM, 2 * part + 3);
+                    next[0] = load_a();
+                    next[1] = load_a();
                 }
             }
+        }
+
+        if (half_end) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) ha[i] = widen4_a(aw[i].y);
+#pragma unroll
+            for (int j = 0; j < WN; ++j) hb[j] = widen4_b(bw[j].y);
+            multiply(ha, hb);
         }
 
         // The output bit is the complement of the accumulator's sign (mfma_output_words).
@@ -214,8 +240,9 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
                 part[j] = (~neg & 0x0F0F0F0Fu) << (4 * fh);
             }
             const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
-            const int m = row0 + (i * WAVE_ROWS + wr) * 32 + fr;
-            if (m < row_end && cols_left > 0) out[int64_t(m) * bn.ld_out] = ((sw[0] | sw[1]) ^ flip_word) & live_word;
+            const int m = row0 - row_begin + (i * WAVE_ROWS + wr) * 32 + fr;
+            if (m < row_end - row_begin && cols_left > 0)
+                *reinterpret_cast<uint32_t*>(strip_out + (uint32_t(m) * out_row + 4u * fh)) = ((sw[0] | sw[1]) ^ flip_word) & live_word;
         }
     };
 
@@ -223,7 +250,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     for (int row0 = row_begin;;) {
         const bool more = row_end - row0 > BM;
         const int blocks = (min(BM, row_end - row0) + 31) / 32, mine = (blocks - wr + WAVE_ROWS - 1) / WAVE_ROWS;
-        if (mine == 4) run(std::integral_constant<int, 4>{}, row0, buf, more);
+        if (__builtin_expect(mine == 4, 1)) run(std::integral_constant<int, 4>{}, row0, buf, more);
         else if (mine == 3) run(std::integral_constant<int, 3>{}, row0, buf, more);
         else if (mine == 2) run(std::integral_constant<int, 2>{}, row0, buf, more);
         else if (mine == 1) run(std::integral_constant<int, 1>{}, row0, buf, more);
@@ -236,18 +263,17 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 
 }  // namespace row_strip
 
-// Strips of more than one block row per wavefront; K from 577 on (shorter rows have kernels 6 and 7, chosen by alignment); at most
-// an eighth of columns that do not exist (16384 x 300 x 900 6.4 us before, 6.7 in strips); strips of one tile, or of two
-// tiles and more whose two buffers are refilled under K loops of at most 7 quads: 5000 x 4096 x 784 (640 rows, the second tile of one
-// block row) 10.9 and 11.4, 10000 x 4096 x 1024 20.1 and 20.8; and with K > 832 only where the 128 x 128 tiles are more than two to a
-// compute unit: 15227 x 512 x 987 (476 tiles) 6.6 and 6.9, 1853 x 4224 x 1002 (495) 6.8 and 7.4, 609 x 12519 x 912 (490) 6.7 and 7.2,
-// but 5105 x 1732 x 862 (560) 8.0 and 7.1, 36308 x 238 x 926 (568) 8.0 and 7.2; shorter K 2940 x 3000 x 671 (552) 7.9 and 6.4, 2924 x
-// 2048 x 784 (368) 6.5 and 6.0.
-// Strips that keep most of the chip at work, where the tiles taken otherwise fill it by themselves: 65 % of it with strips of one
-// tile (2000 x 6656 x 784, 79 %, 10.1 and 8.3; 1164 x 19579 x 600, 59 %, 13.1 and 15.7), 74 % of two to four (4000 x 6656 x 784, 79 %,
-// 15.6 and 14.3; 4000 x 12000 x 784, 73 %, 25.1 and 26.0), 82 % with longer ones (10000 x 6656 x 784, 80 %, 31.2 and 32.0, 10000 x 12000
-// x 784, 72 %, 53.7 and 60.9, 10000 x 16512 x 784, 50 %, 82 and 116; 10000 x 5504 x 784, 83 %, level, 4000 x 32768 x 784, 98 %, 53.3
-// and 49.4).  A last tile counts as half of one at least (4141 x 7168 x 810, 1056 rows, 15.9 and 17.6).
+// Which of the products that fit are taken.  Measured on 481 products of 96 < K <= 1024, 44 to 21148 columns and 137 to 28168 rows (us,
+// tiles and strips):
+//  - strips of more than 128 rows, a block row for every wavefront along the rows and more: with 128 rows 726 x 5243 x 449 4.2 and 4.7, 10120
+//    x 260 x 415 4.1 and 4.5; with 160 13618 x 278 x 784 6.2 and 5.4, 388 x 8704 x 674 6.3 and 5.4;
+//  - enough of the chip at work: 60 % of it in strips of one or two tiles (9890 x 2048 x 784, 640 rows, 11.2 and 10.1, 2534 x 8485 x 784, 77 %,
+//    13.9 and 11.5; 577 x 18637 x 784, 43 %, 8.1 and 9.8), 74 % up to four and 82 % beyond (10019 x 18758 x 784, 57 %, 82.3 and 97.8); a
+//    last tile counts as half of one at least.
+// What is left to the tiles beside that was slower here before the staging was shortened, and no longer is: K <= 576 (11175 x 2225 x 539
+// 13.5 and 10.0; only 384 < K <= 512 on at most 512 tiles of 128 x 128 is 0.92 to 0.98 times as fast in strips), K > 832 on as many tiles
+// (13015 x 640 x 838, 510 of them, 6.5 and 5.9), K > 896 in strips of several tiles (18769 x 3584 x 1015 34.3 and 28.7), and long
+// strips that keep 65 to 82 % of the chip at work (10397 x 12419 x 784, 77 %, 58.3 and 54.2).
 constexpr int64_t kRowStripMinRows = 160;
 static_assert(starts_in_bf16_pairs(128 * row_strip::MAX_QUADS));
 
@@ -256,17 +282,19 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
                                 const BnSignArgs& bn, void* stream) {
     using namespace row_strip;
     const int64_t tiles_n = ceil_div(N, BN);
-    if (K <= 576 || K > 128 * MAX_QUADS || tiles_n > kStripUnits || 8 * N < 7 * BN * tiles_n) return BNN_ERR_UNSUPPORTED;
+    if (K <= 576 || K > 128 * MAX_QUADS || tiles_n > kStripUnits) return BNN_ERR_UNSUPPORTED;
     const StripPlan plan = strip_plan(M, tiles_n);
     const int64_t rows = plan.rows, groups = plan.groups;
+    if (rows < kRowStripMinRows || (rows > BM && K > 128 * (MAX_QUADS - 1))) return BNN_ERR_UNSUPPORTED;
     if (K > 832 && ceil_div(M, 128) * tiles_n <= 512) return BNN_ERR_UNSUPPORTED;
-    if (rows < kRowStripMinRows || (rows > BM && (rows < 2 * BM || K > 128 * (MAX_QUADS - 1)))) return BNN_ERR_UNSUPPORTED;
     const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 2 ? rows - last + BM / 2 : rows;
-    if (!strips_fill(M, tiles_n, cost, rows <= BM ? 65 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
+    if (!strips_fill(M, tiles_n, cost, rows <= 2 * BM ? 60 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
-    const int64_t kq = ceil_div(K, 128);
+    // Byte offsets from a strip's first row, and a column tile's, are 32 bits.
+    const int64_t ld = lda > bn.ld_out ? lda : bn.ld_out;
+    if (ldb >= int64_t(1) << 22 || ld >= (int64_t(1) << 29) / (rows + 2 * BM)) return BNN_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(xnor_gemm_mfma_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(T),
-                       size_t(2 * kq * (PLANE_B + (rows > BM ? 2 : 1) * PLANE_A)) * sizeof(uint2), static_cast<hipStream_t>(stream), A, lda,
+                       size_t(2 * MAX_QUADS * (PLANE_B + (rows > BM ? 2 : 1) * PLANE_A)) * sizeof(uint2), static_cast<hipStream_t>(stream), A, lda,
                        B, ldb, int(M), int(N), int(K), bn, cut);
     return check_launch();
 }

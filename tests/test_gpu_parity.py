@@ -1602,6 +1602,37 @@ def test_fused_convolutions_of_any_map_in_strips_and_windows(shape):
     assert torch.equal(got, pooled)
 
 
+@pytest.mark.parametrize("M,N,K,ld,ld_out", [
+    (2648, 7283, 769, 25, 228),      # a last quad of one word with one bit; strips of 672 rows: a whole tile and five blocks of 32
+    (13618, 278, 801, 29, 11),       # of two words; a last column tile of 22 columns, rows apart
+    (2600, 8192, 639, 20, 256),      # five whole quads, the last word a bit short; 672 rows
+    (20020, 256, 608, 19, 8),        # of three words; 160 rows
+    (9990, 3072, 896, 31, 97),       # seven whole quads, odd distances; 992 rows
+])
+def test_fused_products_of_short_rows_in_strips_of_any_end(M, N, K, ld, ld_out):
+    """Row strips: a last quad masked where it was loaded, against the product on the vector ALU: every word, and nothing beside them.
+    Words past the rows are random."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    kw, nw = (K + 31) // 32, (N + 31) // 32
+    a, w, flip = words(M, ld)[:, :kw], words(N, ld)[:, :kw], words(nw)
+    clean = []
+    for m in (a, w):
+        c = m.clone()
+        if K % 32:
+            c[:, -1] &= (1 << K % 32) - 1
+        clean.append(c.contiguous())
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    thr = torch.randint(-40, 40, (N,), generator=g, device=DEV, dtype=torch.int32)
+    thr[::9], thr[4::9] = 2 ** 31 - 1, -2 ** 31
+    want = bnn.xnor_gemm_bn_sign_pack(*clean, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    out = words(M + 1, ld_out)
+    kept = out.clone()
+    bnn.xnor_gemm_bn_sign_pack(a, w, K, thr, flip, out=out[:M, :nw])
+    assert torch.equal(out[:M, :nw], want) and torch.equal(out[M], kept[M]) and torch.equal(out[:, nw:], kept[:, nw:])
+
+
 @pytest.mark.parametrize("M,N,K,tight", [
     (100, 4096, 784, False),     # 13 pieces of 64, the last a quarter full; seven steps of 128
     (1, 1, 33, True),            # the shortest rows, one column
