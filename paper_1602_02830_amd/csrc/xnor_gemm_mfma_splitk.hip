@@ -208,7 +208,11 @@ __global__ __launch_bounds__(256, 4) void xnor_gemm_mfma_splitk_kernel(
 // holds 16 columns of one output row in groups of 4, and 8 neighbouring threads finish the 32 columns of one row: an
 // int32 row leaves in 16-byte stores (with one column per lane, four-byte stores of two rows each, the epilogue took
 // 1400 cycles instead of 800: 100 x 4096 x 784 3.7 -> 3.2 us), a fused one is OR-ed together to one word.
-template <int RB, bool FUSED, bool STAGED>
+// REST (staged): up to kRestMost quads past whole rounds of 32 make no round, whose trip to memory nothing would cover: every wavefront
+// has a pair of them at most, loaded with its first round's by the lanes that multiply it.  1000 x 1000 x 4097 6.7 -> 5.9 us (4096 5.7),
+// x 8193 9.3 -> 8.4, fused 1000 x 1000 x 4097 6.4 -> 5.9.  A kernel of its own: as a branch it made products without such a rest up to 4 % slower.
+constexpr int kRound = kWaves * kChunk, kRestMost = 2 * kWaves;
+template <int RB, bool FUSED, bool STAGED, bool REST = false>
 __global__ __launch_bounds__(256, RB == 1 ? 4 : 2) void xnor_gemm_mfma_splitk_rows_kernel(
     const uint32_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ B, int64_t ldb,
     int32_t* __restrict__ C, int64_t ldc, int M, int N, int K, TileMap tiles, BnSignArgs bn) {
@@ -256,19 +260,28 @@ __global__ __launch_bounds__(256, RB == 1 ? 4 : 2) void xnor_gemm_mfma_splitk_ro
         for (int l = 0; l < 4; ++l) from[4 * RB + l] = B + int64_t(min(col0 + 8 * l + st_r, N - 1)) * ldb;
         uint4 r[LOADS];
         // Rounds of 32 quads, 8 per wavefront; the last round's are shared out evenly, in pairs (the lane halves).
-        const int rounds = (nq + kWaves * kChunk - 1) / (kWaves * kChunk);
-        const int share = ((nq - (rounds - 1) * kWaves * kChunk + 7) >> 3) * 2;        // 2, 4, 6 or 8
-        auto first_quad = [&](int round) { return round * kWaves * kChunk + wave * (round + 1 < rounds ? kChunk : share); };
+        const int n_staged = REST ? nq - nq % kRound : nq, rounds = (n_staged + kRound - 1) / kRound;
+        const int share = REST ? kChunk : ((n_staged - (rounds - 1) * kRound + 7) >> 3) * 2;       // 2, 4, 6 or 8
+        auto first_quad = [&](int round) { return round * kWaves * kChunk + wave * (REST || round + 1 < rounds ? kChunk : share); };
         auto fetch = [&](int round) {
-            const int q = first_quad(round) + min(st_q, round + 1 < rounds ? kChunk : share - 1);
-            const int w = min(4 * q, kw - 4);                                          // see load_row_quad
+            const int q = first_quad(round) + (REST ? st_q : min(st_q, round + 1 < rounds ? kChunk : share - 1));
+            const int w = REST ? 4 * q : min(4 * q, kw - 4);                           // see load_row_quad
 #pragma unroll
             for (int l = 0; l < LOADS; ++l) r[l] = load_quad_any(from[l] + w);
         };
         fetch(0);
+        const int rest_q = n_staged + 2 * wave;
+        const bool my_rest = REST && rest_q < nq;
+        uint4 rest_words[ROWS];
+        if (my_rest) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+                rest_words[i] = load_row_quad(A + int64_t(min(row0 + 32 * i + fr, M - 1)) * lda, rest_q + fh, kw);
+            rest_words[RB] = load_row_quad(B + int64_t(min(col0 + fr, N - 1)) * ldb, rest_q + fh, kw);
+        }
         load_thresholds();
         for (int round = 0; round < rounds; ++round) {
-            const int q0 = first_quad(round), q_end = min(nq, round + 1 < rounds ? q0 + kChunk : q0 + share);
+            const int q0 = first_quad(round), q_end = min(n_staged, round + 1 < rounds ? q0 + kChunk : q0 + share);
 #pragma unroll
             for (int l = 0; l < LOADS; ++l) mine[64 * l + st_slot] = r[l];
             if (round + 1 < rounds) fetch(round + 1);
@@ -276,12 +289,12 @@ __global__ __launch_bounds__(256, RB == 1 ? 4 : 2) void xnor_gemm_mfma_splitk_ro
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int t = 0; t < kChunk / 2; ++t) {
-                if (q0 + 2 * t >= q_end) break;
+                if (!REST && q0 + 2 * t >= q_end) break;
                 uint4 q[ROWS];
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i) q[i] = mine[(32 * i + fr) * kChunk + ((2 * t + fh) ^ (fr & 7))];
                 // A quad that is not whole, or not there, was loaded from the row's last four words.
-                if (q0 + 2 * t + 2 > n_whole) {
+                if (!REST && q0 + 2 * t + 2 > n_whole) {
 #pragma unroll
                     for (int i = 0; i < ROWS; ++i) q[i] = place_row_quad(q[i], q0 + 2 * t + fh, kw, tmask);
                 }
@@ -289,6 +302,11 @@ __global__ __launch_bounds__(256, RB == 1 ? 4 : 2) void xnor_gemm_mfma_splitk_ro
             }
             asm volatile("" : : : "memory");
             __builtin_amdgcn_wave_barrier();
+        }
+        if (my_rest) {
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) rest_words[i] = place_row_quad(rest_words[i], rest_q + fh, kw, tmask);
+            part.multiply(rest_words);
         }
     } else {
         const uint32_t* row[ROWS];
@@ -394,19 +412,25 @@ bool mfma_splitk_supports(int64_t M, int64_t N, int64_t K) {
     return K > 96 && K <= kMfmaMaxAcc && M >= 1 && N >= 1 && ceil_div(M, 32) * ceil_div(N, 32) <= kMaxDim;
 }
 
-template <int RB, bool STAGED>
+template <int RB, bool STAGED, bool REST = false>
 static int launch_splitk_rows(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                               int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn, hipStream_t s) {
+    if constexpr (STAGED && !REST) {
+        // (Fused 32 x 32 tiles have no such kernel: 100 x 4096 x 4097 would gain 8 %.)
+        const int64_t nq = ceil_div(K, 128), past = nq % splitk::kRound;
+        if (nq > splitk::kRound && past > 0 && past <= splitk::kRestMost && (RB > 1 || !fused))
+            return launch_splitk_rows<RB, true, true>(A, lda, B, ldb, C, ldc, M, N, K, fused, bn, s);
+    }
     const int64_t tiles_m = ceil_div(M, 32 * RB), tiles_n = ceil_div(N, 32);
     const dim3 grid(unsigned(tiles_m * tiles_n));
     if (!fused) {
-        hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_rows_kernel<RB, false, STAGED>), grid, dim3(256), 0, s, A, lda, B, ldb,
+        hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_rows_kernel<RB, false, STAGED, REST>), grid, dim3(256), 0, s, A, lda, B, ldb,
                            C, ldc, int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     } else if constexpr (RB == 1 && !STAGED) {
         hipLaunchKernelGGL(splitk::xnor_gemm_mfma_splitk_kernel, grid, dim3(256), 0, s, A, lda, B, ldb, int(M), int(N), int(K),
                            tile_map(tiles_m, tiles_n), bn);
-    } else {
-        hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_rows_kernel<RB, true, STAGED>), grid, dim3(256), 0, s, A, lda, B, ldb,
+    } else if constexpr (RB > 1 || !REST) {
+        hipLaunchKernelGGL((splitk::xnor_gemm_mfma_splitk_rows_kernel<RB, true, STAGED, REST>), grid, dim3(256), 0, s, A, lda, B, ldb,
                            static_cast<int32_t*>(nullptr), int64_t(0), int(M), int(N), int(K), tile_map(tiles_m, tiles_n), bn);
     }
     return check_launch();

@@ -1633,6 +1633,37 @@ def test_fused_products_of_short_rows_in_strips_of_any_end(M, N, K, ld, ld_out):
     assert torch.equal(out[:M, :nw], want) and torch.equal(out[M], kept[M]) and torch.equal(out[:, nw:], kept[:, nw:])
 
 
+@pytest.mark.parametrize("M,N,K,ld", [
+    (1000, 1000, 4097, 129),     # one quad of one bit past a round of 32: one wavefront's
+    (1000, 1000, 5120, 160),     # eight whole quads: a pair for every wavefront
+    (990, 1030, 4900, 155),      # seven, the last of two words and a bit
+    (1023, 1001, 8193, 257),     # past two rounds
+    (1000, 1000, 5121, 161),     # nine: a round of their own
+    (512, 640, 4100, 128),       # 32 x 32 tiles
+])
+@pytest.mark.parametrize("fused", [False, True])
+def test_products_with_a_short_rest_of_k(M, N, K, ld, fused):
+    """Products whose K is split over wavefronts, a few quads past whole rounds: every result against the vector-ALU tiles; words past
+    the rows are random."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    kw = (K + 31) // 32
+    a, w = words(M, max(ld, kw))[:, :kw], words(N, max(ld, kw))[:, :kw]
+    clean = [m.clone().contiguous() for m in (a, w)]
+    if K % 32:
+        for c in clean:
+            c[:, -1] &= (1 << K % 32) - 1
+    if not fused:
+        assert torch.equal(bnn.xnor_gemm(a, w, K), bnn.xnor_gemm(*clean, K, kernel=bnn.KERNEL_TILED64))
+        return
+    flip = words((N + 31) // 32)
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    thr = torch.randint(-80, 80, (N,), generator=g, device=DEV, dtype=torch.int32)
+    assert torch.equal(bnn.xnor_gemm_bn_sign_pack(a, w, K, thr, flip),
+                       bnn.xnor_gemm_bn_sign_pack(*clean, K, thr, flip, kernel=bnn.KERNEL_TILED64))
+
+
 @pytest.mark.parametrize("M,N,K,tight", [
     (100, 4096, 784, False),     # 13 pieces of 64, the last a quarter full; seven steps of 128
     (1, 1, 33, True),            # the shortest rows, one column
