@@ -506,15 +506,15 @@ bool conv_patch_tiles_fill(const ConvArgs& cv, bool pool, int64_t K);
 constexpr int kStripResident = 5, kStripResidentMost = 9;     // K-tiles of 512 bits of the resident filters
 constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, beside what the kernel declares itself
 static_assert(starts_in_bf16_pairs(kStripResidentMost * 512));
-// Strips of more than 128 rows, a block row for each of the four wavefronts along the pixels and more.  us, conv_patch.hip and
-// strips: 192 rows 48 of 32 x 32, 128 -> 128 7.8 and 6.8, 96 of 16 x 16, 256 -> 256 11.3 and 9.0, 160 of 8 x 8, 512 -> 512 (160
-// rows) 18.2 and 14.6; with 128 rows 64 of 16 x 16, 256 -> 256 8.65 and 8.6, 128 -> 256 6.5 and 6.7.  Windows that do not overlap
-// reuse nothing of a patch: 1 x 1, 64 of 32 x 32, 256 -> 256 6.6 and 7.4, 256 of 28 x 28, 512 -> 256 21.4 and 23.0, 2 x 2 at
-// stride 2, 233 of 16 x 16, 128 -> 512 7.7 and 7.95; but 2 x 2 at stride 1, 128 of 28 x 28, 256 -> 256 17.3 and 14.9.
-constexpr int64_t kStripMinRows = 160;
-
-// Which of the layers that fit are faster here than on the tiles of conv_patch.hip and the gathering kernels.  Measured on 3600
+// Which of the layers that fit are faster here than on the tiles of conv_patch.hip and the gathering kernels.  Measured on 4100
 // layers, pooled and not, of 1 to 25 taps, 128 to 1024 channels and 32 to 32768 filters; us, tiles and strips:
+//  - strips of fewer than 160 rows, down to 32 and however little of the chip they fill, for 3 x 3 windows: 380 layers 1.02 to 1.5 times as
+//    fast (66 images of 14 x 14, 256 -> 256 8.4 and 7.4; 12 of 28 x 28, 256 -> 256 8.9 and 7.3; 16 of 32 x 32, 128 -> 64 5.5 and 4.95; 4
+//    of 30 x 30, 512 -> 512 12.2 and 10.2), but for 64 rows of K > 2560, where a pair of 32-row blocks shares the filters that tiles
+//    of 64 pixels keep for themselves (52 of 14 x 14, 512 -> 99 9.8 and 10.0).  Windows of other sizes, which have no kernel for strips of
+//    one tile, lose more instructions before the first product than they gain (10 of 14 x 14, 128 -> 128, 5 x 5 7.5 and 8.3).
+//    Maps whose rows are whole blocks of 32 pixels keep to tiles in strips of several rows but not of pairs of rows: such a strip of
+//    a pooled layer cuts its windows' rows, and its patch is larger than the plain layer's;
 //  - enough of the chip at work: 60 % with strips of one tile, 80 % up to four, 86 % beyond (41 images of 16 x 16, 256 -> 8576,
 //    78 %, 75.5 and 79.1; 47 of 14 x 14, 512 -> 12288, 75 %, 169 and 190), 93 % with K <= 1152, whose tiles are short (40 of 28 x 28,
 //    128 -> 9984, 91 %, 138 and 148; 58 of 32 x 32, 128 -> 4700 pooled, 87 %, 123 and 139);
@@ -532,8 +532,11 @@ constexpr int64_t kStripMinRows = 160;
 // cv: the layer, its pooled_units if pool.
 static bool strips_preferred(const ConvArgs& cv, bool pool, int64_t M, int64_t K, int64_t tiles_n, int64_t rows, int64_t cells,
                              int64_t pixels) {
-    const int64_t tiles = ceil_div(rows, strip::BM), taps = int64_t(cv.kh) * cv.kw;
-    if (!strips_fill(M, tiles_n, rows, tiles == 1 ? 60 : tiles <= 4 ? 80 : K <= 1152 ? 93 : 86)) return false;
+    const int64_t tiles = ceil_div(rows, strip::BM), taps = int64_t(cv.kh) * cv.kw, row = pool ? 2 * int64_t(cv.Wo) : cv.Wo;
+    if (rows < 5 * kStripStep && (cv.kh != 3 || cv.kw != 3)) return false;
+    if (rows == 2 * kStripStep && K > kStripResident * 512) return false;
+    if (rows < 5 * kStripStep && row % kStripStep == 0 && rows > row && rows % (2 * row) != 0) return false;
+    if (rows > 2 * kStripStep && !strips_fill(M, tiles_n, rows, tiles == 1 ? 60 : tiles <= 4 ? 80 : K <= 1152 ? 93 : 86)) return false;
     if (taps < 9 && K <= 512 && cells > 8 * pixels) return false;
     if (K <= 1536 && !conv_patch_tiles_fill(cv, pool, K)) return true;
     if (K <= 1152 && rows > 576 && rows <= 768) return false;
@@ -557,7 +560,9 @@ int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, 
     Cut cut;
     const StripPlan plan = strip_plan(M, tiles_n);
     const int64_t rows = plan.rows, groups = plan.groups;
-    if (rows < kStripMinRows || (cv.kh <= cv.stride && cv.kw <= cv.stride)) return BNN_ERR_UNSUPPORTED;
+    // Windows that do not overlap reuse nothing of a patch: 1 x 1, 64 of 32 x 32, 256 -> 256 6.6 us on tiles and 7.4, 2 x 2 at stride 2, 233
+    // of 16 x 16, 128 -> 512 7.7 and 7.95; but 2 x 2 at stride 1, 128 of 28 x 28, 256 -> 256 17.3 and 14.9.
+    if (cv.kh <= cv.stride && cv.kw <= cv.stride) return BNN_ERR_UNSUPPORTED;
     if (pool) cv = pooled_units(cv);
     // Tiles start at multiples of the strips' rows, and 512 pixels further on.
     const int64_t tile = rows < BM ? rows : BM, align = rows <= BM ? rows : std::gcd(rows, int64_t(BM));

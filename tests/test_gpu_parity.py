@@ -1701,6 +1701,37 @@ def test_first_layer_on_reals_in_one_call(M, N, K, tight):
         assert torch.equal(now[M], kept[M]) and torch.equal(now[:, c], kept[:, c])
 
 
+@pytest.mark.parametrize("shape", [
+    # B, H, W, Cin, Cout, stride, padding: strips of fewer than 160 rows
+    (1, 1, 1, 128, 1, 1, 1),              # one pixel, one filter
+    (1, 2, 2, 256, 33, 1, 1),             # one pooling window
+    (10, 14, 14, 256, 256, 1, 1),         # 32 rows
+    (7, 9, 11, 384, 130, 2, 0),           # stride 2 without padding, images that end inside a strip
+    (63, 16, 16, 128, 64, 1, 1),          # 64
+    (4, 30, 30, 512, 512, 1, 1),          # 64 with filters of nine K-tiles
+    (12, 28, 28, 256, 264, 1, 1),         # 128; a last column tile of eight filters
+    (22, 32, 32, 256, 64, 1, 1),          # 96 = three image rows
+    (3, 4, 260, 128, 96, 1, 2),           # wide maps, wide padding
+])
+def test_fused_convolutions_in_short_strips(shape):
+    """3 x 3 layers in strips of 32 to 128 pixels, and pooled 2 x 2 on even maps, against the im2col matrix through the vector-ALU
+    product and the pooling of its output bits: every word."""
+    B, H, W, Cin, Cout, stride, pad = shape
+    g = torch.Generator(device=DEV).manual_seed(sum(shape))
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    x, K, nw = words(B, H, W, Cin // 32), 9 * Cin, (Cout + 31) // 32
+    w, flip = words(Cout, K // 32), words(nw)
+    if Cout % 32:
+        flip[-1] &= (1 << Cout % 32) - 1
+    thr = torch.randint(-60, 60, (Cout,), generator=g, device=DEV, dtype=torch.int32)
+    Ho, Wo = (H + 2 * pad - 3) // stride + 1, (W + 2 * pad - 3) // stride + 1
+    want = bnn.xnor_gemm_bn_sign_pack(bnn.conv_im2col_pack(x, Cin, 3, 3, stride, pad), w, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    assert torch.equal(bnn.conv_bn_sign_pack(x, Cin, w, thr, flip, 3, 3, stride, pad), want)
+    if (Ho | Wo) % 2 == 0:
+        pooled = bnn.maxpool_bits(want.view(B, Ho, Wo, nw), Cout, flip, 2, 2, 2).reshape(-1, nw)
+        assert torch.equal(bnn.conv_pool_windows_bn_sign_pack(x, Cin, w, thr, flip, 3, 3, stride, pad), pooled)
+
+
 def test_pooled_convolution_of_any_map_refuses_odd_maps_and_partial_quads():
     thr, flip = torch.zeros(8, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
     for (H, W, Cin, pool) in ((7, 6, 128, 2), (6, 7, 128, 2), (6, 6, 96, 2), (6, 6, 128, 3)):
