@@ -1633,6 +1633,28 @@ def test_fused_products_of_short_rows_in_strips_of_any_end(M, N, K, ld, ld_out):
     assert torch.equal(out[:M, :nw], want) and torch.equal(out[M], kept[M]) and torch.equal(out[:, nw:], kept[:, nw:])
 
 
+@pytest.mark.parametrize("rows,cols,ld,offset", [
+    (3, 385, 385, 0),            # 13 words: a fourth piece of one word with one element
+    (65, 513, 520, 1),           # a word past four pieces; rows apart, not 16-byte aligned
+    (1, 416, 416, 3),            # one row that ends with a word
+    (130, 894, 894, 2),          # a last load of two elements
+    (33, 1024, 1027, 1),         # whole pieces, unaligned
+    (257, 639, 639, 0),          # a last load of three
+])
+def test_pack_sign_of_long_rows_in_pieces(rows, cols, ld, offset):
+    """Against the oracle, zeros of both signs, infinities and NaN among the elements; nothing beside the words is written."""
+    g = torch.Generator(device=DEV).manual_seed(rows + cols)
+    flat = torch.randn(rows * ld + offset, generator=g, device=DEV)
+    flat[::7], flat[1::11], flat[2::13], flat[3::17], flat[4::17] = 0.0, -0.0, float("nan"), float("inf"), -float("inf")
+    x = torch.as_strided(flat, (rows, cols), (ld, 1), offset)
+    kw = (cols + 31) // 32
+    out = torch.full((rows + 1, kw + 2), 77, dtype=torch.int32, device=DEV)
+    bnn.pack_sign(x, out=out[:rows, :kw])
+    want = oracle.pack_bits(np.where(x.cpu().numpy() >= 0, 1, -1).astype(np.int8))
+    assert (words_to_host(out[:rows, :kw].contiguous()) == want).all()
+    assert bool((out[rows] == 77).all()) and bool((out[:, kw:] == 77).all())
+
+
 @pytest.mark.parametrize("M,N,K,ld", [
     (1000, 1000, 4097, 129),     # one quad of one bit past a round of 32: one wavefront's
     (1000, 1000, 5120, 160),     # eight whole quads: a pair for every wavefront
