@@ -3,7 +3,7 @@
 // bnn_conv_xnor / bnn_conv_bn_sign_pack: a kh x kw binary convolution (3 x 3 in the paper's
 // nets, Sec. 3.3) as the XnorDotProduct of Alg. 4 over receptive fields that the GEMM's tile
 // loader gathers straight from the packed NHWC input (taps outside the image are +1: zero
-// padding through Eq. (1)).  The kernels: fused layers that fill the chip in equal strips of pixels, filters resident
+// padding through Eq. (1)).  The kernels: fused layers, 3 x 3 ones first of all, in equal strips of pixels, filters resident
 // (conv_strip.hip); the LDS-patch kernel (conv_patch.hip) wherever the
 // input patch of a tile fits; else the conv modes of the matrix-engine
 // GEMMs (xnor_gemm_mfma.hip, xnor_gemm_mfma_shortk.hip); launch_conv_mfma chooses.

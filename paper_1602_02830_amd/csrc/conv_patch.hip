@@ -38,7 +38,7 @@
 // with ldb % 4 == 0, a patch within kPatchMaxBytes of LDS, and Cin % 128 == 0 - or Cin % 32 == 0 for same-size stride-1
 // layers whose tiles are whole image rows or images, with a receptive field of at most kResidentKTiles * 512 bits.
 // Some layers that would fit are faster gathered (better_gathered).
-// Fused layers that fill the chip in strips leave before these tiles are chosen (conv_strip.hip).
+// Fused 3 x 3 layers, and others that fill the chip in strips, leave before these tiles are chosen (conv_strip.hip).
 // Against gathering the receptive fields K-tile by K-tile, fused, on layers that now run in strips: 128 images of 28 x 28, 128 -> 256
 // channels 22.4 -> 18.9 us, 200 of 13 x 13, 128 -> 396 17.8 -> 13.9, 100 of 14 x 14, 256 -> 256 13.4 -> 11.7, 256 of 32 x 32, 128 -> 256
 // at stride 2 15.5 -> 13.0, 128 of 56 x 56, 128 -> 128 37.0 -> 31.6; as int32, which stays here, 128 of 28 x 28, 128 -> 256 30.1 -> 25.6.
@@ -49,7 +49,7 @@
 
 namespace bnn {
 
-// Layers that fill the chip (conv_strip.hip): BNN_ERR_UNSUPPORTED, with nothing launched, for those it leaves to this kernel.
+// Fused layers in strips (conv_strip.hip): BNN_ERR_UNSUPPORTED, with nothing launched, for those it leaves to this kernel.
 int launch_conv_strip_fused(const uint32_t* in, const uint32_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             BnSignArgs bn, ConvArgs cv, bool pool, ConvUse use, void* stream);
 

@@ -1,4 +1,4 @@
-// Binary convolution layers on bits (fused with Sign(BatchNorm), with or without 2 x 2 max pooling) that fill the chip:
+// Binary convolution layers on bits (fused with Sign(BatchNorm), with or without 2 x 2 max pooling) in strips:
 // one workgroup of eight wavefronts per compute unit, 128 filters resident in LDS, a strip of output pixels walked in tiles
 // of 512.
 //
