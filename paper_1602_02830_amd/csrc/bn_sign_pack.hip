@@ -9,7 +9,8 @@
 // consecutive int32 (one 16-byte load, whatever the row's alignment), nibbles combined by
 // three DPP permutes.  Rows that are whole numbers of 128 channels take
 // bn_sign_pack_units_kernel (4 words per group, thresholds in registers,
-// 16-byte stores); everything else bn_sign_pack_kernel.
+// 16-byte stores), most other rows of 97 channels or more
+// bn_sign_pack_pieces_kernel; everything else bn_sign_pack_kernel.
 #include "bnn_internal.h"
 
 namespace bnn {
@@ -163,6 +164,54 @@ __global__ __launch_bounds__(kBnThreads) void bn_sign_pack_units_kernel(
     }
 }
 
+// The same for rows of any length and alignment, in pieces of 128 channels of which a row's last may be partial: loads that would pass
+// the row's end take its last four channels instead, and the nibble is shifted to where it belongs.  Lane q < 4 of a group stores
+// word q.  In cached matrices the number of instructions bounds such rows: against bn_sign_pack_kernel no carry from word to word, half the
+// loads of thresholds, no mask per row.  us, before and now: 10000 x 4095 26.9 and 24.2, 10000 x 1000 8.2 and 6.6, 1000 x 1000 2.9 and
+// 2.4, 700 x 6001 3.9 and 3.0, 300000 x 100 22.9 and 18.6.
+template <bool ONCE>
+__global__ __launch_bounds__(kBnThreads) void bn_sign_pack_pieces_kernel(
+    const int32_t* __restrict__ C, int64_t ldc, int64_t M, int N, const int32_t* __restrict__ thr,
+    const uint32_t* __restrict__ flip_bits, uint32_t* __restrict__ out, int64_t ld_out, int units_per_row) {
+    const int q = threadIdx.x & 7, nw = (N + 31) >> 5;
+    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, units_per_row, kBnUnitRows);
+    int n_at[4], past[4];
+    quad_int t[4];
+    uint32_t flip[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int n0 = at.unit * 128 + q * 4 + 32 * u;
+        n_at[u] = min(n0, N - 4);
+        past[u] = min(n0 - n_at[u], 4);                        // channels before the ones wanted, four where there are none
+        t[u] = *reinterpret_cast<const quad_int*>(thr + n_at[u]);
+        flip[u] = (flip_bits[min(at.unit * 4 + u, nw - 1)] >> (4 * q)) & (0xFu >> past[u]);
+    }
+    const int word = at.unit * 4 + q;
+#pragma unroll
+    for (int i = 0; i < kBnUnitRows; ++i) {
+        const int64_t row = at.row + i;
+        if (row >= M) break;
+        const int32_t* p = C + row * ldc;
+        int4 c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = load_preact<ONCE>(p + n_at[u]);
+        uint32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t nib = uint32_t(c[u].x >= t[u][0]) | (uint32_t(c[u].y >= t[u][1]) << 1) |
+                                 (uint32_t(c[u].z >= t[u][2]) << 2) | (uint32_t(c[u].w >= t[u][3]) << 3);
+            w[u] = or_reduce8(((nib >> past[u]) ^ flip[u]) << (4 * q));
+        }
+        if (q < 4 && word < nw) out[row * ld_out + word] = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
+    }
+}
+
+// Which rows take it: at most a fifth of the words of their pieces do not exist, and as many workgroups as a launch holds.
+static int64_t piece_blocks(int64_t M, int64_t N, int64_t nw) {
+    const int64_t units = ceil_div(nw, 4), blocks = ceil_div(ceil_div(M, kBnUnitRows) * units, kUnitsPerBlock);
+    return N >= 4 && 16 * units <= 5 * nw && blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
+}
+
 }  // namespace bnn
 
 extern "C" int bnn_bn_sign_pack(const int32_t* C, int64_t ldc, int64_t M, int64_t N,
@@ -193,6 +242,18 @@ extern "C" int bnn_bn_sign_pack(const int32_t* C, int64_t ldc, int64_t M, int64_
             hipLaunchKernelGGL(bn_sign_pack_units_kernel<false>, dim3(unsigned(units)), dim3(kBnThreads), 0, s, C, ldc, M,
                                thr, flip_bits, out, ld_out, int(N / 128));
         return check_launch();
+    }
+    if (const int64_t pieces = piece_blocks(M, N, nw)) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(unsigned(pieces)), dim3(kBnThreads), 0, s, C, ldc, M, int(N), thr, flip_bits, out, ld_out,
+                               int(ceil_div(nw, 4)));
+            return check_launch();
+        };
+        // A non-temporal load fetches a line again for the neighbour that shares it, so only rows of whole lines are read past the
+        // cache: 20000 x 4000, before, now and with the default policy 60.1, 58.7 and 62.7 us; 28754 x 3005, before, now and
+        // non-temporal 67.8, 67.3 and 79.5, 32768 x 8191 227.7, 209.5 and 249.9.
+        return once && ldc % 32 == 0 && aligned_to(C, 128) ? launch(bn_sign_pack_pieces_kernel<true>)
+                                                           : launch(bn_sign_pack_pieces_kernel<false>);
     }
     if (once)
         hipLaunchKernelGGL(bn_sign_pack_kernel<true>, dim3(unsigned(blocks)), dim3(kBnThreads), 0, s, C, ldc,

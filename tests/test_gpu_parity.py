@@ -1655,6 +1655,40 @@ def test_pack_sign_of_long_rows_in_pieces(rows, cols, ld, offset):
     assert bool((out[rows] == 77).all()) and bool((out[:, kw:] == 77).all())
 
 
+@pytest.mark.parametrize("M,N,ld,offset", [
+    (3, 385, 385, 0),            # 13 words: a fourth piece of one word with one channel; an odd number of rows
+    (65, 513, 520, 1),           # a word past four pieces; rows apart, not 16-byte aligned
+    (1, 97, 97, 3),              # the shortest
+    (130, 894, 894, 2),          # a last load of two channels
+    (33, 1024, 1027, 1),         # whole pieces, unaligned
+    (257, 639, 639, 0),          # a last load of three
+    (33601, 1999, 2016, 0),      # larger than the cache: rows of whole lines, read past it
+    (33601, 1999, 1999, 0),      # and not
+])
+def test_bn_sign_pack_of_long_rows_in_pieces(M, N, ld, offset):
+    """Against the definition, thresholds of the type's ends among them; nothing beside the words is written."""
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    flat = torch.randint(-40, 41, (M * ld + offset,), generator=g, device=DEV, dtype=torch.int32)
+    flat[::19], flat[1::23] = 2**31 - 1, -2**31
+    C = torch.as_strided(flat, (M, N), (ld, 1), offset)
+    thr = torch.randint(-40, 41, (N + 1,), generator=g, device=DEV, dtype=torch.int32)[1:]
+    thr[::17], thr[1::29] = 2**31 - 1, -2**31
+    flip = torch.randint(0, 2, (N,), generator=g, device=DEV, dtype=torch.bool)
+    nw = (N + 31) // 32
+    place = 1 << torch.arange(32, device=DEV, dtype=torch.int64)
+
+    def words(bits):
+        padded = torch.zeros(len(bits), 32 * nw, dtype=torch.bool, device=DEV)
+        padded[:, :N] = bits
+        sums = torch.stack([(padded[:, 32 * w:32 * w + 32] * place).sum(1) for w in range(nw)], 1)
+        return torch.where(sums >= 2**31, sums - 2**32, sums).to(torch.int32)
+
+    out = torch.full((M + 1, nw + 2), 77, dtype=torch.int32, device=DEV)
+    bnn.bn_sign_pack(C, thr, words(flip[None])[0], out=out[:M, :nw])
+    assert torch.equal(out[:M, :nw], words((C >= thr) ^ flip))
+    assert bool((out[M] == 77).all()) and bool((out[:, nw:] == 77).all())
+
+
 @pytest.mark.parametrize("M,N,K,ld", [
     (1000, 1000, 4097, 129),     # one quad of one bit past a round of 32: one wavefront's
     (1000, 1000, 5120, 160),     # eight whole quads: a pair for every wavefront
