@@ -12,6 +12,7 @@
 // 16-byte stores), most other rows of 97 channels or more
 // bn_sign_pack_pieces_kernel; everything else bn_sign_pack_kernel.
 #include "bnn_internal.h"
+#include "row_pieces.h"
 
 namespace bnn {
 
@@ -171,45 +172,42 @@ __global__ __launch_bounds__(kBnThreads) void bn_sign_pack_units_kernel(
 // 2.4, 700 x 6001 3.9 and 3.0, 300000 x 100 22.9 and 18.6.
 template <bool ONCE>
 __global__ __launch_bounds__(kBnThreads) void bn_sign_pack_pieces_kernel(
-    const int32_t* __restrict__ C, int64_t ldc, int64_t M, int N, const int32_t* __restrict__ thr,
-    const uint32_t* __restrict__ flip_bits, uint32_t* __restrict__ out, int64_t ld_out, int units_per_row) {
-    const int q = threadIdx.x & 7, nw = (N + 31) >> 5;
-    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, units_per_row, kBnUnitRows);
-    int n_at[4], past[4];
+    const int32_t* __restrict__ C, int64_t ldc, int64_t M, PieceRow row, const int32_t* __restrict__ thr,
+    const uint32_t* __restrict__ flip_bits, uint32_t* __restrict__ out, int64_t ld_out) {
+    const int q = threadIdx.x & 7;
+    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, row.pieces(), kBnUnitRows);
+    PieceRow::Quad quad[4];
     quad_int t[4];
     uint32_t flip[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int n0 = at.unit * 128 + q * 4 + 32 * u;
-        n_at[u] = min(n0, N - 4);
-        past[u] = min(n0 - n_at[u], 4);                        // channels before the ones wanted, four where there are none
-        t[u] = *reinterpret_cast<const quad_int*>(thr + n_at[u]);
-        flip[u] = (flip_bits[min(at.unit * 4 + u, nw - 1)] >> (4 * q)) & (0xFu >> past[u]);
+        quad[u] = row.quad(at.unit, u, q);
+        t[u] = *reinterpret_cast<const quad_int*>(thr + quad[u].at);
+        flip[u] = (flip_bits[row.word(at.unit, u)] >> (4 * q)) & (0xFu >> quad[u].past);
     }
-    const int word = at.unit * 4 + q;
 #pragma unroll
     for (int i = 0; i < kBnUnitRows; ++i) {
-        const int64_t row = at.row + i;
-        if (row >= M) break;
-        const int32_t* p = C + row * ldc;
+        const int64_t m = at.row + i;
+        if (m >= M) break;
+        const int32_t* p = C + m * ldc;
         int4 c[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = load_preact<ONCE>(p + n_at[u]);
+        for (int u = 0; u < 4; ++u) c[u] = load_preact<ONCE>(p + quad[u].at);
         uint32_t w[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t nib = uint32_t(c[u].x >= t[u][0]) | (uint32_t(c[u].y >= t[u][1]) << 1) |
                                  (uint32_t(c[u].z >= t[u][2]) << 2) | (uint32_t(c[u].w >= t[u][3]) << 3);
-            w[u] = or_reduce8(((nib >> past[u]) ^ flip[u]) << (4 * q));
+            w[u] = or_reduce8(((nib >> quad[u].past) ^ flip[u]) << (4 * q));
         }
-        if (q < 4 && word < nw) out[row * ld_out + word] = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
+        if (row.stores(at.unit, q)) out[m * ld_out + at.unit * 4 + q] = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
     }
 }
 
-// Which rows take it: at most a fifth of the words of their pieces do not exist, and as many workgroups as a launch holds.
-static int64_t piece_blocks(int64_t M, int64_t N, int64_t nw) {
-    const int64_t units = ceil_div(nw, 4), blocks = ceil_div(ceil_div(M, kBnUnitRows) * units, kUnitsPerBlock);
-    return N >= 4 && 16 * units <= 5 * nw && blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
+// Workgroups for the rows that take it, 0 for others: those of pieces_of, while one launch holds them.
+static int64_t piece_blocks(int64_t M, int64_t nw) {
+    const int64_t blocks = ceil_div(ceil_div(M, kBnUnitRows) * pieces_of(nw), kUnitsPerBlock);
+    return blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
 }
 
 }  // namespace bnn
@@ -243,10 +241,10 @@ extern "C" int bnn_bn_sign_pack(const int32_t* C, int64_t ldc, int64_t M, int64_
                                thr, flip_bits, out, ld_out, int(N / 128));
         return check_launch();
     }
-    if (const int64_t pieces = piece_blocks(M, N, nw)) {
+    if (const int64_t pieces = piece_blocks(M, nw)) {
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(unsigned(pieces)), dim3(kBnThreads), 0, s, C, ldc, M, int(N), thr, flip_bits, out, ld_out,
-                               int(ceil_div(nw, 4)));
+            hipLaunchKernelGGL(kernel, dim3(unsigned(pieces)), dim3(kBnThreads), 0, s, C, ldc, M, piece_row(N), thr, flip_bits, out,
+                               ld_out);
             return check_launch();
         };
         // A non-temporal load fetches a line again for the neighbour that shares it, so only rows of whole lines are read past the

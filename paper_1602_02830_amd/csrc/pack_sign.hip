@@ -11,6 +11,7 @@
 // take pack_sign_units_kernel (4 words per group, one 16-byte store), long rows of other lengths pack_sign_pieces_kernel.
 #include "bit_transpose.h"
 #include "bnn_internal.h"
+#include "row_pieces.h"
 
 namespace bnn {
 
@@ -145,31 +146,31 @@ __global__ __launch_bounds__(kPackThreads) void pack_sign_units_kernel(
 // per word.  us, before and now: 10000 x 784 4.9 and 3.9, 1000 x 784 2.25 and 2.05, 700 x 6001 3.2 and 2.5, 100000 x 500 29.7 and 29.0.
 // Larger inputs are read past the cache, which does not bear lines that two loads share: 28754 x 3005 54 and 75.
 __global__ __launch_bounds__(kPackThreads) void pack_sign_pieces_kernel(
-    const float* __restrict__ x, int64_t rows, int cols, int64_t ld_x, uint32_t* __restrict__ out, int64_t ld_out,
-    int units_per_row) {
+    const float* __restrict__ x, int64_t rows, PieceRow row, int64_t ld_x, uint32_t* __restrict__ out, int64_t ld_out) {
     const int q = threadIdx.x & 7;
-    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, units_per_row, 1);
+    const UnitAt at = unit_at(blockIdx.x, threadIdx.x >> 3, row.pieces(), 1);
     if (at.row >= rows) return;
     const float* p = x + at.row * ld_x;
-    const int first = at.unit * 128 + q * 4;
+    PieceRow::Quad quad[4];
     float4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_input<false>(p + min(first + 32 * u, cols - 4));
+    for (int u = 0; u < 4; ++u) {
+        quad[u] = row.quad(at.unit, u, q);
+        v[u] = load_input<false>(p + quad[u].at);
+    }
     uint32_t w[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const uint32_t nib = ge_zero(v[u].x) | (ge_zero(v[u].y) << 1) | (ge_zero(v[u].z) << 2) | (ge_zero(v[u].w) << 3);
-        const int past = first + 32 * u - (cols - 4);          // elements before the ones wanted, four where there are none
-        w[u] = or_reduce8((nib >> min(max(past, 0), 4)) << (4 * q));
+        w[u] = or_reduce8((nib >> quad[u].past) << (4 * q));
     }
-    const int word = at.unit * 4 + q, kw = (cols + 31) >> 5;
-    if (q < 4 && word < kw) out[at.row * ld_out + word] = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
+    if (row.stores(at.unit, q)) out[at.row * ld_out + at.unit * 4 + q] = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
 }
 
-// Which rows take it: at most a fifth of the words of their pieces do not exist, and as many workgroups as a launch holds.
-static int64_t piece_blocks(int64_t rows, int64_t cols, int64_t kw) {
-    const int64_t units = ceil_div(kw, 4), blocks = ceil_div(rows * units, kUnitsPerBlock);
-    return cols >= 4 && 16 * units <= 5 * kw && blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
+// Workgroups for the rows that take it, 0 for others: those of pieces_of, while one launch holds them.
+static int64_t piece_blocks(int64_t rows, int64_t kw) {
+    const int64_t blocks = ceil_div(rows * pieces_of(kw), kUnitsPerBlock);
+    return blocks <= max_blocks(8 * kUnitsPerBlock) ? blocks : 0;
 }
 
 // ----------------------------------------------------------------------------
@@ -327,9 +328,9 @@ extern "C" int bnn_pack_sign(const float* x, int64_t rows, int64_t cols, int64_t
                                out, ld_out, int(cols / 128));
         return check_launch();
     }
-    if (const int64_t pieces = once ? 0 : piece_blocks(rows, cols, kw)) {
-        hipLaunchKernelGGL(pack_sign_pieces_kernel, dim3(unsigned(pieces)), dim3(kPackThreads), 0, s, x, rows, int(cols), ld_x, out, ld_out,
-                           int(ceil_div(kw, 4)));
+    if (const int64_t pieces = once ? 0 : piece_blocks(rows, kw)) {
+        hipLaunchKernelGGL(pack_sign_pieces_kernel, dim3(unsigned(pieces)), dim3(kPackThreads), 0, s, x, rows, piece_row(cols), ld_x, out,
+                           ld_out);
         return check_launch();
     }
     const WordStep slice = word_step(groups_per_block, kw);

@@ -231,7 +231,7 @@ def test_pooled_maps_of_whole_rows_keep_their_call(launches_of, B_, H, W, Cin): 
 @pytest.fixture(scope="module")
 def seen_by_launch(tmp_path_factory):
     """(what, calls) -> that expression of the stand-in for every call's launch: its local memory beside what the kernel declares, its
-    kernel, its workgroups."""
+    kernel, its workgroups, the PieceRow among its arguments."""
     folder = tmp_path_factory.mktemp("seen")
     line = "launch_log[launches][2] = *(uint64_t*)args[0];"
     assert line in RUNTIME and "(void)f; (void)shared;" in RUNTIME
@@ -239,7 +239,8 @@ def seen_by_launch(tmp_path_factory):
     def run(what, *calls):
         src, so = folder / f"{what}.c", folder / f"{what}.so"
         if not so.exists():
-            expression = {"local_memory": "shared", "kernel": "(uint64_t)f", "workgroups": "g.x"}[what]
+            expression = {"local_memory": "shared", "kernel": "(uint64_t)f", "workgroups": "g.x",
+                          "piece_row": "*(uint64_t*)args[3]", "piece_row_2": "*(uint64_t*)args[2]"}[what]
             src.write_text(RUNTIME.replace(line, f"launch_log[launches][2] = {expression};"))
             subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
         r = subprocess.run([sys.executable, "-c", CHILD, str(so), LIB], input=json.dumps([[n, list(a)] for n, a in calls]),
