@@ -36,6 +36,8 @@ struct Cut {
     int rows;                  // rows per strip, a multiple of 32
 };
 
+// Offset: of bytes, from a strip's first row and from a column tile's.  32 bits but for rows so far apart that they do not hold it.
+template <typename Offset>
 __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32_t* __restrict__ A, int64_t lda,
                                                                     const uint32_t* __restrict__ B, int64_t ldb, int M, int N,
                                                                     int K, BnSignArgs bn, Cut cut) {
@@ -65,10 +67,10 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     uint32_t mask[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) mask[p] = words_left <= 0 || p < 4 - words_left ? 0u : p == 3 && words_left <= 4 ? tmask : ~0u;
-    const uint32_t quad_at = 4u * uint32_t(min(4 * st_q, kw - 4));
-    // 16 bytes at `offset` (below 2^31) from a uniform address.
-    auto load_at = [&](const uint32_t* P, uint32_t offset) __attribute__((always_inline)) {
-        asm volatile("" : "+v"(offset));               // or it becomes a 64-bit address per lane
+    const Offset quad_at = 4u * uint32_t(min(4 * st_q, kw - 4));
+    // 16 bytes at `offset` from a uniform address.
+    auto load_at = [&](const uint32_t* P, Offset offset) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(offset));               // or 32 bits become a 64-bit address per lane
         return load_quad_any(reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(P) + offset));
     };
     // Words to LDS, set bits of the row in every one of its 8 lanes.
@@ -84,11 +86,11 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     };
     // Rows from the strip's first on, pass by pass, through all its tiles; past the strip's end its last row again.
     const uint32_t* strip_a = A + int64_t(row_begin) * lda;
-    const uint32_t pass_bytes = uint32_t(PASS_ROWS) * uint32_t(lda) * 4u;
-    const uint32_t last_row_at = uint32_t(row_end - 1 - row_begin) * uint32_t(lda) * 4u + quad_at;
-    uint32_t row_at = uint32_t(st_r) * uint32_t(lda) * 4u + quad_at;
+    const Offset pass_bytes = Offset(PASS_ROWS) * Offset(lda) * 4u;
+    const Offset last_row_at = Offset(row_end - 1 - row_begin) * Offset(lda) * 4u + quad_at;
+    Offset row_at = Offset(st_r) * Offset(lda) * 4u + quad_at;
     auto load_a = [&]() __attribute__((always_inline)) {
-        const uint4 v = load_at(strip_a, min(row_at, last_row_at));
+        const uint4 v = load_at(strip_a, row_at < last_row_at ? row_at : last_row_at);
         row_at += pass_bytes;
         return v;
     };
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 #pragma unroll
         for (int p = 0; p < BN / PASS_ROWS; ++p) {
             const int n = min(p * PASS_ROWS + st_r, N - 1 - col0);
-            vb[p] = load_at(B + int64_t(col0) * ldb, uint32_t(n) * uint32_t(ldb) * 4u + quad_at);
+            vb[p] = load_at(B + int64_t(col0) * ldb, Offset(n) * Offset(ldb) * 4u + quad_at);
             thr[p] = bn.thr[col0 + n];
         }
 #pragma unroll
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
     const int half_end = kw - 4 * (kq - 1) == 1;       // the last quad's one word is its fourth: no products of its first step
     // Bytes from the strip's first output word of the wavefront's columns to this lane's.
     char* strip_out = reinterpret_cast<char*>(bn.out + (int64_t(row_begin) * bn.ld_out + ((col0 + wn * 64) >> 5)));
-    const uint32_t out_row = uint32_t(bn.ld_out) * 4u;
+    const Offset out_row = Offset(bn.ld_out) * 4u;
 
     auto run = [&](auto nb_tag, int row0, int buf, bool more_tiles) __attribute__((always_inline)) {
         constexpr int NB = decltype(nb_tag)::value;
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
             const auto sw = __builtin_amdgcn_permlane32_swap(part[0], part[1], false, false);
             const int m = row0 - row_begin + (i * WAVE_ROWS + wr) * 32 + fr;
             if (m < row_end - row_begin && cols_left > 0)
-                *reinterpret_cast<uint32_t*>(strip_out + (uint32_t(m) * out_row + 4u * fh)) = ((sw[0] | sw[1]) ^ flip_word) & live_word;
+                *reinterpret_cast<uint32_t*>(strip_out + (Offset(m) * out_row + 4u * fh)) = ((sw[0] | sw[1]) ^ flip_word) & live_word;
         }
     };
 
@@ -290,13 +292,16 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
     const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 2 ? rows - last + BM / 2 : rows;
     if (!strips_fill(M, tiles_n, cost, rows <= 2 * BM ? 60 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};
-    // Byte offsets from a strip's first row, and a column tile's, are 32 bits.
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(groups * tiles_n)), dim3(T),
+                           size_t(2 * MAX_QUADS * (PLANE_B + (rows > BM ? 2 : 1) * PLANE_A)) * sizeof(uint2), static_cast<hipStream_t>(stream), A,
+                           lda, B, ldb, int(M), int(N), int(K), bn, cut);
+        return check_launch();
+    };
+    // Rows of A and of the output are counted from a strip's first, up to two tiles past its last; 128 rows of B.
     const int64_t ld = lda > bn.ld_out ? lda : bn.ld_out;
-    if (ldb >= int64_t(1) << 22 || ld >= (int64_t(1) << 29) / (rows + 2 * BM)) return BNN_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(xnor_gemm_mfma_strip_kernel, dim3(unsigned(groups * tiles_n)), dim3(T),
-                       size_t(2 * MAX_QUADS * (PLANE_B + (rows > BM ? 2 : 1) * PLANE_A)) * sizeof(uint2), static_cast<hipStream_t>(stream), A, lda,
-                       B, ldb, int(M), int(N), int(K), bn, cut);
-    return check_launch();
+    const bool near = ldb < int64_t(1) << 22 && ld < (int64_t(1) << 29) / (rows + 2 * BM);
+    return near ? launch(xnor_gemm_mfma_strip_kernel<uint32_t>) : launch(xnor_gemm_mfma_strip_kernel<uint64_t>);
 }
 
 }  // namespace bnn

@@ -1633,6 +1633,39 @@ def test_fused_products_of_short_rows_in_strips_of_any_end(M, N, K, ld, ld_out):
     assert torch.equal(out[:M, :nw], want) and torch.equal(out[M], kept[M]) and torch.equal(out[:, nw:], kept[:, nw:])
 
 
+@pytest.mark.parametrize("M,N,K,lda,ldb,ld_out", [
+    (160, 32768, 600, 453437, 19, 1024),     # the last distance whose byte offsets fit 32 bits, in strips of 160 rows
+    (160, 32768, 600, 453438, 19, 1024),
+    (160, 32768, 609, 20, 20, 453438),
+    (40960, 33, 784, 25, 2 ** 22, 2),
+    (2600, 8192, 639, 330001, 20, 256),      # strips of two tiles, bytes 2^31 past a strip's first row
+])
+def test_fused_products_of_rows_far_apart_in_strips(M, N, K, lda, ldb, ld_out):
+    """Row strips with byte offsets of 32 and of 64 bits, against the product on the vector ALU: every word, and nothing beside them."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    words = lambda *s: torch.randint(-2 ** 31, 2 ** 31 - 1, s, generator=g, device=DEV, dtype=torch.int32)
+    kw, nw = (K + 31) // 32, (N + 31) // 32
+
+    def apart(rows, cols, ld):
+        return torch.empty((rows - 1) * ld + cols + 3, dtype=torch.int32, device=DEV).as_strided((rows, cols), (ld, 1))
+
+    a, w = apart(M, kw, lda), apart(N, kw, ldb)
+    a.copy_(words(M, kw))
+    w.copy_(words(N, kw))
+    clean = [m.clone().contiguous() for m in (a, w)]
+    if K % 32:
+        for c in clean:
+            c[:, -1] &= (1 << K % 32) - 1
+    thr, flip = torch.randint(-40, 40, (N,), generator=g, device=DEV, dtype=torch.int32), words(nw)
+    if N % 32:
+        flip[-1] &= (1 << N % 32) - 1
+    want = bnn.xnor_gemm_bn_sign_pack(*clean, K, thr, flip, kernel=bnn.KERNEL_TILED64)
+    beside = min(ld_out - nw, 3)
+    out = apart(M, nw + beside, ld_out).fill_(77)
+    bnn.xnor_gemm_bn_sign_pack(a, w, K, thr, flip, out=out[:, :nw])
+    assert torch.equal(out[:, :nw], want) and bool((out[:, nw:] == 77).all())
+
+
 @pytest.mark.parametrize("rows,cols,ld,offset", [
     (3, 385, 385, 0),            # 13 words: a fourth piece of one word with one element
     (65, 513, 520, 1),           # a word past four pieces; rows apart, not 16-byte aligned

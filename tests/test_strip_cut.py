@@ -144,6 +144,15 @@ def test_row_strips_are_taken_where_they_fill_the_chip(launches_of, M, N, K, tak
     assert st == 0 and (log == strips(M, N, 128)) == taken
 
 
+@pytest.mark.parametrize("M,N,lda,ldb,ld_out", [
+    (160, 32768, 453437, 19, 1024), (160, 32768, 453438, 19, 1024), (160, 32768, 19, 19, 453438), (160, 32768, 2 ** 40, 19, 1024),
+    (40960, 33, 19, 2 ** 22 - 1, 2), (40960, 33, 19, 2 ** 22, 2), (2000, 8000, 360000, 19, 250)])
+def test_row_strips_are_taken_however_far_apart_rows_lie(launches_of, M, N, lda, ldb, ld_out):  # noqa: F811
+    """On both sides of the distances whose byte offsets fit 32 bits."""
+    (st, log), = launches_of(("bnn_xnor_gemm_bn_sign_pack", (A, lda, B, ldb, M, N, 600, THR, FLIP, OUT, ld_out, 0)))
+    assert st == 0 and log == strips(M, N, 128)
+
+
 @pytest.mark.parametrize("M,N,K,taken", [
     (10000, 4096, 784, True), (10000, 4096, 300, True), (2400, 8192, 257, False), (12300, 1226, 440, False), (5190, 3247, 258, False),
     (8192, 4096, 300, True), (16412, 3697, 309, True), (2539, 8192, 496, False), (2539, 8192, 513, True), (9101, 1701, 743, False),
