@@ -268,14 +268,16 @@ __global__ __launch_bounds__(T, 2) void xnor_gemm_mfma_strip_kernel(const uint32
 // Which of the products that fit are taken.  Measured on 481 products of 96 < K <= 1024, 44 to 21148 columns and 137 to 28168 rows (us,
 // tiles and strips):
 //  - strips of more than 128 rows, a block row for every wavefront along the rows and more: with 128 rows 726 x 5243 x 449 4.2 and 4.7, 10120
-//    x 260 x 415 4.1 and 4.5; with 160 13618 x 278 x 784 6.2 and 5.4, 388 x 8704 x 674 6.3 and 5.4;
+//    x 260 x 415 4.1 and 4.5; with 192 13618 x 278 x 784 6.2 and 5.4, 388 x 8704 x 674 6.3 and 5.4;
 //  - enough of the chip at work: 60 % of it in strips of one or two tiles (9890 x 2048 x 784, 640 rows, 11.2 and 10.1, 2534 x 8485 x 784, 77 %,
 //    13.9 and 11.5; 577 x 18637 x 784, 43 %, 8.1 and 9.8), 74 % up to four and 82 % beyond (10019 x 18758 x 784, 57 %, 82.3 and 97.8); a
-//    last tile counts as half of one at least.
-// What is left to the tiles beside that was slower here before the staging was shortened, and no longer is: K <= 576 (11175 x 2225 x 539
-// 13.5 and 10.0; only 384 < K <= 512 on at most 512 tiles of 128 x 128 is 0.92 to 0.98 times as fast in strips), K > 832 on as many tiles
-// (13015 x 640 x 838, 510 of them, 6.5 and 5.9), K > 896 in strips of several tiles (18769 x 3584 x 1015 34.3 and 28.7), and long
-// strips that keep 65 to 82 % of the chip at work (10397 x 12419 x 784, 77 %, 58.3 and 54.2).
+//    last tile counts as half of one at least;
+//  - where the 128 x 128 tiles are at most two to a compute unit, one round, not strips of more than 320 rows with K > 704: 343 x 21148 x 784
+//    6.50 and 6.65, 384 x 21248 x 832 6.54 and 6.83, K = 704 6.51 and 6.47, 640 6.50 and 6.09, 310 x 20480 x 784 6.51 and 6.14.
+// Three limits date from a kernel whose staging took three times as long, and strips are the faster form beyond them too: K <= 576 (11175 x
+// 2225 x 539 13.5 and 10.0; only 384 < K <= 512 on at most 512 tiles of 128 x 128 is 0.92 to 0.98 times as fast in strips), K > 832 on at
+// most 512 tiles (13015 x 640 x 838, 510 of them, 6.5 and 5.9), K > 896 in strips of several tiles (18769 x 3584 x 1015 34.3 and 28.7); and
+// long strips gain from 65 % of the chip on in part (10397 x 12419 x 784, 77 %, 58.3 and 54.2).
 constexpr int64_t kRowStripMinRows = 160;
 static_assert(starts_in_bf16_pairs(128 * row_strip::MAX_QUADS));
 
@@ -288,7 +290,7 @@ int launch_xnor_gemm_mfma_strip(const uint32_t* A, int64_t lda, const uint32_t* 
     const StripPlan plan = strip_plan(M, tiles_n);
     const int64_t rows = plan.rows, groups = plan.groups;
     if (rows < kRowStripMinRows || (rows > BM && K > 128 * (MAX_QUADS - 1))) return BNN_ERR_UNSUPPORTED;
-    if (K > 832 && ceil_div(M, 128) * tiles_n <= 512) return BNN_ERR_UNSUPPORTED;
+    if (ceil_div(M, 128) * tiles_n <= 512 && (K > 832 || (K > 704 && rows > 320))) return BNN_ERR_UNSUPPORTED;
     const int64_t last = rows % BM, cost = rows > BM && last > 0 && last < BM / 2 ? rows - last + BM / 2 : rows;
     if (!strips_fill(M, tiles_n, cost, rows <= 2 * BM ? 60 : rows <= 4 * BM ? 74 : 82)) return BNN_ERR_UNSUPPORTED;
     const Cut cut{fast_div(tiles_n), int(tiles_n), int(groups * tiles_n / kDies), int(rows)};

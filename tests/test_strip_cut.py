@@ -137,7 +137,9 @@ def strips(M, N, tile_n):
 @pytest.mark.parametrize("M,N,K,taken", [
     (2000, 6656, 784, True), (2000, 5504, 600, True), (1164, 19579, 600, False), (3060, 16512, 600, False), (1853, 4224, 1002, False),
     (1853, 4224, 800, True), (5105, 1732, 862, True), (36308, 238, 926, True), (795, 10452, 991, True), (15227, 512, 987, False), (609, 12519, 912, False), (609, 12519, 832, True), (10000, 4096, 784, True), (10000, 3000, 700, True), (4000, 6656, 784, True), (4000, 12000, 784, False), (10000, 6656, 784, False), (10000, 12000, 600, False),
-    (4000, 16512, 784, False), (10000, 16640, 784, False), (4141, 7168, 810, False), (4112, 15104, 784, True), (4000, 32768, 784, True)])
+    (4000, 16512, 784, False), (10000, 16640, 784, False), (4141, 7168, 810, False), (4112, 15104, 784, True), (4000, 32768, 784, True),
+    (343, 21148, 784, False), (352, 20480, 832, False), (384, 21248, 705, False), (384, 21248, 704, True), (343, 21148, 640, True),
+    (310, 20480, 784, True), (404, 20839, 800, True)])
 def test_row_strips_are_taken_where_they_fill_the_chip(launches_of, M, N, K, taken):  # noqa: F811
     kw = (K + 31) // 32
     (st, log), = launches_of(("bnn_xnor_gemm_bn_sign_pack", (A, kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
