@@ -175,6 +175,7 @@ int bnn_xnor_gemm_bn_sign_pack(const uint32_t *A, int64_t lda, const uint32_t *B
  * bnn_xnor_gemm_bn_sign_pack(a_bits, B -> out), in one launch where that is faster
  * (small batches, K <= 1024), else in two.  Same arguments, results and status as
  * those calls; x [M][ldx] float32, ldx >= K; a_bits [M][ld_a] receives the packed input.
+ * Two launches also where out reaches into x, or a_bits into B, thr or flip_bits.
  */
 int bnn_sign_gemm_bn_sign_pack(const float *x, int64_t ldx, const uint32_t *B, int64_t ldb,
                                int64_t M, int64_t N, int64_t K, const int32_t *thr,

@@ -143,6 +143,17 @@ static bool preferred(int64_t M, int64_t N, int64_t K, int64_t ldb) {
     return ldb < (1 << 24) && K > 32 && K <= 64 * kMostPieces && ceil_div(M, BM) * ceil_div(N, BN) <= kMaxTiles;
 }
 
+// Whether two matrices of 4-byte elements share memory, from their first element to their last.
+struct Operand {
+    const void* first;
+    int64_t rows, cols, ld;
+};
+static bool overlap(const Operand& a, const Operand& b) {
+    auto begin = [](const Operand& o) { return reinterpret_cast<uintptr_t>(o.first); };
+    auto end = [&](const Operand& o) { return begin(o) + 4u * (uint64_t(o.rows - 1) * uint64_t(o.ld) + uint64_t(o.cols)); };
+    return begin(a) < end(b) && begin(b) < end(a);
+}
+
 }  // namespace sign_gemm
 }  // namespace bnn
 
@@ -156,7 +167,13 @@ extern "C" int bnn_sign_gemm_bn_sign_pack(const float* x, int64_t ldx, const uin
     const bool plain = M > 0 && N > 0 && M <= kMaxDim && N <= kMaxDim && K > 0 && K <= kMaxK && ldx >= K && ldb >= kw && ld_a >= kw &&
                        ld_out >= nw && x && B && thr && flip_bits && a_bits && out && aligned_to(x, 4) && aligned_to(B, 4) &&
                        aligned_to(thr, 4) && aligned_to(flip_bits, 4) && aligned_to(a_bits, 4) && aligned_to(out, 4);
-    if (plain && preferred(M, N, K, ldb)) {
+    // So is what they read before they write it: here workgroups write results while others still read reals and filters.
+    auto separate = [&] {
+        const Operand bits{a_bits, M, kw, ld_a};
+        return !overlap({x, M, K, ldx}, {out, M, nw, ld_out}) && !overlap(bits, {B, N, kw, ldb}) && !overlap(bits, {thr, 1, N, N}) &&
+               !overlap(bits, {flip_bits, 1, nw, nw});
+    };
+    if (plain && preferred(M, N, K, ldb) && separate()) {
         const int64_t tiles_n = ceil_div(N, BN);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(unsigned(ceil_div(M, BM) * tiles_n)), dim3(T), 0, static_cast<hipStream_t>(stream), x, ldx, B,

@@ -1790,6 +1790,23 @@ def test_first_layer_on_reals_in_one_call(M, N, K, tight):
         assert torch.equal(now[M], kept[M]) and torch.equal(now[:, c], kept[:, c])
 
 
+def test_first_layer_whose_results_take_the_place_of_its_reals():
+    """Results written over the reals they come from (rows 784 words apart): what the two calls give."""
+    M, N, K = 100, 4096, 784
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x = torch.randn(M, K, generator=g, device=DEV)
+    w = bnn.pack_sign(torch.randn(N, K, generator=g, device=DEV))
+    thr = torch.randint(-60, 60, (N,), generator=g, device=DEV, dtype=torch.int32)
+    flip = torch.randint(-2 ** 31, 2 ** 31 - 1, (N // 32,), generator=g, device=DEV, dtype=torch.int32)
+    bits = bnn.pack_sign(x)
+    want = bnn.xnor_gemm_bn_sign_pack(bits, w, K, thr, flip)
+    for _ in range(20):
+        both = x.clone()
+        a_bits, out = torch.zeros_like(bits), both.view(torch.int32)[:, :N // 32]
+        bnn.sign_gemm_bn_sign_pack(both, w, K, thr, flip, a_bits, out)
+        assert torch.equal(a_bits, bits) and torch.equal(out, want)
+
+
 @pytest.mark.parametrize("shape", [
     # B, H, W, Cin, Cout, stride, padding: strips of fewer than 160 rows
     (1, 1, 1, 128, 1, 1, 1),              # one pixel, one filter

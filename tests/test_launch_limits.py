@@ -184,3 +184,30 @@ def test_short_rows_at_any_alignment_take_the_tiles_that_fit_them(launches_of, M
     (st, log), (st7, log7), (st_aligned, log_aligned) = launches_of(call(0, odd), call(7, aligned), call(0, aligned))
     assert st == st7 == st_aligned == 0 and log_aligned == log7 != [[-(-M // 128) * -(-N // 128), 256, A]]
     assert log == (log7 if id_ == 7 else [[-(-M // 128) * -(-N // 128), 256, A]])
+
+
+def first_layer(M=100, N=4096, K=784, ldx=None, ldb=None, ld_a=None, ld_out=None, x=A, b=B, thr=THR, flip=FLIP, bits=C, out=OUT):
+    kw, nw = (K + 31) // 32, (N + 31) // 32
+    return ("bnn_sign_gemm_bn_sign_pack", (x, ldx or K, b, ldb or kw, M, N, K, thr, flip, bits, ld_a or kw, out, ld_out or nw, 0))
+
+
+@pytest.mark.parametrize("written,read", [("out", "x"), ("bits", "b"), ("bits", "thr"), ("bits", "flip")])
+def test_first_layer_whose_operands_overlap_takes_two_launches(launches_of, written, read):
+    """What the two calls read before they write is read before it is written: a matrix that reaches into another by four bytes, and the
+    same right beside it."""
+    size = {"x": 100 * 784, "b": 4096 * 25, "thr": 4096, "flip": 128, "bits": 100 * 25, "out": 100 * 128}
+    at = {"x": A, "b": B, "thr": THR, "flip": FLIP}[read]
+    runs = launches_of(*(first_layer(**{written: at + d}) for d in (0, 4 * size[read] - 4, 4 - 4 * size[written], 4 * size[read],
+                                                                     -4 * size[written])))
+    assert [st for st, _ in runs] == [0] * 5 and [len(log) for _, log in runs] == [2, 2, 2, 1, 1]
+
+
+def test_first_layer_rows_apart_overlap_as_they_lie(launches_of):
+    """Rows 1000 reals, 200 words of bits and 300 of results apart."""
+    def run(**at):
+        (st, log), = launches_of(first_layer(ldx=1000, ld_a=200, ld_out=300, **at))
+        return st, len(log)
+
+    assert run(out=A + 4 * (99 * 1000 + 784)) == run(out=A - 4 * (99 * 300 + 128)) == (0, 1)
+    assert run(out=A + 4 * (99 * 1000 + 783)) == run(out=A - 4 * (99 * 300 + 127)) == (0, 2)
+    assert run(bits=THR - 4 * (99 * 200 + 25)) == (0, 1) and run(bits=THR - 4 * (99 * 200 + 24)) == (0, 2)
