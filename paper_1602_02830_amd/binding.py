@@ -254,6 +254,17 @@ def bn_sign_pack(C: torch.Tensor, thr: torch.Tensor, flip_bits: torch.Tensor,
     return out
 
 
+def _layer(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.Tensor, flip_bits: torch.Tensor):
+    """Packed rows of at least K bits, and the thresholds and flip bits of B's rows."""
+    N, kw = B.shape[0], words_per_row(K)
+    if A.shape[1] < kw or B.shape[1] < kw:
+        raise ValueError("packed operands have fewer words per row than K needs")
+    if thr.dtype != torch.int32 or flip_bits.dtype != torch.int32 or not thr.is_cuda or not flip_bits.is_cuda:
+        raise ValueError("thr and flip_bits must be int32 device tensors")
+    if thr.numel() != N or flip_bits.numel() != words_per_row(N) or not thr.is_contiguous() or not flip_bits.is_contiguous():
+        raise ValueError("thr must be [N] and flip_bits [ceil(N/32)], contiguous")
+
+
 def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.Tensor, flip_bits: torch.Tensor,
                            out: torch.Tensor | None = None, ld_out: int | None = None,
                            kernel: int = KERNEL_AUTO) -> torch.Tensor:
@@ -266,14 +277,8 @@ def xnor_gemm_bn_sign_pack(A: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
     _dev(A, torch.int32, "A")
     _dev(B, torch.int32, "B")
     M, N = A.shape[0], B.shape[0]
-    kw = words_per_row(K)
     nw = words_per_row(N)
-    if A.shape[1] < kw or B.shape[1] < kw:
-        raise ValueError("packed operands have fewer words per row than K needs")
-    if thr.dtype != torch.int32 or flip_bits.dtype != torch.int32 or not thr.is_cuda or not flip_bits.is_cuda:
-        raise ValueError("thr and flip_bits must be int32 device tensors")
-    if thr.numel() != N or flip_bits.numel() != nw or not thr.is_contiguous() or not flip_bits.is_contiguous():
-        raise ValueError("thr must be [N] and flip_bits [ceil(N/32)], contiguous")
+    _layer(A, B, K, thr, flip_bits)
     if out is None:
         out = _alloc_words(M, nw, A.device, ld_out)
     _dev(out, torch.int32, "out")
@@ -297,8 +302,19 @@ def sign_gemm_bn_sign_pack(x: torch.Tensor, B: torch.Tensor, K: int, thr: torch.
         st = _calls.sign_gemm_bn_sign_pack(x, B, K, thr, flip_bits, a_bits, out)
         if st == 0 or _took("bnn_sign_gemm_bn_sign_pack", st):
             return out
-    pack_sign(x, out=a_bits)
-    return xnor_gemm_bn_sign_pack(a_bits, B, K, thr, flip_bits, out=out)
+    if out is None or tuple(x.shape) != (a_bits.shape[0], K):             # other rows than the product's: no one call
+        pack_sign(x, out=a_bits)
+        return xnor_gemm_bn_sign_pack(a_bits, B, K, thr, flip_bits, out=out)
+    lib = load_library()
+    for t, dtype, name in ((x, torch.float32, "x"), (B, torch.int32, "B"), (a_bits, torch.int32, "a_bits"), (out, torch.int32, "out")):
+        _dev(t, dtype, name)
+    M, N = x.shape[0], B.shape[0]
+    _layer(a_bits, B, K, thr, flip_bits)
+    _holds(out, M, words_per_row(N), "out")
+    _check("bnn_sign_gemm_bn_sign_pack",
+           lib.bnn_sign_gemm_bn_sign_pack(x.data_ptr(), _ld(x), B.data_ptr(), _ld(B), M, N, K, thr.data_ptr(), flip_bits.data_ptr(),
+                                          a_bits.data_ptr(), _ld(a_bits), out.data_ptr(), _ld(out), _stream(out)))
+    return out
 
 
 def pack_bitplanes(x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:

@@ -338,6 +338,11 @@ def _call_forms():
         ("norm, strided thresholds", bnn.bn_sign_pack, (bits(M, 35), thr[::2], flip[:2]), lambda: out(M, 2)),
         ("layer", bnn.xnor_gemm_bn_sign_pack, (a, w, K, thr, flip), lambda: out(M, 3)),
         ("layer, wide flips", bnn.xnor_gemm_bn_sign_pack, (a, w, K, thr, flip.long()), lambda: out(M, 3)),
+        ("taken: first layer", bnn.sign_gemm_bn_sign_pack, (x, w, K, thr, flip, bits(M, 6, 8)), lambda: out(M, 3)),
+        ("taken: first layer, fewer reals than rows", bnn.sign_gemm_bn_sign_pack, (x[:20], w, K, thr, flip, bits(M, 6)), lambda: out(M, 3)),
+        ("refused: first layer, short thresholds", bnn.sign_gemm_bn_sign_pack, (x, w, K, thr[1:], flip, bits(M, 6)), lambda: out(M, 3)),
+        ("refused: first layer, narrow output", bnn.sign_gemm_bn_sign_pack, (x, w, K, thr, flip, bits(M, 6)), lambda: out(M, 4)[:, :2]),
+        ("refused: first layer, narrow bits", bnn.sign_gemm_bn_sign_pack, (x, w, K, thr, flip, bits(M, 5, 6)), lambda: out(M, 3)),
         ("planes", bnn.pack_bitplanes, (u8,), lambda: out(M, 48)),
         ("planes of floats", bnn.pack_bitplanes, (x,), lambda: out(M, 48)),
         ("bytes product", bnn.bitplane_gemm, (planes, w, K), lambda: out(M, N)),

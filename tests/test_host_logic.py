@@ -6,10 +6,12 @@ import ctypes
 import os
 import re
 import sys
+import types
 import warnings
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1602_02830_amd as bnn
@@ -248,6 +250,41 @@ def test_native_call_path_is_built_and_its_absence_leaves_the_wrappers(monkeypat
     with warnings.catch_warnings():
         warnings.simplefilter("error")
         assert binding.load_library() is lib
+
+
+class OnDevice(torch.Tensor):
+    """A host tensor that says it is a device's, for wrappers whose library is a stand-in."""
+    is_cuda = True
+
+
+@pytest.mark.parametrize("ldx,ld_a,ld_out", [(784, 25, 10), (800, 28, 12)])
+def test_first_layer_without_the_native_path_is_one_call(monkeypatch, ldx, ld_a, ld_out):
+    """Through ctypes too the library decides whether one launch or two make the layer; what is not one call's operands takes two."""
+    M, N, K, seen = 100, 300, 784, []
+    lib = types.SimpleNamespace(**{name: lambda *a, name=name: seen.append((name, *a)) or 0 for name in (
+        "bnn_sign_gemm_bn_sign_pack", "bnn_pack_sign", "bnn_xnor_gemm_bn_sign_pack")})
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(binding, "_lib", lib)
+    monkeypatch.setattr(binding, "_stream", lambda t: 7)
+
+    def matrix(rows, cols, ld, dtype=torch.int32):
+        return torch.zeros(rows, ld, dtype=dtype)[:, :cols].as_subclass(OnDevice)
+
+    x, w = matrix(M, K, ldx, torch.float32), matrix(N, 25, 25)
+    thr, flip = (torch.zeros(n, dtype=torch.int32).as_subclass(OnDevice) for n in (N, 10))
+    bits, out = matrix(M, 25, ld_a), matrix(M, 10, ld_out)
+    at = [t.data_ptr() for t in (x, w, thr, flip, bits, out)]
+    assert bnn.sign_gemm_bn_sign_pack(x, w, K, thr, flip, bits, out) is out
+    assert seen == [("bnn_sign_gemm_bn_sign_pack", at[0], ldx, at[1], 25, M, N, K, at[2], at[3], at[4], ld_a, at[5], ld_out, 7)]
+    seen.clear()
+    bnn.sign_gemm_bn_sign_pack(x[:60], w, K, thr, flip, bits, out)               # fewer reals than rows of bits
+    assert [c[0] for c in seen] == ["bnn_pack_sign", "bnn_xnor_gemm_bn_sign_pack"] and (seen[0][2], seen[1][5]) == (60, M)
+    for bad in ((x, w, K, thr[:-1], flip, bits, out), (x, w[:, :24], K, thr, flip, bits, out), (x, w, K, thr, flip, bits[:, :24], out),
+                (x, w, K, thr, flip, bits, out[:99]), (x.double(), w, K, thr, flip, bits, out)):
+        seen.clear()
+        with pytest.raises(ValueError):
+            bnn.sign_gemm_bn_sign_pack(*bad)
+        assert "bnn_sign_gemm_bn_sign_pack" not in [c[0] for c in seen]
 
 
 def test_missing_library_fails_loudly(monkeypatch):
