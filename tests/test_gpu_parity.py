@@ -1607,7 +1607,7 @@ def test_fused_convolutions_of_any_map_in_strips_and_windows(shape):
     (13618, 278, 801, 29, 11),       # of two words; a last column tile of 22 columns, rows apart
     (2600, 8192, 639, 20, 256),      # five whole quads, the last word a bit short; 672 rows
     (20020, 256, 608, 19, 8),        # of three words; 160 rows
-    (9990, 3072, 896, 31, 97),       # seven whole quads, odd distances; 992 rows
+    (9990, 3072, 896, 31, 97),       # seven whole quads, odd distances; 1024 rows
 ])
 def test_fused_products_of_short_rows_in_strips_of_any_end(M, N, K, ld, ld_out):
     """Row strips: a last quad masked where it was loaded, against the product on the vector ALU: every word, and nothing beside them.
@@ -1725,7 +1725,11 @@ def test_bn_sign_pack_of_long_rows_in_pieces(M, N, ld, offset):
 @pytest.mark.parametrize("M,N,K,ld", [
     (1000, 1000, 4097, 129),     # one quad of one bit past a round of 32: one wavefront's
     (1000, 1000, 5120, 160),     # eight whole quads: a pair for every wavefront
-    (990, 1030, 4900, 155),      # seven, the last of two words and a bit
+    (990, 1030, 4900, 155),      # seven, the last of two words and a bit, in rows that are read without staging
+    (990, 1030, 4900, 160),      # and staged, 32 x 32 tiles: a last pair of one quad
+    (1023, 1001, 4900, 160),     # 64 x 32 tiles
+    (1000, 999, 4500, 160),      # four, the last of one word: two wavefronts have a pair, two none
+    (1279, 1201, 4352, 136),     # two whole quads
     (1023, 1001, 8193, 257),     # past two rounds
     (1000, 1000, 5121, 161),     # nine: a round of their own
     (512, 640, 4100, 128),       # 32 x 32 tiles
@@ -1813,10 +1817,14 @@ def test_first_layer_whose_results_take_the_place_of_its_reals():
     (1, 2, 2, 256, 33, 1, 1),             # one pooling window
     (10, 14, 14, 256, 256, 1, 1),         # 32 rows
     (7, 9, 11, 384, 130, 2, 0),           # stride 2 without padding, images that end inside a strip
+    (10, 14, 14, 512, 200, 1, 1),         # 32 with filters of nine K-tiles
     (63, 16, 16, 128, 64, 1, 1),          # 64
-    (4, 30, 30, 512, 512, 1, 1),          # 64 with filters of nine K-tiles
+    (4, 30, 30, 512, 512, 1, 1),          # 64 with filters of nine K-tiles: tiles
+    (27, 30, 30, 256, 64, 1, 1),          # 96
+    (25, 30, 30, 512, 128, 1, 1),         # 96 with filters of nine K-tiles
+    (22, 32, 32, 256, 64, 1, 1),          # 96 = three image rows: tiles
     (12, 28, 28, 256, 264, 1, 1),         # 128; a last column tile of eight filters
-    (22, 32, 32, 256, 64, 1, 1),          # 96 = three image rows
+    (41, 28, 28, 512, 128, 1, 1),         # 128 with filters of nine K-tiles
     (3, 4, 260, 128, 96, 1, 2),           # wide maps, wide padding
 ])
 def test_fused_convolutions_in_short_strips(shape):

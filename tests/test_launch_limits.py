@@ -211,3 +211,36 @@ def test_first_layer_rows_apart_overlap_as_they_lie(launches_of):
     assert run(out=A + 4 * (99 * 1000 + 784)) == run(out=A - 4 * (99 * 300 + 128)) == (0, 1)
     assert run(out=A + 4 * (99 * 1000 + 783)) == run(out=A - 4 * (99 * 300 + 127)) == (0, 2)
     assert run(bits=THR - 4 * (99 * 200 + 25)) == (0, 1) and run(bits=THR - 4 * (99 * 200 + 24)) == (0, 2)
+
+
+@pytest.mark.parametrize("M,N,K,one", [
+    (16, 128, 32, False), (16, 128, 33, True),                      # rows of one word keep to the product of few words
+    (100, 4096, 832, True), (100, 4096, 833, True), (100, 4096, 1024, True), (100, 4096, 1025, False),
+    (256, 4096, 784, True), (257, 4096, 784, False),                # 512 tiles of 16 x 128
+    (1, 65536, 784, True), (1, 65537, 784, False), (8192, 128, 784, True), (8193, 128, 784, False)])
+def test_first_layers_of_few_tiles_take_one_launch(launches_of, M, N, K, one):
+    kw = (K + 31) // 32
+    (st, log), pack, product = launches_of(
+        first_layer(M, N, K), ("bnn_pack_sign", (A, M, K, K, C, kw, 0)),
+        ("bnn_xnor_gemm_bn_sign_pack", (C, kw, B, kw, M, N, K, THR, FLIP, OUT, (N + 31) // 32, 0)))
+    assert st == pack[0] == product[0] == 0
+    assert log == ([[-(-M // 16) * -(-N // 128), 512, A]] if one else pack[1] + product[1])
+
+
+def test_first_layer_rows_of_filters_far_apart_take_two_launches(launches_of):
+    for ldb, n in ((2 ** 24 - 1, 1), (2 ** 24, 2)):
+        (st, log), = launches_of(first_layer(ldb=ldb))
+        assert (st, len(log)) == (0, n)
+
+
+@pytest.mark.parametrize("change", [
+    {"M": 0}, {"N": 0}, {"M": -1}, {"N": -1}, {"K": -5}, {"ldx": 783}, {"ldb": 24}, {"ld_a": 24}, {"ld_out": 127}, {"x": 0}, {"b": 0},
+    {"thr": 0}, {"flip": 0}, {"bits": 0}, {"out": 0}, {"x": A + 2}, {"b": B + 2}, {"thr": THR + 1}, {"flip": FLIP + 2}, {"bits": C + 2},
+    {"out": OUT + 2}, {"M": 2 ** 31}, {"N": 2 ** 31}, {"K": 2 ** 31 - 31}])
+def test_first_layer_answers_as_the_two_calls(launches_of, change):
+    """The first status that is not good, and what was launched before it."""
+    name, args = first_layer(**change)
+    x, ldx, b, ldb, M, N, K, thr, flip, bits, ld_a, out, ld_out, stream = args
+    one, pack, product = launches_of((name, args), ("bnn_pack_sign", (x, M, K, ldx, bits, ld_a, stream)),
+                                     ("bnn_xnor_gemm_bn_sign_pack", (bits, ld_a, b, ldb, M, N, K, thr, flip, out, ld_out, stream)))
+    assert one == (pack if pack[0] else [product[0], pack[1] + product[1]])

@@ -262,6 +262,26 @@ def seen_by_launch(tmp_path_factory):
     return run
 
 
+@pytest.mark.parametrize("B_,H,W,Cin,Cout,k,rows,taken", [
+    (1, 8, 8, 256, 128, 3, 32, True), (10, 14, 14, 256, 256, 3, 32, True), (10, 14, 14, 512, 256, 3, 32, True),
+    (63, 16, 16, 128, 64, 3, 64, True), (4, 30, 30, 256, 512, 3, 64, True), (4, 30, 30, 512, 512, 3, 64, False),    # 64 rows: K <= 2560
+    (27, 30, 30, 256, 64, 3, 96, True), (25, 30, 30, 512, 128, 3, 96, True),
+    (22, 32, 32, 256, 64, 3, 96, False), (44, 16, 32, 256, 64, 3, 96, False), (30, 32, 32, 256, 64, 3, 128, True),    # map rows of whole blocks: pairs of them
+    (12, 28, 28, 256, 264, 3, 128, True), (41, 28, 28, 512, 128, 3, 128, True),
+    (1, 15, 15, 256, 11264, 3, 128, True), (1, 15, 15, 256, 11008, 3, 128, False),                                   # 60 % of the chip
+    (1, 13, 10, 256, 11008, 3, 96, False), (1, 10, 10, 256, 11008, 3, 64, True),                                     # asked from 96 rows on
+    (10, 14, 14, 128, 128, 5, 32, False), (156, 14, 14, 128, 128, 5, 128, False), (190, 14, 14, 128, 128, 5, 160, True)])
+def test_short_convolution_strips_are_taken_where_they_are_faster(seen_by_launch, B_, H, W, Cin, Cout, k, rows, taken):
+    """By the kernel that is launched, against that of a layer of the same channels in strips of 256 or 512 rows."""
+    def call(B_, H, W, Cout):
+        return ("bnn_conv_bn_sign_pack", (A, B_, H, W, Cin, WB, k * k * Cin // 32, Cout, k, k, 1, k // 2, THR, FLIP, OUT,
+                                          (Cout + 31) // 32, 0))
+
+    assert strips(B_ * H * W, Cout, 128) == [[-(-B_ * H * W // rows) * -(-Cout // 128), 512, A]]
+    got, strip = seen_by_launch("kernel", call(B_, H, W, Cout), call(256, 16, 16, 256) if Cin <= 256 else call(256, 8, 8, 512))
+    assert (got == strip) == taken
+
+
 @pytest.mark.parametrize("B_,HW,Cin", [(100, 32, 768), (168, 32, 1024), (22, 32, 256), (8, 16, 512)])
 def test_pooled_patches_of_whole_rows_are_no_larger_than_plain_ones(seen_by_launch, B_, HW, Cin):
     """Tiles of pooling windows that are whole image rows cover the same rows as the tiles of the unpooled layer."""
@@ -287,6 +307,20 @@ def product(fused, M, N, K, ld=0):
 def test_k_split_products_are_staged_where_that_is_faster(seen_by_launch, fused, M, N, K, ld, staged):
     got, direct, lines = seen_by_launch("kernel", product(fused, M, N, K, ld), product(fused, 512, 640, 2000), product(fused, 512, 640, 4096))
     assert direct != lines and got == (lines if staged else direct)
+
+
+@pytest.mark.parametrize("fused,M,N,K,ld,rest", [
+    (False, 1000, 1000, 4097, 129, True), (False, 1000, 1000, 4500, 160, True), (False, 1000, 1000, 4900, 160, True),        # 1, 4, 7 quads
+    (False, 1000, 1000, 5120, 160, True), (False, 1000, 1000, 5121, 161, False), (False, 1000, 1000, 4096, 129, False),     # 8, 9, none
+    (False, 1000, 1000, 1024, 33, False),                                                                                   # less than a round
+    (False, 512, 640, 4500, 160, True), (False, 512, 640, 4900, 160, True), (False, 512, 640, 5121, 161, False),
+    (True, 1000, 1000, 4500, 160, True), (True, 1000, 1000, 4900, 160, True), (True, 1280, 1200, 4352, 136, True),
+    (True, 1280, 1200, 4600, 144, True), (True, 512, 640, 4500, 160, False), (True, 512, 640, 4900, 160, False)])
+def test_a_short_rest_of_k_is_loaded_with_the_first_round(seen_by_launch, fused, M, N, K, ld, rest):
+    """Products staged in rounds of 32 quads, one to eight quads past whole rounds; not fused 32 x 32 tiles."""
+    tiles = (512, 640) if (M, N) == (512, 640) else (1000, 1000)
+    got, with_rest, whole = seen_by_launch("kernel", product(fused, M, N, K, ld), product(fused, *tiles, 4097, 129), product(fused, *tiles, 4096))
+    assert (got == with_rest != whole) == rest
 
 
 @pytest.mark.parametrize("fused,M,N,K,workgroups", [
