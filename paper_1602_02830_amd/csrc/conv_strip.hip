@@ -24,7 +24,7 @@
 //     cycles for each): 900 of them, 8000 cycles of 31000, for 256 -> 256 of 16 x 16, 5300 now.  Hence the divisions in float32
 //     (strip_cells.h), a kernel for each way of walking a strip (Walk) and for 3 x 3 windows, the arguments that the first loads
 //     need in the first line of the argument block, and the pixels' cells held before the barrier, while the loads are in flight.
-// Batch 256, us, tiles of conv_patch.hip, strips before that and now: 128 -> 128 of 32 x 32 pooled 19.3, 17.0, 15.7, 128 -> 256 of
+// Batch 256, us of the kernel replayed from a graph, tiles of conv_patch.hip, strips before that and now: 128 -> 128 of 32 x 32 pooled 19.3, 17.0, 15.7, 128 -> 256 of
 // 16 x 16 10.9, 10.1, 9.0, 256 -> 256 16.3, 15.0, 13.6, 256 -> 512 of 8 x 8 11.3, 10.0, 9.5, 512 -> 512 pooled 18.3, 16.2, 15.6;
 // 128 images of 28 x 28, 128 -> 256 pooled (on tiles two launches) 21.7, 15.1, 13.6.
 // Signs (+-1) for the filters' bits would need no popcounts of the pixels (2600 cycles less before the first product), but operands
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(T, 2) void conv_strip_mfma_kernel(
     if (tid < BN / 32 && col0 + 32 * tid < N) flip_reg = bn.flip_bits[(col0 >> 5) + tid];
 
     // ---- patches -------------------------------------------------------------------------------------------
-    // Loaded ahead (cut.ahead: at most PF_SLOTS cells per thread of at most PF_QUADS quads): cell u * T + tid of a patch.
+    // Loaded ahead (Walk::AHEAD: at most PF_SLOTS cells per thread of at most PF_QUADS quads): cell u * T + tid of a patch.
     uint4 ahead[PF_QUADS];
     bool ahead_inside = false;
     auto load_ahead = [&](Origin o, int u) __attribute__((always_inline)) {
@@ -508,14 +508,16 @@ constexpr int64_t kStripLdsBytes = 158 * 1024;                // of 160 KB, besi
 static_assert(starts_in_bf16_pairs(kStripResidentMost * 512));
 // Which of the layers that fit are faster here than on the tiles of conv_patch.hip and the gathering kernels.  Measured on 4100
 // layers, pooled and not, of 1 to 25 taps, 128 to 1024 channels and 32 to 32768 filters; us, tiles and strips:
-//  - strips of fewer than 160 rows, down to 32 and however little of the chip they fill, for 3 x 3 windows: 380 layers 1.02 to 1.5 times as
-//    fast (66 images of 14 x 14, 256 -> 256 8.4 and 7.4; 12 of 28 x 28, 256 -> 256 8.9 and 7.3; 16 of 32 x 32, 128 -> 64 5.5 and 4.95; 4
-//    of 30 x 30, 512 -> 512 12.2 and 10.2), but for 64 rows of K > 2560, where a pair of 32-row blocks shares the filters that tiles
-//    of 64 pixels keep for themselves (52 of 14 x 14, 512 -> 99 9.8 and 10.0).  Windows of other sizes, which have no kernel for strips of
-//    one tile, lose more instructions before the first product than they gain (10 of 14 x 14, 128 -> 128, 5 x 5 7.5 and 8.3).
-//    Maps whose rows are whole blocks of 32 pixels keep to tiles in strips of several rows but not of pairs of rows: such a strip of
-//    a pooled layer cuts its windows' rows, and its patch is larger than the plain layer's;
-//  - enough of the chip at work: 60 % with strips of one tile, 80 % up to four, 86 % beyond (41 images of 16 x 16, 256 -> 8576,
+//  - strips of fewer than 160 rows for 3 x 3 windows, those of 32 and 64 rows however little of the chip they fill: 212 of the layers taken
+//    1.01 to 1.53 times as fast, 1.12 in the mean (66 images of 14 x 14, 256 -> 256 8.4 and 7.4; 12 of 28 x 28, 256 -> 256 8.9 and 7.3; 16
+//    of 32 x 32, 128 -> 64 5.5 and 4.95).  Windows of other sizes, which have no kernel for strips of one tile, lose more instructions
+//    before the first product than they gain (10 of 14 x 14, 128 -> 128, 5 x 5 7.5 and 8.3).
+//    Two kinds of them are left to tiles by lines that are coarser than what they separate.  64 rows of K > 2560, where a pair of 32-row
+//    blocks shares the filters that tiles of 64 pixels keep for themselves: of 72 layers 35 lose up to 3 % in strips (52 of 14 x 14, 512 -> 99
+//    9.75 and 9.99), 28 would gain more than that (4 of 30 x 30, 512 -> 512 12.1 and 10.2).  And strips of several map rows, but not of pairs of them,
+//    where these are whole blocks of 32 pixels, so that a pooled layer's patch is no larger than the plain layer's: 72 of 72 layers
+//    would be 1.06 to 1.55 times as fast in strips, plain ones as well (20 of 32 x 32, 256 -> 128 8.9 and 7.2);
+//  - enough of the chip at work, from 96 rows on: 60 % with strips of one tile, 80 % up to four, 86 % beyond (41 images of 16 x 16, 256 -> 8576,
 //    78 %, 75.5 and 79.1; 47 of 14 x 14, 512 -> 12288, 75 %, 169 and 190), 93 % with K <= 1152, whose tiles are short (40 of 28 x 28,
 //    128 -> 9984, 91 %, 138 and 148; 58 of 32 x 32, 128 -> 4700 pooled, 87 %, 123 and 139);
 //  - K <= 1536: whatever follows holds only for layers whose tiles fill a compute unit (conv_patch_tiles_fill: three of 256 pixels or

@@ -3,8 +3,8 @@
 //
 // A launch costs the host 3.6 us and the device 2.1 us before it has done anything, more than packing 100 x 784 reals takes: a
 // network of five launches is bound by their number (784-4096-4096-4096-10 at batch 100: 19.2 us in five launches, 16.8 in four).  So
-// every workgroup binarizes the 16 rows it needs itself, 50 KB of reals from L2, and goes on to multiply: 100 x 4096 x 784 4.0 us on
-// the device, 5.2 in two launches.
+// every workgroup binarizes the 16 rows it needs itself, 50 KB of reals from L2, and goes on to multiply: 100 x 4096 x 784 4.0 us
+// replayed from a graph, 5.2 in two launches.
 //
 // A workgroup is eight wavefronts and owns 16 rows x 128 columns (v_mfma_f32_16x16x128_f8f6f4: 16 rows rather than 32 halve the reals
 // that go through a compute unit at 64 bytes a cycle).  Lane l of a 64-element piece of a row compares element l with zero, so the
@@ -133,9 +133,9 @@ __global__ __launch_bounds__(T) void sign_gemm_kernel(const float* __restrict__ 
         reinterpret_cast<uint16_t*>(bn.out + int64_t(row0 + r) * bn.ld_out + word)[half] = uint16_t((bits ^ (flip >> (16 * half))) & live);
 }
 
-constexpr int kFewPieces = 13, kMostPieces = 16;           // 784 inputs (28 x 28), 1024
+constexpr int kFewPieces = 13, kMostPieces = 16;           // 784 inputs (28 x 28), 1024; shorter rows compare and multiply zeros up to 13
 // Whether one launch is faster than two: up to two workgroups per compute unit, where the reals that all column tiles read again cost
-// less than a launch.  us on the device, two launches and one: 16 x 4096 x 784 (32 tiles) 4.8 and 3.9, 256 x 4096 x 784 (512) 5.95 and
+// less than a launch.  us replayed from a graph, two launches and one: 16 x 4096 x 784 (32 tiles) 4.8 and 3.9, 256 x 4096 x 784 (512) 5.95 and
 // 5.4, 2000 x 512 x 100 (500) 6.2 and 5.3, 100 x 4096 x 1024 (224) 5.3 and 5.0; 400 x 4096 x 784 (800) 6.9 and 8.2.
 constexpr int64_t kMaxTiles = 512;
 

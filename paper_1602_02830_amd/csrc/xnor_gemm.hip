@@ -421,7 +421,7 @@ static void launch_tiled(const uint32_t* A, int64_t lda, const uint32_t* B, int6
 // on a grid that fills the chip, the short-K organisation (B tile resident, several A tiles per
 // workgroup, only the K words that exist) is 5-25 % faster still (short_ok: 96 < K <= 1152).  Before any of these, fused products
 // of 577 <= K <= 1024 that fill the compute units with equal strips of rows go to xnor_gemm_mfma_strip.hip, whose launcher decides
-// (3 to 22 % faster: see there); they are not seen here.  Skinny outputs
+// (up to 1.45 times as fast: see there); they are not seen here.  Skinny outputs
 // that are too large for the split-K kernel go to the lane-group kernel; K beyond the exact-fp32 range
 // stays on the vector ALU.
 //

@@ -416,7 +416,7 @@ template <int RB, bool STAGED, bool REST = false>
 static int launch_splitk_rows(const uint32_t* A, int64_t lda, const uint32_t* B, int64_t ldb, int32_t* C, int64_t ldc,
                               int64_t M, int64_t N, int64_t K, bool fused, const BnSignArgs& bn, hipStream_t s) {
     if constexpr (STAGED && !REST) {
-        // (Fused 32 x 32 tiles have no such kernel: 100 x 4096 x 4097 would gain 8 %.)
+        // Fused 32 x 32 tiles have no such kernel, though they would gain as others do (100 x 4096 x 4097 8 %).
         const int64_t nq = ceil_div(K, 128), past = nq % splitk::kRound;
         if (nq > splitk::kRound && past > 0 && past <= splitk::kRestMost && (RB > 1 || !fused))
             return launch_splitk_rows<RB, true, true>(A, lda, B, ldb, C, ldc, M, N, K, fused, bn, s);
@@ -454,7 +454,8 @@ static int launch_splitk_rows(const uint32_t* A, int64_t lda, const uint32_t* B,
 //      other rows only where the last round of 32 quads is well filled: 49 to 64 quads (t = 776 int32 K = 7680 1.08 times faster; fused
 //      up to t = 896 from 57 on; 64 x 32 fused from 41 on, and above t = 1024 from 34 on without end), 89 to 96, 121 to 128 and so
 //      on above t = 512 (1.03), and 24 to 30, one round, int32 up to t = 896 (1.02).  With 33 to 40 quads staged takes 1.05 to 1.15 times as long (t = 750 fused K = 4160 5.9 vs 5.4),
-//      with 65 to 88 as well (1003 tiles, int32 K = 8704 11.5 vs 10.2).
+//      with 65 to 88 as well (1003 tiles, int32 K = 8704 11.5 vs 10.2).  Those figures are of rounds alone: where a short rest makes no
+//      round (REST), 33 to 40 and 65 to 72 quads of such rows were not measured again and are read directly.
 static bool splitk_two_rows(int64_t M, int64_t N) {
     const int64_t t = ceil_div(M, 32) * ceil_div(N, 32), t64 = ceil_div(M, 64) * ceil_div(N, 32);
     return t > 896 && t64 <= (t <= 1024 ? 512 : 768) && 16 * ceil_div(M, 64) <= 9 * ceil_div(M, 32);

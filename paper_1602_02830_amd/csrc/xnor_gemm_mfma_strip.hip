@@ -11,7 +11,8 @@
 // steps, a row's last quad is masked where it was loaded instead of shifted into place, and planes for all eight quads are written
 // whatever K is.  (With 64-bit addresses, shifts and stores under a mask, 65, a tile took 14000 cycles for 6700 of products.)  us, before
 // that and now: 10000 x 4096 x 784 18.4 and 15.9, 16384 x 4096 x 784 26.4 and 22.9, 3000 x 3000 x 784 6.7 and 6.2, 16000 x 1000 x 800
-// 8.3 and 7.7; on the 128 x 128 tiles 20.6, 28.4, 7.9 and 11.2.
+// 8.3 and 7.7; on the 128 x 128 tiles 20.6, 28.4, 7.9 and 11.2.  Rows too far apart for 32 bits have a kernel with 64-bit offsets: 2000 x 8000 x
+// 784 with rows 360000 words apart 8.0, on the tiles 10.6, with 340000 7.8.
 #include <type_traits>
 
 #include "bnn_internal.h"
